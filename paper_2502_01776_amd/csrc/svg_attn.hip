@@ -4,27 +4,37 @@
 //
 // One workgroup owns one query tile of one head; each of its NW wavefronts owns 32
 // query rows and all BN keys of the current key tile.  Both matrix products are
-// computed TRANSPOSED with v_mfma_f32_32x32x16_bf16:
+// computed TRANSPOSED with v_mfma_f32_16x16x32_bf16, every LDS operand feeding two products,
+// one per 16-query block of the wavefront:
 //     S^T = K Q^T      (A = K tile from LDS,  B = Q^T held in registers)
 //     O^T += V^T P^T   (A = V^T from LDS,     B = P^T taken from S^T's registers)
-// In the 32x32 accumulator layout a lane holds ONE query column (lane % 32) and 16
-// key rows, so the softmax row statistics are per-lane register reductions plus one
-// exchange between lane l and lane l+32, the rescale factor is one scalar per lane,
-// and the exponentiated S^T registers are, after bf16 packing, exactly the B operand
-// of the second product: register pair (2kk, 2kk+1) of a 32-key block holds keys
-// {16kk+4g+j} and {16kk+8+4g+j}, j<4, g = lane/32, and the V^T operand is read in
-// the same key order, so P never moves between lanes or through LDS.
+// In the 16x16 accumulator layout a lane holds ONE query column (lane % 16) and the key rows
+// 4 g + {0..3}, g = lane / 16, so the softmax row statistics are per-lane register reductions
+// plus an exchange among lanes l, l ^ 16, l ^ 32, l ^ 48 where one is needed at all, the rescale
+// factor is one scalar per lane and query block, and the exponentiated S^T registers of two
+// 16-key blocks are, after bf16 packing, exactly the B operand of the second product: its
+// k-slots 8 g + {0..7} hold keys {4 g + j} and {16 + 4 g + j}, j < 4, of a 32-key step, and the
+// V^T operand is read in the same key order, so P never moves between lanes or through LDS.
 //
-// Staging: K and V tiles go global -> registers (raw buffer loads, bounds-checked
-// descriptors, loop-invariant offsets) -> LDS as straight 16-byte copies, double
-// buffered, with the loads of tile j+1 in flight while tile j is computed and one
-// barrier per tile.  K rows are padded by 16 bytes (conflict-free ds_read_b128 of the A
-// operand with compile-time offsets).  V stays row-major too: the transposing LDS read
-// of gfx950 (ds_read_b64_tr_b16) hands a lane the same channel of four consecutive
+// Why 16x16x32 and not 32x32x16: the chip is power-limited here, and the smaller form moves
+// half the accumulator traffic per operation.  Loops of the kernel's instruction mix measured
+// 2093 against 1788 TFLOP/s (products only) and 1419 against 1364 (with one 1 KB operand
+// read per 32768 operations and the softmax).
+//
+// Staging: K and V tiles go from memory straight into LDS (buffer_load_dwordx4 ... lds, bounds-checked
+// descriptors, loop-invariant offsets), double buffered, with the loads of tile j+1 in flight
+// while tile j is computed and one barrier per tile.  Such a load writes 64 x 16 consecutive
+// bytes, so rows cannot be padded; the bank swizzles are applied on the memory side (a lane
+// fetches the piece of its row that belongs at its place).  V stays row-major too: the transposing
+// LDS read of gfx950 (ds_read_b64_tr_b16) hands a lane the same channel of four consecutive
 // keys, so two of them are a whole A operand of the second product and nothing is
-// transposed in registers.  Operand reads run a few
-// products ahead of their use (rolling window), including the first V^T operands,
-// which are requested before the softmax starts.
+// transposed in registers.  Operand reads run several operands ahead of their use (rolling
+// window), including the first V^T operands, which are requested before the softmax starts.
+// (With the tiles staged through registers and ds_write_b128, and 32x32x16 products, the sparse pass
+// took 24.5 ms instead of 22.3 at the 119k-token shape with 15 % of the tiles kept, 3.22
+// instead of 2.89 ms at 40 heads of 32760 tokens, 4.08 instead of 3.69 ms at head dimension 64, and
+// the dense pass 19.7 instead of 17.9 ms; the LDS writes alone occupied the LDS a quarter of the
+// time, and the 32 staging registers now hold operands.)
 //
 // Softmax: fp32, base-2 exponentials with scale * log2 e folded into one FMA per
 // element.  The exponentials are taken against the current reference maximum without
@@ -34,20 +44,17 @@
 // uses the unrounded P at head dimension 128 and the rounded P at head dimension 64.
 //
 // Measured on MI355X:
-//  * With 32 query rows per wavefront every MFMA needs a fresh 1 KB operand from LDS.  The
-//    LDS reads 256 B/clk per CU (two or more wavefronts per SIMD; a lone one reaches
-//    half of that) and writes 79 B/clk; operand reads and staging writes together keep
-//    it busy about 55 % of the time at the speed reached here, the matrix cores 59 %.
+//  * With 32 query rows per wavefront every 32768 operations need a fresh 1 KB operand from LDS.
 //  * The chip is power-limited under this load: the shader clock sits near 1.7 GHz (2.4 GHz
 //    nominal), and a loop of nothing but MFMAs on random operands is held there too.  A
 //    variant that idles more runs at a higher clock and ends up at the same rate; what
 //    pays is less work per tile (instructions, LDS and memory traffic), not fewer cycles.
-//  * A lone wavefront hides only about 12 cycles of other instructions behind each
-//    32-cycle MFMA; two wavefronts on a SIMD overlap one's VALU work with the other's
+//  * A lone wavefront hides few cycles of other instructions behind its own
+//    MFMAs; two wavefronts on a SIMD overlap one's VALU work with the other's
 //    products much better, and best when each runs long homogeneous phases (products /
 //    softmax) and the one issuing products has the higher wave priority.  Interleaving
 //    softmax slices between the products of the same wavefront was 10 % slower.
-//  * 64 query rows per wavefront (every LDS operand feeding two products) needs more than
+//  * 64 query rows per wavefront (every LDS operand feeding twice as many products) needs more than
 //    the 256 registers a wavefront has at two per SIMD; with one wavefront per SIMD it
 //    loses the overlap above and was 5 % slower.  A 256-row workgroup (two query tiles
 //    sharing every staged tile, the two halves one phase apart) halved staging and L2
@@ -69,13 +76,31 @@ constexpr int kNoTile = 0x7fffffff;
 constexpr int kPrioFirstProduct = 2;
 constexpr int kPrioSecondProduct = 1;
 constexpr int kCohort = 64;   // dense: consecutive query tiles that share an XCD (and its L2) at a time
-// LDS operand reads kept in flight ahead of the products: eight where the registers allow it
-// (the dense and the plain sparse pass at head dimension 128; 0.3 % over four), six in the
-// gathering form (0.5-0.9 % over four), four elsewhere
+// LDS operands kept in flight ahead of the products: twelve where the registers allow it (the
+// unmasked passes at head dimension 128; 1.2 % less time than eight, 0.9 % than six), eight in the
+// forms with mask state, four at head dimension 64 (three to six measured within 1 %)
 constexpr int prefetch_depth(int D, int NW, int MODE) {
-  return D != 128 || NW != 4 ? 4 : MODE == kDense || MODE == kSparse ? 8 : MODE == kSparseGather ? 6 : 4;
+  return D != 128 || NW != 4 ? 4 : MODE == kProfile || MODE == kSparseExact ? 8 : 12;
 }
 constexpr unsigned kRsrcFlags = 0x00020000u;   // raw buffer, 32-bit data format (gfx9 encoding)
+
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+
+// Raw buffer descriptor as four scalar words.
+__device__ __forceinline__ u32x4 buffer_words(const void* base, unsigned bytes) {
+  const uintptr_t p = reinterpret_cast<uintptr_t>(base);
+  return u32x4{(unsigned)__builtin_amdgcn_readfirstlane((unsigned)p), (unsigned)__builtin_amdgcn_readfirstlane((unsigned)(p >> 32) & 0xffffu),
+               (unsigned)__builtin_amdgcn_readfirstlane(bytes), kRsrcFlags};
+}
+// 16 bytes per lane straight from memory into LDS, lane l at lds_address + 16 l; out of range reads
+// give zeros.  Written as assembly because the compiler, which cannot tell the two staging buffers
+// apart, puts a wait for every such load in front of the next LDS read; the one wait that is needed
+// is wait_loads_to_lds() in front of the barrier that publishes the tile.
+__device__ __forceinline__ void load_to_lds(const u32x4 rsrc, int voffset, int soffset, unsigned lds_address) {
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               :: "v"(voffset), "s"(rsrc), "s"(soffset), "s"(lds_address) : "memory", "m0");
+}
+__device__ __forceinline__ void wait_loads_to_lds() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Wavefronts per SIMD the register budget is set for.  Head dimension 128 fills 256 registers
 // (two wavefronts).  At head dimension 64 the accumulators are half as large and every form fits
@@ -91,7 +116,9 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   constexpr int BM = 32 * NW;            // query rows per workgroup = rows of a query tile
   constexpr int THREADS = 64 * NW;
   constexpr int CPR = D / 8;             // 16-byte pieces per row
-  constexpr int KB = BN / 32;            // 32-key blocks per tile
+  constexpr int QB = 2;                  // 16-query blocks per wavefront
+  constexpr int KB = BN / 16;            // 16-key blocks per tile
+  constexpr int KS = BN / 32;            // 32-key steps of the second product
   // kSparseExact is kSparse with the head's element mask applied inside every visited tile
   // kSparseGather is kSparse with k and v of the temporal heads left in token order: the rows of
   // a key tile are fetched from where the layout transformation would have taken them
@@ -99,36 +126,38 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   constexpr bool GATHER = MODE == kSparseGather;
   static_assert(!GATHER || NW == 4, "the gathering form exists for 128-row query tiles");
   constexpr bool MASKABLE = MODE == kProfile || MODE == kSparseExact;
-  constexpr int DS = D / 16;             // k-steps of the first product
-  constexpr int DB = D / 32;             // 32-row blocks of O^T
+  constexpr int DS = D / 32;             // 32-channel steps of the first product
+  constexpr int CB = D / 16;             // 16-channel blocks of O^T
   constexpr int PIECES = BN * CPR;       // 16-byte pieces of a K tile, and of a V tile
   // Staging work: every thread copies PER_THREAD pieces of K and of V, global -> registers -> LDS,
   // so all wavefronts reach the barrier with the same amount of work behind them.
   constexpr int PER_THREAD = PIECES / THREADS;
   static_assert(PIECES % THREADS == 0 && THREADS % CPR == 0, "every thread stages the same piece of whole rows");
-  // K staging: row-major, rows padded by 16 bytes so that the 16 lanes served together
-  // by a ds_read_b128 of the A operand (16 consecutive keys, same channel piece) fall on
-  // different banks, while every operand address stays base + compile-time offset.
-  constexpr int K_ROW = D * 2 + 16;
+  // K staging: row-major, the 16-byte pieces of a row XOR-swizzled with the row number (k_swizzle),
+  // which puts the same piece of 16 consecutive keys, what 16 lanes of an A operand read, on
+  // different banks.
+  constexpr int K_ROW = D * 2;
   constexpr int K_BYTES = BN * K_ROW;
   // V staging: row-major as well, not transposed.  The A operand of the second product is V^T,
   // which the transposing LDS read of gfx950 (ds_read_b64_tr_b16) delivers directly: the 16
   // lanes of a quarter wavefront read 4 rows x 16 channels (lane s: 8 bytes of row s / 4 at
   // channel 4 (s % 4)) and lane i receives channel i of the four rows.  Two such reads (rows
-  // 4 g + {0..3} and 8 + 4 g + {0..3} of a 16-key step) are one operand in the key order the
-  // weights are held in.  The 32-byte slots of a row are XOR-swizzled with the row's two low bits
-  // (v_swizzle), which puts the four rows of a quarter wavefront, and the eight row pieces of a
-  // half wavefront, on different banks; rows stay unpadded.
+  // 4 q + {0..3} and 16 + 4 q + {0..3} of a 32-key step, q = lane / 16) are one operand in the key
+  // order the weights are held in.  The 32-byte slots of a row are XOR-swizzled with the row number
+  // (v_swizzle), so that the same slot of the eight rows a half wavefront reads falls on different
+  // banks.
   constexpr int V_ROW = D * 2;
   constexpr int V_BYTES = BN * V_ROW;
   constexpr int STAGE_BYTES = K_BYTES + V_BYTES;
 
-  __shared__ __attribute__((aligned(16))) unsigned char lds[2 * STAGE_BYTES];
-  __shared__ __attribute__((aligned(16))) int key_code[MASKABLE ? 2 * BN : 4];
-  // profile: per staged tile {smallest coordinate code, largest, flags}; flags bit 0: some key
-  // is kept by every query, bit 1: some key is out of range, bit 2: coordinates span a wrap
-  __shared__ int tile_info[MASKABLE ? 2 * 4 : 4];
-  __shared__ int wg_range[4];    // profile: min / max coordinate of the workgroup's rows
+  // One block, the staged tiles first: the direct loads take a 16-bit LDS address.
+  struct Shared {
+    unsigned char tiles[2 * STAGE_BYTES];
+    int wave_range[2 * NW];    // profile: smallest and largest coordinate of each wavefront's rows
+  };
+  static_assert(2 * STAGE_BYTES <= 65536, "the direct loads take a 16-bit LDS address");
+  __shared__ __attribute__((aligned(1024))) Shared shared;
+  unsigned char* const lds = shared.tiles;
 
   // ======================================================================================
   // Which (head, row group) is this workgroup?  Consecutive logical ids are placed on the
@@ -182,57 +211,94 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int g = lane >> 5;       // which half of the wavefront
-  const int r = lane & 31;       // query column within the wave / row of the A operand
+  const int g = lane >> 4;       // which quarter of the wavefront
+  const int r = lane & 15;       // query column within a 16-query block / row of the A operand
 
   const size_t head = (size_t)bh * a.N;
 
   // ======================================================================================
-  // This lane's query row, its mask window (profile), and Q^T as the B operand.
+  // This lane's query rows (one per 16-query block), their mask windows, and Q^T as the B operand.
   // ======================================================================================
-  int qslot = grp * BM + wave * 32 + r;     // row (profile: index into rows[])
-  int qrow;
+  int qslot[QB], qrow[QB];       // row (profile: index into rows[])
   if (MODE == kProfile) {
     // The sampled rows are dealt evenly to the row groups (rows_per_group each, so that no
     // group is left with a handful of rows and idle wavefronts); a lane without a row of
     // its own shadows the group's first row and writes nothing.
-    const int in_group = wave * 32 + r;
-    const int first = min(grp * a.rows_per_group, a.t - 1);
-    qslot = in_group < a.rows_per_group ? grp * a.rows_per_group + in_group : a.t;
+    int slot[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      const int in_group = wave * 32 + qb * 16 + r;
+      qslot[qb] = in_group < a.rows_per_group ? grp * a.rows_per_group + in_group : a.t;
+      slot[qb] = qslot[qb] < a.t ? qslot[qb] : min(grp * a.rows_per_group, a.t - 1);
+    }
     // The temporal variant takes the sampled rows grouped by in-frame position, so that
     // a workgroup's rows share a narrow position range and most key tiles can be
     // skipped; results are still written at the row's own slot.
-    int slot = qslot < a.t ? qslot : first;
-    if (variant == 2) slot = a.order_t[slot];
-    if (qslot < a.t) qslot = slot;
-    qrow = a.rows[slot];
+    if (variant == 2) {
+      const int s0 = a.order_t[slot[0]], s1 = a.order_t[slot[1]];
+      slot[0] = s0;
+      slot[1] = s1;
+    }
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      if (qslot[qb] < a.t) qslot[qb] = slot[qb];
+      qrow[qb] = a.rows[slot[qb]];
+    }
   } else {
-    qrow = min(qslot, a.N - 1);
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      qslot[qb] = grp * BM + wave * 32 + qb * 16 + r;
+      qrow[qb] = min(qslot[qb], a.N - 1);
+    }
   }
 
-  // profile: a key with code c is kept iff (unsigned)(c - win_lo) <= win_span or c == kCodeKeep
-  int win_lo = 0;
-  unsigned win_span = 0x7ffffffeu;
-  if (MODE == kProfile) {
-    if (tid == 0) {
-      wg_range[0] = 0x7fffffff;
-      wg_range[1] = -1;
-    }
-    __syncthreads();
-    if (variant != 0 && qrow >= a.off && qrow < a.video_end) {
-      const int vq = qrow - a.off;
-      const int fq = vq / a.P;
-      const int c = variant == 1 ? fq : vq - fq * a.P;
-      const int w = variant == 1 ? a.w_s : a.w_t;
-      win_lo = c - w;
-      win_span = 2u * (unsigned)w;
-      atomicMin(&wg_range[0], c);
-      atomicMax(&wg_range[1], c);
-    }
+  // Element masks.  In the order the keys are read in, a row keeps one run of keys beside those every
+  // row keeps (rows below keep_head: text prefix and first-frame sink; rows from video_end on:
+  // text suffix): [win_lo, win_hi) in key rows, because both patterns group consecutive rows, frames
+  // (P rows) for a spatial head, positions (F rows, F - 1 behind the sink block) for a temporal
+  // head in P-outer order.  Only the temporal profiling pass, which reads the keys in F-outer order,
+  // has such a run in every frame: there the window is in in-frame positions.
+  const int keep_head = a.sink ? a.off + a.P : a.off;
+  const bool by_position = MODE == kProfile && variant == 2;
+  int win_lo[QB], win_hi[QB];
+  auto row_window = [&](int c, int groups, int w, int base, int unit, int& lo, int& hi) {
+    w = min(w, groups);
+    lo = base + max(0, c - w) * unit;
+    hi = base + min(groups, c + w + 1) * unit;
+  };
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {      // a text query keeps everything
+    win_lo[qb] = 0;
+    win_hi[qb] = by_position ? a.P : a.N;
+  }
+  int c_lo = 0x7fffffff, c_hi = -1;      // profile: smallest and largest coordinate of the workgroup's rows
+  if (MODE == kProfile && masked) {
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb)
+      if (qrow[qb] >= a.off && qrow[qb] < a.video_end) {
+        const int vq = qrow[qb] - a.off;
+        const int fq = vq / a.P;
+        const int c = variant == 1 ? fq : vq - fq * a.P;
+        if (variant == 1) row_window(c, a.F, a.w_s, a.off, a.P, win_lo[qb], win_hi[qb]);
+        else row_window(c, a.P, a.w_t, 0, 1, win_lo[qb], win_hi[qb]);
+        c_lo = min(c_lo, c);
+        c_hi = max(c_hi, c);
+      }
     // (a text query attends to everything under both masks, so its masked outputs equal
     // the unmasked one by definition: it adds nothing to either error, the error kernel
     // skips it, and it need not widen this workgroup's key range)
+    // reduced inside the wavefronts first: LDS atomics of all 64 lanes on one address are expanded into
+    // a loop over the lanes, 1 us per atomic at the start of every workgroup
+    shared.wave_range[2 * wave] = quad_rows_min(c_lo);
+    shared.wave_range[2 * wave + 1] = -quad_rows_min(-c_hi);
     __syncthreads();
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      c_lo = min(c_lo, shared.wave_range[2 * w]);
+      c_hi = max(c_hi, shared.wave_range[2 * w + 1]);
+    }
+    c_lo = __builtin_amdgcn_readfirstlane(c_lo);
+    c_hi = __builtin_amdgcn_readfirstlane(c_hi);
   }
 
   // sparse: this head's pattern; with q and o kept in token order, the row of a temporal
@@ -244,29 +310,42 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   const bool kv_copy = SPARSE && __builtin_amdgcn_readfirstlane(pat) != 0 && a.k_t != nullptr;
   const __bf16* kh = (kv_copy ? a.k_t : a.k) + head * D;
   const __bf16* vh = (kv_copy ? a.v_t : a.v) + head * D;
-  int io_row = qrow;
-  if (SPARSE && a.qo_token_order && pat && qrow >= a.off && qrow < a.video_end)
-    io_row = a.off + (int)transformed_to_token((unsigned)(qrow - a.off), (unsigned)a.F, (unsigned)a.P, a.sink);
-  if (MODE == kSparseExact && qrow >= a.off && qrow < a.video_end) {
-    // element mask of the head's pattern in the order its tile list refers to: a spatial head
-    // compares frames (coordinate = row / P), a temporal head in P-outer order compares in-frame
-    // positions (coordinate = row / F); text queries keep the default window (everything)
-    int cq = (qrow - a.off) / a.P;
-    if (pat) {
-      unsigned pq;
-      transformed_to_token((unsigned)(qrow - a.off), (unsigned)a.F, (unsigned)a.P, a.sink, &pq);
-      cq = (int)pq;
+  int io_row[QB];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    const int n = qrow[qb];
+    const bool video = n >= a.off && n < a.video_end;
+    io_row[qb] = n;
+    if (SPARSE && a.qo_token_order && pat && video)
+      io_row[qb] = a.off + (int)transformed_to_token((unsigned)(n - a.off), (unsigned)a.F, (unsigned)a.P, a.sink);
+    if (MODE == kSparseExact && video) {
+      // the window of the head's pattern in the order its tile list refers to
+      if (pat) {
+        unsigned pq;
+        transformed_to_token((unsigned)(n - a.off), (unsigned)a.F, (unsigned)a.P, a.sink, &pq);
+        row_window((int)pq, a.P, a.w_t, keep_head, a.sink ? a.F - 1 : a.F, win_lo[qb], win_hi[qb]);
+      } else {
+        row_window((n - a.off) / a.P, a.F, a.w_s, a.off, a.P, win_lo[qb], win_hi[qb]);
+      }
     }
-    const int w = pat ? a.w_t : a.w_s;
-    win_lo = cq - w;
-    win_span = 2u * (unsigned)w;
   }
 
-  bf16x8 qreg[DS];     // lane (g, r) holds Q[qrow][16 s + 8 g .. +8]
-  {
-    const __bf16* qp = a.q + (head + io_row) * D + g * 8;
+  // smallest and largest window bounds over the rows of the wavefront: most tiles lie inside every
+  // row's window or outside all of them, which these decide without a look at the rows
+  int lo_min = 0, lo_max = 0, hi_min = 0, hi_max = 0;
+  if (MASKABLE) {
+    lo_min = quad_rows_min(min(win_lo[0], win_lo[1]));
+    lo_max = -quad_rows_min(-max(win_lo[0], win_lo[1]));
+    hi_min = quad_rows_min(min(win_hi[0], win_hi[1]));
+    hi_max = -quad_rows_min(-max(win_hi[0], win_hi[1]));
+  }
+
+  bf16x8 qreg[QB][DS];     // lane (g, r) holds Q[row 16 qb + r][32 s + 8 g .. +8]
 #pragma unroll
-    for (int s = 0; s < DS; ++s) qreg[s] = *reinterpret_cast<const bf16x8*>(qp + s * 16);
+  for (int qb = 0; qb < QB; ++qb) {
+    const __bf16* qp = a.q + (head + io_row[qb]) * D + g * 8;
+#pragma unroll
+    for (int s = 0; s < DS; ++s) qreg[qb][s] = *reinterpret_cast<const bf16x8*>(qp + s * 32);
   }
 
   // ======================================================================================
@@ -299,7 +378,6 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   } else if (MODE == kDense) {
     lend = a.nk;
   }
-  const int c_lo = MODE == kProfile ? wg_range[0] : 0, c_hi = MODE == kProfile ? wg_range[1] : -1;
   int pseg = 0, pj = 0, pjb = -1;
   auto profile_segment = [&](int sidx, int& k0, int& k1) -> bool {   // false: no more segments
     if (variant == 0) {      // unmasked pass: the key tiles of part chunk
@@ -406,30 +484,33 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   // ======================================================================================
   // Staging of one K/V tile.
   // ======================================================================================
-  u32x4 kst[PER_THREAD], vst[PER_THREAD];     // this thread's pieces of K and of V
-
+  // The copy is done by the load unit (buffer_load_dwordx4 ... lds): lane l of a wavefront's load
+  // lands at the load's LDS address + 16 l, so piece u = tid + THREADS i of the LDS image is thread
+  // tid's i-th load, and the swizzles below are applied on the memory side: the lane fetches the
+  // piece of its row that belongs at that place.  No staging registers, no LDS write instructions.
+  //
   // The descriptor of a tile starts at the tile's first key row and covers the rows up to
   // N, so the per-thread offsets are loop invariant, no clamping arithmetic is needed, and
-  // rows beyond N (ragged last tile) read as zero.  A thread stages piece tid % CPR of PER_THREAD
-  // rows: rows tid / CPR + i (THREADS / CPR), so that a wavefront's load covers consecutive rows,
-  // or, in the gathering form, where the rows come from anywhere, the consecutive rows
-  // PER_THREAD (tid / CPR) + i, whose row numbers one load fetches.
-  constexpr int ROW_STEP = GATHER ? 1 : THREADS / CPR;
-  const int stage_row = (tid / CPR) * (GATHER ? PER_THREAD : 1), stage_piece = tid % CPR;
-  const int stage_off = (stage_row * D + stage_piece * 8) * 2;
-  // 32-byte slot s of V row n sits at slot s ^ v_swizzle(n) of the row in LDS
-  auto v_swizzle = [](int n) { const int j = n & 3; return D == 128 ? (2 * j) ^ (j >> 1) : j; };
-  const int k_lds_off = stage_row * K_ROW + (stage_piece << 4);
-  int v_lds_off[PER_THREAD];
-#pragma unroll
-  for (int i = 0; i < PER_THREAD; ++i)
-    v_lds_off[i] = (stage_row + i * ROW_STEP) * V_ROW + (((stage_piece >> 1) ^ v_swizzle(stage_row + i * ROW_STEP)) << 5) + ((stage_piece & 1) << 4);
+  // rows beyond N (ragged last tile) read as zero.
+  constexpr int ROW_STEP = THREADS / CPR;
+  const int stage_row = tid / CPR, stage_piece = tid % CPR;      // row stage_row + ROW_STEP i of the tile
+  // In LDS, 16-byte piece p of K row n sits at piece p ^ k_swizzle(n) of the row and 32-byte slot s
+  // of V row n at slot s ^ v_swizzle(n) (head dimension 64: two rows share the 64 banks)
+  auto k_swizzle = [](int n) { return D == 128 ? n & 15 : (n >> 1) & 7; };
+  auto v_swizzle = [](int n) { return D == 128 ? n & 7 : (n >> 1) & 3; };
+  auto k_piece = [&](int i) { return stage_piece ^ k_swizzle(stage_row + i * ROW_STEP); };
+  auto v_piece = [&](int i) { return stage_piece ^ (v_swizzle(stage_row + i * ROW_STEP) << 1); };
+  // 128-row query tiles: ROW_STEP is a multiple of the swizzles' period, every i has the same piece
+  constexpr bool SAME_PIECE = NW == 4;
+  static_assert(!SAME_PIECE || ROW_STEP % 16 == 0, "the swizzles repeat every 16 rows");
+  const unsigned lds_wave = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lds_byte*)lds + wave * 1024);
 
   // Gathering form: every K/V row is fetched through a table of source rows.  For a temporal
   // head row v of the P-outer order is token row_table[entries + v] (Sec. 4.2; text rows map to
   // themselves); a spatial head uses the identity half row_table[v], so that both kinds run the
   // same instructions.  Rows beyond N map to a row outside the tensor, which the bounds-checked
-  // loads return as zero.  The entries of a tile are loaded one tile ahead of its K/V rows; a
+  // loads return as zero.  The entries of a tile are loaded one tile ahead of its K/V rows, a
+  // thread's PER_THREAD entries in one load (the table keeps them together, row_table_kernel); a
   // row is 2 D contiguous bytes, so the loads stay whole cache lines.
   const int tab_base = GATHER && pat != 0 ? a.nk * BN * 4 : 0;
   int tab[GATHER ? PER_THREAD : 1];
@@ -438,125 +519,67 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
     const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<int32_t*>(a.row_table), 0, 2u * (unsigned)a.nk * BN * 4u, kRsrcFlags);
     if constexpr (GATHER && PER_THREAD == 4) {
-      const u32x4 e = __builtin_amdgcn_raw_buffer_load_b128(rt, stage_row * 4, tab_base + key0 * 4, 0);
+      const u32x4 e = __builtin_amdgcn_raw_buffer_load_b128(rt, stage_row * 16, tab_base + key0 * 4, 0);
 #pragma unroll
       for (int i = 0; i < 4; ++i) tab[i] = (int)e[i];
     } else if constexpr (GATHER) {
       static_assert(!GATHER || PER_THREAD == 4 || PER_THREAD == 2, "one load fetches a thread's row numbers");
-      const u32x2 e = __builtin_amdgcn_raw_buffer_load_b64(rt, stage_row * 4, tab_base + key0 * 4, 0);
+      const u32x2 e = __builtin_amdgcn_raw_buffer_load_b64(rt, stage_row * 8, tab_base + key0 * 4, 0);
       tab[0] = (int)e[0];
       tab[1] = (int)e[1];
     }
   };
 
-  auto load_tile = [&](int col_any) {
+  auto load_tile = [&](int buf, int col_any) {
+    const unsigned kdst = lds_wave + buf * STAGE_BYTES, vdst = kdst + K_BYTES;
     if constexpr (GATHER) {
       const unsigned head_bytes = (unsigned)a.N * (D * 2);
-      const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(kh), 0, head_bytes, kRsrcFlags);
-      const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(const_cast<__bf16*>(vh), 0, head_bytes, kRsrcFlags);
+      const u32x4 rk = buffer_words(kh, head_bytes), rv = buffer_words(vh, head_bytes);
 #pragma unroll
       for (int i = 0; i < PER_THREAD; ++i)
-        kst[i] = __builtin_amdgcn_raw_buffer_load_b128(rk, tab[i] * (D * 2) + stage_piece * 16, 0, 0);
+        load_to_lds(rk, tab[i] * (D * 2) + k_piece(i) * 16, 0, kdst + i * THREADS * 16);
 #pragma unroll
       for (int i = 0; i < PER_THREAD; ++i)
-        vst[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, tab[i] * (D * 2) + stage_piece * 16, 0, 0);
+        load_to_lds(rv, tab[i] * (D * 2) + v_piece(i) * 16, 0, vdst + i * THREADS * 16);
       return;
     }
     // the tile index is the same in every lane; saying so keeps the descriptors scalar
     const int key0 = __builtin_amdgcn_readfirstlane(col_any) * BN;
     const unsigned bytes_left = (unsigned)(a.N - key0) * (D * 2);
-    const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<__bf16*>(kh + (size_t)key0 * D), 0, bytes_left, kRsrcFlags);
-    const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<__bf16*>(vh + (size_t)key0 * D), 0, bytes_left, kRsrcFlags);
+    const u32x4 rk = buffer_words(kh + (size_t)key0 * D, bytes_left), rv = buffer_words(vh + (size_t)key0 * D, bytes_left);
+    auto offset = [&](int piece, int i) { return stage_row * (D * 2) + piece * 16 + (SAME_PIECE ? 0 : i * ROW_STEP * (D * 2)); };
 #pragma unroll
     for (int i = 0; i < PER_THREAD; ++i)
-      kst[i] = __builtin_amdgcn_raw_buffer_load_b128(rk, stage_off + i * ROW_STEP * (D * 2), 0, 0);
+      load_to_lds(rk, offset(k_piece(i), i), SAME_PIECE ? i * ROW_STEP * (D * 2) : 0, kdst + i * THREADS * 16);
 #pragma unroll
     for (int i = 0; i < PER_THREAD; ++i)
-      vst[i] = __builtin_amdgcn_raw_buffer_load_b128(rv, stage_off + i * ROW_STEP * (D * 2), 0, 0);
-  };
-
-  auto store_tile = [&](int buf, int col) {
-    unsigned char* kb = lds + buf * STAGE_BYTES;
-    unsigned char* vb = kb + K_BYTES;
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i)
-      *reinterpret_cast<u32x4*>(kb + k_lds_off + i * ROW_STEP * K_ROW) = kst[i];
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i)
-      *reinterpret_cast<u32x4*>(vb + v_lds_off[i]) = vst[i];
-    if (MASKABLE && masked && tid < BN) {
-      // per-key mask code: the key's frame (spatial) or in-frame position (temporal), or
-      // "kept by every query" (text / sink key, unmasked pass), or "out of range"
-      const int key = col * BN + tid;
-      int code;
-      if (key >= a.N) {
-        code = kCodeDrop;
-      } else if ((MODE == kProfile && variant == 0) || key < a.off || key >= a.video_end) {
-        code = kCodeKeep;
-      } else if (MODE == kSparseExact) {
-        // spatial: the key's frame; temporal (transformed order): its in-frame position
-        unsigned pk, fk;
-        if (pat) {
-          transformed_to_token((unsigned)(key - a.off), (unsigned)a.F, (unsigned)a.P, a.sink, &pk, &fk);
-        } else {
-          fk = (unsigned)(key - a.off) / (unsigned)a.P;
-          pk = fk;
-        }
-        code = (int)pk;
-        if (a.sink && fk == 0) code = kCodeKeep;
-      } else {
-        const int vk = key - a.off;
-        const int fk = vk / a.P;
-        code = variant == 1 ? fk : vk - fk * a.P;
-        if (a.sink && fk == 0) code = kCodeKeep;
-      }
-      key_code[buf * BN + tid] = code;
-      // Summary of the tile for the wave-uniform shortcuts in the masking step.  The
-      // coordinate codes of consecutive keys ascend (frames) or ascend by one with a
-      // wrap at frame ends (positions), so first and last coordinate lane bound them.
-      const bool is_coord = code != kCodeKeep && code != kCodeDrop;
-      const unsigned long long coord_lanes = __builtin_amdgcn_ballot_w64(is_coord);
-      int flags = (__builtin_amdgcn_ballot_w64(code == kCodeKeep) != 0 ? 1 : 0) |
-                  (__builtin_amdgcn_ballot_w64(code == kCodeDrop) != 0 ? 2 : 0);
-      int cmin = 0, cmax = -1;          // empty coordinate range
-      if (coord_lanes != 0) {
-        const int first = __builtin_ctzll(coord_lanes), last = 63 - __builtin_clzll(coord_lanes);
-        cmin = __builtin_amdgcn_readlane(code, first);
-        cmax = __builtin_amdgcn_readlane(code, last);
-        // (positions in frame-major order wrap at frame ends; the coordinates of the exact
-        // sparse form never decrease, so first and last always bound them)
-        if (MODE == kProfile && variant == 2 && cmax - cmin != last - first) flags |= 4;    // wrapped: treat as mixed
-      }
-      if (tid == 0) {
-        tile_info[buf * 4 + 0] = cmin;
-        tile_info[buf * 4 + 1] = cmax;
-        tile_info[buf * 4 + 2] = flags;
-      }
-    }
+      load_to_lds(rv, offset(v_piece(i), i), SAME_PIECE ? i * ROW_STEP * (D * 2) : 0, vdst + i * THREADS * 16);
   };
 
   // ======================================================================================
   // Main loop.
   // ======================================================================================
-  f32x16 oacc[DB];
+  f32x4 oacc[CB][QB];
 #pragma unroll
-  for (int db = 0; db < DB; ++db)
+  for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) oacc[db][e] = 0.f;
-  float m_run = kNegBig;   // reference maximum (raw logits, before scaling)
-  float l_run = 0.f;       // this lane's share of the running row sum
+    for (int qb = 0; qb < QB; ++qb) oacc[cb][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m_run[QB], l_run[QB];      // reference maximum (raw logits, before scaling), this lane's share of the running row sum
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    m_run[qb] = kNegBig;
+    l_run[qb] = 0.f;
+  }
 
   // a ring holds the current tile and the next three, so no scalar load sits between one
   // tile's barrier and the next tile's global loads
   int col = next_tile(), col1 = next_tile(), col2 = next_tile(), col3 = next_tile();
   if (col != kNoTile) {
     if (GATHER) load_table(col);
-    load_tile(col);
-    store_tile(0, col);
+    load_tile(0, col);
   }
   if (GATHER && col1 != kNoTile) load_table(col1);
+  wait_loads_to_lds();
   __syncthreads();
 
   // Touch Q here so that its loads are known to have completed before the loop.  Without
@@ -564,86 +587,127 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   // and emits vmcnt waits in front of the first products of every iteration, which then
   // wait for the NEXT tile's freshly issued global loads instead.
 #pragma unroll
-  for (int s = 0; s < DS; ++s) asm volatile("" ::"v"(qreg[s]));
+  for (int s = 0; s < DS; ++s) asm volatile("" ::"v"(qreg[0][s]), "v"(qreg[1][s]));
 
   int buf = 0;
-  // V^T operand reads: this lane's source address inside a 16-key step for channel block db.  As
-  // a source lane of the transposing read, lane 16 q + s of the wavefront (q = 2 g + h) supplies
-  // the 8 bytes of row 4 g + s / 4 at channel 32 db + 16 h + 4 (s % 4).
-  int v_off[DB];
+  // Operand reads.  K: lane (g, r) reads piece 4 s + g of row r of a 16-key block.  V^T: as a source
+  // lane of the transposing read, lane 16 g + s supplies the 8 bytes of row 4 g + s / 4 of a 16-key
+  // half step at channel 16 cb + 4 (s % 4).
+  int k_off[DS], v_off[CB];
   {
-    const int s = lane & 15, j = s >> 2, h = (lane >> 4) & 1;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
-      v_off[db] = (4 * g + j) * V_ROW + (((2 * db + h) ^ v_swizzle(j)) << 5) + ((s & 3) << 3);
+    for (int s = 0; s < DS; ++s) k_off[s] = r * K_ROW + (((4 * s + g) ^ k_swizzle(r)) << 4);
+    const int row = 4 * g + (r >> 2);
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) v_off[cb] = row * V_ROW + ((cb ^ v_swizzle(row)) << 5) + ((r & 3) << 3);
   }
   const bool ragged = (a.N % BN) != 0;
+  int pos_tile = 0, pos_first = -a.off;      // temporal profiling pass: a tile and its first key's in-frame position
 
   while (col != kNoTile) {
     const int next_col = col1;
     col1 = col2;
     col2 = col3;
     fetch_begin();
-    if (next_col != kNoTile) load_tile(next_col);
+    if (next_col != kNoTile) load_tile(buf ^ 1, next_col);
     if (GATHER && col1 != kNoTile) load_table(col1);      // entries of the tile after it
     const int tile = col;          // key tile of this iteration
 
-    // profile: does this wavefront need the tile at all, and does it need per-element masks?
-    // (a lane whose row keeps none of the tile's keys while other lanes do needs no element masks
+    // masked: does this wavefront need the tile at all, and does it need per-element masks?
+    // (a row that keeps none of the tile's keys while others do needs no element masks
     // either: it takes its exponentials against +inf, i.e. all weights zero)
-    bool skip = false, need_masks = MASKABLE && masked, drop_lane = false;
+    bool skip = false, need_masks = false, drop[QB] = {false, false};
+    unsigned long long keep[QB];       // mixed tiles: bit n = the row keeps the tile's n-th key
     if (MASKABLE && masked) {
-      const int cmin = tile_info[buf * 4 + 0], cmax = tile_info[buf * 4 + 1], flags = tile_info[buf * 4 + 2];
-      bool lane_all = (flags & 6) == 0, lane_none = (flags & 5) == 0;
-      if (cmax >= cmin) {       // the tile has coordinate keys
-        const bool in_lo = (unsigned)(cmin - win_lo) <= win_span;
-        const bool in_hi = (unsigned)(cmax - win_lo) <= win_span;
-        lane_all = lane_all && in_lo && in_hi;
-        // disjoint: the whole range lies below or above this row's window
-        const long long lo = win_lo, hi = lo + (long long)win_span;
-        lane_none = lane_none && (cmax < lo || cmin > hi);
+      const int k0 = __builtin_amdgcn_readfirstlane(tile) * BN, k1 = k0 + BN;
+      const bool special = k0 < keep_head || k1 > a.video_end;   // some key is kept by every row, or lies beyond N
+      int first = k0;              // the tile's first key in the coordinate of the windows
+      if (by_position) {
+        // its in-frame position: the tiles of a pass ascend, by less than a frame except at its start
+        pos_first += (tile - pos_tile) * BN;
+        pos_tile = tile;
+        if (pos_first >= a.P) pos_first -= a.P;
+        if (pos_first >= a.P) pos_first = (int)((unsigned)pos_first % (unsigned)a.P);
+        first = pos_first;
       }
-      skip = __builtin_amdgcn_ballot_w64(!lane_none) == 0;   // no row of this wave keeps any key
-      need_masks = __builtin_amdgcn_ballot_w64(!lane_all && !lane_none) != 0;   // some row keeps a part of them
-      drop_lane = !need_masks && lane_none;
+      bool all = false, none = false;
+      if (special) {
+        all = k1 <= keep_head || (k0 >= a.video_end && k1 <= a.N);
+      } else if (!by_position || first + BN <= a.P) {
+        all = first >= lo_max && first + BN <= hi_min;
+        none = first + BN <= lo_min || first >= hi_max;
+      } else if (first + BN <= 2 * a.P) {        // the end of one frame and the start of the next
+        none = first >= hi_max && first + BN - a.P <= lo_min;
+      }
+      skip = none;
+      if (!all && !none) {
+        auto ones = [](int n) -> unsigned long long {      // the n lowest bits
+          n = min(max(n, 0), 64);
+          return n == 0 ? 0ull : ~0ull >> (64 - n);
+        };
+        const unsigned long long full = ones(BN), in_range = ones(a.N - k0) & full;
+        const unsigned long long always = (ones(keep_head - k0) | ~ones(a.video_end - k0)) & in_range;
+        bool any_kept = false, any_part = false;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+          unsigned long long m = 0;
+          // (by position: one window in every frame the tile touches)
+          int f = first;
+#pragma unroll 1
+          do {
+            m |= ones(win_hi[qb] - f) & ~ones(win_lo[qb] - f);
+            f -= a.P;
+          } while (by_position && f + BN > 0);
+          keep[qb] = (m & in_range) | always;
+          any_kept = any_kept || keep[qb] != 0;
+          any_part = any_part || (keep[qb] != 0 && keep[qb] != full);
+        }
+        skip = __builtin_amdgcn_ballot_w64(any_kept) == 0;         // no row of this wave keeps any key
+        need_masks = __builtin_amdgcn_ballot_w64(any_part) != 0;   // some row keeps a part of them
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+          drop[qb] = !need_masks && keep[qb] == 0;
+          keep[qb] >>= 4 * g;        // this lane's keys are 16 kb + 4 g + i
+        }
+      }
     }
 
     if (!skip) {
       const unsigned char* kbuf = lds + buf * STAGE_BYTES;
       const unsigned char* vbuf = kbuf + K_BYTES;
 
-      // ---- S^T = K Q^T.  Operand reads run PF products ahead of their use (a rolling
+      // ---- S^T = K Q^T.  Operand reads run PF operands ahead of their use (a rolling
       // window of PF operand registers), so after the first few the LDS latency is hidden
       // behind the MFMAs; the scheduling barriers pin the read / product interleave.
       constexpr int PF = prefetch_depth(D, NW, MODE);
-      constexpr int NS = KB * DS;          // operands of the first product, order (kb, s)
-      constexpr int NV = KB * 2 * DB;      // operands of the second product, order (kb, kk, db)
+      constexpr int NS = KB * DS;          // operands of the first product, order (pair of kb, s, kb in the pair)
+      constexpr int NV = KS * CB;          // operands of the second product, order (ks, cb)
+      auto k_block = [](int i) { return (i / (2 * DS)) * 2 + (i & 1); };
+      auto k_step = [](int i) { return (i >> 1) % DS; };
       auto k_operand = [&](int i) -> bf16x8 {
-        const int kb = i / DS, s = i % DS;
-        return *reinterpret_cast<const bf16x8*>(kbuf + (kb * 32 + r) * K_ROW + ((2 * s + g) << 4));
+        return *reinterpret_cast<const bf16x8*>(kbuf + k_block(i) * 16 * K_ROW + k_off[k_step(i)]);
       };
       auto v_operand = [&](int i) -> bf16x8 {
-        const int step = i / DB, db = i % DB;     // step = kb * 2 + kk: rows 16 step .. 16 step + 15
-        const unsigned char* src = vbuf + step * 16 * V_ROW + v_off[db];
+        const unsigned char* src = vbuf + (i / CB) * 32 * V_ROW + v_off[i % CB];
         const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)src);
-        const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(src + 8 * V_ROW));
+        const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(src + 16 * V_ROW));
         return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
       };
-      f32x16 sacc[KB];
+      f32x4 sacc[KB][QB];
       bf16x8 opnd[PF];
 #pragma unroll
       for (int i = 0; i < PF; ++i) opnd[i] = k_operand(i);
       __builtin_amdgcn_s_setprio(kPrioFirstProduct);
 #pragma unroll
       for (int i = 0; i < NS; ++i) {
-        const int kb = i / DS, s = i % DS;
+        const int kb = k_block(i), s = k_step(i);
         const bf16x8 ka = opnd[i % PF];
         __builtin_amdgcn_sched_barrier(0);
-        if (s == 0) {
 #pragma unroll
-          for (int e = 0; e < 16; ++e) sacc[kb][e] = 0.f;
+        for (int qb = 0; qb < QB; ++qb) {
+          if (s == 0) sacc[kb][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+          sacc[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qreg[qb][s], sacc[kb][qb], 0, 0, 0);
         }
-        sacc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka, qreg[s], sacc[kb], 0, 0, 0);
         // refill the slot just consumed: next K operand, or (at the tail) the first V^T
         // operands, which then arrive while the softmax runs
         if (i + PF < NS) opnd[i % PF] = k_operand(i + PF);
@@ -652,23 +716,21 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
       }
 
       __builtin_amdgcn_s_setprio(0);
-      // ---- masking.  sacc[kb][4 i + jj] belongs to key  col*BN + 32 kb + 8 i + 4 g + jj.
+      // ---- masking.  sacc[kb][qb][i] belongs to key  col*BN + 16 kb + 4 g + i.
       if (MASKABLE && masked) {
         if (need_masks) {
 #pragma unroll
-          for (int kb = 0; kb < KB; ++kb)
+          for (int qb = 0; qb < QB; ++qb) {
+            const unsigned word[2] = {(unsigned)keep[qb], (unsigned)(keep[qb] >> 32)};
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const i32x4 cc = *reinterpret_cast<const i32x4*>(&key_code[buf * BN + kb * 32 + 8 * i + 4 * g]);
+            for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-              for (int jj = 0; jj < 4; ++jj) {
-                const bool keep = ((unsigned)(cc[jj] - win_lo) <= win_span) || cc[jj] == kCodeKeep;
-                if (!keep) sacc[kb][4 * i + jj] = -INFINITY;
-              }
-            }
+              for (int i = 0; i < 4; ++i)
+                if (!(word[kb >> 1] & (1u << (16 * (kb & 1) + i)))) sacc[kb][qb][i] = -INFINITY;
+          }
         }
       } else if (ragged && col == a.nk - 1) {
-        int lim = a.N - tile * BN - 4 * g;     // keys with 32 kb + 8 i + jj >= lim are out of range
+        int lim = a.N - tile * BN - 4 * g;     // keys with 16 kb + i >= lim are out of range
         // opaque to the optimiser: keeps this rarely taken masking code inside the
         // branch instead of being speculated into every tile
         asm volatile("" : "+v"(lim));
@@ -676,11 +738,12 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
         for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
           for (int i = 0; i < 4; ++i)
+            if (kb * 16 + i >= lim) {
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj)
-              if (kb * 32 + 8 * i + jj >= lim) sacc[kb][4 * i + jj] = -INFINITY;
+              for (int qb = 0; qb < QB; ++qb) sacc[kb][qb][i] = -INFINITY;
+            }
       }
-      // ---- online softmax: one query per lane.
+      // ---- online softmax: two queries per lane.
       // Fast path: exponentials are taken against the current reference m_run without
       // looking at the tile's maximum.  That is the same softmax as long as nothing
       // overflows, which the row sum reveals: if any lane's partial sum exceeds
@@ -689,113 +752,108 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
       // the tile's exponentials.  With a reference within 2^13 of the true maximum the
       // fp32 sums and bf16 weights lose nothing, and almost every tile after the first
       // few stays on the fast path (no max reduction, no rescale).
-      bf16x8 pb[KB][2];
-      auto exponentiate = [&](float mc) -> float {
+      bf16x8 pb[KS][QB];
+      auto exponentiate = [&](int qb, float mc) -> float {
         float l_loc = 0.f;
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
+        for (int ks = 0; ks < KS; ++ks) {
+          f32x8 p;
 #pragma unroll
-          for (int kk = 0; kk < 2; ++kk) {
-            f32x8 p;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[kb][8 * kk + e], a.scale_log2, -mc));
-              if (D != 64) l_loc += p[e];
-            }
-            pb[kb][kk] = __builtin_convertvector(p, bf16x8);
-            if (D == 64) {
-              // Head dimension 64 is bound by the softmax's VALU work, so the row sum is taken two
-              // weights per instruction: dot products of the packed pairs with (1, 1), i.e. over
-              // the ROUNDED weights.  (At D = 128 this was slower: the dot products run on the
-              // matrix pipeline and compete with the MFMAs there.)  The pairs are taken by vector
-              // shuffles: extracted as 32-bit words of the bit-cast vector, the compiler fed all
-              // four dot products the same register.
-              const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-              const bf16x8 pv = pb[kb][kk];
-              l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 0, 1), ones, l_loc, false);
-              l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 2, 3), ones, l_loc, false);
-              l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 4, 5), ones, l_loc, false);
-              l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 6, 7), ones, l_loc, false);
-            }
+          for (int e = 0; e < 8; ++e) {
+            p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[2 * ks + (e >> 2)][qb][e & 3], a.scale_log2, -mc));
+            if (D != 64) l_loc += p[e];
           }
+          pb[ks][qb] = __builtin_convertvector(p, bf16x8);
+          if (D == 64) {
+            // Head dimension 64 is bound by the softmax's VALU work, so the row sum is taken two
+            // weights per instruction: dot products of the packed pairs with (1, 1), i.e. over
+            // the ROUNDED weights.  (At D = 128 this was slower: the dot products run on the
+            // matrix pipeline and compete with the MFMAs there.)  The pairs are taken by vector
+            // shuffles: extracted as 32-bit words of the bit-cast vector, the compiler fed all
+            // four dot products the same register.
+            const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+            const bf16x8 pv = pb[ks][qb];
+            l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 0, 1), ones, l_loc, false);
+            l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 2, 3), ones, l_loc, false);
+            l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 4, 5), ones, l_loc, false);
+            l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 6, 7), ones, l_loc, false);
+          }
+        }
         return l_loc;
       };
-      float l_loc = exponentiate(MASKABLE && drop_lane ? INFINITY : m_run * a.scale_log2);
-      if (__builtin_amdgcn_ballot_w64(!(l_loc <= kLazySum)) != 0) {
-        float m_loc = sacc[0][0];
+      float l_loc[QB];
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
+      for (int qb = 0; qb < QB; ++qb)
+        l_loc[qb] = exponentiate(qb, MASKABLE && drop[qb] ? INFINITY : m_run[qb] * a.scale_log2);
+      if (__builtin_amdgcn_ballot_w64(!(l_loc[0] <= kLazySum && l_loc[1] <= kLazySum)) != 0) {
 #pragma unroll
-          for (int e = 0; e < 16; ++e) m_loc = fmaxf(m_loc, sacc[kb][e]);
-        m_loc = both_halves_max(m_loc);
-        if (MASKABLE && drop_lane) m_loc = -INFINITY;
-        const float m_new = fmaxf(m_run, m_loc);
-        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * a.scale_log2);
-        m_run = m_new;
-        l_run *= alpha;
+        for (int qb = 0; qb < QB; ++qb) {
+          float m_loc = sacc[0][qb][0];
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+          for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
-        l_loc = exponentiate(MASKABLE && drop_lane ? INFINITY : m_new * a.scale_log2);
+            for (int e = 0; e < 4; ++e) m_loc = fmaxf(m_loc, sacc[kb][qb][e]);
+          m_loc = quarters_max(m_loc);
+          if (MASKABLE && drop[qb]) m_loc = -INFINITY;
+          const float m_new = fmaxf(m_run[qb], m_loc);
+          const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_new) * a.scale_log2);
+          m_run[qb] = m_new;
+          l_run[qb] *= alpha;
+#pragma unroll
+          for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) oacc[cb][qb][e] *= alpha;
+          l_loc[qb] = exponentiate(qb, MASKABLE && drop[qb] ? INFINITY : m_new * a.scale_log2);
+        }
       }
-      l_run += l_loc;
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) l_run[qb] += l_loc[qb];
 
       // ---- O^T += V^T P^T.  The first PF operands were requested at the end of the first
       // product (slot (NS + i) % PF).
       __builtin_amdgcn_s_setprio(kPrioSecondProduct);
 #pragma unroll
       for (int i = 0; i < NV; ++i) {
-        const int kbkk = i / DB, db = i % DB;
+        const int ks = i / CB, cb = i % CB;
         const bf16x8 va = opnd[(NS + i) % PF];
         __builtin_amdgcn_sched_barrier(0);
-        oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[kbkk >> 1][kbkk & 1], oacc[db], 0, 0, 0);
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+          oacc[cb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb[ks][qb], oacc[cb][qb], 0, 0, 0);
         if (i + PF < NV) opnd[(NS + i) % PF] = v_operand(i + PF);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
 
     __builtin_amdgcn_s_setprio(0);
-    if (next_col != kNoTile) store_tile(buf ^ 1, next_col);
     col3 = fetch_end();
+    wait_loads_to_lds();
     __syncthreads();
     buf ^= 1;
     col = next_col;
   }
 
   // ======================================================================================
-  // Epilogue: normalise and store.  oacc[db][4 i + jj] = O[query r][32 db + 8 i + 4 g + jj]
+  // Epilogue: normalise and store.  oacc[cb][qb][i] = O[query 16 qb + r][16 cb + 4 g + i]
   // ======================================================================================
-  const float l_tot = both_halves_sum(l_run);
-  const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-  if (MODE == kProfile) {
-    if (qslot < a.t) {
-      // output slots: the parts of the unmasked pass, of the spatial pass, of the temporal pass
-      const int slot = variant == 0 ? chunk : a.plan.n_full + (variant - 1) * a.plan.n_masked + chunk;
-      float* op = static_cast<float*>(a.o) + (((size_t)slot * a.BH + bh) * a.t + qslot) * D;
-      if (g == 0) a.stats[((size_t)slot * a.BH + bh) * a.t + qslot] = make_float2(m_run, l_tot);
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
+  for (int qb = 0; qb < QB; ++qb) {
+    const float l_tot = quarters_sum(l_run[qb]);
+    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+    if (MODE == kProfile) {
+      if (qslot[qb] < a.t) {
+        // output slots: the parts of the unmasked pass, of the spatial pass, of the temporal pass
+        const int slot = variant == 0 ? chunk : a.plan.n_full + (variant - 1) * a.plan.n_masked + chunk;
+        float* op = static_cast<float*>(a.o) + (((size_t)slot * a.BH + bh) * a.t + qslot[qb]) * D;
+        if (g == 0) a.stats[((size_t)slot * a.BH + bh) * a.t + qslot[qb]] = make_float2(m_run[qb], l_tot);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          f32x4 x;
+        for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<f32x4*>(op + cb * 16 + 4 * g) = oacc[cb][qb] * inv;
+      }
+    } else if (qslot[qb] < a.N) {
+      __bf16* op = static_cast<__bf16*>(a.o) + (head + io_row[qb]) * D;
 #pragma unroll
-          for (int jj = 0; jj < 4; ++jj) x[jj] = oacc[db][4 * i + jj] * inv;
-          *reinterpret_cast<f32x4*>(op + db * 32 + 8 * i + 4 * g) = x;
-        }
-    }
-  } else {
-    if (qslot < a.N) {
-      __bf16* op = static_cast<__bf16*>(a.o) + (head + io_row) * D;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          f32x4 x;
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj) x[jj] = oacc[db][4 * i + jj] * inv;
-          *reinterpret_cast<bf16x4*>(op + db * 32 + 8 * i + 4 * g) = __builtin_convertvector(x, bf16x4);
-        }
+      for (int cb = 0; cb < CB; ++cb)
+        *reinterpret_cast<bf16x4*>(op + cb * 16 + 4 * g) = __builtin_convertvector(oacc[cb][qb] * inv, bf16x4);
     }
   }
 }
@@ -976,16 +1034,21 @@ int dispatch(const Geo& g, const AttnArgs& a, int rows_total, hipStream_t stream
 
 // Source rows for the gathering form: table[v] = v (spatial heads), table[entries + v] = token
 // row of row v of the P-outer order (text rows: themselves); padding: a row outside the tensor.
-__global__ void row_table_kernel(int32_t* table, int entries, int N, int off, int video_end, int F, int P, int sink) {
-  const int v = blockIdx.x * blockDim.x + threadIdx.x;
-  if (v >= entries) return;
+// Inside a 64-key tile the entries are kept in the order in which the threads take them: the rows
+// s, s + 64 / per_thread, ... that one thread of the attention kernel stages stand together.
+__global__ void row_table_kernel(int32_t* table, int entries, int per_thread_log2, int N, int off, int video_end,
+                                 int F, int P, int sink) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= entries) return;
+  const int place = e & 63;
+  const int v = (e & ~63) + (place >> per_thread_log2) + ((place & ((1 << per_thread_log2) - 1)) << (6 - per_thread_log2));
   int same = 0x00ffffff, moved = 0x00ffffff;
   if (v < N) {
     same = v;
     moved = v >= off && v < video_end ? off + (int)transformed_to_token((unsigned)(v - off), (unsigned)F, (unsigned)P, sink) : v;
   }
-  table[v] = same;
-  table[entries + v] = moved;
+  table[e] = same;
+  table[entries + e] = moved;
 }
 
 AttnArgs base_args(const Geo& g, const void* q, const void* k, const void* v, void* o) {
@@ -1019,8 +1082,8 @@ int launch_attention(const Geo& g, const void* q, const void* k, const void* v, 
     if (element_mask || g.bm != 128) return SVG_ERR_UNSUPPORTED;
     const int entries = g.nk * g.bn;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(row_table_kernel, dim3((entries + 255) / 256), dim3(256), 0, stream, row_table, entries, g.N,
-                       g.off, g.video_end, g.F, g.P, g.sink);
+    hipLaunchKernelGGL(row_table_kernel, dim3((entries + 255) / 256), dim3(256), 0, stream, row_table, entries,
+                       g.D == 128 ? 2 : 1, g.N, g.off, g.video_end, g.F, g.P, g.sink);
     const int rc = hip_status(hipGetLastError());
     if (rc != SVG_OK) return rc;
     a.row_table = row_table;

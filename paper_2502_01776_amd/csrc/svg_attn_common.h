@@ -19,8 +19,6 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;   // operand type of 
 
 enum Mode { kDense = 0, kSparse = 1, kProfile = 2, kSparseExact = 3, kSparseGather = 4 };
 
-constexpr int kCodeDrop = 0x7fffffff;   // key beyond N: never kept
-constexpr int kCodeKeep = 0x7ffffffe;   // text key / sink key: kept by every query
 constexpr float kNegBig = -1.0e30f;     // finite stand-in for -inf as the initial row maximum
 constexpr float kLazySum = 8192.0f;      // a lane's per-tile sum of exponentials above this forces a new reference maximum
 
@@ -222,6 +220,26 @@ __device__ __forceinline__ float both_halves_sum(float x) {
   const unsigned u = __float_as_uint(x);
   const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// Lanes l, l ^ 16, l ^ 32 and l ^ 48 own the quarters of one query's keys (the bf16 kernels);
+// v_permlane16_swap exchanges neighbouring quarters the way v_permlane32_swap exchanges halves.
+__device__ __forceinline__ float quarters_max(float x) {
+  const unsigned u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return both_halves_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ __forceinline__ float quarters_sum(float x) {
+  const unsigned u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return both_halves_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
+// Minimum over the 16 lanes of a quarter wavefront (the rows of a 16-query block), the same in every lane.
+__device__ __forceinline__ int quad_rows_min(int x) {
+#pragma unroll
+  for (int m = 1; m < 16; m <<= 1) x = min(x, __shfl_xor(x, m, 16));
+  return __builtin_amdgcn_readfirstlane(x);
 }
 
 }  // namespace attn
