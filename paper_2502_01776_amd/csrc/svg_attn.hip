@@ -59,6 +59,8 @@
 //    loses the overlap above and was 5 % slower.  A 256-row workgroup (two query tiles
 //    sharing every staged tile, the two halves one phase apart) halved staging and L2
 //    traffic per product and came out even: more cycles at a higher clock.
+#include <type_traits>
+
 #include "svg_attn_common.h"
 
 namespace svg {
@@ -68,6 +70,15 @@ namespace {
 using namespace attn;
 
 constexpr int kNoTile = 0x7fffffff;
+
+// Coarse position bin of a sampled row for the temporal profiling pass (text rows first).
+constexpr int kOrderBins = 2048;
+__device__ __forceinline__ int order_bin(int n, int off, int video_end, int P) {
+  if (n < off || n >= video_end) return 0;
+  const int p = (n - off) % P;
+  return 1 + (int)(((long long)p * (kOrderBins - 1)) / P);
+}
+
 // Wave priority while a wavefront issues a batch of products (0 elsewhere).  The two
 // wavefronts sharing a SIMD then settle into opposite phases: the products of one run
 // back to back while the other's softmax and staging instructions fill the gaps.  The first
@@ -235,9 +246,30 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
     // a workgroup's rows share a narrow position range and most key tiles can be
     // skipped; results are still written at the row's own slot.
     if (variant == 2) {
-      const int s0 = a.order_t[slot[0]], s1 = a.order_t[slot[1]];
-      slot[0] = s0;
-      slot[1] = s1;
+      const int32_t* order = a.order_t;
+      if (order == nullptr) {
+        // all rows belong to this one group (t <= BM): the group sorts them itself, each row counting
+        // the rows in front of it, in the order profile_order_kernel would give them (that kernel, a
+        // launch of 3.7 us in front of a call of 40, is left to more than one group)
+        int* const bin = reinterpret_cast<int*>(lds);
+        int* const sorted = bin + BM;
+        if (tid < a.t) bin[tid] = order_bin(a.rows[tid], a.off, a.video_end, a.P);
+        __syncthreads();
+        if (tid < a.t) {
+          const int own = bin[tid];
+          int rank = 0;
+#pragma unroll 8
+          for (int j = 0; j < a.t; ++j) rank += bin[j] < own || (bin[j] == own && j < tid);
+          sorted[rank] = tid;
+        }
+        __syncthreads();
+        slot[0] = sorted[slot[0]];
+        slot[1] = sorted[slot[1]];
+        __syncthreads();       // the first tile is staged over the list
+      } else {
+        slot[0] = order[slot[0]];
+        slot[1] = order[slot[1]];
+      }
     }
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
@@ -865,17 +897,12 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
 // decides where that wavefront renews its reference maximum, i.e. the rounding of the
 // results, so every bin is sorted afterwards to make the grouping, and with it every
 // output bit, the same on every run.
-constexpr int kOrderBins = 2048;
 __global__ __launch_bounds__(1024) void profile_order_kernel(const int32_t* rows, int t, int off,
                                                              int video_end, int P, int32_t* order) {
   __shared__ int hist[kOrderBins];
   __shared__ int part[1024];
   const int tid = threadIdx.x;
-  auto bin_of = [&](int n) -> int {
-    if (n < off || n >= video_end) return 0;
-    const int p = (n - off) % P;
-    return 1 + (int)(((long long)p * (kOrderBins - 1)) / P);
-  };
+  auto bin_of = [&](int n) -> int { return order_bin(n, off, video_end, P); };
   for (int i = tid; i < kOrderBins; i += 1024) hist[i] = 0;
   __syncthreads();
   for (int i = tid; i < t; i += 1024) atomicAdd(&hist[bin_of(rows[i])], 1);
@@ -912,94 +939,159 @@ __global__ __launch_bounds__(1024) void profile_order_kernel(const int32_t* rows
 }
 
 // Squared errors of the two masked outputs against the unmasked one (Alg. 1, last
-// block), first stage: block (x, bh) sums kErrRows sampled rows of head bh and writes
-// one partial pair.  Each of the three outputs of a row is first reassembled from the
-// parts its pass was cut into: part r holds its normalised output O_r, its reference
-// maximum m_r and its row sum l_r, and O = sum_r w_r O_r / sum_r w_r with
+// block): block (x, bh) sums rows_per_block sampled rows of head bh.  Each of the three outputs of
+// a row is first reassembled from the parts its pass was cut into: part r holds its normalised
+// output O_r, its reference maximum m_r and its row sum l_r, and O = sum_r w_r O_r / sum_r w_r with
 // w_r = l_r * 2^((m_r - max_r m_r) * scale_log2); a part that kept no key of the row has
 // l_r = 0.  Text query rows are skipped (both masks keep every key for them, so they
 // contribute exactly zero).
-constexpr int kErrRows = 16;
-constexpr int kMaxSlots = kMaxProfileParts + 2 * 4;
-__global__ __launch_bounds__(256) void profile_error_kernel(const float* ws, const float2* stats,
-                                                            const int32_t* rows, int BH, int t, int D,
-                                                            int n_full, int n_masked, float scale_log2, int off,
-                                                            int video_end, float2* partial) {
-  // weight[row][slot] = w_r / sum w_r within the slot's pass: one thread per (row, pass)
-  __shared__ float weight[kErrRows][kMaxSlots];
-  const int bh = blockIdx.y;
-  const size_t per = (size_t)t * D;
-  const int row0 = blockIdx.x * kErrRows, row1 = min(t, row0 + kErrRows);
-  const int slots = n_full + 2 * n_masked;
-  if (threadIdx.x < kErrRows * 3) {
-    const int rr = threadIdx.x / 3, pass = threadIdx.x % 3, row = row0 + rr;
-    const int slot0 = pass == 0 ? 0 : n_full + (pass - 1) * n_masked, parts = pass == 0 ? n_full : n_masked;
-    if (row < row1) {
-      float m_max = -3.0e38f;
-      for (int r = slot0; r < slot0 + parts; ++r) {
-        const float2 st = stats[((size_t)r * BH + bh) * t + row];
-        if (st.y > 0.f) m_max = fmaxf(m_max, st.x);
-      }
-      float den = 0.f;
-      for (int r = slot0; r < slot0 + parts; ++r) {
-        const float2 st = stats[((size_t)r * BH + bh) * t + row];
-        const float w = st.y > 0.f ? st.y * __builtin_amdgcn_exp2f((st.x - m_max) * scale_log2) : 0.f;
-        weight[rr][r] = w;
-        den += w;
-      }
-      const float inv = den > 0.f ? 1.0f / den : 0.f;
-      for (int r = slot0; r < slot0 + parts; ++r) weight[rr][r] *= inv;
-    }
-  }
-  __syncthreads();
-  float acc_s = 0.f, acc_t = 0.f;
-  for (size_t e = (size_t)row0 * D + threadIdx.x; e < (size_t)row1 * D; e += 256) {
-    const int row = (int)(e / D);
-    const int n = rows[row];
-    if (n < off || n >= video_end) continue;
-    const float* wr = weight[row - row0];
-    const float* x = ws + (size_t)bh * per + e;       // slot r of this element: x[r * BH * per]
-    float f = 0.f, os = 0.f, ot = 0.f;
-    for (int r = 0; r < n_full; ++r) f = __builtin_fmaf(wr[r], x[(size_t)r * BH * per], f);
-    for (int r = n_full; r < n_full + n_masked; ++r) os = __builtin_fmaf(wr[r], x[(size_t)r * BH * per], os);
-    for (int r = n_full + n_masked; r < slots; ++r) ot = __builtin_fmaf(wr[r], x[(size_t)r * BH * per], ot);
-    const float ds = f - os, dt = f - ot;
-    acc_s = __builtin_fmaf(ds, ds, acc_s);
-    acc_t = __builtin_fmaf(dt, dt, acc_t);
-  }
-  __shared__ float red_s[256], red_t[256];
-  red_s[threadIdx.x] = acc_s;
-  red_t[threadIdx.x] = acc_t;
-  __syncthreads();
-  for (unsigned step = 128; step > 0; step >>= 1) {      // fixed order: deterministic
-    if (threadIdx.x < step) {
-      red_s[threadIdx.x] += red_s[threadIdx.x + step];
-      red_t[threadIdx.x] += red_t[threadIdx.x + step];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) partial[(size_t)bh * gridDim.x + blockIdx.x] = make_float2(red_s[0], red_t[0]);
-}
+//
+// Bound by latency for few rows and by memory for many.  A thread owns four channels of a row, so a
+// row takes D / 4 lanes and a block 1024 / (D / 4) rows at a time; every thread works the
+// weights of its row out itself (the lanes of a row read the same words) and all its loads, of the
+// statistics and of every part, are independent of each other.  The numbers of parts are template arguments
+// for that reason: NF is exact, masked parts beyond n_masked (at most NM) are read as the last one with weight zero.
+// (An earlier form, 16 rows per block, worked the weights out on 48 threads and walked the parts in
+// a loop of dependent loads: 24.6 us at 24 rows of 6 heads, 31 at 91 rows of 16, 29 at 328 of 40, 39 at
+// 1191 of 24; now 4.7, 13.4, 12.1 and 23.7, and the first two need no label launch, 4.5 us.)
+constexpr int kErrThreads = 1024;
+constexpr int err_rows(int D) { return kErrThreads / (D / 4); }
+// Heads with few rows take one block each, which also writes the label: a second launch costs as
+// much as four more passes over the rows of a block.
+constexpr int kErrSinglePasses = 4;
 
-// Second stage: MSE_s, MSE_t and the label of one head from its partial sums, added in
-// index order (deterministic).  label = spatial iff MSE_s < MSE_t (Alg. 1).
-__global__ __launch_bounds__(64) void profile_label_kernel(const float2* partial, int n_partial, int t, int D,
-                                                           uint8_t* labels, float* mse) {
-  const int bh = blockIdx.x;
-  if (threadIdx.x != 0) return;
-  float sum_s = 0.f, sum_t = 0.f;
-  for (int i = 0; i < n_partial; ++i) {
-    const float2 p = partial[(size_t)bh * n_partial + i];
-    sum_s += p.x;
-    sum_t += p.y;
-  }
+__device__ __forceinline__ void store_label(float sum_s, float sum_t, int bh, int t, int D, uint8_t* labels, float* mse) {
   const float per = (float)t * (float)D;
   const float ms = sum_s / per, mt = sum_t / per;
   if (mse) {
     mse[2 * bh + 0] = ms;
     mse[2 * bh + 1] = mt;
   }
-  labels[bh] = ms < mt ? SVG_HEAD_SPATIAL : SVG_HEAD_TEMPORAL;
+  labels[bh] = ms < mt ? SVG_HEAD_SPATIAL : SVG_HEAD_TEMPORAL;      // Alg. 1
+}
+
+__device__ __forceinline__ float wave_sum(float x) {      // fixed order: deterministic
+#pragma unroll
+  for (int m = 32; m > 0; m >>= 1) x += __shfl_xor(x, m, 64);
+  return x;
+}
+
+template <int D, int NF, int NM>
+__global__ __launch_bounds__(kErrThreads) void profile_error_kernel(const float* ws, const float2* stats, const int32_t* rows,
+                                                                    int BH, int t, int n_masked, float scale_log2, int off,
+                                                                    int video_end, int rows_per_block, float2* partial,
+                                                                    uint8_t* labels, float* mse) {
+  constexpr int LANES = D / 4, ROWS = err_rows(D);
+  const int bh = blockIdx.y;
+  const int row1 = min(t, (int)(blockIdx.x + 1) * rows_per_block);
+  const int c = threadIdx.x % LANES;
+  // reassembles one pass from its parts
+  auto merged = [&](auto parts_c, int slot0, int parts, int row) -> f32x4 {
+    constexpr int PARTS = decltype(parts_c)::value;
+    float2 st[PARTS];
+    f32x4 x[PARTS];
+#pragma unroll
+    for (int r = 0; r < PARTS; ++r) {
+      const size_t at = ((size_t)(slot0 + min(r, parts - 1)) * BH + bh) * t + row;
+      st[r] = stats[at];
+      x[r] = *reinterpret_cast<const f32x4*>(ws + at * D + 4 * c);
+      if (r >= parts) st[r].y = 0.f;
+    }
+    float m_max = -3.0e38f;
+#pragma unroll
+    for (int r = 0; r < PARTS; ++r)
+      if (st[r].y > 0.f) m_max = fmaxf(m_max, st[r].x);
+    float w[PARTS], den = 0.f;
+#pragma unroll
+    for (int r = 0; r < PARTS; ++r) {
+      w[r] = st[r].y > 0.f ? st[r].y * __builtin_amdgcn_exp2f((st[r].x - m_max) * scale_log2) : 0.f;
+      den += w[r];
+    }
+    const float inv = den > 0.f ? 1.0f / den : 0.f;
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < PARTS; ++r)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = __builtin_fmaf(w[r] * inv, x[r][e], o[e]);
+    return o;
+  };
+  float acc_s = 0.f, acc_t = 0.f;
+  for (int row0 = blockIdx.x * rows_per_block; row0 < row1; row0 += ROWS) {
+    const int own = row0 + (int)threadIdx.x / LANES, row = min(own, t - 1);
+    const int n = rows[row];
+    const f32x4 f = merged(std::integral_constant<int, NF>{}, 0, NF, row);
+    const f32x4 os = merged(std::integral_constant<int, NM>{}, NF, n_masked, row);
+    const f32x4 ot = merged(std::integral_constant<int, NM>{}, NF + n_masked, n_masked, row);
+    if (own < row1 && n >= off && n < video_end) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float ds = f[e] - os[e], dt = f[e] - ot[e];
+        acc_s = __builtin_fmaf(ds, ds, acc_s);
+        acc_t = __builtin_fmaf(dt, dt, acc_t);
+      }
+    }
+  }
+  __shared__ float2 wave_part[kErrThreads / 64];
+  acc_s = wave_sum(acc_s);
+  acc_t = wave_sum(acc_t);
+  if ((threadIdx.x & 63) == 0) wave_part[threadIdx.x >> 6] = make_float2(acc_s, acc_t);
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  float sum_s = 0.f, sum_t = 0.f;
+  for (int w = 0; w < kErrThreads / 64; ++w) {
+    sum_s += wave_part[w].x;
+    sum_t += wave_part[w].y;
+  }
+  if (gridDim.x == 1) store_label(sum_s, sum_t, bh, t, D, labels, mse);
+  else partial[(size_t)bh * gridDim.x + blockIdx.x] = make_float2(sum_s, sum_t);
+}
+
+// Second stage for heads of more than one block: MSE_s, MSE_t and the label from the partial sums.
+__global__ __launch_bounds__(64) void profile_label_kernel(const float2* partial, int n_partial, int t, int D,
+                                                           uint8_t* labels, float* mse) {
+  const int bh = blockIdx.x;
+  float sum_s = 0.f, sum_t = 0.f;
+  for (int i = threadIdx.x; i < n_partial; i += 64) {
+    const float2 p = partial[(size_t)bh * n_partial + i];
+    sum_s += p.x;
+    sum_t += p.y;
+  }
+  sum_s = wave_sum(sum_s);
+  sum_t = wave_sum(sum_t);
+  if (threadIdx.x == 0) store_label(sum_s, sum_t, bh, t, D, labels, mse);
+}
+
+// Number of blocks a head's error takes for t sampled rows; profile_workspace_bytes keeps room for
+// ceil(t / 16) partial sums per head, which is at least as many.
+inline int error_blocks(int D, int t) {
+  const int passes = (t + err_rows(D) - 1) / err_rows(D);
+  return passes <= kErrSinglePasses ? 1 : passes;
+}
+
+template <int D, int NF>
+void launch_error(const AttnArgs& a, const float2* stats, float2* partial, uint8_t* labels, float* mse, hipStream_t stream) {
+  const int blocks = error_blocks(D, a.t);
+  const int rows_per_block = blocks == 1 ? a.t : err_rows(D);
+  auto kernel = a.plan.n_masked == 1 ? profile_error_kernel<D, NF, 1> : profile_error_kernel<D, NF, kMaxMaskedParts>;
+  hipLaunchKernelGGL(kernel, dim3(blocks, a.BH), dim3(kErrThreads), 0, stream, static_cast<const float*>(a.o), stats, a.rows,
+                     a.BH, a.t, a.plan.n_masked, a.scale_log2, a.off, a.video_end, rows_per_block, partial, labels, mse);
+}
+
+template <int D>
+int launch_error_parts(const AttnArgs& a, const float2* stats, float2* partial, uint8_t* labels, float* mse, hipStream_t stream) {
+  (void)hipGetLastError();
+  switch (a.plan.n_full) {      // the numbers of parts profile_plan gives the unmasked pass
+    case 1: launch_error<D, 1>(a, stats, partial, labels, mse, stream); break;
+    case 3: launch_error<D, 3>(a, stats, partial, labels, mse, stream); break;
+    case 4: launch_error<D, 4>(a, stats, partial, labels, mse, stream); break;
+    case 6: launch_error<D, 6>(a, stats, partial, labels, mse, stream); break;
+    default: return SVG_ERR_UNSUPPORTED;
+  }
+  int rc = hip_status(hipGetLastError());
+  const int blocks = error_blocks(D, a.t);
+  if (rc != SVG_OK || blocks == 1) return rc;
+  hipLaunchKernelGGL(profile_label_kernel, dim3(a.BH), dim3(64), 0, stream, partial, blocks, a.t, D, labels, mse);
+  return hip_status(hipGetLastError());
 }
 
 // rows_total: N for dense / sparse, t for profiling
@@ -1107,26 +1199,22 @@ int launch_profile(const Geo& g, const void* q, const void* k, const void* v, co
   a.rows_per_group = (t + groups - 1) / groups;
   const size_t out_floats = (size_t)ns * a.BH * t * g.D;
   float2* stats = reinterpret_cast<float2*>(workspace + out_floats);
-  const int n_partial = (t + kErrRows - 1) / kErrRows;
   float2* partial = stats + (size_t)ns * a.BH * t;
-  int32_t* order = reinterpret_cast<int32_t*>(partial + (size_t)a.BH * n_partial);
   a.stats = stats;
-  a.order_t = order;
-  (void)hipGetLastError();
-  hipLaunchKernelGGL(profile_order_kernel, dim3(1), dim3(1024), 0, stream, rows, t, g.off, g.video_end,
-                     g.P, order);
-  int rc = hip_status(hipGetLastError());
+  if (groups > 1) {
+    // one group sorts its rows itself
+    int32_t* order = reinterpret_cast<int32_t*>(partial + (size_t)a.BH * ((t + 15) / 16));
+    a.order_t = order;
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(profile_order_kernel, dim3(1), dim3(1024), 0, stream, rows, t, g.off, g.video_end,
+                       g.P, order);
+    const int rc = hip_status(hipGetLastError());
+    if (rc != SVG_OK) return rc;
+  }
+  const int rc = dispatch<kProfile>(g, a, t, stream);
   if (rc != SVG_OK) return rc;
-  rc = dispatch<kProfile>(g, a, t, stream);
-  if (rc != SVG_OK) return rc;
-  (void)hipGetLastError();
-  hipLaunchKernelGGL(profile_error_kernel, dim3(n_partial, a.BH), dim3(256), 0, stream, workspace, stats,
-                     rows, a.BH, t, g.D, a.plan.n_full, a.plan.n_masked, a.scale_log2, g.off, g.video_end, partial);
-  rc = hip_status(hipGetLastError());
-  if (rc != SVG_OK) return rc;
-  hipLaunchKernelGGL(profile_label_kernel, dim3(a.BH), dim3(64), 0, stream, partial, n_partial, t, g.D,
-                     labels, mse);
-  return hip_status(hipGetLastError());
+  return g.D == 128 ? launch_error_parts<128>(a, stats, partial, labels, mse, stream)
+                    : launch_error_parts<64>(a, stats, partial, labels, mse, stream);
 }
 
 }  // namespace svg

@@ -49,7 +49,7 @@ ProfilePlan profile_plan(const Geo& g, int t) {
   const long long pairs_x = (pairs + 7) / 8;
   ProfilePlan plan = {};
   const int slots = g.D == 64 ? kSlots * 3 / 2 : kSlots;
-  plan.n_masked = (int)std::max<long long>(1, std::min<long long>(4, (slots - 8) / (2 * pairs_x)));
+  plan.n_masked = (int)std::max<long long>(1, std::min<long long>(kMaxMaskedParts, (slots - 8) / (2 * pairs_x)));
   if (g.nk < 24) fill_bounds(&plan, 1, 0, g.nk);
   else if (pairs_x >= 4 * kSlots) fill_bounds(&plan, 1, 2, g.nk);
   else if (g.nk < 96) fill_bounds(&plan, 2, 2, g.nk);

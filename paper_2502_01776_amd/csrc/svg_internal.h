@@ -30,6 +30,7 @@ int make_geo(const svg_shape_t* s, Geo* g);
 // shorter, so that the workgroups finishing last are short ones), each masked pass n_masked <= 4
 // equal parts.  The choice depends on the shape and t only (profile_plan in svg_host.cpp).
 constexpr int kMaxProfileParts = 16;
+constexpr int kMaxMaskedParts = 4;
 struct ProfilePlan {
   int n_full, n_masked;
   int full_bound[kMaxProfileParts + 1];
