@@ -69,8 +69,6 @@ namespace {
 
 using namespace attn;
 
-constexpr int kNoTile = 0x7fffffff;
-
 // Coarse position bin of a sampled row for the temporal profiling pass (text rows first).
 constexpr int kOrderBins = 2048;
 __device__ __forceinline__ int order_bin(int n, int off, int video_end, int P) {
@@ -93,26 +91,6 @@ constexpr int kCohort = 64;   // dense: consecutive query tiles that share an XC
 constexpr int prefetch_depth(int D, int NW, int MODE) {
   return D != 128 || NW != 4 ? 4 : MODE == kProfile || MODE == kSparseExact ? 8 : 12;
 }
-constexpr unsigned kRsrcFlags = 0x00020000u;   // raw buffer, 32-bit data format (gfx9 encoding)
-
-typedef __attribute__((address_space(3))) unsigned char lds_byte;
-
-// Raw buffer descriptor as four scalar words.
-__device__ __forceinline__ u32x4 buffer_words(const void* base, unsigned bytes) {
-  const uintptr_t p = reinterpret_cast<uintptr_t>(base);
-  return u32x4{(unsigned)__builtin_amdgcn_readfirstlane((unsigned)p), (unsigned)__builtin_amdgcn_readfirstlane((unsigned)(p >> 32) & 0xffffu),
-               (unsigned)__builtin_amdgcn_readfirstlane(bytes), kRsrcFlags};
-}
-// 16 bytes per lane straight from memory into LDS, lane l at lds_address + 16 l; out of range reads
-// give zeros.  Written as assembly because the compiler, which cannot tell the two staging buffers
-// apart, puts a wait for every such load in front of the next LDS read; the one wait that is needed
-// is wait_loads_to_lds() in front of the barrier that publishes the tile.
-__device__ __forceinline__ void load_to_lds(const u32x4 rsrc, int voffset, int soffset, unsigned lds_address) {
-  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-               :: "v"(voffset), "s"(rsrc), "s"(soffset), "s"(lds_address) : "memory", "m0");
-}
-__device__ __forceinline__ void wait_loads_to_lds() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-
 // Wavefronts per SIMD the register budget is set for.  Head dimension 128 fills 256 registers
 // (two wavefronts).  At head dimension 64 the accumulators are half as large and every form fits
 // 168 registers: three workgroups per CU, whose wavefronts cover each other's softmax phases
@@ -611,7 +589,7 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
     load_tile(0, col);
   }
   if (GATHER && col1 != kNoTile) load_table(col1);
-  wait_loads_to_lds();
+  wait_loads_to_lds<0>();
   __syncthreads();
 
   // Touch Q here so that its loads are known to have completed before the loop.  Without
@@ -859,7 +837,7 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
 
     __builtin_amdgcn_s_setprio(0);
     col3 = fetch_end();
-    wait_loads_to_lds();
+    wait_loads_to_lds<0>();
     __syncthreads();
     buf ^= 1;
     col = next_col;

@@ -22,6 +22,70 @@ enum Mode { kDense = 0, kSparse = 1, kProfile = 2, kSparseExact = 3, kSparseGath
 constexpr float kNegBig = -1.0e30f;     // finite stand-in for -inf as the initial row maximum
 constexpr float kLazySum = 8192.0f;      // a lane's per-tile sum of exponentials above this forces a new reference maximum
 
+constexpr int kNoTile = 0x7fffffff;
+constexpr unsigned kRsrcFlags = 0x00020000u;   // raw buffer, 32-bit data format (gfx9 encoding)
+
+typedef __attribute__((address_space(3))) unsigned char lds_byte;
+
+// Raw buffer descriptor as four scalar words.
+__device__ __forceinline__ u32x4 buffer_words(const void* base, unsigned bytes) {
+  const uintptr_t p = reinterpret_cast<uintptr_t>(base);
+  return u32x4{(unsigned)__builtin_amdgcn_readfirstlane((unsigned)p), (unsigned)__builtin_amdgcn_readfirstlane((unsigned)(p >> 32) & 0xffffu),
+               (unsigned)__builtin_amdgcn_readfirstlane(bytes), kRsrcFlags};
+}
+// 16 bytes per lane straight from memory into LDS, lane l at lds_address + 16 l; out of range reads
+// give zeros.  Written as assembly because the compiler, which cannot tell the two staging buffers
+// apart, puts a wait for every such load in front of the next LDS read; the one wait that is needed
+// is wait_loads_to_lds() in front of the barrier that publishes the tile.
+__device__ __forceinline__ void load_to_lds(const u32x4 rsrc, int voffset, int soffset, unsigned lds_address) {
+  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+               :: "v"(voffset), "s"(rsrc), "s"(soffset), "s"(lds_address) : "memory", "m0");
+}
+// Waits until at most N of this wavefront's loads are outstanding (they complete in order).
+template <int N>
+__device__ __forceinline__ void wait_loads_to_lds() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// A bare workgroup barrier.  For loops in which LDS is written by such loads only and every read of the
+// staging buffers was consumed before.
+__device__ __forceinline__ void barrier_loads_done() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// The tiles of a kept-tile list row, handed out in turn, from entry `start` on and around its end:
+// 64 entries at a time wait in a register (one per lane), the next 64 are in flight.  Every value taken
+// is the same in all lanes.
+struct TileList {
+  const int32_t* row;
+  int len, start, taken, now, ahead;
+
+  __device__ __forceinline__ int load(int base) const {
+    int i = base + (int)(threadIdx.x & 63);
+    if (i >= len) return kNoTile;
+    i += start;
+    return row[i >= len ? i - len : i];
+  }
+  __device__ __forceinline__ void open(const int32_t* row_, int len_, int start_) {
+    row = row_;
+    len = len_;
+    start = start_;
+    taken = 0;
+    now = load(0);
+    ahead = kNoTile;
+    if (len > 64) ahead = load(64);
+  }
+  __device__ __forceinline__ int next() {
+    if (taken >= len) return kNoTile;
+    const int lane = taken & 63;
+    if (lane == 0 && taken > 0) {
+      now = ahead;
+      if (taken + 64 < len) ahead = load(taken + 64);
+    }
+    ++taken;
+    return __builtin_amdgcn_readlane(now, lane);
+  }
+};
+
 // --------------------------------------------------------------------------------------------
 // Dispatch order of the block-sparse passes.
 //

@@ -1,0 +1,61 @@
+"""Kept-tile lists of every length at which the attention kernels change what they do: none, one and two
+tiles, odd and even numbers, and the ends of the 64 entries that are fetched at a time; with and without a
+ragged last key tile in them."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2502_01776_amd as S
+from oracle import svg_oracle as O
+from workloads import get_config, make_plain_qkv
+from helpers import f64, dev_i32, gpu_fp8_quantize, assert_attn_close, assert_fp8_attn_close
+
+pytestmark = pytest.mark.gpu
+
+LENGTHS = [0, 1, 2, 3, 4, 5, 62, 63, 64, 65, 66, 126, 127, 128, 129, 130, 131, 132]
+
+
+@pytest.mark.parametrize("last_tile", [False, True])
+@pytest.mark.parametrize("D, fp8", [(64, False), (128, False), (128, True)])
+def test_list_lengths(D, fp8, last_tile):
+    cfg = dict(get_config("mid128"), B=1, H=1, F=3, P=2812, T=0, D=D, spatial_heads=[0])
+    cfg["N"] = cfg["F"] * cfg["P"]                      # 8436 = 131 * 64 + 52
+    sh, g = S.shape_from_config(cfg), O.Geometry.from_config(cfg)
+    nq, nk = S.svg_tile_counts(sh)
+    assert nk == 132 and nq >= len(LENGTHS)
+    rng = np.random.default_rng(D + last_tile)
+    lists = [np.zeros(0, np.int32)] * nq
+    for i, n in enumerate(LENGTHS):
+        cols = np.sort(rng.choice(nk, n, replace=False)).astype(np.int32)
+        if last_tile and n:
+            cols[-1] = nk - 1
+        elif n and n < nk:
+            cols = np.sort(rng.choice(nk - 1, n, replace=False)).astype(np.int32)
+        lists[i] = cols
+    rp = np.concatenate([[0], np.cumsum([len(c) for c in lists])]).astype(np.int32)
+    ci = np.concatenate(lists)
+    csr = [dev_i32(rp), dev_i32(ci), dev_i32(rp), dev_i32(ci)]
+    # logits that grow along the sequence, so that the reference maximum of the softmax has to follow
+    q, k, v = make_plain_qkv(1, 1, g.N, D, seed=D)
+    k = (k.float() * torch.linspace(0.2, 3.0, g.N)[None, None, :, None]).bfloat16()
+    qc, kc, vc = q.cuda(), k.cuda(), v.cuda()
+    lab = torch.zeros(1, dtype=torch.uint8, device="cuda")
+    o = torch.full_like(qc, float("nan"))
+    if fp8:
+        bufs = gpu_fp8_quantize(sh, qc, kc, vc, lab)
+        S.svg_sparse_attn_fp8_fwd(sh, *bufs, o, lab, *csr)
+        qh, kh, vh = (O.fp8_dequantize(*O.fp8_quantize_head(f64(x)[0, 0])) for x in (q, k, v))
+    else:
+        S.svg_sparse_attn_fwd_ex(sh, qc, kc, vc, o, lab, *csr)
+        qh, kh, vh = (f64(x)[0, 0] for x in (q, k, v))
+    torch.cuda.synchronize()
+    tiles = list(range(len(LENGTHS)))
+    ref = O.sparse_attention_head(qh, kh, vh, rp.astype(np.int64), ci, g, q_tiles=[a for a in tiles if LENGTHS[a]])
+    for a in tiles:
+        rows = slice(a * g.block_m, min(g.N, (a + 1) * g.block_m))
+        if LENGTHS[a] == 0:
+            assert (o[0, 0, rows] == 0).all()
+        elif fp8:
+            assert_fp8_attn_close(o[0, 0, rows], ref[rows], float(np.abs(vh).max()), f"{LENGTHS[a]} tiles")
+        else:
+            assert_attn_close(o[0, 0, rows], ref[rows], f"{LENGTHS[a]} tiles")
