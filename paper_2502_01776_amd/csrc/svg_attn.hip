@@ -21,15 +21,24 @@
 // 2093 against 1788 TFLOP/s (products only) and 1419 against 1364 (with one 1 KB operand
 // read per 32768 operations and the softmax).
 //
+// The loop is skewed by one tile: with the scores of tile j in registers a wavefront takes their
+// exponentials, one run of VALU work, and then issues the products of tile j + 1's scores and of tile
+// j's output as one batch, one run of matrix work.  The first operands of a batch are read from LDS before
+// the exponentials, every other one behind the products, and no wavefront waits for the results of
+// the products it has just issued.  (Taken tile by tile, scores, exponentials, output: dense 18.33 ms instead of
+// 17.65 at 40 heads of 32760 tokens, profiling 2.99 instead of 2.84 at the 119k-token shape, the sparse
+// pass 5.45 instead of 5.12 at head dimension 64 and 45k tokens, and no difference at head
+// dimension 128.)  The masked passes still take their tiles one by one: see the main loop.
+//
 // Staging: K and V tiles go from memory straight into LDS (buffer_load_dwordx4 ... lds, bounds-checked
-// descriptors, loop-invariant offsets), double buffered, with the loads of tile j+1 in flight
-// while tile j is computed and one barrier per tile.  Such a load writes 64 x 16 consecutive
+// descriptors, loop-invariant offsets), two buffers each, with the loads of K of tile j + 2 and V of j + 1
+// in flight during trip j and one barrier per trip.  Such a load writes 64 x 16 consecutive
 // bytes, so rows cannot be padded; the bank swizzles are applied on the memory side (a lane
 // fetches the piece of its row that belongs at its place).  V stays row-major too: the transposing
 // LDS read of gfx950 (ds_read_b64_tr_b16) hands a lane the same channel of four consecutive
 // keys, so two of them are a whole A operand of the second product and nothing is
-// transposed in registers.  Operand reads run several operands ahead of their use (rolling
-// window), including the first V^T operands, which are requested before the softmax starts.
+// transposed in registers.  (Loads that always hit L2 make the dense pass 1 % faster, no loads at all 12 %:
+// it is the moving of the bytes into LDS that costs, not their latency.)
 // (With the tiles staged through registers and ds_write_b128, and 32x32x16 products, the sparse pass
 // took 24.5 ms instead of 22.3 at the 119k-token shape with 15 % of the tiles kept, 3.22
 // instead of 2.89 ms at 40 heads of 32760 tokens, 4.08 instead of 3.69 ms at head dimension 64, and
@@ -77,19 +86,19 @@ __device__ __forceinline__ int order_bin(int n, int off, int video_end, int P) {
   return 1 + (int)(((long long)p * (kOrderBins - 1)) / P);
 }
 
-// Wave priority while a wavefront issues a batch of products (0 elsewhere).  The two
+// Wave priority while a wavefront issues products (0 elsewhere).  The two
 // wavefronts sharing a SIMD then settle into opposite phases: the products of one run
-// back to back while the other's softmax and staging instructions fill the gaps.  The first
-// product of a tile ranks above the second (1 % less time than equal ranks, 1 % more with the
+// back to back while the other's softmax and staging instructions fill the gaps.  Where a tile is
+// taken in one go, its first product ranks above its second (1 % less time than equal ranks, 1 % more with the
 // ranks swapped): a wavefront that starts a tile is not held up by one that finishes one.
-constexpr int kPrioFirstProduct = 2;
-constexpr int kPrioSecondProduct = 1;
+constexpr int kPrioOutput = 1;
+constexpr int prio_scores(bool sequential) { return sequential ? 2 : 1; }
 constexpr int kCohort = 64;   // dense: consecutive query tiles that share an XCD (and its L2) at a time
 // LDS operands kept in flight ahead of the products: twelve where the registers allow it (the
 // unmasked passes at head dimension 128; 1.2 % less time than eight, 0.9 % than six), eight in the
-// forms with mask state, four at head dimension 64 (three to six measured within 1 %)
+// forms with mask state or row numbers in registers, four at head dimension 64 (three to six measured within 1 %)
 constexpr int prefetch_depth(int D, int NW, int MODE) {
-  return D != 128 || NW != 4 ? 4 : MODE == kProfile || MODE == kSparseExact ? 8 : 12;
+  return D != 128 || NW != 4 ? 4 : MODE == kDense || MODE == kSparse ? 12 : 8;
 }
 // Wavefronts per SIMD the register budget is set for.  Head dimension 128 fills 256 registers
 // (two wavefronts).  At head dimension 64 the accumulators are half as large and every form fits
@@ -141,7 +150,7 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
 
   // One block, the staged tiles first: the direct loads take a 16-bit LDS address.
   struct Shared {
-    unsigned char tiles[2 * STAGE_BYTES];
+    unsigned char tiles[2 * STAGE_BYTES];      // two K tiles, two V tiles
     int wave_range[2 * NW];    // profile: smallest and largest coordinate of each wavefront's rows
   };
   static_assert(2 * STAGE_BYTES <= 65536, "the direct loads take a 16-bit LDS address");
@@ -368,16 +377,12 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   //             (temporal) | text suffix; the unmasked pass walks its key range.  A superset
   //             is enough: the element mask is still applied inside every visited tile.
   // ======================================================================================
-  const int32_t* cols = nullptr;
-  int lj = 0, lend = 0;              // sparse: cursor and end in col_idx;  dense: counter and nk
-  int lbeg = 0, lleft = 0;           // sparse: start of the list row, entries still to hand out
+  TileList list = {};                // sparse
+  int lj = 0;                        // dense: counter
   if (SPARSE) {
     const int32_t* rp = a.row_ptr[pat];
-    cols = a.col_idx[pat];
-    lbeg = __builtin_amdgcn_readfirstlane(rp[grp]);
-    lend = __builtin_amdgcn_readfirstlane(rp[grp + 1]);
-    lj = lbeg;
-    lleft = lend - lbeg;
+    const int lbeg = __builtin_amdgcn_readfirstlane(rp[grp]), lend = __builtin_amdgcn_readfirstlane(rp[grp + 1]);
+    list.open(a.col_idx[pat] + lbeg, lend - lbeg, 0);
     // The list is walked from its first entry.  Neighbouring query tiles run at the same time on
     // one XCD with key windows shifted by BM / BN tiles against each other, so each finds in L2
     // what its neighbour fetched a moment ago.  (An earlier form started all query tiles of a
@@ -385,8 +390,6 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
     // dealt to the XCDs that saved a third of the traffic past L2, with the dispatch order used
     // now it cost 1-2 % time and nearly doubled that traffic: 47.9 against 27.5 GB per launch at
     // the 119k-token shape.)
-  } else if (MODE == kDense) {
-    lend = a.nk;
   }
   int pseg = 0, pj = 0, pjb = -1;
   auto profile_segment = [&](int sidx, int& k0, int& k1) -> bool {   // false: no more segments
@@ -439,31 +442,9 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
     }
     return true;
   };
-  // The cursor works in two halves.  fetch_begin() at the top of an iteration issues the
-  // loads of the next list entries; fetch_end() late in the iteration, where the staged data
-  // has just been waited for anyway, turns them into the next entry and advances the
-  // cursor.  The entry is needed three tiles later.  The loads are ordinary per-lane loads
-  // (the opaque zero keeps the compiler from treating the address as uniform and waiting
-  // for the value on the spot, which would also wait for every staging load in flight).
-  int lane_zero = 0;
-  asm volatile("" : "+v"(lane_zero));
-  int pend0 = kNoTile;
-  auto fetch_begin = [&]() {
-    if (SPARSE) pend0 = lleft > 0 ? cols[lj + lane_zero] : kNoTile;
-  };
-  auto fetch_end = [&]() -> int {
-    if (SPARSE) {
-      if (lleft <= 0) return kNoTile;
-      const int c = __builtin_amdgcn_readfirstlane(pend0);
-      --lleft;
-      ++lj;
-      return c;
-    }
-    if (MODE == kDense) {
-      const int j = lj++;
-      if (j >= lend) return kNoTile;
-      return j;
-    }
+  auto next_tile = [&]() -> int {
+    if (SPARSE) return list.next();
+    if (MODE == kDense) return lj < a.nk ? lj++ : kNoTile;
     if (pleft <= 0) return kNoTile;     // profile
     if (!profile_interval()) return kNoTile;
     --pleft;
@@ -486,11 +467,6 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
       skip -= n;
     }
   }
-  auto next_tile = [&]() -> int {      // both halves at once (prologue)
-    fetch_begin();
-    return fetch_end();
-  };
-
   // ======================================================================================
   // Staging of one K/V tile.
   // ======================================================================================
@@ -523,53 +499,50 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   // thread's PER_THREAD entries in one load (the table keeps them together, row_table_kernel); a
   // row is 2 D contiguous bytes, so the loads stay whole cache lines.
   const int tab_base = GATHER && pat != 0 ? a.nk * BN * 4 : 0;
-  int tab[GATHER ? PER_THREAD : 1];
-  auto load_table = [&](int col_any) {
+  struct Rows { int row[GATHER ? PER_THREAD : 1]; };
+  auto load_table = [&](int col_any) -> Rows {
+    Rows rows = {};
     const int key0 = __builtin_amdgcn_readfirstlane(col_any) * BN;
     const __amdgpu_buffer_rsrc_t rt = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<int32_t*>(a.row_table), 0, 2u * (unsigned)a.nk * BN * 4u, kRsrcFlags);
     if constexpr (GATHER && PER_THREAD == 4) {
       const u32x4 e = __builtin_amdgcn_raw_buffer_load_b128(rt, stage_row * 16, tab_base + key0 * 4, 0);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) tab[i] = (int)e[i];
+      for (int i = 0; i < 4; ++i) rows.row[i] = (int)e[i];
     } else if constexpr (GATHER) {
       static_assert(!GATHER || PER_THREAD == 4 || PER_THREAD == 2, "one load fetches a thread's row numbers");
       const u32x2 e = __builtin_amdgcn_raw_buffer_load_b64(rt, stage_row * 8, tab_base + key0 * 4, 0);
-      tab[0] = (int)e[0];
-      tab[1] = (int)e[1];
+      rows.row[0] = (int)e[0];
+      rows.row[1] = (int)e[1];
     }
+    return rows;
   };
 
-  auto load_tile = [&](int buf, int col_any) {
-    const unsigned kdst = lds_wave + buf * STAGE_BYTES, vdst = kdst + K_BYTES;
+  // one tensor's rows of a tile into the LDS image at dst; piece(i): the piece of its row a thread's
+  // i-th load fetches
+  auto load_rows = [&](const __bf16* src, int col_any, const Rows& rows, auto piece, unsigned dst) {
     if constexpr (GATHER) {
-      const unsigned head_bytes = (unsigned)a.N * (D * 2);
-      const u32x4 rk = buffer_words(kh, head_bytes), rv = buffer_words(vh, head_bytes);
+      const u32x4 rsrc = buffer_words(src, (unsigned)a.N * (D * 2));
 #pragma unroll
       for (int i = 0; i < PER_THREAD; ++i)
-        load_to_lds(rk, tab[i] * (D * 2) + k_piece(i) * 16, 0, kdst + i * THREADS * 16);
+        load_to_lds(rsrc, rows.row[i] * (D * 2) + piece(i) * 16, 0, dst + i * THREADS * 16);
+    } else {
+      // the tile index is the same in every lane; saying so keeps the descriptors scalar
+      const int key0 = __builtin_amdgcn_readfirstlane(col_any) * BN;
+      const u32x4 rsrc = buffer_words(src + (size_t)key0 * D, (unsigned)(a.N - key0) * (D * 2));
 #pragma unroll
       for (int i = 0; i < PER_THREAD; ++i)
-        load_to_lds(rv, tab[i] * (D * 2) + v_piece(i) * 16, 0, vdst + i * THREADS * 16);
-      return;
+        load_to_lds(rsrc, stage_row * (D * 2) + piece(i) * 16 + (SAME_PIECE ? 0 : i * ROW_STEP * (D * 2)),
+                    SAME_PIECE ? i * ROW_STEP * (D * 2) : 0, dst + i * THREADS * 16);
     }
-    // the tile index is the same in every lane; saying so keeps the descriptors scalar
-    const int key0 = __builtin_amdgcn_readfirstlane(col_any) * BN;
-    const unsigned bytes_left = (unsigned)(a.N - key0) * (D * 2);
-    const u32x4 rk = buffer_words(kh + (size_t)key0 * D, bytes_left), rv = buffer_words(vh + (size_t)key0 * D, bytes_left);
-    auto offset = [&](int piece, int i) { return stage_row * (D * 2) + piece * 16 + (SAME_PIECE ? 0 : i * ROW_STEP * (D * 2)); };
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i)
-      load_to_lds(rk, offset(k_piece(i), i), SAME_PIECE ? i * ROW_STEP * (D * 2) : 0, kdst + i * THREADS * 16);
-#pragma unroll
-    for (int i = 0; i < PER_THREAD; ++i)
-      load_to_lds(rv, offset(v_piece(i), i), SAME_PIECE ? i * ROW_STEP * (D * 2) : 0, vdst + i * THREADS * 16);
   };
+  auto load_k = [&](int col, const Rows& rows, int buf) { load_rows(kh, col, rows, k_piece, lds_wave + buf * K_BYTES); };
+  auto load_v = [&](int col, const Rows& rows, int buf) { load_rows(vh, col, rows, v_piece, lds_wave + 2 * K_BYTES + buf * V_BYTES); };
 
   // ======================================================================================
-  // Main loop.
+  // The parts of a trip.
   // ======================================================================================
-  f32x4 oacc[CB][QB];
+  f32x4 oacc[CB][QB], sacc[KB][QB];
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
@@ -581,25 +554,6 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
     l_run[qb] = 0.f;
   }
 
-  // a ring holds the current tile and the next three, so no scalar load sits between one
-  // tile's barrier and the next tile's global loads
-  int col = next_tile(), col1 = next_tile(), col2 = next_tile(), col3 = next_tile();
-  if (col != kNoTile) {
-    if (GATHER) load_table(col);
-    load_tile(0, col);
-  }
-  if (GATHER && col1 != kNoTile) load_table(col1);
-  wait_loads_to_lds<0>();
-  __syncthreads();
-
-  // Touch Q here so that its loads are known to have completed before the loop.  Without
-  // this the compiler's wait-count bookkeeping still sees them pending at the loop head
-  // and emits vmcnt waits in front of the first products of every iteration, which then
-  // wait for the NEXT tile's freshly issued global loads instead.
-#pragma unroll
-  for (int s = 0; s < DS; ++s) asm volatile("" ::"v"(qreg[0][s]), "v"(qreg[1][s]));
-
-  int buf = 0;
   // Operand reads.  K: lane (g, r) reads piece 4 s + g of row r of a 16-key block.  V^T: as a source
   // lane of the transposing read, lane 16 g + s supplies the 8 bytes of row 4 g + s / 4 of a 16-key
   // half step at channel 16 cb + 4 (s % 4).
@@ -611,236 +565,320 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) v_off[cb] = row * V_ROW + ((cb ^ v_swizzle(row)) << 5) + ((r & 3) << 3);
   }
+  constexpr int PF = prefetch_depth(D, NW, MODE), PRIO_SCORES = prio_scores(MODE == kSparseExact);
+  constexpr int NS = KB * DS;          // operands of the first product, order (pair of kb, s, kb in the pair)
+  constexpr int NV = KS * CB;          // operands of the second product, order (ks, cb)
+  static_assert(PF <= NS && PF <= NV, "the window of operands in flight spans at most two products");
+  auto k_block = [](int i) { return (i / (2 * DS)) * 2 + (i & 1); };
+  auto k_step = [](int i) { return (i >> 1) % DS; };
+  auto k_operand = [&](int buf, int i) -> bf16x8 {
+    return *reinterpret_cast<const bf16x8*>(lds + buf * K_BYTES + k_block(i) * 16 * K_ROW + k_off[k_step(i)]);
+  };
+  auto v_operand = [&](int buf, int i) -> bf16x8 {
+    const unsigned char* src = lds + 2 * K_BYTES + buf * V_BYTES + (i / CB) * 32 * V_ROW + v_off[i % CB];
+    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)src);
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(src + 16 * V_ROW));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+
   const bool ragged = (a.N % BN) != 0;
-  int pos_tile = 0, pos_first = -a.off;      // temporal profiling pass: a tile and its first key's in-frame position
-
-  while (col != kNoTile) {
-    const int next_col = col1;
-    col1 = col2;
-    col2 = col3;
-    fetch_begin();
-    if (next_col != kNoTile) load_tile(buf ^ 1, next_col);
-    if (GATHER && col1 != kNoTile) load_table(col1);      // entries of the tile after it
-    const int tile = col;          // key tile of this iteration
-
-    // masked: does this wavefront need the tile at all, and does it need per-element masks?
-    // (a row that keeps none of the tile's keys while others do needs no element masks
-    // either: it takes its exponentials against +inf, i.e. all weights zero)
-    bool skip = false, need_masks = false, drop[QB] = {false, false};
+  // What a masked pass knows of a tile: does this wavefront need it at all, and does it need
+  // per-element masks?  (a row that keeps none of the tile's keys while others do needs no element
+  // masks either: it takes its exponentials against +inf, i.e. all weights zero)
+  struct TileMask {
+    bool skip, need_masks, drop[QB];
     unsigned long long keep[QB];       // mixed tiles: bit n = the row keeps the tile's n-th key
-    if (MASKABLE && masked) {
-      const int k0 = __builtin_amdgcn_readfirstlane(tile) * BN, k1 = k0 + BN;
-      const bool special = k0 < keep_head || k1 > a.video_end;   // some key is kept by every row, or lies beyond N
-      int first = k0;              // the tile's first key in the coordinate of the windows
-      if (by_position) {
-        // its in-frame position: the tiles of a pass ascend, by less than a frame except at its start
-        pos_first += (tile - pos_tile) * BN;
-        pos_tile = tile;
-        if (pos_first >= a.P) pos_first -= a.P;
-        if (pos_first >= a.P) pos_first = (int)((unsigned)pos_first % (unsigned)a.P);
-        first = pos_first;
-      }
-      bool all = false, none = false;
-      if (special) {
-        all = k1 <= keep_head || (k0 >= a.video_end && k1 <= a.N);
-      } else if (!by_position || first + BN <= a.P) {
-        all = first >= lo_max && first + BN <= hi_min;
-        none = first + BN <= lo_min || first >= hi_max;
-      } else if (first + BN <= 2 * a.P) {        // the end of one frame and the start of the next
-        none = first >= hi_max && first + BN - a.P <= lo_min;
-      }
-      skip = none;
-      if (!all && !none) {
-        auto ones = [](int n) -> unsigned long long {      // the n lowest bits
-          n = min(max(n, 0), 64);
-          return n == 0 ? 0ull : ~0ull >> (64 - n);
-        };
-        const unsigned long long full = ones(BN), in_range = ones(a.N - k0) & full;
-        const unsigned long long always = (ones(keep_head - k0) | ~ones(a.video_end - k0)) & in_range;
-        bool any_kept = false, any_part = false;
+  };
+  int pos_tile = 0, pos_first = -a.off;      // temporal profiling pass: a tile and its first key's in-frame position
+  auto tile_mask = [&](int tile) -> TileMask {
+    TileMask t = {};
+    if (!(MASKABLE && masked)) return t;
+    const int k0 = __builtin_amdgcn_readfirstlane(tile) * BN, k1 = k0 + BN;
+    const bool special = k0 < keep_head || k1 > a.video_end;   // some key is kept by every row, or lies beyond N
+    int first = k0;              // the tile's first key in the coordinate of the windows
+    if (by_position) {
+      // its in-frame position: the tiles of a pass ascend, by less than a frame except at its start
+      pos_first += (tile - pos_tile) * BN;
+      pos_tile = tile;
+      if (pos_first >= a.P) pos_first -= a.P;
+      if (pos_first >= a.P) pos_first = (int)((unsigned)pos_first % (unsigned)a.P);
+      first = pos_first;
+    }
+    bool all = false, none = false;
+    if (special) {
+      all = k1 <= keep_head || (k0 >= a.video_end && k1 <= a.N);
+    } else if (!by_position || first + BN <= a.P) {
+      all = first >= lo_max && first + BN <= hi_min;
+      none = first + BN <= lo_min || first >= hi_max;
+    } else if (first + BN <= 2 * a.P) {        // the end of one frame and the start of the next
+      none = first >= hi_max && first + BN - a.P <= lo_min;
+    }
+    t.skip = none;
+    if (!all && !none) {
+      auto ones = [](int n) -> unsigned long long {      // the n lowest bits
+        n = min(max(n, 0), 64);
+        return n == 0 ? 0ull : ~0ull >> (64 - n);
+      };
+      const unsigned long long full = ones(BN), in_range = ones(a.N - k0) & full;
+      const unsigned long long always = (ones(keep_head - k0) | ~ones(a.video_end - k0)) & in_range;
+      bool any_kept = false, any_part = false;
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-          unsigned long long m = 0;
-          // (by position: one window in every frame the tile touches)
-          int f = first;
+      for (int qb = 0; qb < QB; ++qb) {
+        unsigned long long m = 0;
+        // (by position: one window in every frame the tile touches)
+        int f = first;
 #pragma unroll 1
-          do {
-            m |= ones(win_hi[qb] - f) & ~ones(win_lo[qb] - f);
-            f -= a.P;
-          } while (by_position && f + BN > 0);
-          keep[qb] = (m & in_range) | always;
-          any_kept = any_kept || keep[qb] != 0;
-          any_part = any_part || (keep[qb] != 0 && keep[qb] != full);
-        }
-        skip = __builtin_amdgcn_ballot_w64(any_kept) == 0;         // no row of this wave keeps any key
-        need_masks = __builtin_amdgcn_ballot_w64(any_part) != 0;   // some row keeps a part of them
+        do {
+          m |= ones(win_hi[qb] - f) & ~ones(win_lo[qb] - f);
+          f -= a.P;
+        } while (by_position && f + BN > 0);
+        t.keep[qb] = (m & in_range) | always;
+        any_kept = any_kept || t.keep[qb] != 0;
+        any_part = any_part || (t.keep[qb] != 0 && t.keep[qb] != full);
+      }
+      t.skip = __builtin_amdgcn_ballot_w64(any_kept) == 0;         // no row of this wave keeps any key
+      t.need_masks = __builtin_amdgcn_ballot_w64(any_part) != 0;   // some row keeps a part of them
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-          drop[qb] = !need_masks && keep[qb] == 0;
-          keep[qb] >>= 4 * g;        // this lane's keys are 16 kb + 4 g + i
-        }
+      for (int qb = 0; qb < QB; ++qb) {
+        t.drop[qb] = !t.need_masks && t.keep[qb] == 0;
+        t.keep[qb] >>= 4 * g;        // this lane's keys are 16 kb + 4 g + i
       }
     }
-
-    if (!skip) {
-      const unsigned char* kbuf = lds + buf * STAGE_BYTES;
-      const unsigned char* vbuf = kbuf + K_BYTES;
-
-      // ---- S^T = K Q^T.  Operand reads run PF operands ahead of their use (a rolling
-      // window of PF operand registers), so after the first few the LDS latency is hidden
-      // behind the MFMAs; the scheduling barriers pin the read / product interleave.
-      constexpr int PF = prefetch_depth(D, NW, MODE);
-      constexpr int NS = KB * DS;          // operands of the first product, order (pair of kb, s, kb in the pair)
-      constexpr int NV = KS * CB;          // operands of the second product, order (ks, cb)
-      auto k_block = [](int i) { return (i / (2 * DS)) * 2 + (i & 1); };
-      auto k_step = [](int i) { return (i >> 1) % DS; };
-      auto k_operand = [&](int i) -> bf16x8 {
-        return *reinterpret_cast<const bf16x8*>(kbuf + k_block(i) * 16 * K_ROW + k_off[k_step(i)]);
-      };
-      auto v_operand = [&](int i) -> bf16x8 {
-        const unsigned char* src = vbuf + (i / CB) * 32 * V_ROW + v_off[i % CB];
-        const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)src);
-        const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(src + 16 * V_ROW));
-        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-      };
-      f32x4 sacc[KB][QB];
-      bf16x8 opnd[PF];
-#pragma unroll
-      for (int i = 0; i < PF; ++i) opnd[i] = k_operand(i);
-      __builtin_amdgcn_s_setprio(kPrioFirstProduct);
-#pragma unroll
-      for (int i = 0; i < NS; ++i) {
-        const int kb = k_block(i), s = k_step(i);
-        const bf16x8 ka = opnd[i % PF];
-        __builtin_amdgcn_sched_barrier(0);
+    return t;
+  };
+  // sacc[kb][qb][i] belongs to key  tile * BN + 16 kb + 4 g + i
+  auto mask_scores = [&](int tile, const TileMask& t) {
+    if (MASKABLE && masked) {
+      if (t.need_masks) {
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-          if (s == 0) sacc[kb][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
-          sacc[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qreg[qb][s], sacc[kb][qb], 0, 0, 0);
-        }
-        // refill the slot just consumed: next K operand, or (at the tail) the first V^T
-        // operands, which then arrive while the softmax runs
-        if (i + PF < NS) opnd[i % PF] = k_operand(i + PF);
-        else opnd[i % PF] = v_operand(i + PF - NS);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-
-      __builtin_amdgcn_s_setprio(0);
-      // ---- masking.  sacc[kb][qb][i] belongs to key  col*BN + 16 kb + 4 g + i.
-      if (MASKABLE && masked) {
-        if (need_masks) {
-#pragma unroll
-          for (int qb = 0; qb < QB; ++qb) {
-            const unsigned word[2] = {(unsigned)keep[qb], (unsigned)(keep[qb] >> 32)};
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-              for (int i = 0; i < 4; ++i)
-                if (!(word[kb >> 1] & (1u << (16 * (kb & 1) + i)))) sacc[kb][qb][i] = -INFINITY;
-          }
-        }
-      } else if (ragged && col == a.nk - 1) {
-        int lim = a.N - tile * BN - 4 * g;     // keys with 16 kb + i >= lim are out of range
-        // opaque to the optimiser: keeps this rarely taken masking code inside the
-        // branch instead of being speculated into every tile
-        asm volatile("" : "+v"(lim));
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (kb * 16 + i >= lim) {
-#pragma unroll
-              for (int qb = 0; qb < QB; ++qb) sacc[kb][qb][i] = -INFINITY;
-            }
-      }
-      // ---- online softmax: two queries per lane.
-      // Fast path: exponentials are taken against the current reference m_run without
-      // looking at the tile's maximum.  That is the same softmax as long as nothing
-      // overflows, which the row sum reveals: if any lane's partial sum exceeds
-      // kLazySum (or is inf / NaN) the whole wave takes the slow path, which finds the
-      // tile maximum, raises the reference, rescales O^T and the running sum, and redoes
-      // the tile's exponentials.  With a reference within 2^13 of the true maximum the
-      // fp32 sums and bf16 weights lose nothing, and almost every tile after the first
-      // few stays on the fast path (no max reduction, no rescale).
-      bf16x8 pb[KS][QB];
-      auto exponentiate = [&](int qb, float mc) -> float {
-        float l_loc = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          f32x8 p;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[2 * ks + (e >> 2)][qb][e & 3], a.scale_log2, -mc));
-            if (D != 64) l_loc += p[e];
-          }
-          pb[ks][qb] = __builtin_convertvector(p, bf16x8);
-          if (D == 64) {
-            // Head dimension 64 is bound by the softmax's VALU work, so the row sum is taken two
-            // weights per instruction: dot products of the packed pairs with (1, 1), i.e. over
-            // the ROUNDED weights.  (At D = 128 this was slower: the dot products run on the
-            // matrix pipeline and compete with the MFMAs there.)  The pairs are taken by vector
-            // shuffles: extracted as 32-bit words of the bit-cast vector, the compiler fed all
-            // four dot products the same register.
-            const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-            const bf16x8 pv = pb[ks][qb];
-            l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 0, 1), ones, l_loc, false);
-            l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 2, 3), ones, l_loc, false);
-            l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 4, 5), ones, l_loc, false);
-            l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 6, 7), ones, l_loc, false);
-          }
-        }
-        return l_loc;
-      };
-      float l_loc[QB];
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb)
-        l_loc[qb] = exponentiate(qb, MASKABLE && drop[qb] ? INFINITY : m_run[qb] * a.scale_log2);
-      if (__builtin_amdgcn_ballot_w64(!(l_loc[0] <= kLazySum && l_loc[1] <= kLazySum)) != 0) {
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-          float m_loc = sacc[0][qb][0];
+          const unsigned word[2] = {(unsigned)t.keep[qb], (unsigned)(t.keep[qb] >> 32)};
 #pragma unroll
           for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) m_loc = fmaxf(m_loc, sacc[kb][qb][e]);
-          m_loc = quarters_max(m_loc);
-          if (MASKABLE && drop[qb]) m_loc = -INFINITY;
-          const float m_new = fmaxf(m_run[qb], m_loc);
-          const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_new) * a.scale_log2);
-          m_run[qb] = m_new;
-          l_run[qb] *= alpha;
-#pragma unroll
-          for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) oacc[cb][qb][e] *= alpha;
-          l_loc[qb] = exponentiate(qb, MASKABLE && drop[qb] ? INFINITY : m_new * a.scale_log2);
+            for (int i = 0; i < 4; ++i)
+              if (!(word[kb >> 1] & (1u << (16 * (kb & 1) + i)))) sacc[kb][qb][i] = -INFINITY;
         }
       }
+    } else if (ragged && tile == a.nk - 1) {
+      int lim = a.N - tile * BN - 4 * g;     // keys with 16 kb + i >= lim are out of range
+      // opaque to the optimiser: keeps this rarely taken masking code inside the
+      // branch instead of being speculated into every tile
+      asm volatile("" : "+v"(lim));
 #pragma unroll
-      for (int qb = 0; qb < QB; ++qb) l_run[qb] += l_loc[qb];
+      for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (kb * 16 + i >= lim) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) sacc[kb][qb][i] = -INFINITY;
+          }
+    }
+  };
 
-      // ---- O^T += V^T P^T.  The first PF operands were requested at the end of the first
-      // product (slot (NS + i) % PF).
-      __builtin_amdgcn_s_setprio(kPrioSecondProduct);
+  // Online softmax, two queries per lane.
+  // Fast path: exponentials are taken against the current reference m_run without
+  // looking at the tile's maximum.  That is the same softmax as long as nothing
+  // overflows, which the row sum reveals: if any lane's partial sum exceeds
+  // kLazySum (or is inf / NaN) the whole wave takes the slow path, which finds the
+  // tile maximum, raises the reference, rescales O^T and the running sum, and redoes
+  // the tile's exponentials.  With a reference within 2^13 of the true maximum the
+  // fp32 sums and bf16 weights lose nothing, and almost every tile after the first
+  // few stays on the fast path (no max reduction, no rescale).
+  bf16x8 pb[KS][QB];
+  auto exponentiate = [&](int qb, float mc) -> float {
+    float l_loc = 0.f;
 #pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int ks = i / CB, cb = i % CB;
-        const bf16x8 va = opnd[(NS + i) % PF];
-        __builtin_amdgcn_sched_barrier(0);
+    for (int ks = 0; ks < KS; ++ks) {
+      f32x8 p;
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-          oacc[cb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb[ks][qb], oacc[cb][qb], 0, 0, 0);
-        if (i + PF < NV) opnd[(NS + i) % PF] = v_operand(i + PF);
-        __builtin_amdgcn_sched_barrier(0);
+      for (int e = 0; e < 8; ++e) {
+        p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[2 * ks + (e >> 2)][qb][e & 3], a.scale_log2, -mc));
+        if (D != 64) l_loc += p[e];
+      }
+      pb[ks][qb] = __builtin_convertvector(p, bf16x8);
+      if (D == 64) {
+        // Head dimension 64 is bound by the softmax's VALU work, so the row sum is taken two
+        // weights per instruction: dot products of the packed pairs with (1, 1), i.e. over
+        // the ROUNDED weights.  (At D = 128 this was slower: the dot products run on the
+        // matrix pipeline and compete with the MFMAs there.)  The pairs are taken by vector
+        // shuffles: extracted as 32-bit words of the bit-cast vector, the compiler fed all
+        // four dot products the same register.
+        const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+        const bf16x8 pv = pb[ks][qb];
+        l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 0, 1), ones, l_loc, false);
+        l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 2, 3), ones, l_loc, false);
+        l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 4, 5), ones, l_loc, false);
+        l_loc = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 6, 7), ones, l_loc, false);
       }
     }
+    return l_loc;
+  };
+  auto softmax = [&](const bool (&drop)[QB]) {
+    float l_loc[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb)
+      l_loc[qb] = exponentiate(qb, MASKABLE && drop[qb] ? INFINITY : m_run[qb] * a.scale_log2);
+    if (__builtin_amdgcn_ballot_w64(!(l_loc[0] <= kLazySum && l_loc[1] <= kLazySum)) != 0) {
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        float m_loc = sacc[0][qb][0];
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) m_loc = fmaxf(m_loc, sacc[kb][qb][e]);
+        m_loc = quarters_max(m_loc);
+        if (MASKABLE && drop[qb]) m_loc = -INFINITY;
+        const float m_new = fmaxf(m_run[qb], m_loc);
+        const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_new) * a.scale_log2);
+        m_run[qb] = m_new;
+        l_run[qb] *= alpha;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) oacc[cb][qb][e] *= alpha;
+        l_loc[qb] = exponentiate(qb, MASKABLE && drop[qb] ? INFINITY : m_new * a.scale_log2);
+      }
+    }
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) l_run[qb] += l_loc[qb];
+  };
 
+  // The products.  Operand reads run PF operands ahead of their use (a rolling window of PF operand
+  // registers, through both products of a batch); the scheduling barriers pin the read / product interleave.
+  bf16x8 opnd[PF];
+  auto read_k_ahead = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < PF; ++i) opnd[i] = k_operand(buf, i);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // S^T = K Q^T of the tile in K buffer kbuf; v_follows: the window goes on with the V^T operands of V buffer vbuf
+  auto scores = [&](int kbuf, auto v_follows, int vbuf) {
+    __builtin_amdgcn_s_setprio(PRIO_SCORES);
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      const int kb = k_block(i), s = k_step(i);
+      const bf16x8 ka = opnd[i % PF];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        if (s == 0) sacc[kb][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        sacc[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka, qreg[qb][s], sacc[kb][qb], 0, 0, 0);
+      }
+      if (i + PF < NS) opnd[i % PF] = k_operand(kbuf, i + PF);
+      else if (decltype(v_follows)::value) opnd[i % PF] = v_operand(vbuf, i + PF - NS);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // O^T += V^T P^T; at: window slot of the first operand
+  auto output = [&](int vbuf, auto at_c) {
+    constexpr int AT = decltype(at_c)::value;
+    __builtin_amdgcn_s_setprio(kPrioOutput);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int ks = i / CB, cb = i % CB;
+      const bf16x8 va = opnd[(AT + i) % PF];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb)
+        oacc[cb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pb[ks][qb], oacc[cb][qb], 0, 0, 0);
+      if (i + PF < NV) opnd[(AT + i) % PF] = v_operand(vbuf, i + PF);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     __builtin_amdgcn_s_setprio(0);
-    col3 = fetch_end();
-    wait_loads_to_lds<0>();
-    __syncthreads();
-    buf ^= 1;
-    col = next_col;
+  };
+  const std::true_type yes;
+  const std::false_type no;
+  const std::integral_constant<int, 0> first_slot;
+  const std::integral_constant<int, NS> after_scores;
+
+  // ======================================================================================
+  // Main loop, skewed by one tile: trip j holds the scores of tile j.  LDS holds K of tile j + 1 and V of
+  // j; K of j + 2 and V of j + 1 are on their way into it.  The forms with mask state take one tile
+  // after the other under masks (K and V of j in LDS, of j + 1 on their way): which wavefronts need a tile
+  // differs, and the registers do not hold the masks of two tiles beside the rest.
+  // ======================================================================================
+  const bool sequential = MASKABLE && masked;
+  int col = next_tile(), col1 = next_tile(), col2 = sequential ? kNoTile : next_tile();
+  Rows rows_v = {}, rows_k = {};        // gathering form: rows of the tiles whose V and K are fetched next
+  if (col != kNoTile) {
+    if (GATHER) rows_k = load_table(col);
+    load_k(col, rows_k, 0);
+    load_v(col, rows_k, 0);
+  }
+  if (!sequential && col1 != kNoTile) {
+    if (GATHER) rows_v = load_table(col1);
+    load_k(col1, rows_v, 1);
+  }
+  if (GATHER && col2 != kNoTile) rows_k = load_table(col2);
+  wait_loads_to_lds<0>();
+  __syncthreads();
+
+  // Touch Q here so that its loads are known to have completed before the loop.  Without
+  // this the compiler's wait-count bookkeeping still sees them pending at the loop head
+  // and emits vmcnt waits in front of the first products of every iteration, which then
+  // wait for the NEXT tile's freshly issued global loads instead.
+#pragma unroll
+  for (int s = 0; s < DS; ++s) asm volatile("" ::"v"(qreg[0][s]), "v"(qreg[1][s]));
+
+  int buf = 0;
+  if (sequential) {
+    while (col != kNoTile) {
+      if (col1 != kNoTile) {
+        load_k(col1, rows_k, buf ^ 1);
+        load_v(col1, rows_k, buf ^ 1);
+      }
+      col2 = next_tile();
+      const TileMask t = tile_mask(col);
+      if (!t.skip) {
+        read_k_ahead(buf);
+        scores(buf, yes, buf);
+        __builtin_amdgcn_s_setprio(0);
+        mask_scores(col, t);
+        softmax(t.drop);
+        output(buf, after_scores);
+      }
+      wait_loads_to_lds<0>();
+      barrier_loads_done();
+      buf ^= 1;
+      col = col1;
+      col1 = col2;
+    }
+  } else if constexpr (MODE != kSparseExact) {
+    const bool no_drop[QB] = {false, false};
+    if (col != kNoTile) {
+      read_k_ahead(0);
+      scores(0, no, 0);
+      __builtin_amdgcn_s_setprio(0);
+      mask_scores(col, TileMask{});
+    }
+    __syncthreads();                      // the first trip stages tile 2 over tile 0's keys
+    while (col1 != kNoTile) {
+      const int col3 = next_tile();
+      if (col2 != kNoTile) load_k(col2, rows_k, buf);
+      load_v(col1, rows_v, buf ^ 1);
+      if (GATHER) {
+        rows_v = rows_k;
+        if (col3 != kNoTile) rows_k = load_table(col3);
+      }
+      read_k_ahead(buf ^ 1);
+      softmax(no_drop);
+      scores(buf ^ 1, yes, buf);
+      output(buf, after_scores);
+      mask_scores(col1, TileMask{});
+      wait_loads_to_lds<0>();
+      barrier_loads_done();
+      buf ^= 1;
+      col = col1;
+      col1 = col2;
+      col2 = col3;
+    }
+    if (col != kNoTile) {
+#pragma unroll
+      for (int i = 0; i < PF; ++i) opnd[i] = v_operand(buf, i);
+      softmax(no_drop);
+      output(buf, first_slot);
+    }
   }
 
   // ======================================================================================
