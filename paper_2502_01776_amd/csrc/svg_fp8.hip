@@ -82,30 +82,36 @@ __global__ __launch_bounds__(256) void fp8_zero_kernel(unsigned* p, int n) {
 constexpr int kAmaxPieces = 16;            // 16-byte pieces per thread
 
 // Largest magnitude of each (tensor, head): bf16 magnitudes compare like their bit patterns.
-__global__ __launch_bounds__(256) void fp8_amax_kernel(const u32x4* q, const u32x4* k, const u32x4* v,
-                                                       unsigned long long pieces_per_head, unsigned* amax,
-                                                       int BH) {
+// Heads of up to 1024 rows take one block of 1024 threads, which writes the maximum itself; longer ones
+// several blocks of 256 that meet in an atomic maximum, for which the words are cleared first (a launch that
+// is nothing beside a pass over a long head but 4 of 62 us of a whole layer of 960 rows and 6 heads).
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void fp8_amax_kernel(const u32x4* q, const u32x4* k, const u32x4* v,
+                                                           unsigned long long pieces_per_head, unsigned* amax,
+                                                           int BH) {
   const int bh = blockIdx.y, tensor = blockIdx.z;
   const u32x4* src = (tensor == 0 ? q : tensor == 1 ? k : v) + (size_t)bh * pieces_per_head;
-  const unsigned long long base = (unsigned long long)blockIdx.x * (256 * kAmaxPieces) + threadIdx.x;
+  const unsigned long long base = (unsigned long long)blockIdx.x * (THREADS * kAmaxPieces) + threadIdx.x;
   unsigned m = 0;
 #pragma unroll 4
   for (int i = 0; i < kAmaxPieces; ++i) {
-    const unsigned long long u = base + (unsigned long long)i * 256;
+    const unsigned long long u = base + (unsigned long long)i * THREADS;
     if (u < pieces_per_head) {
       const u32x4 x = __builtin_nontemporal_load(&src[u]);
 #pragma unroll
       for (int w = 0; w < 4; ++w) m = max(m, max(x[w] & 0x7fffu, (x[w] >> 16) & 0x7fffu));
     }
   }
-  __shared__ unsigned red[256];
+  __shared__ unsigned red[THREADS];
   red[threadIdx.x] = m;
   __syncthreads();
-  for (unsigned step = 128; step > 0; step >>= 1) {
+  for (unsigned step = THREADS / 2; step > 0; step >>= 1) {
     if (threadIdx.x < step) red[threadIdx.x] = max(red[threadIdx.x], red[threadIdx.x + step]);
     __syncthreads();
   }
-  if (threadIdx.x == 0) atomicMax(&amax[tensor * BH + bh], red[0] << 16);    // as fp32 bits
+  if (threadIdx.x != 0) return;
+  if (gridDim.x == 1) amax[tensor * BH + bh] = red[0] << 16;      // as fp32 bits
+  else atomicMax(&amax[tensor * BH + bh], red[0] << 16);
 }
 
 struct QuantArgs {
@@ -503,14 +509,18 @@ int launch_fp8_quantize(const Geo& g, const void* q, const void* k, const void* 
   if (BH > 65535) return SVG_ERR_UNSUPPORTED;
   unsigned* amax = reinterpret_cast<unsigned*>(scales + 3 * BH);
   (void)hipGetLastError();
-  hipLaunchKernelGGL(fp8_zero_kernel, dim3((3 * BH + 255) / 256), dim3(256), 0, stream, amax, 3 * BH);
-  int rc = hip_status(hipGetLastError());
-  if (rc != SVG_OK) return rc;
   const unsigned long long pieces = (unsigned long long)g.N * (kD / 8);
-  const unsigned chunks = (unsigned)((pieces + 256 * kAmaxPieces - 1) / (256 * kAmaxPieces));
-  hipLaunchKernelGGL(fp8_amax_kernel, dim3(chunks, BH, 3), dim3(256), 0, stream, static_cast<const u32x4*>(q),
-                     static_cast<const u32x4*>(k), static_cast<const u32x4*>(v), pieces, amax, BH);
-  rc = hip_status(hipGetLastError());
+  const u32x4 *qp = static_cast<const u32x4*>(q), *kp = static_cast<const u32x4*>(k), *vp = static_cast<const u32x4*>(v);
+  if (pieces <= 1024 * kAmaxPieces) {
+    hipLaunchKernelGGL(fp8_amax_kernel<1024>, dim3(1, BH, 3), dim3(1024), 0, stream, qp, kp, vp, pieces, amax, BH);
+  } else {
+    hipLaunchKernelGGL(fp8_zero_kernel, dim3((3 * BH + 255) / 256), dim3(256), 0, stream, amax, 3 * BH);
+    const int rc = hip_status(hipGetLastError());
+    if (rc != SVG_OK) return rc;
+    const unsigned chunks = (unsigned)((pieces + 256 * kAmaxPieces - 1) / (256 * kAmaxPieces));
+    hipLaunchKernelGGL(fp8_amax_kernel<256>, dim3(chunks, BH, 3), dim3(256), 0, stream, qp, kp, vp, pieces, amax, BH);
+  }
+  const int rc = hip_status(hipGetLastError());
   if (rc != SVG_OK) return rc;
   QuantArgs a;
   a.in[0] = static_cast<const u32x4*>(q);

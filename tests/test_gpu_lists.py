@@ -59,3 +59,18 @@ def test_list_lengths(D, fp8, last_tile):
             assert_fp8_attn_close(o[0, 0, rows], ref[rows], float(np.abs(vh).max()), f"{LENGTHS[a]} tiles")
         else:
             assert_attn_close(o[0, 0, rows], ref[rows], f"{LENGTHS[a]} tiles")
+
+
+@pytest.mark.parametrize("P", [1, 7, 1023, 1024, 1025, 1027])
+def test_fp8_scales_of_heads_around_one_block(P):
+    """The largest magnitude of a head, wherever it stands, for heads of one block of rows and of several."""
+    cfg = dict(get_config("mid128"), B=1, H=2, F=1, P=P, T=0, spatial_heads=[0])
+    cfg["N"] = P
+    sh = S.shape_from_config(cfg)
+    for at in sorted({0, P // 2, P - 1}):
+        q, k, v = make_plain_qkv(1, 2, P, 128, seed=P + at)
+        for x, peak in ((q, 31.0), (k, -47.0), (v, 63.0)):
+            x[0, 1, at, 127 if at else 0] = peak
+        scales = gpu_fp8_quantize(sh, q.cuda(), k.cuda(), v.cuda(), torch.zeros(2, dtype=torch.uint8, device="cuda"))[3]
+        want = np.array([[np.abs(f64(x)[0, h]).max() for h in range(2)] for x in (q, k, v)], np.float32) / np.float32(448)
+        assert np.array_equal(scales[:6].cpu().numpy().reshape(3, 2), want)
