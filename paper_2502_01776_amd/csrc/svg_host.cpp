@@ -20,6 +20,11 @@ void note_hip_error(hipError_t e) { g_last_hip_error = e; }
 //    that finish last are short ones (1-3 % less time than eight equal parts; anything from
 //    four to eight parts measured within 1 % of each other).  Fewer parts for short sequences,
 //    and three when the sampled rows alone already give every XCD hundreds of workgroups.
+//    Below 24 key tiles one part, except at head dimension 128 where the masked passes are cut: there
+//    three, and one part less of each masked pass (the same workspace), because a workgroup walks its
+//    tiles one after the other and those of the unmasked pass were the longest chain of the call: a layer of
+//    960 rows and 6 heads 62.0 -> 57.9 us.  At head dimension 64, with half the products per tile, the
+//    shorter cut of the masked passes costs more: 40.8 -> 41.9 us at 787 rows and 8 heads.
 //  * Masked passes: one part each, unless the (head, row group) pairs are so few that the two
 //    masked workgroups per pair cannot fill an XCD; then as many parts (up to four) as keep
 //    them within its resident places.  CogVideoX-v1 at 1 % (12 pairs per XCD): three parts,
@@ -50,7 +55,10 @@ ProfilePlan profile_plan(const Geo& g, int t) {
   ProfilePlan plan = {};
   const int slots = g.D == 64 ? kSlots * 3 / 2 : kSlots;
   plan.n_masked = (int)std::max<long long>(1, std::min<long long>(kMaxMaskedParts, (slots - 8) / (2 * pairs_x)));
-  if (g.nk < 24) fill_bounds(&plan, 1, 0, g.nk);
+  if (g.nk >= 6 && g.nk < 24 && plan.n_masked >= 3 && g.D == 128) {
+    --plan.n_masked;
+    fill_bounds(&plan, 3, 0, g.nk);
+  } else if (g.nk < 24) fill_bounds(&plan, 1, 0, g.nk);
   else if (pairs_x >= 4 * kSlots) fill_bounds(&plan, 1, 2, g.nk);
   else if (g.nk < 96) fill_bounds(&plan, 2, 2, g.nk);
   else fill_bounds(&plan, 4, 2, g.nk);

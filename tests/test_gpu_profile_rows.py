@@ -36,8 +36,10 @@ def test_numbers_of_sampled_rows(t, blocks, D):
     check(dict(get_config("mid64"), D=D, B=1, H=3, spatial_heads=[0, 2], block_m=blocks[0], block_n=blocks[1]), t)
 
 
-@pytest.mark.parametrize("H, F, P, t, n_full", [(2, 5, 150, 24, 1), (2, 9, 190, 130, 4), (2, 9, 700, 70, 6), (64, 5, 200, 1024, 3)])
-def test_parts_of_the_unmasked_pass(H, F, P, t, n_full):
-    b = (32, 32) if H == 64 else (128, 64)
-    plan = check(dict(get_config("mid64"), B=1, H=H, F=F, P=P, spatial_heads=[0], block_m=b[0], block_n=b[1]), t)
+@pytest.mark.parametrize("H, F, P, t, n_full, D", [(2, 5, 150, 24, 1, 64), (2, 9, 190, 130, 4, 64), (2, 9, 700, 70, 6, 64),
+                                                   (64, 5, 200, 1024, 3, 64), (2, 1, 250, 24, 1, 128), (2, 1, 300, 24, 3, 128),
+                                                   (2, 9, 150, 24, 3, 128), (64, 5, 150, 140, 1, 128)])
+def test_parts_of_the_unmasked_pass(H, F, P, t, n_full, D):
+    b = (32, 32) if t == 1024 else (128, 64)
+    plan = check(dict(get_config("mid64"), D=D, B=1, H=H, F=F, P=P, spatial_heads=[0], block_m=b[0], block_n=b[1]), t)
     assert plan[0] == n_full
