@@ -127,7 +127,7 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   constexpr int DS = D / 32;             // 32-channel steps of the first product
   constexpr int CB = D / 16;             // 16-channel blocks of O^T
   constexpr int PIECES = BN * CPR;       // 16-byte pieces of a K tile, and of a V tile
-  // Staging work: every thread copies PER_THREAD pieces of K and of V, global -> registers -> LDS,
+  // Staging work: every thread requests PER_THREAD pieces of K and of V,
   // so all wavefronts reach the barrier with the same amount of work behind them.
   constexpr int PER_THREAD = PIECES / THREADS;
   static_assert(PIECES % THREADS == 0 && THREADS % CPR == 0, "every thread stages the same piece of whole rows");
@@ -495,7 +495,7 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   // head row v of the P-outer order is token row_table[entries + v] (Sec. 4.2; text rows map to
   // themselves); a spatial head uses the identity half row_table[v], so that both kinds run the
   // same instructions.  Rows beyond N map to a row outside the tensor, which the bounds-checked
-  // loads return as zero.  The entries of a tile are loaded one tile ahead of its K/V rows, a
+  // loads return as zero.  The entries of a tile are loaded one tile ahead of its K rows and kept for its V rows, a
   // thread's PER_THREAD entries in one load (the table keeps them together, row_table_kernel); a
   // row is 2 D contiguous bytes, so the loads stay whole cache lines.
   const int tab_base = GATHER && pat != 0 ? a.nk * BN * 4 : 0;

@@ -272,7 +272,7 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
   const float v_scale = a.scales[2 * a.BH + bh];
 
   // ---- tile cursor: the query tile's list row, walked cyclically from the cohort's common
-  // starting tile (same scheme as the bf16 kernel)
+  // starting tile
   const int32_t* rp = a.row_ptr[pat];
   const int32_t* cols = a.col_idx[pat];
   const int lbeg = __builtin_amdgcn_readfirstlane(rp[grp]);
