@@ -16,14 +16,16 @@ def hipcc_path() -> str:
     return os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
+def compile_flags() -> list:
+    return ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
+            # packed fp32 instructions are kept out of the generated code on this target
+            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+            "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+
+
 def build(verbose: bool = False, extra_flags=()) -> str:
     """Always recompiles; returns the path of the shared object."""
-    cmd = [hipcc_path(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
-           "-x", "hip",
-           # packed fp32 instructions are kept out of the generated code on this target
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-           *extra_flags,
+    cmd = [hipcc_path(), *compile_flags(), "-shared", *extra_flags,
            *[os.path.join(CSRC, s) for s in SOURCES], "-o", LIB_PATH]
     if verbose:
         print(" ".join(cmd), flush=True)

@@ -130,6 +130,7 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   // Staging work: every thread requests PER_THREAD pieces of K and of V,
   // so all wavefronts reach the barrier with the same amount of work behind them.
   constexpr int PER_THREAD = PIECES / THREADS;
+  static_assert(PER_THREAD % 2 == 0, "the direct loads come in pairs");
   static_assert(PIECES % THREADS == 0 && THREADS % CPR == 0, "every thread stages the same piece of whole rows");
   // K staging: row-major, the 16-byte pieces of a row XOR-swizzled with the row number (k_swizzle),
   // which puts the same piece of 16 consecutive keys, what 16 lanes of an A operand read, on
@@ -524,16 +525,19 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
     if constexpr (GATHER) {
       const u32x4 rsrc = buffer_words(src, (unsigned)a.N * (D * 2));
 #pragma unroll
-      for (int i = 0; i < PER_THREAD; ++i)
-        load_to_lds(rsrc, rows.row[i] * (D * 2) + piece(i) * 16, 0, dst + i * THREADS * 16);
+      for (int i = 0; i < PER_THREAD; i += 2)
+        load_to_lds(rsrc, rows.row[i] * (D * 2) + piece(i) * 16, rows.row[i + 1] * (D * 2) + piece(i + 1) * 16, 0, 0,
+                    dst + i * THREADS * 16, THREADS * 16);
     } else {
       // the tile index is the same in every lane; saying so keeps the descriptors scalar
       const int key0 = __builtin_amdgcn_readfirstlane(col_any) * BN;
       const u32x4 rsrc = buffer_words(src + (size_t)key0 * D, (unsigned)(a.N - key0) * (D * 2));
 #pragma unroll
-      for (int i = 0; i < PER_THREAD; ++i)
-        load_to_lds(rsrc, stage_row * (D * 2) + piece(i) * 16 + (SAME_PIECE ? 0 : i * ROW_STEP * (D * 2)),
-                    SAME_PIECE ? i * ROW_STEP * (D * 2) : 0, dst + i * THREADS * 16);
+      for (int i = 0; i < PER_THREAD; i += 2) {
+        auto lane_offset = [&](int n) { return stage_row * (D * 2) + piece(n) * 16 + (SAME_PIECE ? 0 : n * ROW_STEP * (D * 2)); };
+        auto tile_offset = [&](int n) { return SAME_PIECE ? n * ROW_STEP * (D * 2) : 0; };
+        load_to_lds(rsrc, lane_offset(i), lane_offset(i + 1), tile_offset(i), tile_offset(i + 1), dst + i * THREADS * 16, THREADS * 16);
+      }
     }
   };
   auto load_k = [&](int col, const Rows& rows, int buf) { load_rows(kh, col, rows, k_piece, lds_wave + buf * K_BYTES); };

@@ -33,13 +33,21 @@ __device__ __forceinline__ u32x4 buffer_words(const void* base, unsigned bytes) 
   return u32x4{(unsigned)__builtin_amdgcn_readfirstlane((unsigned)p), (unsigned)__builtin_amdgcn_readfirstlane((unsigned)(p >> 32) & 0xffffu),
                (unsigned)__builtin_amdgcn_readfirstlane(bytes), kRsrcFlags};
 }
-// 16 bytes per lane straight from memory into LDS, lane l at lds_address + 16 l; out of range reads
-// give zeros.  Written as assembly because the compiler, which cannot tell the two staging buffers
-// apart, puts a wait for every such load in front of the next LDS read; the one wait that is needed
-// is wait_loads_to_lds() in front of the barrier that publishes the tile.
-__device__ __forceinline__ void load_to_lds(const u32x4 rsrc, int voffset, int soffset, unsigned lds_address) {
-  asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-               :: "v"(voffset), "s"(rsrc), "s"(soffset), "s"(lds_address) : "memory", "m0");
+// Two loads of 16 bytes per lane straight from memory into LDS, lane l at lds_address + 16 l and, for
+// the second, `step` bytes behind; out of range reads give zeros.  Written as assembly because the compiler,
+// which cannot tell the two staging buffers apart, puts a wait for every such load in front of the next
+// LDS read; the one wait that is needed is wait_loads_to_lds() in front of the barrier that publishes the tile.
+// A load must issue five wait states after a vector instruction (v_readfirstlane, v_readlane of a spilled
+// register) that wrote a scalar register it reads.  The compiler keeps that distance for loads it knows of but
+// not in front of this statement, so the statement holds all of it: one for s_mov, four for s_nop 3.  Two loads
+// share it (a statement with the same wait for every load cost 0.0-0.4 % of the attention passes, this one
+// nothing that could be measured).
+__device__ __forceinline__ void load_to_lds(const u32x4 rsrc, int voffset0, int voffset1, int soffset0, int soffset1,
+                                            unsigned lds_address, const int step) {
+  asm volatile("s_mov_b32 m0, %5\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %2, %3 offen lds\n\t"
+               "s_add_u32 m0, m0, %6\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %4 offen lds"
+               :: "v"(voffset0), "v"(voffset1), "s"(rsrc), "s"(soffset0), "s"(soffset1), "s"(lds_address), "i"(step)
+               : "memory", "m0", "scc");
 }
 // Waits until at most N of this wavefront's loads are outstanding (they complete in order).
 template <int N>

@@ -316,8 +316,7 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
   const int k_src = (tid >> 3) * kD + (((tid & 7) ^ k_swizzle(tid >> 3)) << 4), v_src = tid * 16;
   auto load_image = [&](const unsigned char* images, int tile, int voffset0, int voffset1, unsigned dst) {
     const u32x4 rsrc = buffer_words(images + (size_t)__builtin_amdgcn_readfirstlane(tile) * kTileBytes, kTileBytes);
-    load_to_lds(rsrc, voffset0, 0, dst);
-    load_to_lds(rsrc, voffset1, 4096, dst + 4096);
+    load_to_lds(rsrc, voffset0, voffset1, 0, 4096, dst, 4096);
   };
   // (a list of odd length ends with a pair whose second half repeats the first and is masked)
   struct Pair { int a, b; };

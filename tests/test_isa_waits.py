@@ -1,0 +1,124 @@
+"""What the assembly statements of the kernels take for granted about the code around them, checked in the
+compiler's output for gfx950 (CPU only).
+
+The loads straight into LDS are assembly, so the compiler neither sees a buffer load in them nor keeps the
+distances the hardware asks for: a load that reads a scalar register which a vector instruction wrote must issue at
+least five wait states later, or it may see the register's old value."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2502_01776_amd import build as B
+
+WAIT_STATES = 5
+INF = 1 << 20
+
+pytestmark = pytest.mark.skipif(not os.path.exists(B.hipcc_path()), reason="needs hipcc")
+
+
+def registers(operand):
+    """Scalar registers named by an operand: s7, s[4:7], vcc."""
+    operand = operand.strip()
+    m = re.fullmatch(r"s(\d+)", operand)
+    if m:
+        return {int(m.group(1))}
+    m = re.fullmatch(r"s\[(\d+):(\d+)\]", operand)
+    return set(range(int(m.group(1)), int(m.group(2)) + 1)) if m else set()
+
+
+class Kernel:
+    def __init__(self, name):
+        self.name, self.ins, self.labels = name, [], {}      # ins: (mnemonic, [operands], inside an assembly statement)
+
+    def predecessors(self):
+        pred = [[] for _ in self.ins]
+        for i, (op, args, _) in enumerate(self.ins):
+            if op.startswith(("s_branch", "s_cbranch")):
+                at = self.labels[args[0]]
+                if at < len(self.ins):
+                    pred[at].append(i)
+            if i + 1 < len(self.ins) and op not in ("s_branch", "s_endpgm", "s_setpc_b64"):
+                pred[i + 1].append(i)
+        return pred
+
+    def direct_loads(self):
+        return [i for i, (op, args, asm) in enumerate(self.ins) if asm and op.startswith("buffer_load") and args[-1].endswith(" lds")]
+
+    def nearest_vector_write(self, at, pred):
+        """Fewest wait states between a vector instruction that writes one of the load's scalar registers and the load."""
+        wanted = set().union(*(registers(a) for arg in self.ins[at][1] for a in arg.split()))
+        best, seen, work = INF, {}, [(p, 0) for p in pred[at]]
+        while work:
+            i, passed = work.pop()
+            if passed >= best or seen.get(i, INF) <= passed:
+                continue
+            seen[i] = passed
+            op, args, _ = self.ins[i]
+            written = set().union(*(registers(a) for a in args[:2 if "_co_" in op or "div_scale" in op else 1])) if args else set()
+            if op.startswith("v_") and written & wanted:
+                best = passed
+                continue
+            passed += int(args[0], 0) + 1 if op == "s_nop" else 1
+            if passed < WAIT_STATES:
+                work += [(p, passed) for p in pred[i]]
+        return best
+
+
+def parse(text):
+    kernels, k, asm = [], None, False
+    for line in text.splitlines():
+        m = re.match(r"(\w+):\s*; @", line)
+        if m:
+            k = Kernel(m.group(1))
+            kernels.append(k)
+        elif k is None:
+            continue
+        elif line.startswith(".Lfunc_end"):
+            k = None
+        elif "#ASMSTART" in line or "#ASMEND" in line:
+            asm = "#ASMSTART" in line
+        elif re.match(r"\.LBB\w+:", line):
+            k.labels[line.split(":")[0]] = len(k.ins)
+        else:
+            code = line.split(";")[0].strip()
+            if code and not code.startswith("."):
+                op, *rest = code.split(None, 1)
+                k.ins.append((op, [a.strip() for a in rest[0].split(",")] if rest else [], asm))
+    return kernels
+
+
+@pytest.fixture(scope="module", params=["svg_attn.hip", "svg_fp8.hip"])
+def compiled(request, tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("isa") / "kernels.s")
+    subprocess.run([B.hipcc_path(), *B.compile_flags(), "--offload-device-only", "-S", os.path.join(B.CSRC, request.param), "-o", out],
+                   check=True, capture_output=True, text=True)
+    text = open(out).read()
+    kernels = parse(text)
+    assert sum(len(k.direct_loads()) for k in kernels) > 0
+    return text, kernels
+
+
+def test_reader_of_the_listing_finds_a_missing_wait():
+    """The check itself: a register written four wait states ahead of a load is reported, also across a
+    branch; five are enough; the address and offset registers count as well."""
+    def listing(gap, written="s6", branch=""):
+        return (f"kern:  ; @kern\n.LBB0_1:\n\tv_readfirstlane_b32 {written}, v1\n{branch}\ts_nop {gap}\n\t;;#ASMSTART\n"
+                "\ts_mov_b32 m0, s9\n\tbuffer_load_dwordx4 v0, s[4:7], s8 offen lds\n\t;;#ASMEND\n\ts_endpgm\n.Lfunc_end0:\n")
+    def nearest(text):
+        k, = parse(text)
+        at, = k.direct_loads()
+        return k.nearest_vector_write(at, k.predecessors())
+    assert nearest(listing(2)) == 4 and nearest(listing(2, "s8")) == 4
+    assert nearest(listing(3)) == INF and nearest(listing(0, "s9")) == INF
+    assert nearest(listing(1, branch="\ts_branch .LBB0_2\n.LBB0_2:\n")) == 4
+
+
+def test_direct_loads_read_settled_scalar_registers(compiled):
+    for k in compiled[1]:
+        pred = k.predecessors()
+        for at in k.direct_loads():
+            n = k.nearest_vector_write(at, pred)
+            lines = "; ".join(f"{op} {', '.join(args)}" for op, args, _ in k.ins[max(0, at - 8):at + 1])
+            assert n >= WAIT_STATES, f"{k.name}: {n} wait states in front of load {at}: {lines}"
