@@ -267,8 +267,11 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
     const i32x4 lo = *reinterpret_cast<const i32x4*>(qp), hi = *reinterpret_cast<const i32x4*>(qp + 16);
     qreg[qb] = i32x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
   }
-  // logits in units of log2: s_raw * c with the two quantisation scales folded in
-  const float c_log2 = a.scale_log2 * a.scales[bh] * a.scales[a.BH + bh];
+  // logits in units of log2: s_raw * c with the two quantisation scales folded in.  The product of tiny scales
+  // underflows to zero; the smallest normal number in its place leaves the logits zero as well, but a masked
+  // score times it stays -inf, where times zero it would be NaN.
+  const float c_product = a.scale_log2 * a.scales[bh] * a.scales[a.BH + bh];
+  const float c_log2 = c_product == 0.f ? 0x1p-126f : c_product;
   const float v_scale = a.scales[2 * a.BH + bh];
 
   // ---- tile cursor: the query tile's list row, walked cyclically from the cohort's common
