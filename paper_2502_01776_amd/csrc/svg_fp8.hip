@@ -1,7 +1,7 @@
 // FP8 variant of the block-sparse attention pass (Sec. 4.3 "Quantization", Sec. 5.2) for
 // gfx950 (MI355X): q, k, v quantised to 8-bit floating point (OCP E4M3, one scale per head
 // and tensor, scale = max|x| / 448), both matrix products on the FP8 matrix instruction
-// v_mfma_f32_16x16x128_f8f6f4 (twice the bf16 rate, half the operand bytes), fp32
+// v_mfma_f32_32x32x64_f8f6f4 (twice the bf16 rate, half the operand bytes), fp32
 // accumulation and softmax, bf16 output.  Head dimension 128 and 128 x 64 tiles only (the
 // paper applies FP8 only there: with head dimension 64 it gains nothing, Sec. 5.2).
 //
@@ -12,31 +12,31 @@
 //                            v is written as ready-made LDS images of its 64-key tiles.
 //   svg_sparse_attn_fp8_fwd  the attention kernel.  Same decomposition as the bf16 kernel
 //                            (one workgroup per query tile, 32 query rows per wavefront, both
-//                            products transposed so that a lane owns one query of each 16-query block).  A
-//                            trip of the loop takes TWO 64-key tiles: their 128 keys are one k-step of the
-//                            second product, as the 128 channels are of the first.  The
-//                            attention weights are packed four to a register (E4M3 after scaling by
-//                            2^8, which puts weights down to 2^-17 of the row maximum inside the
-//                            format's range), and the row sums come out of the matrix unit too: one more
-//                            product per 16 queries multiplies the weights with a block of
+//                            products transposed so that a lane owns one query), but a whole
+//                            64-key tile is ONE k-step of the second product, the attention
+//                            weights are packed four to a register (E4M3 after scaling by 2^8,
+//                            which puts weights down to 2^-17 of the row maximum inside the
+//                            format's range), and the row sums come out of the matrix unit too:
+//                            a ninth product per tile multiplies the weights with a block of
 //                            ones, so the denominator is the sum of the ROUNDED weights, the
-//                            result is an exact weighted mean of v rows, and 64 additions per
-//                            lane and trip leave the VALU, which is the busiest unit here.
+//                            result is an exact weighted mean of v rows, and 32 additions per
+//                            lane and tile leave the VALU, which is the busiest unit here.
 //
-// The loop is skewed by one trip: with the scores of pair j in registers, a wavefront takes their
-// exponentials (one long run of VALU work) and then issues the products of pair j + 1's scores
-// and of pair j's output back to back (one long run of matrix work).  The operands of the first products are
-// read from LDS before the exponentials, the others behind the products, and the K and V images
-// come from memory straight into LDS a trip ahead, so nothing in a trip waits for LDS or memory.
+// The loop is skewed by one tile: with the scores of tile j in registers, a wavefront takes their
+// exponentials (one long run of VALU work) and then issues the products of tile j + 1's scores
+// and of tile j's output back to back (one long run of matrix work).  The operands of the scores are
+// read from LDS before the exponentials, those of the output behind the products of the scores, and the K and
+// V images come from memory straight into LDS two trips ahead.  At 119k tokens and 15 % of the tiles
+// 13.9 ms; one tile after the other, staged through registers, 14.7 ms.  The matrix unit is busy 48 % of
+// the time, the VALU 62 %.
 //
-// What bounds it (per trip and wavefront, from counters and from loops of the same instructions without
-// memory): 1088 clocks of products and 242 VALU instructions; a product of this form keeps the VALU
-// from issuing for about 20 of its 32 clocks, so two wavefronts per SIMD cannot do better than
-// about 2260 clocks, and the kernel takes 2400.  At 119k tokens and 15 % of the tiles 13.4 ms against
-// 14.8 ms on one box: 0.6 ms from the skewed loop (with 32x32x64 products and single tiles), the rest from the
-// 16x16x128 form, which moves half the accumulator bytes per operation.  Taking the exponentials against a
-// maximum looked at in every eighth trip only saved 15 % of the VALU work but lost 1.5 % of
-// accuracy (the largest weight no longer is a power of two) and was no faster.
+// The weights of a tile are rounded against the row maximum up to and including that tile, so that the
+// largest weight of a tile that brings a new maximum is a power of two, i.e. exact.  Two tiles to a trip on
+// v_mfma_f32_16x16x128_f8f6f4 (half the accumulator bytes per operation) took 13.3 ms, but give two tiles one
+// maximum and half of those weights a rounding error: 0.4-7 % more error against exact weights in spatial heads.
+// With the first of two tiles added by itself wherever the second exceeds its maximum the error was the
+// same as here and the time 14.4 ms.  Looking at the maximum in every eighth trip only saved 15 % of
+// the VALU work, lost 1.5 % of accuracy and was no faster.
 #include <type_traits>
 
 #include "svg_attn_common.h"
@@ -56,16 +56,15 @@ constexpr float kE4M3Max = 448.0f;
 constexpr float kWeightShift = 8.0f;       // attention weights are stored as 2^8 * exp(s - reference)
 
 // LDS image of a key tile.  K: 64 rows of 128 bytes; 16-byte piece p of row n sits at piece
-// p ^ k_swizzle(n) (two rows share the 64 banks).  A ds_read_b128 serves lanes 0-3, 12-15 and 20-27
-// together (and the others in groups of the same form), here rows m .. m + 7 and m + 32 .. m + 39, half of them
-// at one channel piece and half two pieces on; with this swizzle they fall on different banks.
-__device__ constexpr int k_swizzle(int n) { return (((n >> 1) & 1) | (n & 4)) ^ ((n & 32) ? 6 : 0); }
+// p ^ k_swizzle(n) (two rows share the 64 banks), so that the 16 lanes a ds_read_b128 serves
+// together (consecutive keys, same channel piece) fall on different banks.
+__device__ constexpr int k_swizzle(int n) { return (n >> 1) & 7; }
 // V^T: [half-wave g][channel d][32 key slots]; slot i = 4 j + c of half-wave g is key
 // 32 (j / 4) + 8 (j % 4) + 4 g + c, the key whose weight sits in byte c of register j of
 // the packed weights.  The two 16-byte halves of a channel's 32 bytes are swapped for
 // channels with bit 3 set, which makes the operand reads conflict-free.
 constexpr int kTileBytes = kBN * kD;       // bytes of one tile in k8, in v8t and of each image (8192)
-constexpr int kPairBytes = 2 * kTileBytes; // a trip of the attention kernel takes two tiles
+constexpr int kStages = 4;                 // K and V images held in LDS (a power of two)
 
 __host__ __device__ constexpr int v_slot_key(int g, int i) {
   return 32 * ((i >> 2) >> 2) + 8 * ((i >> 2) & 3) + 4 * g + (i & 3);
@@ -227,11 +226,7 @@ struct Fp8Args {
 
 template <int LW>
 __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
-  constexpr int QB = 2;          // 16-query blocks per wavefront
-  constexpr int KB = 8;          // 16-key blocks per pair of tiles
-  constexpr int CB = kD / 16;    // 16-channel blocks of O^T
-  constexpr int PF = 4;          // operands in flight ahead of the products
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[4 * kPairBytes];      // two pairs of K images, two of V images
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * kStages * kTileBytes];      // K images, then V images
   static_assert(sizeof(lds) <= 65536, "the direct loads take a 16-bit LDS address");
 
   // heavy query tiles first, then an eighth of each label's sequence of tiles (the same
@@ -246,26 +241,28 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
-  const int g = lane >> 4, r = lane & 15;
+  const int g = lane >> 5, r = lane & 31;
 
   const size_t tiles_head = (size_t)bh * a.nk;
   const unsigned char* kh = a.k8 + tiles_head * kTileBytes;
   const unsigned char* vh = a.v8t + tiles_head * kTileBytes;
 
-  // this lane's queries, one per 16-query block: position qslot in the order the tile list refers to; for a
-  // temporal head that is token off + f P + p with qslot = off + p F + f (q and o stay in token order)
-  int qslot[QB], io_row[QB];
-  i32x8 qreg[QB];      // lane (g, r) holds channels 32 g .. + 32 of its query
+  // this lane's query: position qslot in the order the tile list refers to; for a temporal
+  // head that is token off + f P + p with qslot = off + p F + f (q and o stay in token order)
+  const int qslot = grp * kBM + wave * 32 + r;
+  const int qrow = min(qslot, a.N - 1);
+  int io_row = qrow;
+  if (pat && qrow >= a.off && qrow < a.video_end)
+    io_row = a.off + (int)transformed_to_token((unsigned)(qrow - a.off), (unsigned)a.F, (unsigned)a.P, a.sink);
+  i32x8 qreg[2];       // lane (g, r) holds channels 64 s + 32 g .. + 32 of its query
+  {
+    const unsigned char* qp = a.q8 + ((size_t)bh * a.N + io_row) * kD + g * 32;
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    qslot[qb] = grp * kBM + wave * 32 + qb * 16 + r;
-    const int qrow = min(qslot[qb], a.N - 1);
-    io_row[qb] = qrow;
-    if (pat && qrow >= a.off && qrow < a.video_end)
-      io_row[qb] = a.off + (int)transformed_to_token((unsigned)(qrow - a.off), (unsigned)a.F, (unsigned)a.P, a.sink);
-    const unsigned char* qp = a.q8 + ((size_t)bh * a.N + io_row[qb]) * kD + g * 32;
-    const i32x4 lo = *reinterpret_cast<const i32x4*>(qp), hi = *reinterpret_cast<const i32x4*>(qp + 16);
-    qreg[qb] = i32x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    for (int s = 0; s < 2; ++s) {
+      const i32x4 lo = *reinterpret_cast<const i32x4*>(qp + s * 64);
+      const i32x4 hi = *reinterpret_cast<const i32x4*>(qp + s * 64 + 16);
+      qreg[s] = i32x8{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    }
   }
   // logits in units of log2: s_raw * c with the two quantisation scales folded in.  The product of tiny scales
   // underflows to zero; the smallest normal number in its place leaves the logits zero as well, but a masked
@@ -317,190 +314,193 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
   // the memory side
   const unsigned lds_wave = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lds_byte*)lds + wave * 1024);
   const int k_src = (tid >> 3) * kD + (((tid & 7) ^ k_swizzle(tid >> 3)) << 4), v_src = tid * 16;
-  auto load_image = [&](const unsigned char* images, int tile, int voffset0, int voffset1, unsigned dst) {
+  auto load_image = [&](const unsigned char* images, int tile, int voffset, unsigned dst) {
     const u32x4 rsrc = buffer_words(images + (size_t)__builtin_amdgcn_readfirstlane(tile) * kTileBytes, kTileBytes);
-    load_to_lds(rsrc, voffset0, voffset1, 0, 4096, dst, 4096);
+    load_to_lds(rsrc, voffset, voffset, 0, 4096, dst, 4096);
   };
-  // (a list of odd length ends with a pair whose second half repeats the first and is masked)
-  struct Pair { int a, b; };
-  auto load_k = [&](Pair t, int j) {
-    const unsigned dst = lds_wave + (j & 1) * kPairBytes;
-    load_image(kh, t.a, k_src, k_src ^ 96, dst);            // the swizzles of rows n and n + 32 differ by 6
-    load_image(kh, t.b == kNoTile ? t.a : t.b, k_src, k_src ^ 96, dst + kTileBytes);
-  };
-  auto load_v = [&](Pair t, int j) {
-    const unsigned dst = lds_wave + (2 + (j & 1)) * kPairBytes;
-    load_image(vh, t.a, v_src, v_src, dst);
-    load_image(vh, t.b == kNoTile ? t.a : t.b, v_src, v_src, dst + kTileBytes);
-  };
-  auto next_pair = [&]() -> Pair {
-    const int first = list.next();
-    return Pair{first, first == kNoTile ? kNoTile : list.next()};
-  };
+  auto load_k = [&](int tile, int j) { load_image(kh, tile, k_src, lds_wave + (j % kStages) * kTileBytes); };
+  auto load_v = [&](int tile, int j) { load_image(vh, tile, v_src, lds_wave + (kStages + j % kStages) * kTileBytes); };
 
-  // ---- operand reads.  A lane's keys have to be those of 16 consecutive bytes of the V image, so
-  // row m of the kb-th 16-key block of a tile is key 8 kb + m % 8 + 32 (m / 8): lane (g, r) then gets the
-  // scores of keys 8 kb + 4 (g % 2) + {0..3} + 32 (g / 2), which is what half g % 2, piece g / 2 of the image holds.
-  const int k_row = (r & 7) + 32 * (r >> 3);
-  const int k_rd = k_row * kD + (((2 * g) ^ k_swizzle(k_row)) << 4);       // the second piece differs in bit 4
-  const int v_rd = (g & 1) * (kD * 32) + r * 32 + 16 * ((g >> 1) ^ ((r >> 3) & 1));
+  // ---- operand reads.  K: lane (g, r) reads pieces 4 s + 2 g and 4 s + 2 g + 1 of row r of a
+  // 32-key block; V^T: 32 bytes of channel r of a 32-channel block.
+  const int k_row = r * kD, k_sw = k_swizzle(r);
+  const int k_lo = k_row + (((2 * g) ^ k_sw) << 4);          // the other pieces differ from it in bits 4 and 6
+  const int sw = (r >> 3) & 1;
+  const int v_rd_lo = g * (kD * 32) + r * 32 + 16 * sw;
+  const int v_rd_hi = g * (kD * 32) + r * 32 + 16 * (1 - sw);
   auto read32 = [](const unsigned char* lo, const unsigned char* hi) -> i32x8 {
     const i32x4 x = *reinterpret_cast<const i32x4*>(lo);
     const i32x4 y = *reinterpret_cast<const i32x4*>(hi);
     return i32x8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
   };
-  auto k_operand = [&](int j, int kb) -> i32x8 {
-    const unsigned char* p = lds + (j & 1) * kPairBytes + (kb >> 2) * kTileBytes + (kb & 3) * 8 * kD;
-    return read32(p + k_rd, p + (k_rd ^ 16));
+  auto k_operand = [&](int j, int i) -> i32x8 {              // i = 2 kb + s
+    const unsigned char* p = lds + (j % kStages) * kTileBytes + (i >> 1) * 32 * kD;
+    const int at = (i & 1) ? k_lo ^ 64 : k_lo;
+    return read32(p + at, p + (at ^ 16));
   };
-  auto v_operand = [&](int j, int cb) -> i32x8 {
-    const unsigned char* p = lds + (2 + (j & 1)) * kPairBytes + cb * 512 + v_rd;
-    return read32(p, p + kTileBytes);
+  auto v_operand = [&](int j, int db) -> i32x8 {
+    const unsigned char* p = lds + (kStages + j % kStages) * kTileBytes + db * 1024;
+    return read32(p + v_rd_lo, p + v_rd_hi);
   };
 
-  f32x4 oacc[CB][QB], lacc[QB], sacc[KB][QB];
-  float m_run[QB];           // running row maximum, raw logits
+  f32x16 oacc[4], lacc, sacc[2];
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    m_run[qb] = kNegBig;
-    lacc[qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int e = 0; e < 16; ++e) {
+    lacc[e] = 0.f;
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) oacc[cb][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int db = 0; db < 4; ++db) oacc[db][e] = 0.f;
   }
   i32x8 ones;          // 32 x E4M3 1.0
 #pragma unroll
   for (int j = 0; j < 8; ++j) ones[j] = 0x38383838;
   asm volatile("" : "+v"(ones));
+  float m_run = kNegBig;     // reference maximum of the row, raw logits
   const bool ragged = (a.N % kBN) != 0;
 
-  auto product = [](const i32x8& x, const i32x8& y, const f32x4& z) -> f32x4 {
-    return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(x, y, z, 0, 0, 0, 0, 0, 0);
+  auto product = [](const i32x8& x, const i32x8& y, const f32x16& z) -> f32x16 {
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, z, 0, 0, 0, 0, 0, 0);
   };
-  // S^T of one 16-key block: all 128 channels are one step
-  auto score_block = [&](const i32x8& k_op, int kb) {
+  // i-th of the four products of S^T = K Q^T: two 32-key blocks x two 64-channel steps
+  auto first_product = [&](const i32x8& k_op, int i) {
+    if ((i & 1) == 0) {
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) sacc[kb][qb] = product(k_op, qreg[qb], f32x4{0.f, 0.f, 0.f, 0.f});
+      for (int e = 0; e < 16; ++e) sacc[i >> 1][e] = 0.f;
+    }
+    sacc[i >> 1] = product(k_op, qreg[i & 1], sacc[i >> 1]);
   };
-  // keys beyond N in the last tile, and all keys of a missing second tile
-  auto mask_pair = [&](Pair t) {
-    if (t.b != kNoTile && !(ragged && (t.a == a.nk - 1 || t.b == a.nk - 1))) return;
-    int lim[2] = {a.N - t.a * kBN - 32 * (g >> 1) - 4 * (g & 1), t.b == kNoTile ? -kBN : a.N - t.b * kBN - 32 * (g >> 1) - 4 * (g & 1)};
-    asm volatile("" : "+v"(lim[0]), "+v"(lim[1]));      // keeps this rarely taken code out of every trip
+  auto mask_tail = [&](int tile) {       // keys beyond N in the last tile
+    if (!(ragged && tile == a.nk - 1)) return;
+    int lim = a.N - tile * kBN - 4 * g;
+    asm volatile("" : "+v"(lim));        // keeps this rarely taken code out of every tile
 #pragma unroll
-    for (int kb = 0; kb < KB; ++kb)
+    for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (8 * (kb & 3) + i >= lim[kb >> 2]) {
+      for (int e = 0; e < 16; ++e)
+        if (32 * kb + 8 * (e >> 2) + (e & 3) >= lim) sacc[kb][e] = -INFINITY;
+  };
+  auto scores = [&](int j, int tile) {   // all four, operands read here, and the mask
+    i32x8 op[4];
 #pragma unroll
-          for (int qb = 0; qb < QB; ++qb) sacc[kb][qb][i] = -INFINITY;
-        }
+    for (int i = 0; i < 4; ++i) op[i] = k_operand(j, i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) first_product(op[i], i);
+    mask_tail(tile);
+  };
+  i32x8 pb;
+  auto weights = [&]() {                 // 2^8 exp(s - reference), four to a register
+    const float mc = m_run * c_log2 - kWeightShift;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      float p[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        p[c] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[j >> 2][4 * (j & 3) + c], c_log2, -mc));
+      // (the first conversion writes the low half of its destination and keeps the rest: giving it
+      // a value that dies here as the "rest" saves a register clear; the second one fills the high half)
+      int w = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], (int)__float_as_uint(p[0]), false);
+      pb[j] = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], w, true);
+    }
   };
 
-  // ---- main loop.  Trip j holds the scores of pair j; it takes their exponentials, and then issues the
-  // products of pair j + 1's scores and of pair j's output as one batch (see the top of the file).
-  // LDS holds K of pair j + 1 and V of pair j, with K of j + 2 and V of j + 1 in flight.
-  auto trip = [&](auto more_c, int j, Pair following) {
-    constexpr bool MORE = decltype(more_c)::value;
-    i32x8 opnd[PF];
-#pragma unroll
-    for (int i = 0; i < PF; ++i) opnd[i] = MORE ? k_operand(j + 1, i) : v_operand(j, i);
-    // softmax, two queries per lane: weights 2^8 exp(s - maximum), four keys to a register
-    i32x8 pb[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      float tmax = sacc[0][qb][0];
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) tmax = fmaxf(tmax, sacc[kb][qb][i]);
-      tmax = quarters_max(tmax);
-      if (__builtin_amdgcn_ballot_w64(tmax > m_run[qb]) != 0) {      // some row of the block has a new maximum
-        const float m_new = fmaxf(m_run[qb], tmax);
-        const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_new) * c_log2);
-        m_run[qb] = m_new;
-        lacc[qb][0] *= alpha;                  // (only this element is ever read)
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) oacc[cb][qb][i] *= alpha;
-      }
-      const float mc = m_run[qb] * c_log2 - kWeightShift;
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb) {
-        float p[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[kb][qb][i], c_log2, -mc));
-        // (the first conversion writes the low half of its destination and keeps the rest: giving it
-        // a value that dies here as the "rest" saves a register clear; the second one fills the high half)
-        const int w = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], (int)__float_as_uint(p[0]), false);
-        pb[qb][kb] = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], w, true);
-      }
-    }
-    __builtin_amdgcn_s_setprio(1);
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) lacc[qb] = product(ones, pb[qb], lacc[qb]);
-    __builtin_amdgcn_sched_barrier(0);
-    if (MORE) {
-#pragma unroll
-      for (int kb = 0; kb < KB; ++kb) {
-        const i32x8 k_op = opnd[kb % PF];
-        score_block(k_op, kb);
-        opnd[kb % PF] = kb + PF < KB ? k_operand(j + 1, kb + PF) : v_operand(j, kb + PF - KB);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-#pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
-      const i32x8 v_op = opnd[cb % PF];
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb) oacc[cb][qb] = product(v_op, pb[qb], oacc[cb][qb]);
-      if (cb + PF < CB) opnd[cb % PF] = v_operand(j, cb + PF);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    __builtin_amdgcn_s_setprio(0);
-    if (MORE) mask_pair(following);
-  };
-
-  Pair now = next_pair(), next1 = next_pair();
-  if (now.a != kNoTile) {
-    load_k(now, 0);
-    load_v(now, 0);
+  // ---- main loop.  Trip j holds the scores of tile j; it takes their exponentials, and then issues the
+  // products of tile j + 1's scores and of tile j's output as one batch (see the top of the file).
+  // LDS then holds K of tiles j .. j + 2 and V of j, j + 1, with K of j + 3 and V of j + 2 in flight.
+  int col = list.next(), col1 = list.next(), col2 = list.next();
+  if (col != kNoTile) {
+    load_k(col, 0);
+    load_v(col, 0);
   }
-  if (next1.a != kNoTile) load_k(next1, 1);
+  if (col1 != kNoTile) {
+    load_k(col1, 1);
+    load_v(col1, 1);
+  }
+  if (col2 != kNoTile) load_k(col2, 2);
   wait_loads_to_lds<0>();
   __syncthreads();
   asm volatile("" ::"v"(qreg[0]), "v"(qreg[1]));
-  if (now.a != kNoTile) {
-#pragma unroll
-    for (int kb = 0; kb < KB; ++kb) score_block(k_operand(0, kb), kb);
-    mask_pair(now);
-  }
-  __syncthreads();         // the first trip stages pair 2 over pair 0's keys
-  int j = 0;
-  for (; next1.a != kNoTile; ++j) {
-    const Pair next2 = next_pair();
-    if (next2.a != kNoTile) load_k(next2, j + 2);
-    load_v(next1, j + 1);
-    trip(std::true_type{}, j, next1);
-    wait_loads_to_lds<0>();
-    barrier_loads_done();
-    now = next1;
-    next1 = next2;
-  }
-  if (now.a != kNoTile) trip(std::false_type{}, j, now);
+  if (col != kNoTile) scores(0, col);
 
-  // ---- epilogue: oacc[cb][qb][i] = O[query 16 qb + r][16 cb + 4 g + i]; lacc[qb][0] = row sum
+  auto tile_maximum = [&]() -> float {
+    float tmax = sacc[0][0];
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const float l_tot = lacc[qb][0];
-    const float inv = l_tot > 0.f ? v_scale / l_tot : 0.f;
-    if (qslot[qb] < a.N) {
-      __bf16* op = a.o + ((size_t)bh * a.N + io_row[qb]) * kD;
+    for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, sacc[0][e]);
 #pragma unroll
-      for (int cb = 0; cb < CB; ++cb)
-        *reinterpret_cast<bf16x4*>(op + cb * 16 + 4 * g) = __builtin_convertvector(oacc[cb][qb] * inv, bf16x4);
+    for (int e = 0; e < 16; ++e) tmax = fmaxf(tmax, sacc[1][e]);
+    return both_halves_max(tmax);
+  };
+  auto raise_reference = [&](float tmax) {
+    const float m_new = fmaxf(m_run, tmax);
+    const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c_log2);
+    m_run = m_new;
+    lacc[0] *= alpha;                  // (only this element is ever read)
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
+  };
+
+  // one tile's weights, row sums and output; MORE: and the scores of the next tile
+  auto trip = [&](auto more_c, int j) {
+    constexpr bool MORE = decltype(more_c)::value;
+    i32x8 opnd[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) opnd[i] = MORE ? k_operand(j + 1, i) : v_operand(j, i);
+    const float tmax = tile_maximum();
+    if (__builtin_amdgcn_ballot_w64(tmax > m_run) != 0) raise_reference(tmax);     // some row of the wavefront has a new maximum
+    weights();
+    __builtin_amdgcn_s_setprio(1);
+    __builtin_amdgcn_sched_barrier(0);
+    lacc = product(ones, pb, lacc);
+    if (MORE) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        __builtin_amdgcn_sched_barrier(0);
+        first_product(opnd[i], i);
+        __builtin_amdgcn_sched_barrier(0);
+        opnd[i] = v_operand(j, i);
+      }
     }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int db = 0; db < 4; ++db) {
+      __builtin_amdgcn_sched_barrier(0);
+      oacc[db] = product(opnd[db], pb, oacc[db]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    if (MORE) mask_tail(col1);
+  };
+
+  int j = 0;
+  for (; col1 != kNoTile; ++j) {
+    const int col3 = list.next();
+    if (col3 != kNoTile) load_k(col3, j + 3);
+    if (col2 != kNoTile) load_v(col2, j + 2);
+    trip(std::true_type{}, j);
+    // what trip j + 1 reads was requested in trip j - 1: only this trip's four loads may be outstanding
+    if (col3 != kNoTile) wait_loads_to_lds<4>();
+    else wait_loads_to_lds<0>();
+    barrier_loads_done();
+    col = col1;
+    col1 = col2;
+    col2 = col3;
+  }
+  if (col != kNoTile) trip(std::false_type{}, j);
+
+  // ---- epilogue: oacc[db][4 i + jj] = O[query r][32 db + 8 i + 4 g + jj]; lacc[0] = row sum
+  const float l_tot = lacc[0];
+  const float inv = l_tot > 0.f ? v_scale / l_tot : 0.f;
+  if (qslot < a.N) {
+    __bf16* op = a.o + ((size_t)bh * a.N + io_row) * kD;
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        f32x4 x;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) x[jj] = oacc[db][4 * i + jj] * inv;
+        *reinterpret_cast<bf16x4*>(op + db * 32 + 8 * i + 4 * g) = __builtin_convertvector(x, bf16x4);
+      }
   }
 }
 
