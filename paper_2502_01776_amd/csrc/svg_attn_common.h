@@ -159,20 +159,20 @@ __device__ __forceinline__ bool sparse_slot(const SparseOrder so, const int BH, 
                                             int& pat, int& cl, int& head_cl0) {
   const int xcd = blockIdx.x & 7, loc = blockIdx.x >> 3;
   const int lane = threadIdx.x & 63;
-  // the labels as bit masks, 64 heads per word (bit = temporal)
+  // The labels as bit masks, 64 heads per word (bit = temporal).  Words of their own, not an array: the
+  // compiler put an array into LDS (8 KB of it) or scratch memory.
+  static_assert(LW == 1 || LW == 4, "one variable per word");
   const bool classed = labels != nullptr && BH <= 64 * LW;
-  unsigned long long m[LW];
-  int nT = 0;
-#pragma unroll
-  for (int w = 0; w < LW; ++w) {
+  auto label_word = [&](int w) -> unsigned long long {
     const int h = 64 * w + lane;
-    m[w] = classed && 64 * w < BH ? __builtin_amdgcn_ballot_w64(h < BH && labels[h < BH ? h : 0] != 0) : 0ull;
-    nT += __builtin_popcountll(m[w]);
-  }
+    return classed && 64 * w < BH ? __builtin_amdgcn_ballot_w64(h < BH && labels[h < BH ? h : 0] != 0) : 0ull;
+  };
+  const unsigned long long m0 = label_word(0);
+  const unsigned long long m1 = LW > 1 ? label_word(1) : 0ull, m2 = LW > 1 ? label_word(2) : 0ull, m3 = LW > 1 ? label_word(3) : 0ull;
+  const int nT = __builtin_popcountll(m0) + __builtin_popcountll(m1) + __builtin_popcountll(m2) + __builtin_popcountll(m3);
   auto label_bit = [&](int h) -> int {
-    unsigned long long word = m[0];
-#pragma unroll
-    for (int w = 1; w < LW; ++w) word = (h >> 6) == w ? m[w] : word;
+    const int w = h >> 6;
+    const unsigned long long word = LW == 1 || w == 0 ? m0 : w == 1 ? m1 : w == 2 ? m2 : m3;
     return (int)((word >> (h & 63)) & 1);
   };
   cl = -1;
@@ -232,11 +232,10 @@ __device__ __forceinline__ bool sparse_slot(const SparseOrder so, const int BH, 
     bh = 0;
     int before = 0;
     bool found = false;
-#pragma unroll
-    for (int w = 0; w < LW; ++w) {
+    auto look_in = [&](int w, unsigned long long word) {
       const int left = BH - 64 * w;
       const unsigned long long valid = left >= 64 ? ~0ull : left > 0 ? (1ull << left) - 1 : 0ull;
-      const unsigned long long cm = c ? m[w] : ~m[w] & valid;
+      const unsigned long long cm = c ? word : ~word & valid;
       const int cnt = __builtin_popcountll(cm);
       if (!found && kth < before + cnt) {
         const int rank = __builtin_popcountll(cm & ((1ull << lane) - 1));
@@ -245,6 +244,12 @@ __device__ __forceinline__ bool sparse_slot(const SparseOrder so, const int BH, 
         found = true;
       }
       before += cnt;
+    };
+    look_in(0, m0);
+    if (LW > 1) {
+      look_in(1, m1);
+      look_in(2, m2);
+      look_in(3, m3);
     }
     pat = c;
   } else {

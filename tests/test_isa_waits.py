@@ -3,7 +3,8 @@ compiler's output for gfx950 (CPU only).
 
 The loads straight into LDS are assembly, so the compiler neither sees a buffer load in them nor keeps the
 distances the hardware asks for: a load that reads a scalar register which a vector instruction wrote must issue at
-least five wait states later, or it may see the register's old value."""
+least five wait states later, or it may see the register's old value.  Their LDS address has 16 bits, so the staged
+tiles have to lie in the first 64 KB of a kernel's LDS: they are the start of its only object."""
 import os
 import re
 import subprocess
@@ -122,3 +123,15 @@ def test_direct_loads_read_settled_scalar_registers(compiled):
             n = k.nearest_vector_write(at, pred)
             lines = "; ".join(f"{op} {', '.join(args)}" for op, args, _ in k.ins[max(0, at - 8):at + 1])
             assert n >= WAIT_STATES, f"{k.name}: {n} wait states in front of load {at}: {lines}"
+
+
+def test_staged_tiles_are_the_only_object_in_lds(compiled):
+    """Anything else the compiler puts into LDS could stand in front of the tiles and move them out of reach."""
+    text, kernels = compiled
+    size = dict(re.findall(r"\.amdhsa_kernel (\w+)\n\s*\.amdhsa_group_segment_fixed_size (\d+)", text))
+    for k in kernels:
+        if k.direct_loads():
+            m = re.search(r"11attn_kernelILi(\d+)ELi(\d+)ELi(\d+)E", k.name)
+            D, waves, keys = map(int, m.groups()) if m else (128, 0, 64)
+            tiles = 2 * 2 * keys * D * 2 if m else 8 * keys * D       # two stages of K and V in bf16; four in FP8
+            assert tiles <= 65536 and int(size[k.name]) == tiles + 2 * waves * 4, k.name
