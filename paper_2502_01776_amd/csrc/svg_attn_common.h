@@ -42,6 +42,11 @@ __device__ __forceinline__ u32x4 buffer_words(const void* base, unsigned bytes) 
 // not in front of this statement, so the statement holds all of it: one for s_mov, four for s_nop 3.  Two loads
 // share it (a statement with the same wait for every load cost 0.0-0.4 % of the attention passes, this one
 // nothing that could be measured).
+// The statement overwrites m0 and says so; the compiler warns that it will not save a reserved register, once for
+// every place the function is inlined.  Nothing has to be saved: no other instruction of these kernels uses
+// m0 (a test looks through the compiler's output for one).
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ __forceinline__ void load_to_lds(const u32x4 rsrc, int voffset0, int voffset1, int soffset0, int soffset1,
                                             unsigned lds_address, const int step) {
   asm volatile("s_mov_b32 m0, %5\n\ts_nop 3\n\tbuffer_load_dwordx4 %0, %2, %3 offen lds\n\t"
@@ -49,6 +54,7 @@ __device__ __forceinline__ void load_to_lds(const u32x4 rsrc, int voffset0, int 
                :: "v"(voffset0), "v"(voffset1), "s"(rsrc), "s"(soffset0), "s"(soffset1), "s"(lds_address), "i"(step)
                : "memory", "m0", "scc");
 }
+#pragma clang diagnostic pop
 // Waits until at most N of this wavefront's loads are outstanding (they complete in order).
 template <int N>
 __device__ __forceinline__ void wait_loads_to_lds() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }

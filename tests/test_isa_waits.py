@@ -4,7 +4,8 @@ compiler's output for gfx950 (CPU only).
 The loads straight into LDS are assembly, so the compiler neither sees a buffer load in them nor keeps the
 distances the hardware asks for: a load that reads a scalar register which a vector instruction wrote must issue at
 least five wait states later, or it may see the register's old value.  Their LDS address has 16 bits, so the staged
-tiles have to lie in the first 64 KB of a kernel's LDS: they are the start of its only object."""
+tiles have to lie in the first 64 KB of a kernel's LDS: they are the start of its only object.  And they overwrite
+m0, which the compiler does not save for them."""
 import os
 import re
 import subprocess
@@ -93,12 +94,12 @@ def parse(text):
 @pytest.fixture(scope="module", params=["svg_attn.hip", "svg_fp8.hip"])
 def compiled(request, tmp_path_factory):
     out = str(tmp_path_factory.mktemp("isa") / "kernels.s")
-    subprocess.run([B.hipcc_path(), *B.compile_flags(), "--offload-device-only", "-S", os.path.join(B.CSRC, request.param), "-o", out],
-                   check=True, capture_output=True, text=True)
+    res = subprocess.run([B.hipcc_path(), *B.compile_flags(), "--offload-device-only", "-S", os.path.join(B.CSRC, request.param),
+                          "-o", out], check=True, capture_output=True, text=True)
     text = open(out).read()
     kernels = parse(text)
     assert sum(len(k.direct_loads()) for k in kernels) > 0
-    return text, kernels
+    return text, kernels, res.stderr
 
 
 def test_reader_of_the_listing_finds_a_missing_wait():
@@ -127,7 +128,7 @@ def test_direct_loads_read_settled_scalar_registers(compiled):
 
 def test_staged_tiles_are_the_only_object_in_lds(compiled):
     """Anything else the compiler puts into LDS could stand in front of the tiles and move them out of reach."""
-    text, kernels = compiled
+    text, kernels, _ = compiled
     size = dict(re.findall(r"\.amdhsa_kernel (\w+)\n\s*\.amdhsa_group_segment_fixed_size (\d+)", text))
     for k in kernels:
         if k.direct_loads():
@@ -135,3 +136,16 @@ def test_staged_tiles_are_the_only_object_in_lds(compiled):
             D, waves, keys = map(int, m.groups()) if m else (128, 0, 64)
             tiles = 2 * 2 * keys * D * 2 if m else 8 * keys * D       # two stages of K and V in bf16; four in FP8
             assert tiles <= 65536 and int(size[k.name]) == tiles + 2 * waves * 4, k.name
+
+
+def test_m0_is_used_by_the_direct_loads_only(compiled):
+    for k in compiled[1]:
+        if k.direct_loads():
+            other = [(op, args) for op, args, asm in k.ins if not asm and "m0" in args]
+            assert not other, f"{k.name}: {other[:3]}"
+
+
+def test_the_compiler_has_nothing_to_say(compiled):
+    """(a warning per inlined load, 600 of them, once hid whatever else there was)"""
+    lines = [l for l in compiled[2].splitlines() if "warning" in l and "--hip-link" not in l]
+    assert not lines, lines[:3]
