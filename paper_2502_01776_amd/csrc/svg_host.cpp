@@ -20,11 +20,15 @@ void note_hip_error(hipError_t e) { g_last_hip_error = e; }
 //    that finish last are short ones (1-3 % less time than eight equal parts; anything from
 //    four to eight parts measured within 1 % of each other).  Fewer parts for short sequences,
 //    and three when the sampled rows alone already give every XCD hundreds of workgroups.
-//    Below 24 key tiles one part, except at head dimension 128 where the masked passes are cut: there
-//    three, and one part less of each masked pass (the same workspace), because a workgroup walks its
-//    tiles one after the other and those of the unmasked pass were the longest chain of the call: a layer of
-//    960 rows and 6 heads 62.0 -> 57.9 us.  At head dimension 64, with half the products per tile, the
-//    shorter cut of the masked passes costs more: 40.8 -> 41.9 us at 787 rows and 8 heads.
+//    Below 24 key tiles one part, except for few sampled rows at head dimension 128 where the masked
+//    passes are cut: from 13 tiles and up to 64 rows three, and one part less of each masked pass (the same
+//    workspace), because a workgroup walks its tiles one after the other and those of the unmasked pass are the
+//    longest chain of the call.  Profiling of 2 to 24 heads, this cut against one part: 13 tiles 23.9 -> 22.1 us
+//    (16 rows) and 28.0 -> 27.9 (64 rows), 15 tiles 26.8 -> 23.7 and 31.2 -> 29.9, 19 tiles 31.8 -> 28.1 and 36.4 -> 35.3,
+//    23 tiles 36.1 -> 30.7 (16 rows); of all cases inside the line none more than 0.8 % slower.  Outside it the
+//    shorter cut of the masked passes costs more than it gives: 128 rows 33.3 -> 35.5 us at 13 tiles and 42.5 -> 43.6
+//    at 19; 8 tiles 26.3 -> 29.3 (100 rows); 11 tiles 25.8 -> 26.7 (64 rows); head dimension 64, with half the
+//    products per tile, 12 tiles 22.6 -> 24.9 and 19 tiles 28.6 -> 32.3 (100 rows), 23.7 -> 24.3 (19 tiles, 16 rows).
 //  * Masked passes: one part each, unless the (head, row group) pairs are so few that the two
 //    masked workgroups per pair cannot fill an XCD; then as many parts (up to four) as keep
 //    them within its resident places.  CogVideoX-v1 at 1 % (12 pairs per XCD): three parts,
@@ -52,10 +56,10 @@ ProfilePlan profile_plan(const Geo& g, int t) {
   const int groups = (t + g.bm - 1) / g.bm;
   const long long pairs = (long long)g.B * g.H * groups;
   const long long pairs_x = (pairs + 7) / 8;
-  ProfilePlan plan = {};
+  ProfilePlan plan = {};      // the error pass is built for 1, 3, 4 and 6 parts of the unmasked pass
   const int slots = g.D == 64 ? kSlots * 3 / 2 : kSlots;
   plan.n_masked = (int)std::max<long long>(1, std::min<long long>(kMaxMaskedParts, (slots - 8) / (2 * pairs_x)));
-  if (g.nk >= 6 && g.nk < 24 && plan.n_masked >= 3 && g.D == 128) {
+  if (g.nk >= 13 && g.nk < 24 && t <= 64 && plan.n_masked >= 3 && g.D == 128) {
     --plan.n_masked;
     fill_bounds(&plan, 3, 0, g.nk);
   } else if (g.nk < 24) fill_bounds(&plan, 1, 0, g.nk);

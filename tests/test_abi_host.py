@@ -268,6 +268,27 @@ def test_profile_plan_is_well_formed_for_every_workload():
     assert lib.svg_profile_plan(C.byref(sh), 8, C.byref(nf), C.byref(nm), None) == 0
 
 
+def test_profile_plan_part_counts_and_the_line_of_the_three_part_cut():
+    """Every shape gets a number of unmasked parts the error pass is built for, and the cut of short
+    sequences into three starts where it was measured to pay: 13 key tiles, up to 64 sampled rows, head
+    dimension 128 (one part and one masked part more otherwise)."""
+    def plan(nk, t, H=2, D=128):
+        cfg = dict(get_config("mid128"), B=1, H=H, D=D, F=1, P=64 * nk, T=0, N=64 * nk)
+        return S.svg_profile_plan(S.shape_from_config(cfg), t)
+    for nk in (6, 8, 12):
+        assert plan(nk, 16)[:2] == plan(nk, 64)[:2] == (1, 4)
+    for nk in (13, 23):
+        assert plan(nk, 16)[:2] == plan(nk, 64)[:2] == (3, 3)
+        assert plan(nk, 65)[:2] == plan(nk, 128)[:2] == plan(nk, 16, D=64)[:2] == (1, 4)
+    assert plan(13, 16, H=200)[0] == 1                       # the masked passes are not cut
+    for D in (64, 128):
+        for nk in (1, 2, 5, 6, 13, 23, 24, 95, 96, 2000):
+            for H in (1, 7, 24, 65, 300, 3000):
+                for t in (1, 16, 64, 65, 129, 1200, 5000):
+                    nf, nm, bound = plan(nk, t, H, D)
+                    assert nf in (1, 3, 4, 6) and 1 <= nm <= 4 and bound[nf] == nk and bound[0] == 0
+
+
 def test_fp8_buffer_sizes_and_argument_checks_without_gpu():
     lib = S.lib()
     cfg = get_config("mid128")

@@ -37,7 +37,8 @@ def test_numbers_of_sampled_rows(t, blocks, D):
 
 
 @pytest.mark.parametrize("H, F, P, t, n_full, D", [(2, 5, 150, 24, 1, 64), (2, 9, 190, 130, 4, 64), (2, 9, 700, 70, 6, 64),
-                                                   (64, 5, 200, 1024, 3, 64), (2, 1, 250, 24, 1, 128), (2, 1, 300, 24, 3, 128),
+                                                   (64, 5, 200, 1024, 3, 64), (2, 1, 250, 24, 1, 128), (2, 1, 300, 24, 1, 128),
+                                                   (2, 5, 158, 24, 3, 128), (2, 5, 158, 65, 1, 128),
                                                    (2, 9, 150, 24, 3, 128), (64, 5, 150, 140, 1, 128)])
 def test_parts_of_the_unmasked_pass(H, F, P, t, n_full, D):
     b = (32, 32) if t == 1024 else (128, 64)
