@@ -8,11 +8,26 @@ import torch
 import paper_2502_01776_amd as S
 from oracle import svg_oracle as O
 from workloads import get_config, make_plain_qkv
-from helpers import f64, dev_i32, gpu_fp8_quantize, assert_attn_close, assert_fp8_attn_close
+from helpers import (f64, dev_i32, gpu_fp8_quantize, gpu_layer, gpu_layer_in_place, gpu_layer_kv2, assert_attn_close,
+                     assert_fp8_attn_close)
 
 pytestmark = pytest.mark.gpu
 
 LENGTHS = [0, 1, 2, 3, 4, 5, 62, 63, 64, 65, 66, 126, 127, 128, 129, 130, 131, 132]
+
+
+def random_lists(nq, nk, last_tile, seed):
+    """One list of every length for the first query tiles, empty ones for the others."""
+    rng = np.random.default_rng(seed)
+    lists = [np.zeros(0, np.int32)] * nq
+    for i, n in enumerate(LENGTHS):
+        cols = np.sort(rng.choice(nk, n, replace=False)).astype(np.int32)
+        if last_tile and n:
+            cols[-1] = nk - 1
+        elif n and n < nk:
+            cols = np.sort(rng.choice(nk - 1, n, replace=False)).astype(np.int32)
+        lists[i] = cols
+    return np.concatenate([[0], np.cumsum([len(c) for c in lists])]).astype(np.int32), np.concatenate(lists)
 
 
 @pytest.mark.parametrize("last_tile", [False, True])
@@ -23,17 +38,7 @@ def test_list_lengths(D, fp8, last_tile):
     sh, g = S.shape_from_config(cfg), O.Geometry.from_config(cfg)
     nq, nk = S.svg_tile_counts(sh)
     assert nk == 132 and nq >= len(LENGTHS)
-    rng = np.random.default_rng(D + last_tile)
-    lists = [np.zeros(0, np.int32)] * nq
-    for i, n in enumerate(LENGTHS):
-        cols = np.sort(rng.choice(nk, n, replace=False)).astype(np.int32)
-        if last_tile and n:
-            cols[-1] = nk - 1
-        elif n and n < nk:
-            cols = np.sort(rng.choice(nk - 1, n, replace=False)).astype(np.int32)
-        lists[i] = cols
-    rp = np.concatenate([[0], np.cumsum([len(c) for c in lists])]).astype(np.int32)
-    ci = np.concatenate(lists)
+    rp, ci = random_lists(nq, nk, last_tile, D + last_tile)
     csr = [dev_i32(rp), dev_i32(ci), dev_i32(rp), dev_i32(ci)]
     # logits that grow along the sequence, so that the reference maximum of the softmax has to follow
     q, k, v = make_plain_qkv(1, 1, g.N, D, seed=D)
@@ -59,6 +64,53 @@ def test_list_lengths(D, fp8, last_tile):
             assert_fp8_attn_close(o[0, 0, rows], ref[rows], float(np.abs(vh).max()), f"{LENGTHS[a]} tiles")
         else:
             assert_attn_close(o[0, 0, rows], ref[rows], f"{LENGTHS[a]} tiles")
+
+
+@pytest.mark.parametrize("last_tile", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("form, blocks", [("gather", (128, 64)), ("exact", (128, 64)), ("exact", (32, 32)), ("plain", (32, 32))])
+def test_list_lengths_of_the_other_forms(form, blocks, D, last_tile):
+    """The forms with loops of their own: the gathering one (row numbers fetched a tile ahead of their rows), the one
+    under element masks (one tile after the other) and the 32-row ones; a spatial and a temporal head."""
+    P = 2812 if blocks[1] == 64 else 1404
+    cfg = dict(get_config("mid128"), B=1, H=2, F=3, P=P, T=0, D=D, w_s=1, w_t=P // 3, spatial_heads=[0],
+               block_m=blocks[0], block_n=blocks[1])
+    cfg["N"] = cfg["F"] * cfg["P"]                      # 131 full key tiles and a part of one
+    sh, g = S.shape_from_config(cfg), O.Geometry.from_config(cfg)
+    nq, nk = S.svg_tile_counts(sh)
+    assert nk == 132 and nq >= len(LENGTHS) and g.N % blocks[1]
+    csr = [random_lists(nq, nk, last_tile, 2 * D + 10 * h + last_tile) for h in (0, 1)]
+    lists = [dev_i32(x) for rp_ci in csr for x in rp_ci]
+    q, k, v = make_plain_qkv(1, 2, g.N, D, seed=D)
+    k = (k.float() * torch.linspace(0.2, 3.0, g.N)[None, None, :, None]).bfloat16()
+    qc, kc, vc = q.cuda(), k.cuda(), v.cuda()
+    lab = torch.tensor([0, 1], dtype=torch.uint8, device="cuda")
+    if form == "gather":
+        o, guard_ok = gpu_layer_in_place(sh, qc, kc, vc, lab, lists)
+        assert guard_ok
+    elif form == "exact":
+        o, _, _ = gpu_layer_kv2(sh, qc, kc, vc, lab, lists, flags=S.SVG_ATTN_ELEMENT_MASK)
+    else:
+        o = gpu_layer(sh, qc, kc, vc, lab, lists)
+    in_order = np.empty(g.N, np.int64)
+    in_order[O.layout_perm(g)] = np.arange(g.N)
+    for h in (0, 1):
+        token = in_order if h else np.arange(g.N)       # token of each row of the order the lists refer to
+        rp, ci = csr[h]
+        got = f64(o)[0, h][token]
+        for a, n in enumerate(LENGTHS):
+            rows = slice(a * g.block_m, min(g.N, (a + 1) * g.block_m))
+            cols = np.concatenate([np.arange(b * g.block_n, min(g.N, (b + 1) * g.block_n)) for b in ci[rp[a]:rp[a + 1]]] or
+                                  [np.zeros(0, np.int64)])
+            qr, kr, vr = f64(q)[0, h][token[rows]], f64(k)[0, h][token[cols]], f64(v)[0, h][token[cols]]
+            keep = np.ones((len(qr), len(cols)), bool)
+            if form == "exact":
+                keep = (O.temporal_mask if h else O.spatial_mask)(g, token[rows])[:, token[cols]]
+            some = keep.any(1)
+            assert (got[rows][~some] == 0).all(), f"{form} head {h}, {n} tiles: rows without keys"
+            if some.any():
+                ref = O.masked_attention(qr[some], kr, vr, keep[some], g.scale)
+                assert_attn_close(torch.from_numpy(got[rows][some]), ref, f"{form} head {h}, {n} tiles")
 
 
 @pytest.mark.parametrize("P", [1, 7, 1023, 1024, 1025, 1027])
