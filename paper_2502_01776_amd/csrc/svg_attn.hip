@@ -105,8 +105,13 @@ constexpr int prefetch_depth(int D, int NW, int MODE) {
 // 168 registers: three workgroups per CU, whose wavefronts cover each other's softmax phases
 // (the longer phase at this head dimension) better than two workgroups with twice the keys per
 // barrier did (4-7 % less time in the dense and sparse passes, 14 % in profiling).
+// The 32-row form is a single wavefront, and asking for two per SIMD keeps it inside 256 registers: with more
+// allowed (one per SIMD, or LDS for four workgroups on the CU's four SIMDs) the compiler puts every accumulator
+// into the second half of the register file and moves it to the first and back around the softmax, 144 of 480
+// instructions of a tile at head dimension 64 and 240 of 679 at 128: 12 heads of 1410 rows dense 36.8 -> 28.1 and
+// 53.7 -> 42.3 us, sparse 35.2 -> 28.3 and 53.0 -> 40.0.
 constexpr int waves_per_simd(int D, int NW, int MODE) {
-  return NW != 4 ? 1 : D == 64 ? 3 : 2;
+  return NW != 4 ? 2 : D == 64 ? 3 : 2;
 }
 
 template <int D, int NW, int BN, int MODE, int LW>
@@ -149,14 +154,10 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   constexpr int V_BYTES = BN * V_ROW;
   constexpr int STAGE_BYTES = K_BYTES + V_BYTES;
 
-  // One block, the staged tiles first: the direct loads take a 16-bit LDS address.
-  struct Shared {
-    unsigned char tiles[2 * STAGE_BYTES];      // two K tiles, two V tiles
-    int wave_range[2 * NW];    // profile: smallest and largest coordinate of each wavefront's rows
-  };
+  // Two K tiles, two V tiles, and nothing else: the direct loads take a 16-bit LDS address, and with 8 bytes
+  // more the 32-row form at head dimension 128 fits a CU four times, not five (see waves_per_simd).
   static_assert(2 * STAGE_BYTES <= 65536, "the direct loads take a 16-bit LDS address");
-  __shared__ __attribute__((aligned(1024))) Shared shared;
-  unsigned char* const lds = shared.tiles;
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * STAGE_BYTES];
 
   // ======================================================================================
   // Which (head, row group) is this workgroup?  Consecutive logical ids are placed on the
@@ -309,14 +310,16 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
     // skips it, and it need not widen this workgroup's key range)
     // reduced inside the wavefronts first: LDS atomics of all 64 lanes on one address are expanded into
     // a loop over the lanes, 1 us per atomic at the start of every workgroup
-    shared.wave_range[2 * wave] = quad_rows_min(c_lo);
-    shared.wave_range[2 * wave + 1] = -quad_rows_min(-c_hi);
+    int* const wave_range = reinterpret_cast<int*>(lds);      // smallest and largest coordinate of each wavefront's rows
+    wave_range[2 * wave] = quad_rows_min(c_lo);
+    wave_range[2 * wave + 1] = -quad_rows_min(-c_hi);
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      c_lo = min(c_lo, shared.wave_range[2 * w]);
-      c_hi = max(c_hi, shared.wave_range[2 * w + 1]);
+      c_lo = min(c_lo, wave_range[2 * w]);
+      c_hi = max(c_hi, wave_range[2 * w + 1]);
     }
+    __syncthreads();       // the first tile is staged over the ranges
     c_lo = __builtin_amdgcn_readfirstlane(c_lo);
     c_hi = __builtin_amdgcn_readfirstlane(c_hi);
   }

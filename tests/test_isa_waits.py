@@ -132,10 +132,19 @@ def test_staged_tiles_are_the_only_object_in_lds(compiled):
     size = dict(re.findall(r"\.amdhsa_kernel (\w+)\n\s*\.amdhsa_group_segment_fixed_size (\d+)", text))
     for k in kernels:
         if k.direct_loads():
-            m = re.search(r"11attn_kernelILi(\d+)ELi(\d+)ELi(\d+)E", k.name)
-            D, waves, keys = map(int, m.groups()) if m else (128, 0, 64)
+            m = re.search(r"11attn_kernelILi(\d+)ELi\d+ELi(\d+)E", k.name)
+            D, keys = map(int, m.groups()) if m else (128, 64)
             tiles = 2 * 2 * keys * D * 2 if m else 8 * keys * D       # two stages of K and V in bf16; four in FP8
-            assert tiles <= 65536 and int(size[k.name]) == tiles + 2 * waves * 4, k.name
+            assert tiles <= 65536 and int(size[k.name]) == tiles, k.name
+
+
+def test_no_accumulator_is_moved_between_the_halves_of_the_register_file(compiled):
+    """With more than 256 registers allowed the compiler keeps the accumulators in the second half and moves
+    them around every softmax, a third of a tile's instructions."""
+    for k in compiled[1]:
+        if k.direct_loads():
+            moves = [op for op, _, _ in k.ins if op.startswith("v_accvgpr")]
+            assert not moves, f"{k.name}: {len(moves)} moves"
 
 
 def test_m0_is_used_by_the_direct_loads_only(compiled):
