@@ -66,7 +66,7 @@ __device__ __forceinline__ void barrier_loads_done() {
   asm volatile("" ::: "memory");
 }
 
-// The tiles of a kept-tile list row, handed out in turn, from entry `start` on and around its end:
+// The tiles of a kept-tile list row, handed out in turn, from entry `start` on and around its end, then kNoTile:
 // 64 entries at a time wait in a register (one per lane), the next 64 are in flight.  Every value taken
 // is the same in all lanes.
 struct TileList {
@@ -84,16 +84,15 @@ struct TileList {
     len = len_;
     start = start_;
     taken = 0;
-    now = load(0);
-    ahead = kNoTile;
-    if (len > 64) ahead = load(64);
+    ahead = load(0);
   }
+  // One rarely taken branch: a workgroup that has its compute unit to itself feels every instruction between two tiles.
   __device__ __forceinline__ int next() {
-    if (taken >= len) return kNoTile;
     const int lane = taken & 63;
-    if (lane == 0 && taken > 0) {
+    if (lane == 0) {
       now = ahead;
-      if (taken + 64 < len) ahead = load(taken + 64);
+      asm volatile("" : "+v"(now));       // the copy first: the next 64 then go to the register they are waited for in
+      ahead = load(taken + 64);
     }
     ++taken;
     return __builtin_amdgcn_readlane(now, lane);
