@@ -663,8 +663,12 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
 #pragma unroll
           for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-              if (!(word[kb >> 1] & (1u << (16 * (kb & 1) + i)))) sacc[kb][qb][i] = -INFINITY;
+            for (int i = 0; i < 4; ++i) {
+              // the score or -inf by bits: two instructions and no condition register per score, where a
+              // compare and a select took three and a register pair each
+              const unsigned kept = (unsigned)__builtin_amdgcn_sbfe((int)word[kb >> 1], 16 * (kb & 1) + i, 1);
+              sacc[kb][qb][i] = __uint_as_float((__float_as_uint(sacc[kb][qb][i]) & kept) | (0xff800000u & ~kept));
+            }
         }
       }
     } else if (ragged && tile == a.nk - 1) {
