@@ -353,14 +353,29 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
     }
   }
 
-  // smallest and largest window bounds over the rows of the wavefront: most tiles lie inside every
-  // row's window or outside all of them, which these decide without a look at the rows
+  // smallest and largest window bounds over the video rows of the wavefront: most tiles lie inside every
+  // such row's window or outside all of them, which these decide without a look at the rows
   int lo_min = 0, lo_max = 0, hi_min = 0, hi_max = 0;
+  bool video[QB] = {}, has_text = false;
   if (MASKABLE) {
-    lo_min = quad_rows_min(min(win_lo[0], win_lo[1]));
-    lo_max = -quad_rows_min(-max(win_lo[0], win_lo[1]));
-    hi_min = quad_rows_min(min(win_hi[0], win_hi[1]));
-    hi_max = -quad_rows_min(-max(win_hi[0], win_hi[1]));
+    int lo[2] = {0x7fffffff, 0x7fffffff}, hi[2] = {0x7fffffff, 0x7fffffff};      // smallest, smallest negative
+    bool text = false;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      video[qb] = qrow[qb] >= a.off && qrow[qb] < a.video_end;
+      text = text || !video[qb];
+      if (video[qb]) {
+        lo[0] = min(lo[0], win_lo[qb]);
+        lo[1] = min(lo[1], -win_lo[qb]);
+        hi[0] = min(hi[0], win_hi[qb]);
+        hi[1] = min(hi[1], -win_hi[qb]);
+      }
+    }
+    lo_min = quad_rows_min(lo[0]);
+    lo_max = -quad_rows_min(lo[1]);
+    hi_min = quad_rows_min(hi[0]);
+    hi_max = -quad_rows_min(hi[1]);
+    has_text = __builtin_amdgcn_ballot_w64(text) != 0;
   }
 
   bf16x8 qreg[QB][DS];     // lane (g, r) holds Q[row 16 qb + r][32 s + 8 g .. +8]
@@ -620,7 +635,10 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
     } else if (first + BN <= 2 * a.P) {        // the end of one frame and the start of the next
       none = first >= hi_max && first + BN - a.P <= lo_min;
     }
-    t.skip = none;
+    // (a text row keeps everything: beside video rows that keep nothing it needs the tile, but no bits)
+    t.skip = none && !has_text;
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) t.drop[qb] = none && video[qb];
     if (!all && !none) {
       auto ones = [](int n) -> unsigned long long {      // the n lowest bits
         n = min(max(n, 0), 64);

@@ -319,8 +319,10 @@ __device__ __forceinline__ float quarters_sum(float x) {
 
 // Minimum over the 16 lanes of a quarter wavefront (the rows of a 16-query block), the same in every lane.
 __device__ __forceinline__ int quad_rows_min(int x) {
-#pragma unroll
-  for (int m = 1; m < 16; m <<= 1) x = min(x, __shfl_xor(x, m, 16));
+  x = min(x, __builtin_amdgcn_mov_dpp(x, 0x128, 0xf, 0xf, true));      // rotated by 8, 4, 2 and 1 lanes inside the quarter
+  x = min(x, __builtin_amdgcn_mov_dpp(x, 0x124, 0xf, 0xf, true));
+  x = min(x, __builtin_amdgcn_mov_dpp(x, 0x122, 0xf, 0xf, true));
+  x = min(x, __builtin_amdgcn_mov_dpp(x, 0x121, 0xf, 0xf, true));
   return __builtin_amdgcn_readfirstlane(x);
 }
 
