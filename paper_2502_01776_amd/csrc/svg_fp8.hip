@@ -439,8 +439,10 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
       for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
   };
 
-  // one tile's weights, row sums and output; MORE: and the scores of the next tile
-  auto trip = [&](auto more_c, int j) {
+  // one tile's weights, row sums and output; MORE: and the scores of the next tile.  The loads of the trip are
+  // requested behind its first product: in front of the exponentials a workgroup that has its compute unit
+  // to itself waited for every one of their scalar instructions, behind a product they run beside it.
+  auto trip = [&](auto more_c, int j, auto request_loads) {
     constexpr bool MORE = decltype(more_c)::value;
     i32x8 opnd[4];
 #pragma unroll
@@ -451,6 +453,7 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
     __builtin_amdgcn_s_setprio(1);
     __builtin_amdgcn_sched_barrier(0);
     lacc = product(ones, pb, lacc);
+    request_loads();
     if (MORE) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -473,10 +476,12 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
 
   int j = 0;
   for (; col1 != kNoTile; ++j) {
-    const int col3 = list.next();
-    if (col3 != kNoTile) load_k(col3, j + 3);
-    if (col2 != kNoTile) load_v(col2, j + 2);
-    trip(std::true_type{}, j);
+    int col3;
+    trip(std::true_type{}, j, [&]() {
+      col3 = list.next();
+      if (col3 != kNoTile) load_k(col3, j + 3);
+      if (col2 != kNoTile) load_v(col2, j + 2);
+    });
     // what trip j + 1 reads was requested in trip j - 1: only this trip's four loads may be outstanding
     if (col3 != kNoTile) wait_loads_to_lds<4>();
     else wait_loads_to_lds<0>();
@@ -485,7 +490,7 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
     col1 = col2;
     col2 = col3;
   }
-  if (col != kNoTile) trip(std::false_type{}, j);
+  if (col != kNoTile) trip(std::false_type{}, j, []() {});
 
   // ---- epilogue: oacc[db][4 i + jj] = O[query r][32 db + 8 i + 4 g + jj]; lacc[0] = row sum
   const float l_tot = lacc[0];
