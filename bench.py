@@ -191,10 +191,11 @@ def cpu_baseline(cfg, q, k, v, rows, labels_np, nnz_total, o_bf16=None, o_fp8=No
 
 
 def measured_matrix_peak(S, torch, head_dim, ms_target=12.0):
-    """Sustained rate of the bf16 matrix cores on this machine: a loop of products only (form 0) and
-    the same loop with the per-product LDS read and softmax instructions of the attention kernel
-    of this head dimension (form 1: D = 128, form 2: D = 64, twice the softmax instructions per
-    product and three workgroups per CU), on normally distributed operands, each timed over >= 10 ms; and the
+    """Sustained rate of the bf16 matrix cores on this machine: a loop of 32x32x16 products only (form 0) and
+    the same loop with the LDS read and softmax instructions that attention at this head dimension
+    spends per product (form 1: D = 128, form 2: D = 64, twice the softmax instructions per
+    product and three workgroups per CU; yardsticks, not bounds: the attention kernels issue 16x16x32
+    products), on normally distributed operands, each timed over >= 10 ms; and the
     product-only loop on all-zero operands, which shows how much of the published peak is lost to
     the power the data toggling draws (the clock drops under real data, not under zeros)."""
     gen = torch.Generator(device="cuda").manual_seed(11)
@@ -224,8 +225,8 @@ def measured_matrix_peak(S, torch, head_dim, ms_target=12.0):
 
 
 def measured_lds_rates(S, torch, waves=8, iters=4000):
-    """Bytes per clock the LDS of one compute unit delivers for the operand reads and staging
-    writes of the D = 128 attention kernels, with two wavefronts per SIMD as those kernels run
+    """Bytes per clock the LDS of one compute unit delivers for operand reads like those of the D = 128
+    attention kernels and for the writes their direct loads replace, with two wavefronts per SIMD as those kernels run
     (svg_probe_lds: one workgroup, shader clocks per wavefront from the kernel's own clock reads)."""
     scratch = torch.zeros(16 + 512, dtype=torch.int64, device="cuda")
     out = {}
@@ -465,10 +466,11 @@ def main():
         out["roofline"]["measured_peak"] = mp
         out["roofline"]["frac_of_measured_peak"] = achieved / mp
         out["roofline"]["measured_peak_with_kernel_instruction_mix"] = mix
-        out["roofline"]["frac_of_instruction_mix_bound"] = achieved / mix
+        # (not a bound: the kernel's 16x16x32 products draw less power than the loop's 32x32x16 ones)
+        out["roofline"]["frac_of_instruction_mix_loop"] = achieved / mix
         out["roofline"]["measured_peak_constant_operands"] = peak_live["products_only_constant_operands"]["tflops"]
         out["roofline"]["measured_peak_detail"] = peak_live
-        # what the LDS of a compute unit delivers for this kernel's operand reads and staging writes (live)
+        # what the LDS of a compute unit delivers for operand reads like this kernel's, and for the writes its direct loads replace (live)
         try:
             out["roofline"]["lds_rates"] = measured_lds_rates(S, torch)
         except Exception as e:      # an add-on measurement: the bench line is printed without it

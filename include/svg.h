@@ -326,10 +326,11 @@ int svg_sparse_attn_fp8_fwd(const svg_shape_t* shape, const void* q8, const void
  * products v_mfma_f32_32x32x16_bf16 on operands taken from `operands`.
  *   form 0   products only, operands in registers
  *   form 1   per product additionally one 1 KB operand read from LDS and the softmax
- *            instructions the D = 128 attention kernel spends per product (one FMA, one
- *            exponential, one addition, half a bf16 pack): an upper bound for that kernel
- *            design, without its staging, barriers and global memory traffic
- *   form 2   the same for the D = 64 kernel: three workgroups resident per compute unit, and
+ *            instructions that attention at D = 128 spends per 32768 operations (one FMA, one
+ *            exponential, one addition, half a bf16 pack).  No staging, barriers or global memory
+ *            traffic.  A yardstick, not a bound: the attention kernels issue v_mfma_f32_16x16x32_bf16,
+ *            which moves half the accumulator bytes per operation and draws less power
+ *   form 2   the same for D = 64: three workgroups resident per compute unit, and
  *            per product the softmax instructions of two scores per lane (two FMAs, two
  *            exponentials, one bf16 pack, one packed dot product)
  *   operands device, 1 MiB, 16-byte aligned: bf16 values (random data draws the power real
@@ -342,14 +343,15 @@ int svg_sparse_attn_fp8_fwd(const svg_shape_t* shape, const void* q8, const void
 int svg_probe_mfma_bf16(int form, int32_t workgroups, int32_t iterations, const void* operands,
                         float* sink, double* flop_out, void* stream);
 
-/* Measurement aid (no part of the method): what the LDS of one compute unit delivers for the
- * access patterns of the attention kernels (the roofline discussion needs to know whether the
- * LDS is a saturated unit).  One workgroup of `waves` wavefronts (1..16; 8 = two per SIMD, as
+/* Measurement aid (no part of the method): what the LDS of one compute unit delivers for access
+ * patterns of attention (the roofline discussion needs to know whether the LDS is a saturated unit):
+ * the attention kernels read operands with the instructions of forms 0 and 1, conflict-free as these do; they
+ * stage tiles with direct loads, so form 3 shows what those replace.  One workgroup of `waves` wavefronts (1..16; 8 = two per SIMD, as
  * the D = 128 kernels run) issues `iterations` x 16 LDS instructions of one kind per wavefront:
- *   form 0   ds_read_b128, the K operand pattern (rows padded by 16 bytes)
+ *   form 0   ds_read_b128, a K operand (rows padded by 16 bytes; the attention kernels swizzle instead)
  *   form 1   ds_read_b64_tr_b16, the V^T operand pattern on the swizzled row-major V tile
  *   form 2   the same read on plain row-major rows (shows what the swizzle is for)
- *   form 3   ds_write_b128 in the staging pattern
+ *   form 3   ds_write_b128, staging a tile through registers
  *   scratch  device, 16-byte aligned, >= 16 * 8 + 1024 * 4 bytes, written: int64 [16], of which
  *            entry w receives the shader clocks wavefront w took for its iterations x 16
  *            instructions (followed by a sink that keeps the reads alive).  The caller reads it

@@ -27,16 +27,16 @@
 // and of tile j's output back to back (one long run of matrix work).  The operands of the scores are
 // read from LDS before the exponentials, those of the output behind the products of the scores, and the K and
 // V images come from memory straight into LDS two trips ahead.  At 119k tokens and 15 % of the tiles
-// 13.9 ms; one tile after the other, staged through registers, 14.7 ms.  The matrix unit is busy 48 % of
-// the time, the VALU 62 %.
+// 13.9 ms; one tile after the other, staged through registers, 15.0 ms on the same box.  The matrix unit is busy
+// 49 % of the cycles, the VALU 63 %.
 //
 // The weights of a tile are rounded against the row maximum up to and including that tile, so that the
 // largest weight of a tile that brings a new maximum is a power of two, i.e. exact.  Two tiles to a trip on
-// v_mfma_f32_16x16x128_f8f6f4 (half the accumulator bytes per operation) took 13.3 ms, but give two tiles one
-// maximum and half of those weights a rounding error: 0.4-7 % more error against exact weights in spatial heads.
-// With the first of two tiles added by itself wherever the second exceeds its maximum the error was the
-// same as here and the time 14.4 ms.  Looking at the maximum in every eighth trip only saved 15 % of
-// the VALU work, lost 1.5 % of accuracy and was no faster.
+// v_mfma_f32_16x16x128_f8f6f4 (half the accumulator bytes per operation) took 0.90 of the time of the tile-by-tile
+// kernel where this takes 0.93, but give two tiles one maximum and half of those weights a rounding error: 0.4-7 % more
+// error against exact weights in spatial heads.  With the first of two tiles added by itself wherever the second
+// exceeds its maximum the error was the same as here and the time that of the tile-by-tile kernel.  Looking at the
+// maximum in every eighth trip only saved 15 % of the VALU work, lost 1.5 % of accuracy and was no faster.
 #include <type_traits>
 
 #include "svg_attn_common.h"

@@ -4,11 +4,14 @@
 // like real data (random signs and mantissas) the chip runs at a lower clock, and these
 // loops show what is then left.  Form 0 issues only v_mfma_f32_32x32x16_bf16, operands in
 // registers, two wavefronts per SIMD, four independent accumulators per wavefront.  Form 1
-// adds, per product, what the D = 128 attention kernel needs per product besides the
+// adds, per product, what attention at D = 128 needs per product besides the
 // product: one 1 KB operand read from LDS, and for one score per lane one FMA, one
 // exponential, one addition and half a bf16 pack -- and nothing else (no staging, no
-// barriers, no global memory), so it bounds that kernel design from above.  Form 2 is the
-// same for the D = 64 kernel: three wavefronts per SIMD, and per product the softmax
+// barriers, no global memory).  It is a yardstick, not a bound: the attention kernels issue
+// v_mfma_f32_16x16x32_bf16, two products per operand, which moves half the accumulator bytes per
+// operation; in loops of this kind that form reached 2093 against 1788 TFLOP/s (form 0) and 1419
+// against 1364 (form 1).  Form 2 is the
+// same for D = 64: three wavefronts per SIMD, and per product the softmax
 // instructions of TWO scores per lane (half the products per score): two FMAs, two
 // exponentials, one bf16 pack and one packed dot product for the row sum.
 #include "svg_internal.h"
@@ -92,16 +95,18 @@ __global__ __launch_bounds__(kProbeThreads, FORM == 2 ? 3 : 2) void probe_kernel
   sink[blockIdx.x * kProbeThreads + tid] = s;
 }
 
-// What the LDS of one compute unit delivers for the access patterns of the attention kernels at
+// What the LDS of one compute unit delivers for access patterns of attention at
 // head dimension 128: one workgroup of `waves` wavefronts issues `iters` x 16 LDS instructions of
 // one kind per wavefront (the loaded values are consumed by empty statements, so nothing but the LDS
 // instructions and their waits is timed) and every wavefront writes the shader clocks that took to
 // ticks[wave].
-//   form 0  ds_read_b128 of a K operand (rows padded by 16 bytes, 32 rows x 16 bytes per half wave)
+//   form 0  ds_read_b128 of a K operand (rows padded by 16 bytes, 32 rows x 16 bytes per half wave;
+//           the attention kernels swizzle unpadded rows instead, also without bank conflicts)
 //   form 1  ds_read_b64_tr_b16 of a V^T operand from row-major rows whose 32-byte slots are
-//           XOR-swizzled with the row's two low bits (the layout the kernels stage V in)
+//           XOR-swizzled with the row's two low bits (the attention kernels: with three bits)
 //   form 2  the same read from plain row-major rows
-//   form 3  ds_write_b128 in the staging pattern (16 lanes write one row)
+//   form 3  ds_write_b128, 16 lanes writing one row: staging a tile through registers, which the
+//           direct loads of the attention kernels replace
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 typedef int i32x4 __attribute__((ext_vector_type(4)));
