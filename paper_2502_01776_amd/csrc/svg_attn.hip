@@ -54,7 +54,7 @@
 //
 // Measured on MI355X:
 //  * With 32 query rows per wavefront every 32768 operations need a fresh 1 KB operand from LDS.
-//  * The chip is power-limited under this load: the shader clock sits near 1.7 GHz (2.4 GHz
+//  * The chip is power-limited under this load: the shader clock sits near 1.9 GHz (2.4 GHz
 //    nominal), and a loop of nothing but MFMAs on random operands is held there too.  A
 //    variant that idles more runs at a higher clock and ends up at the same rate; what
 //    pays is less work per tile (instructions, LDS and memory traffic), not fewer cycles.
