@@ -415,7 +415,7 @@ def main():
             prof = json.load(f)
         traffic = prof.get("sparse_attn_bytes_per_launch")
         if "sparse_attn_mfma_busy_fraction_of_cycles" in prof:
-            counters = {"live": False, "measured_on": prof.get("measured_on", "another box of the pool, see source"),
+            counters = {"live": False, "measured_on": prof.get("measured_on", "another MI355X, see source"),
                         "mfma_busy_fraction_of_cycles": prof["sparse_attn_mfma_busy_fraction_of_cycles"],
                         "shader_clock_ghz": prof["sparse_attn_shader_clock_ghz"], "source": prof.get("source")}
     # algorithmic bytes of the layout stage: one read and one write of every tensor row that has to move

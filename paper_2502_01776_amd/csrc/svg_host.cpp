@@ -33,7 +33,8 @@ void note_hip_error(hipError_t e) { g_last_hip_error = e; }
 //    masked workgroups per pair cannot fill an XCD; then as many parts (up to four) as keep
 //    them within its resident places.  CogVideoX-v1 at 1 % (12 pairs per XCD): three parts,
 //    -32 % time; 0.1 % of the rows at the 119k-token shape (3 pairs): four parts, 3.9 -> 1.3 ms;
-//    with 15 or more pairs per XCD any cut of the masked passes measured slower (+4-20 %).
+//    with 15 or more pairs per XCD two parts are slower (566 -> 573 us at 40 heads of 32760 rows, 620 -> 639 at 48 of
+//    45104, 2839 -> 2914 at 24 of 119056).
 // ---------------------------------------------------------------------------------------------
 namespace {
 
