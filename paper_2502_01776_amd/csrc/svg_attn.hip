@@ -254,7 +254,10 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
         __syncthreads();
         slot[0] = sorted[slot[0]];
         slot[1] = sorted[slot[1]];
-        __syncthreads();       // the first tile is staged over the list
+        // The first tile is staged over the list.  In the one-wavefront form the barrier is nothing, and a direct
+        // load is not ordered behind LDS reads: the statement has them answered.
+        asm volatile("" ::"v"(slot[0]), "v"(slot[1]) : "memory");
+        __syncthreads();
       } else {
         slot[0] = order[slot[0]];
         slot[1] = order[slot[1]];
@@ -319,9 +322,10 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
       c_lo = min(c_lo, wave_range[2 * w]);
       c_hi = max(c_hi, wave_range[2 * w + 1]);
     }
-    __syncthreads();       // the first tile is staged over the ranges
     c_lo = __builtin_amdgcn_readfirstlane(c_lo);
     c_hi = __builtin_amdgcn_readfirstlane(c_hi);
+    asm volatile("" ::"s"(c_lo), "s"(c_hi) : "memory");      // the reads are answered: the first tile is staged over them
+    __syncthreads();
   }
 
   // sparse: this head's pattern; with q and o kept in token order, the row of a temporal
