@@ -78,14 +78,6 @@ namespace {
 
 using namespace attn;
 
-// Coarse position bin of a sampled row for the temporal profiling pass (text rows first).
-constexpr int kOrderBins = 2048;
-__device__ __forceinline__ int order_bin(int n, int off, int video_end, int P) {
-  if (n < off || n >= video_end) return 0;
-  const int p = (n - off) % P;
-  return 1 + (int)(((long long)p * (kOrderBins - 1)) / P);
-}
-
 // Wave priority while a wavefront issues products (0 elsewhere).  The two
 // wavefronts sharing a SIMD then settle into opposite phases: the products of one run
 // back to back while the other's softmax and staging instructions fill the gaps.  Where a tile is
@@ -198,7 +190,7 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   // sparse: heavy tiles first, then an eighth of each label's sequence of tiles
   int pat = 0, cl = -1, head_cl0 = 0;
   if (SPARSE) {
-    if (!sparse_slot<LW>(a.so, a.BH, a.labels, a.row_ptr[0], a.row_ptr[1], bh, grp, pat, cl, head_cl0)) return;
+    if (!sparse_slot<LW>(a.so, a.BH, a.labels, a.row_ptr[0], a.row_ptr[1], xcd, loc, bh, grp, pat, cl, head_cl0)) return;
     bh = __builtin_amdgcn_readfirstlane(bh);
     grp = __builtin_amdgcn_readfirstlane(grp);
     pat = __builtin_amdgcn_readfirstlane(pat);
@@ -1164,6 +1156,7 @@ int launch_one(AttnArgs a, int rows_total, hipStream_t stream) {
 
 template <int MODE>
 int dispatch(const Geo& g, const AttnArgs& a, int rows_total, hipStream_t stream) {
+  if (split_form(g, MODE, a.t)) return launch_split(g, a, MODE, stream);
   if (g.bm == 128) {
     return g.D == 128 ? launch_one<128, 4, 64, MODE>(a, rows_total, stream)
                       : launch_one<64, 4, 64, MODE>(a, rows_total, stream);
@@ -1219,8 +1212,9 @@ int launch_attention(const Geo& g, const void* q, const void* k, const void* v, 
   a.row_ptr[0] = row_ptr_s; a.col_idx[0] = col_idx_s;
   a.row_ptr[1] = row_ptr_t; a.col_idx[1] = col_idx_t;
   if (sparse && row_table) {
-    // k and v in token order: build the row table, then the gathering form
+    // k and v in token order: build the row table, then the gathering form (the split form needs no table)
     if (element_mask || g.bm != 128) return SVG_ERR_UNSUPPORTED;
+    if (split_form(g, kSparseGather, 0)) return launch_split(g, a, kSparseGather, stream);
     const int entries = g.nk * g.bn;
     (void)hipGetLastError();
     hipLaunchKernelGGL(row_table_kernel, dim3((entries + 255) / 256), dim3(256), 0, stream, row_table, entries,
@@ -1250,8 +1244,8 @@ int launch_profile(const Geo& g, const void* q, const void* k, const void* v, co
   float2* stats = reinterpret_cast<float2*>(workspace + out_floats);
   float2* partial = stats + (size_t)ns * a.BH * t;
   a.stats = stats;
-  if (groups > 1) {
-    // one group sorts its rows itself
+  if (split_form(g, kProfile, t) ? !split_sorts_rows(t) : groups > 1) {
+    // (one group sorts its rows itself, and so does the split form)
     int32_t* order = reinterpret_cast<int32_t*>(partial + (size_t)a.BH * ((t + 15) / 16));
     a.order_t = order;
     (void)hipGetLastError();

@@ -160,9 +160,8 @@ inline unsigned sparse_grid(const SparseOrder& so, int BH) {
 // launcher takes the wide form only when there are more than 64 heads)
 template <int LW>
 __device__ __forceinline__ bool sparse_slot(const SparseOrder so, const int BH, const uint8_t* labels,
-                                            const int32_t* rp_s, const int32_t* rp_t, int& bh, int& grp,
-                                            int& pat, int& cl, int& head_cl0) {
-  const int xcd = blockIdx.x & 7, loc = blockIdx.x >> 3;
+                                            const int32_t* rp_s, const int32_t* rp_t, const int xcd, const int loc,
+                                            int& bh, int& grp, int& pat, int& cl, int& head_cl0) {
   const int lane = threadIdx.x & 63;
   // The labels as bit masks, 64 heads per word (bit = temporal).  Words of their own, not an array: the
   // compiler put an array into LDS (8 KB of it) or scratch memory.
@@ -289,6 +288,26 @@ struct AttnArgs {
   float scale_log2;           // softmax scale * log2(e)
   int off, video_end, F, P, w_s, w_t, sink;
 };
+
+// The form for calls with few rows (svg_split.hip).
+struct SplitArgs {
+  AttnArgs a;
+  int blocks_log2;            // workgroups per query tile: bm = 32 << blocks_log2
+  int halves_log2;            // units of 32 keys per key tile: bn = 32 << halves_log2
+  int bn;
+  unsigned inv_P, inv_per;    // floor((2^32 - 1) / d) of the divisors P and, in the gathering form, frames per position
+};
+bool split_form(const Geo& g, int mode, int t);      // does the split form take this call? (t: sampled rows of a profiling call)
+bool split_sorts_rows(int t);                        // profiling: needs no row order from profile_order_kernel
+int launch_split(const Geo& g, AttnArgs a, int mode, hipStream_t stream);
+
+// Coarse position bin of a sampled row for the temporal profiling pass (text rows first).
+constexpr int kOrderBins = 2048;
+__device__ __forceinline__ int order_bin(int n, int off, int video_end, int P) {
+  if (n < off || n >= video_end) return 0;
+  const int p = (n - off) % P;
+  return 1 + (int)(((long long)p * (kOrderBins - 1)) / P);
+}
 
 // Lanes l and l^32 own the two halves of one query's keys.  v_permlane32_swap with
 // both operands equal returns {x[l % 32], x[32 + l % 32]} in every lane, so the

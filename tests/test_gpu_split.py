@@ -1,0 +1,73 @@
+"""The attention passes of calls with few rows, whose keys are split over the wavefronts of a workgroup: at the ends of
+its groups of 32 rows and units of 32 keys, against the oracle, and against the general kernel, which takes
+the same heads once there are many of them."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2502_01776_amd as S
+from oracle import svg_oracle as O
+from workloads import get_config, make_plain_qkv
+from helpers import f64, gpu_profile, gpu_layer_in_place, gpu_layer_kv2, assert_attn_close, labels_match
+
+pytestmark = pytest.mark.gpu
+
+
+def setup(H, D, F, P, T, **kw):
+    cfg = dict(get_config("mid64"), B=1, H=H, D=D, F=F, P=P, T=T, w_s=1, w_t=max(1, P // 5), spatial_heads=[0], **kw)
+    cfg["N"] = F * P + T
+    return cfg, S.shape_from_config(cfg), O.Geometry.from_config(cfg)
+
+
+def run(form, sh, q, k, v, lab):
+    if form == "dense":
+        o = torch.full_like(q, float("nan"))
+        S.svg_dense_attn_fwd(sh, q, k, v, o)
+        torch.cuda.synchronize()
+        return o
+    if form == "gather":
+        return gpu_layer_in_place(sh, q, k, v, lab)[0]
+    return gpu_layer_kv2(sh, q, k, v, lab, flags=S.SVG_ATTN_ELEMENT_MASK if form == "exact" else 0)[0]
+
+
+@pytest.mark.parametrize("F, P, T, sink", [(1, 1, 0, 0), (1, 31, 0, 1), (3, 11, 0, 0), (2, 15, 3, 1), (5, 25, 3, 0), (4, 37, 45, 1)])
+@pytest.mark.parametrize("form, blocks", [("dense", (128, 64)), ("sparse", (128, 64)), ("sparse", (32, 32)), ("exact", (128, 64)),
+                                          ("exact", (32, 32)), ("gather", (128, 64))])
+@pytest.mark.parametrize("D", [64, 128])
+def test_few_rows_against_the_oracle_and_the_general_kernel(form, blocks, D, F, P, T, sink):
+    cfg, sh, g = setup(2, D, F, P, T, sink_first_frame=sink, text_first=P % 2, block_m=blocks[0], block_n=blocks[1])
+    groups = -(-g.N // 32)
+    many = (1024 // groups + 2) // 2 * 2      # more workgroups than the split form takes
+    assert 2 * groups <= 416 and many * groups > 640
+    q, k, v = make_plain_qkv(1, 2, g.N, D, seed=P)
+    k = (k.float() * torch.linspace(0.2, 3.0, g.N)[None, None, :, None]).bfloat16()
+    lab = torch.tensor([0, 1], dtype=torch.uint8)
+    few = run(form, sh, q.cuda(), k.cuda(), v.cuda(), lab.cuda())
+    rep = lambda x: x.repeat(1, many // 2, 1, 1).cuda()
+    general = run(form, setup(many, D, F, P, T, sink_first_frame=sink, text_first=P % 2, block_m=blocks[0], block_n=blocks[1])[1],
+                  rep(q), rep(k), rep(v), lab.repeat(many // 2).cuda())
+    for h in (0, 1):
+        qh, kh, vh = f64(q)[0, h], f64(k)[0, h], f64(v)[0, h]
+        if form == "dense":
+            ref = O.dense_attention_head(qh, kh, vh, g)
+        elif form == "exact":
+            ref = O.masked_attention(qh, kh, vh, (O.temporal_mask if h else O.spatial_mask)(g), g.scale)
+        else:
+            ref = O.svg_attention_layer(f64(q), f64(k), f64(v), np.array([[0, 1]]), g)[0, h]
+        assert_attn_close(few[0, h], ref, f"{form} head {h}")
+        assert_attn_close(general[0, many - 2 + h], ref, f"{form} head {h}, general kernel")
+
+
+@pytest.mark.parametrize("F, P, t", [(5, 9, 1), (5, 9, 32), (5, 40, 33), (3, 100, 256), (3, 100, 257), (61, 3, 40), (62, 3, 40), (1, 1, 5)])
+@pytest.mark.parametrize("D, blocks", [(64, (128, 64)), (128, (128, 64)), (64, (32, 32))])
+def test_profiling_with_few_rows(F, P, t, D, blocks):
+    """t: groups of rows with and without an order, sorted by the workgroups or before them; F: one run of keys per frame in a
+    lane's hand, and one frame more than there are lanes for (the general kernel)."""
+    cfg, sh, g = setup(2, D, F, P, 7, sink_first_frame=F % 2, text_first=P % 2, block_m=blocks[0], block_n=blocks[1])
+    q, k, v = make_plain_qkv(1, 2, g.N, D, seed=t)
+    rows = np.random.default_rng(t).integers(0, g.N, t).astype(np.int32)
+    labels, mse = gpu_profile(sh, q.cuda(), k.cuda(), v.cuda(), rows)
+    omse, olab = O.profile_heads(f64(q), f64(k), f64(v), rows, g)
+    # the bounds of the other profiling tests: bf16 rounding of the weights under every measured error
+    assert np.allclose(mse.cpu().numpy().reshape(omse.shape), omse, rtol=0.05, atol=2e-5)
+    assert labels_match(labels, omse, olab)
