@@ -139,8 +139,16 @@ def _ptr(x):
     return x.data_ptr()
 
 
+# The current stream's handle as torch's own launchers ask for it.  torch.cuda.current_stream() builds a Stream object,
+# 2.8 us of the 7.5 a call with one kernel takes on the host (now 4.9); the handle alone takes 0.2.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream(stream):
     if stream is None:
+        if _raw_stream is not None and _current_device is not None and torch.cuda.is_initialized():
+            return _raw_stream(_current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
