@@ -289,13 +289,52 @@ struct AttnArgs {
   int off, video_end, F, P, w_s, w_t, sink;
 };
 
+// Quotient and remainder of v < 2^22 by d without a division; inv = floor((2^32 - 1) / d) (the quotient of the product is the true
+// one or one less).
+__device__ __forceinline__ unsigned divide(unsigned v, unsigned d, unsigned inv, unsigned& rest) {
+  unsigned q = __umulhi(v, inv);
+  rest = v - q * d;
+  if (rest >= d) {
+    rest -= d;
+    ++q;
+  }
+  return q;
+}
+
+// transformed_to_token for kernels that are bound by latency and by fetching their own instructions: no division.
+struct POuter {
+  unsigned P, frames, inv_frames;      // frames of a position: F, or F - 1 behind the first frame
+  int sink;
+  // offset of the token at offset v of the P-outer order, and its position
+  __device__ __forceinline__ int token(int v, int& pos) const {
+    const bool first_frame = sink && v < (int)P;
+    unsigned f;
+    const unsigned p = divide(sink ? (unsigned)v - P : (unsigned)v, frames, inv_frames, f);
+    pos = first_frame ? v : (int)p;
+    return first_frame ? v : (int)((f + (sink ? 1u : 0u)) * P + p);
+  }
+  __device__ __forceinline__ int token(int v) const {
+    int pos;
+    return token(v, pos);
+  }
+};
+inline POuter p_outer(const Geo& g) {
+  POuter o;
+  o.P = (unsigned)g.P;
+  o.frames = g.sink ? (unsigned)(g.F > 1 ? g.F - 1 : 1) : (unsigned)g.F;
+  o.inv_frames = 0xffffffffu / o.frames;
+  o.sink = g.sink;
+  return o;
+}
+
 // The form for calls with few rows (svg_split.hip).
 struct SplitArgs {
   AttnArgs a;
   int blocks_log2;            // workgroups per query tile: bm = 32 << blocks_log2
   int halves_log2;            // units of 32 keys per key tile: bn = 32 << halves_log2
   int bn;
-  unsigned inv_P, inv_per;    // floor((2^32 - 1) / d) of the divisors P and, in the gathering form, frames per position
+  unsigned inv_P;             // floor((2^32 - 1) / P)
+  POuter order;
 };
 bool split_form(const Geo& g, int mode, int t);      // does the split form take this call? (t: sampled rows of a profiling call)
 bool split_sorts_rows(int t);                        // profiling: needs no row order from profile_order_kernel

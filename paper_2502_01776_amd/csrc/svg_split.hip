@@ -128,25 +128,6 @@ __global__ __launch_bounds__(64 * kWaves, 2) void split_kernel(SplitArgs s) {
     }
   }
 
-  // quotient and remainder by P, and by the frames of a position in P-outer order, without a division
-  auto divide = [](unsigned v, unsigned d, unsigned inv, unsigned& rest) -> unsigned {
-    unsigned q = __umulhi(v, inv);
-    rest = v - q * d;
-    if (rest >= d) {
-      rest -= d;
-      ++q;
-    }
-    return q;
-  };
-  const unsigned frames = (unsigned)(a.sink ? max(1, a.F - 1) : a.F);
-  auto from_transformed = [&](int v, int& pos) -> int {      // offset of the token at offset v of the P-outer order, and its position
-    const bool first_frame = a.sink && v < a.P;
-    unsigned f;
-    const unsigned p = divide((unsigned)(a.sink ? v - a.P : v), frames, s.inv_per, f);
-    pos = first_frame ? v : (int)p;
-    return first_frame ? v : (int)((f + (a.sink ? 1u : 0u)) * (unsigned)a.P + p);
-  };
-
   // ---- mask windows: the run of keys (temporal profiling pass: of in-frame positions) a row keeps, see attn_kernel
   const bool masked = MODE == kSparseExact || (MODE == kProfile && variant != 0);
   const int keep_head = a.sink ? a.off + a.P : a.off;
@@ -170,7 +151,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void split_kernel(SplitArgs s) {
     const int v = n - a.off;
     int pos = 0;
     if (SPARSE && pat) {
-      const int token = a.off + from_transformed(v, pos);
+      const int token = a.off + s.order.token(v, pos);
       if (a.qo_token_order) io_row[qb] = token;
     }
     if (MASKABLE && masked) {
@@ -304,10 +285,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void split_kernel(SplitArgs s) {
     if constexpr (GATHER) {
       const int key = key0 + (lane & 31);
       int row = key;
-      if (pat && key >= a.off && key < a.video_end) {
-        int pos;
-        row = a.off + from_transformed(key - a.off, pos);
-      }
+      if (pat && key >= a.off && key < a.video_end) row = a.off + s.order.token(key - a.off);
       if (key >= a.N) row = 0x00ffffff;
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb) x.k[kb] = __shfl(row, 16 * kb + r, 64) * ROW;
@@ -625,8 +603,7 @@ int launch_split(const Geo& g, AttnArgs a, int mode, hipStream_t stream) {
   s.halves_log2 = g.bn == 64 ? 1 : 0;
   s.bn = g.bn;
   s.inv_P = 0xffffffffu / (unsigned)g.P;
-  const unsigned per = g.sink ? (unsigned)(g.F > 1 ? g.F - 1 : 1) : (unsigned)g.F;
-  s.inv_per = 0xffffffffu / per;
+  s.order = p_outer(g);
   unsigned grid;
   if (mode == kProfile) {
     a.nqt = (a.t + kRows - 1) / kRows;

@@ -8,7 +8,8 @@ import torch
 import paper_2502_01776_amd as S
 from oracle import svg_oracle as O
 from workloads import get_config, make_plain_qkv
-from helpers import f64, gpu_profile, gpu_layer_in_place, gpu_layer_kv2, assert_attn_close, labels_match
+from helpers import (f64, gpu_fp8_quantize, gpu_profile, gpu_layer_in_place, gpu_layer_kv2, assert_attn_close, assert_fp8_attn_close,
+                     device_tile_lists, labels_match)
 
 pytestmark = pytest.mark.gpu
 
@@ -71,3 +72,32 @@ def test_profiling_with_few_rows(F, P, t, D, blocks):
     # the bounds of the other profiling tests: bf16 rounding of the weights under every measured error
     assert np.allclose(mse.cpu().numpy().reshape(omse.shape), omse, rtol=0.05, atol=2e-5)
     assert labels_match(labels, omse, olab)
+
+
+@pytest.mark.parametrize("F, P, T, sink", [(1, 1, 0, 0), (1, 31, 0, 1), (3, 43, 0, 0), (2, 15, 3, 1), (9, 75, 30, 0), (7, 97, 45, 1)])
+def test_fp8_with_few_rows(F, P, T, sink):
+    """Lists of one to twelve tiles over four wavefronts, a row of the general kernel beside it."""
+    cfg, sh, g = setup(2, 128, F, P, T, sink_first_frame=sink, text_first=P % 2, block_m=128, block_n=64)
+    groups = -(-g.N // 32)
+    many = (1024 // groups + 2) // 2 * 2
+    assert 2 * groups <= 600 < many * groups
+    q, k, v = make_plain_qkv(1, 2, g.N, 128, seed=P)
+    k = (k.float() * torch.linspace(0.2, 3.0, g.N)[None, None, :, None]).bfloat16()
+    lab = torch.tensor([0, 1], dtype=torch.uint8)
+
+    def layer(H):
+        shape = setup(H, 128, F, P, T, sink_first_frame=sink, text_first=P % 2, block_m=128, block_n=64)[1]
+        x = [t.repeat(1, H // 2, 1, 1).cuda() for t in (q, k, v)]
+        labels = lab.repeat(H // 2).cuda()
+        bufs = gpu_fp8_quantize(shape, *x, labels)
+        o = torch.full_like(x[0], float("nan"))
+        S.svg_sparse_attn_fp8_fwd(shape, *bufs, o, labels, *device_tile_lists(shape))
+        torch.cuda.synchronize()
+        return o[0, -2:]
+
+    deq = [np.stack([O.fp8_dequantize(*O.fp8_quantize_head(f64(x)[0, h])) for h in (0, 1)])[None] for x in (q, k, v)]
+    ref = O.svg_attention_layer(*deq, np.array([[0, 1]]), g)
+    few, general = layer(2), layer(many)
+    for h in (0, 1):
+        for o, what in ((few, "few rows"), (general, "general kernel")):
+            assert_fp8_attn_close(o[h], ref[0, h], float(np.abs(deq[2][0, h]).max()), f"{what}, head {h}")
