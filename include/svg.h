@@ -91,7 +91,8 @@ size_t svg_workspace_bytes(const svg_shape_t* shape, int32_t t);
  * [full_bound[c], full_bound[c+1]), c < *n_full (full_bound: host array of 17
  * entries, ascending from 0 to nk; may be NULL), each masked pass as *n_masked <= 4
  * equal parts of its own tile sequence, *n_full <= 6; the parts are merged from per-row (output,
- * maximum, row sum) triples, so the plan changes the results only in fp32 rounding. */
+ * maximum, row sum) triples, so the plan changes the results only in fp32 rounding.  The
+ * workspace has room for these parts; a launch may cut the passes otherwise, into no more. */
 int svg_profile_plan(const svg_shape_t* shape, int32_t t, int32_t* n_full, int32_t* n_masked,
                      int32_t* full_bound);
 

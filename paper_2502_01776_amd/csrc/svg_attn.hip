@@ -1121,11 +1121,12 @@ void launch_error(const AttnArgs& a, const float2* stats, float2* partial, uint8
 template <int D>
 int launch_error_parts(const AttnArgs& a, const float2* stats, float2* partial, uint8_t* labels, float* mse, hipStream_t stream) {
   (void)hipGetLastError();
-  switch (a.plan.n_full) {      // the numbers of parts profile_plan gives the unmasked pass
+  switch (a.plan.n_full) {      // the numbers of parts profile_plan and profile_cut give the unmasked pass
     case 1: launch_error<D, 1>(a, stats, partial, labels, mse, stream); break;
     case 3: launch_error<D, 3>(a, stats, partial, labels, mse, stream); break;
     case 4: launch_error<D, 4>(a, stats, partial, labels, mse, stream); break;
     case 6: launch_error<D, 6>(a, stats, partial, labels, mse, stream); break;
+    case 8: launch_error<D, 8>(a, stats, partial, labels, mse, stream); break;
     default: return SVG_ERR_UNSUPPORTED;
   }
   int rc = hip_status(hipGetLastError());
@@ -1236,7 +1237,8 @@ int launch_profile(const Geo& g, const void* q, const void* k, const void* v, co
   // workspace: fp32 outputs [slots][BH][t][D] (parts of the unmasked, the spatial and the
   // temporal pass), statistics float2 [slots][BH][t], partial error sums float2
   // [BH][ceil(t/16)], row order int32 [t]
-  a.plan = profile_plan(g, t);
+  const bool split = split_form(g, kProfile, t);
+  a.plan = profile_cut(g, t, profile_plan(g, t), split);
   const int ns = a.plan.slots();
   const int groups = (t + g.bm - 1) / g.bm;
   a.rows_per_group = (t + groups - 1) / groups;
@@ -1244,7 +1246,7 @@ int launch_profile(const Geo& g, const void* q, const void* k, const void* v, co
   float2* stats = reinterpret_cast<float2*>(workspace + out_floats);
   float2* partial = stats + (size_t)ns * a.BH * t;
   a.stats = stats;
-  if (split_form(g, kProfile, t) ? !split_sorts_rows(t) : groups > 1) {
+  if (split ? !split_sorts_rows(t) : groups > 1) {
     // (one group sorts its rows itself, and so does the split form)
     int32_t* order = reinterpret_cast<int32_t*>(partial + (size_t)a.BH * ((t + 15) / 16));
     a.order_t = order;

@@ -44,3 +44,10 @@ def test_parts_of_the_unmasked_pass(H, F, P, t, n_full, D):
     b = (32, 32) if t == 1024 else (128, 64)
     plan = check(dict(get_config("mid64"), D=D, B=1, H=H, F=F, P=P, spatial_heads=[0], block_m=b[0], block_n=b[1]), t)
     assert plan[0] == n_full
+
+
+@pytest.mark.parametrize("H, F, P, t, D", [(6, 5, 1300, 90, 128), (8, 9, 400, 60, 64), (2, 9, 160, 700, 128), (5, 9, 160, 700, 64), (10, 5, 330, 256, 64)])
+def test_cuts_of_the_launch(H, F, P, t, D):
+    """The cuts a launch takes in place of the plan's: four equal parts and three of the split form with 24 groups of rows
+    and more, eight parts of the unmasked pass for few heads with many groups, two masked parts at head dimension 64."""
+    check(dict(get_config("mid64"), D=D, B=1, H=H, F=F, P=P, spatial_heads=[0]), t)
