@@ -73,12 +73,12 @@ ProfilePlan profile_plan(const Geo& g, int t) {
 // How a launch cuts the passes: as profile_plan says, which also sizes the workspace, or otherwise into no more parts in all.
 //  * The split form (svg_split.hip) has four times the row groups, so with 24 of them or more four parts and three fill the
 //    chip: 48 groups of 9086 rows 72.8 -> 61.4 us, of 3290 rows 33.1 -> 30.2, of 17776 rows 89.4 -> 78.6 (head dimension
-//    64: 53.0 -> 50.9, 21.8 -> 21.0); with 16 groups of 3290 rows four masked parts stay better (20.7 against 22).
+//    64: 53.0 -> 50.9, 21.8 -> 21.0); with 16 groups of 3290 rows four masked parts stay better (20.7 against 22).  Head
+//    dimension 64 from 96 groups on: two masked parts, 1.09-1.12 times as fast as the plan's cut at 96 to 138 groups.
 //    Where the unmasked pass is not cut, three parts of each pass: 4 heads of 272 rows 9.5 -> 9.0, 24 of 820 12.9 -> 12.1.
 //  * Few heads whose sampled rows make many groups: the windows of a group are narrow, the masked passes short, and the parts of
 //    the unmasked pass the longest chain of the call.  Eight of them and three: 1.15-1.22 times as fast at 24 to 36 pairs
 //    of 6 to 10 groups (3 heads of 119056 rows 496 -> 424 us); with up to 3 groups 0.80-0.95.
-//  * Head dimension 64, up to 40 pairs: two masked parts, 1.09-1.12 times as fast (24 to 40 pairs; 0.83-1.04 at 55 and more).
 ProfilePlan profile_cut(const Geo& g, int t, const ProfilePlan& plan, bool split) {
   const int groups = (t + g.bm - 1) / g.bm;
   const long long heads = (long long)g.B * g.H;
@@ -89,14 +89,12 @@ ProfilePlan profile_cut(const Geo& g, int t, const ProfilePlan& plan, bool split
       cut.n_masked = 3;
       fill_bounds(&cut, 0, 3, g.nk);
     } else if (heads * ((t + 31) / 32) >= 24) {
-      cut.n_masked = 3;
+      cut.n_masked = g.D == 64 && heads * ((t + 31) / 32) >= 96 ? 2 : 3;
       fill_bounds(&cut, 0, 4, g.nk);
     }
   } else if (plan.n_full == 6 && groups >= 6) {
     cut.n_masked = 3;
     fill_bounds(&cut, 6, 2, g.nk);
-  } else if (plan.n_full == 6 && g.D == 64 && heads * groups <= 40) {
-    cut.n_masked = 2;
   }
   return cut;
 }

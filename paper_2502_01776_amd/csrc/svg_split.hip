@@ -588,11 +588,15 @@ namespace attn {
 // to 9746 rows with either tile shape, time of attn_kernel over time here:
 //   head dimension 64:  1.03-3.0 up to 624 workgroups, dense 0.9 at 824 (three workgroups fit a CU)
 //   head dimension 128: 1.04-2.6 up to 414, 0.94 at 432 with 32-row query tiles and 9 key tiles, dense 0.87 at 610 (two fit)
-//   profiling:          1.1-2.7 up to 144 and 1.07-2.3 up to 72 workgroups per pass and part; 0.91 at 168 and 96
+//   profiling:          1.1-2.7 up to 144 and 1.07-2.3 up to 72 workgroups per pass and part; 0.91 at 168 and 96.  The K and V that
+//                       they read between them count as well: 64 x 50000 keys 1.32, 38 x 118800 1.66, but 92 x 72500 0.81 and
+//                       128 x 50000 0.79 at head dimension 64; 48 x 50000 1.24 and 38 x 118800 1.36 at 128
 bool split_form(const Geo& g, int mode, int t) {
   const long long heads = (long long)g.B * g.H;
-  if (mode == kProfile) return g.F <= kMaxFrames && heads * ((t + kRows - 1) / kRows) <= (g.D == 64 ? 144 : 72);
-  return heads * ((g.N + kRows - 1) / kRows) <= (g.D == 64 ? 640 : 416);
+  if (mode != kProfile) return heads * ((g.N + kRows - 1) / kRows) <= (g.D == 64 ? 640 : 416);
+  const long long groups = heads * ((t + kRows - 1) / kRows);
+  if (g.F > kMaxFrames || groups > (g.D == 64 ? 144 : 72)) return false;
+  return groups <= (g.D == 64 ? 64 : 48) || groups * g.N <= (g.D == 64 ? 3200000 : 1600000);
 }
 
 bool split_sorts_rows(int t) { return t <= kSortRows; }
