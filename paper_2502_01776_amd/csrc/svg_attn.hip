@@ -229,11 +229,11 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
     if (variant == 2) {
       const int32_t* order = a.order_t;
       if (order == nullptr) {
-        // all rows belong to this one group (t <= BM): the group sorts them itself, each row counting
-        // the rows in front of it, in the order profile_order_kernel would give them (that kernel, a
-        // launch of 3.7 us in front of a call of 40, is left to more than one group)
+        // as many rows as threads at most: the workgroup sorts them itself, each row counting
+        // the rows in front of it, in the order profile_order_kernel would give them (a launch
+        // of 6 us for 178 rows, left to more rows; the counting takes about 1 us)
         int* const bin = reinterpret_cast<int*>(lds);
-        int* const sorted = bin + BM;
+        int* const sorted = bin + THREADS;
         if (tid < a.t) bin[tid] = order_bin(a.rows[tid], a.off, a.video_end, a.P);
         __syncthreads();
         if (tid < a.t) {
@@ -997,9 +997,10 @@ __global__ __launch_bounds__(1024) void profile_order_kernel(const int32_t* rows
 // 1191 of 24; now 4.7, 13.4, 12.1 and 23.7, and the first two need no label launch, 4.5 us.)
 constexpr int kErrThreads = 1024;
 constexpr int err_rows(int D) { return kErrThreads / (D / 4); }
-// Heads with few rows take one block each, which also writes the label: a second launch costs as
-// much as four more passes over the rows of a block.
-constexpr int kErrSinglePasses = 4;
+// Heads with few rows take one block each, which also writes the label.  A block takes 3-4 us per pass over its
+// rows, a label launch 4.7: with three passes 13.1 us in one block, 6.4 + 4.7 in three (16 heads of 91 rows; 48 of 178 at
+// head dimension 64: 15.0, 7.8 + 4.8).
+constexpr int kErrSinglePasses = 2;
 
 __device__ __forceinline__ void store_label(float sum_s, float sum_t, int bh, int t, int D, uint8_t* labels, float* mse) {
   const float per = (float)t * (float)D;
@@ -1246,8 +1247,8 @@ int launch_profile(const Geo& g, const void* q, const void* k, const void* v, co
   float2* stats = reinterpret_cast<float2*>(workspace + out_floats);
   float2* partial = stats + (size_t)ns * a.BH * t;
   a.stats = stats;
-  if (split ? !split_sorts_rows(t) : groups > 1) {
-    // (one group sorts its rows itself, and so does the split form)
+  if (split ? !split_sorts_rows(t) : t > 2 * g.bm) {
+    // (a workgroup sorts as many rows as it has threads)
     int32_t* order = reinterpret_cast<int32_t*>(partial + (size_t)a.BH * ((t + 15) / 16));
     a.order_t = order;
     (void)hipGetLastError();

@@ -275,7 +275,7 @@ struct AttnArgs {
   const int32_t* row_ptr[2];
   const int32_t* col_idx[2];
   const int32_t* rows;        // profile: sampled rows
-  const int32_t* order_t;     // profile: indices into rows[], grouped by in-frame position (temporal variant); null: one group, which sorts them itself
+  const int32_t* order_t;     // profile: indices into rows[], grouped by in-frame position (temporal variant); null: few rows, which the workgroups sort themselves
   int t;                      // profile: number of sampled rows
   ProfilePlan plan;           // profile: parts of the unmasked pass and of the masked passes
   int rows_per_group;         // profile: sampled rows per workgroup (the groups are balanced)
