@@ -70,7 +70,7 @@
 //    traffic per product and came out even: more cycles at a higher clock.
 #include <type_traits>
 
-#include "svg_attn_common.h"
+#include "svg_split.h"
 
 namespace svg {
 
@@ -190,10 +190,20 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   // sparse: heavy tiles first, then an eighth of each label's sequence of tiles
   int pat = 0, cl = -1, head_cl0 = 0;
   if (SPARSE) {
-    if (!sparse_slot<LW>(a.so, a.BH, a.labels, a.row_ptr[0], a.row_ptr[1], xcd, loc, bh, grp, pat, cl, head_cl0)) return;
+    int part;
+    if (!sparse_slot<LW>(a.so, a.BH, a.labels, a.row_ptr[0], a.row_ptr[1], xcd, loc, bh, grp, pat, cl, head_cl0, part)) return;
     bh = __builtin_amdgcn_readfirstlane(bh);
     grp = __builtin_amdgcn_readfirstlane(grp);
     pat = __builtin_amdgcn_readfirstlane(pat);
+    if constexpr (NW == 4) {
+      if (__builtin_amdgcn_readfirstlane(part) >= 0) {
+        const int row0 = grp * BM + __builtin_amdgcn_readfirstlane(part) * 32;
+        if (row0 >= a.N) return;
+        const int32_t* rp = a.row_ptr[pat];
+        split_body<D, MODE>(a, lds, bh, row0, grp, pat, __builtin_amdgcn_readfirstlane(rp[grp]), __builtin_amdgcn_readfirstlane(rp[grp + 1]), 0, 0);
+        return;
+      }
+    }
   }
 
   // profile: the unmasked pass needs no key codes, tile summaries or element masks (only the
@@ -1144,7 +1154,7 @@ int launch_one(AttnArgs a, int rows_total, hipStream_t stream) {
   a.nqt = (rows_total + BM - 1) / BM;
   a.total = a.BH * a.nqt;
   const unsigned per_xcd = (unsigned)((a.total + 8 * kCohort - 1) / (8 * kCohort)) * kCohort;   // dense
-  if (MODE == kSparse || MODE == kSparseExact || MODE == kSparseGather) a.so = sparse_order(a.BH, a.nqt, BM, a.off, a.video_end, a.N, 32 * (NW == 4 ? waves_per_simd(D, NW, MODE) : 2));
+  if (MODE == kSparse || MODE == kSparseExact || MODE == kSparseGather) a.so = sparse_order(a.BH, a.nqt, BM, a.off, a.video_end, a.N, 32 * (NW == 4 ? waves_per_simd(D, NW, MODE) : 2), NW == 4 ? 2 : 0, a.nk);
   const unsigned grid = MODE == kProfile ? (unsigned)(8 * a.plan.slots() * ((a.total + 7) / 8))
                         : MODE == kDense ? 8u * per_xcd : sparse_grid(a.so, a.BH);
   (void)hipGetLastError();   // drop any stale error left by earlier runtime calls of the process
@@ -1197,6 +1207,11 @@ AttnArgs base_args(const Geo& g, const void* q, const void* k, const void* v, vo
   a.scale_log2 = g.scale * 1.4426950408889634f;
   a.off = g.off; a.video_end = g.video_end; a.F = g.F; a.P = g.P;
   a.w_s = g.w_s; a.w_t = g.w_t; a.sink = g.sink;
+  a.blocks_log2 = g.bm == 128 ? 2 : 0;
+  a.halves_log2 = g.bn == 64 ? 1 : 0;
+  a.bn = g.bn;
+  a.inv_P = 0xffffffffu / (unsigned)g.P;
+  a.order = p_outer(g);
   return a;
 }
 

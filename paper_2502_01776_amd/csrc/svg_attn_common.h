@@ -110,6 +110,12 @@ struct TileList {
 //  * Heavy tiles (those with a text row) start first on every XCD, a head's heavy tiles on
 //    one XCD (they stream the same K and V), heads dealt to the XCDs in turn.  Started last
 //    they would run on alone after every other workgroup of their XCD has finished.
+//  * Where a heavy tile is much longer than an even share of the work it is the whole time of the pass (with few heads or
+//    short lists: 18 heads of 1909 tokens 47 of 51 us).  Then four workgroups take it, 32 rows each, its keys
+//    split over their wavefronts (svg_split.h), dealt to all XCDs.  That costs about 2.5 times the tile's work and takes 0.3 of
+//    its time.  The line, nk > 2.2 (light tiles + 4 heavy tiles) / places, from 2 to 48 heads of 1520 to 18977 tokens
+//    and both head dimensions, time whole over time split: 1.03-2.3 above it (2 heads of 9746 at head dimension 128: 173 ->
+//    90 us; 8 of 3290: 65 -> 37), 0.79-1.25 just below it (1.7 to 2.1), 0.63-1.0 far below.
 //  * The other tiles of all heads with the same label form one sequence (head after head,
 //    ascending query tiles); every XCD takes one contiguous eighth of the spatial sequence
 //    and one of the temporal sequence, the one with the longer lists first.  Each XCD so gets
@@ -133,9 +139,11 @@ struct SparseOrder {
   int nh;      // tiles with a text row per head (the others, ascending)
   int hmax;    // workgroups per XCD reserved for them
   int slots;   // workgroups resident on one XCD (sets the stride, see above)
+  int parts_log2;      // workgroups reserved per tile with a text row: 1 << parts_log2
+  int nk;              // key tiles, what a tile with a text row keeps
 };
 
-inline SparseOrder sparse_order(int BH, int nqt, int BM, int off, int video_end, int N, int slots) {
+inline SparseOrder sparse_order(int BH, int nqt, int BM, int off, int video_end, int N, int slots, int parts_log2 = 0, int nk = 0) {
   SparseOrder so;
   const int lo = off > 0 ? (off + BM - 1) / BM : 0;
   int hi = video_end < N ? video_end / BM : nqt;
@@ -145,12 +153,14 @@ inline SparseOrder sparse_order(int BH, int nqt, int BM, int off, int video_end,
   so.nh = nqt - so.nl;
   so.hmax = so.nh * ((BH + 7) / 8);
   so.slots = slots;
+  so.parts_log2 = parts_log2;
+  so.nk = nk;
   return so;
 }
 
 // grid size: an XCD's two eighths together hold at most floor(BH nl / 8) + 2 tiles
 inline unsigned sparse_grid(const SparseOrder& so, int BH) {
-  return 8u * (unsigned)(so.hmax + (long long)BH * so.nl / 8 + 2);
+  return 8u * (unsigned)(((long long)so.hmax << so.parts_log2) + (long long)BH * so.nl / 8 + 2);
 }
 
 // Which (head, query tile, pattern) does this workgroup take?  false: none.  For a tile without
@@ -161,8 +171,11 @@ inline unsigned sparse_grid(const SparseOrder& so, int BH) {
 template <int LW>
 __device__ __forceinline__ bool sparse_slot(const SparseOrder so, const int BH, const uint8_t* labels,
                                             const int32_t* rp_s, const int32_t* rp_t, const int xcd, const int loc,
-                                            int& bh, int& grp, int& pat, int& cl, int& head_cl0) {
+                                            int& bh, int& grp, int& pat, int& cl, int& head_cl0, int& part) {
   const int lane = threadIdx.x & 63;
+  // List tiles of a head's light query tiles, per pattern: asked for before the labels, whose answer they need not wait for.
+  const int nnz_s = so.nl > 0 ? rp_s[so.g_lo + so.nl] - rp_s[so.g_lo] : 0;
+  const int nnz_t = so.nl > 0 && labels != nullptr ? rp_t[so.g_lo + so.nl] - rp_t[so.g_lo] : 0;
   // The labels as bit masks, 64 heads per word (bit = temporal).  Words of their own, not an array: the
   // compiler put an array into LDS (8 KB of it) or scratch memory.
   static_assert(LW == 1 || LW == 4, "one variable per word");
@@ -181,20 +194,31 @@ __device__ __forceinline__ bool sparse_slot(const SparseOrder so, const int BH, 
   };
   cl = -1;
   head_cl0 = 0;
-  if (loc < so.hmax) {
-    const int hh = loc / so.nh, j = loc - hh * so.nh;
-    bh = xcd + 8 * hh;
+  part = -1;
+  const int nS = BH - nT;
+  const long long light = (long long)nS * nnz_s + (long long)nT * nnz_t;
+  const bool split = so.parts_log2 > 0 && 5 * (so.nk * 8ll * so.slots) > 11 * (light + 4ll * BH * so.nh * so.nk);
+  // (whole heavy tiles leave the workgroups of the other parts at the end of the grid, where they do not come between)
+  const int front = split ? so.hmax << so.parts_log2 : so.hmax;
+  if (loc < front) {
+    int l = loc;
+    if (split) {
+      const int i = loc * 8 + xcd;      // all parts dealt to the XCDs in turn
+      part = i & ((1 << so.parts_log2) - 1);
+      l = i >> so.parts_log2;
+      bh = l / so.nh;
+    } else {
+      bh = xcd + 8 * (loc / so.nh);
+    }
+    const int j = l % so.nh;
     if (bh >= BH) return false;
     grp = j < so.g_lo ? j : j + so.nl;
     pat = classed ? label_bit(bh) : (labels ? labels[bh] != 0 : 0);
     return true;
   }
   if (so.nl == 0) return false;
-  int l = loc - so.hmax;
-  const int nS = BH - nT;
+  int l = loc - front;
   int first = nS == 0;            // the label whose sequence comes first
-  const int nnz_s = nS > 0 ? rp_s[so.g_lo + so.nl] - rp_s[so.g_lo] : 0;      // list tiles of a head's light query tiles
-  const int nnz_t = nT > 0 ? rp_t[so.g_lo + so.nl] - rp_t[so.g_lo] : 0;
   if (nT > 0 && nS > 0) first = nnz_t > nnz_s;
   const int nA = first ? nT : nS;
   const long long NA = (long long)nA * so.nl, NB = (long long)(BH - nA) * so.nl;
@@ -263,32 +287,6 @@ __device__ __forceinline__ bool sparse_slot(const SparseOrder so, const int BH, 
   return true;
 }
 
-struct AttnArgs {
-  const __bf16* q;
-  const __bf16* k;
-  const __bf16* v;
-  const __bf16* k_t;          // sparse: P-outer copies of k and v read by temporal heads instead of k, v; may be null
-  const __bf16* v_t;
-  void* o;                    // bf16 [B,H,N,D] (dense, sparse) or fp32 [3][BH][t][D] (profile)
-  const uint8_t* labels;      // sparse: per-head pattern, may be null
-  const int32_t* row_table;   // gathering sparse form: token row of every P-outer row, nk * BN entries
-  const int32_t* row_ptr[2];
-  const int32_t* col_idx[2];
-  const int32_t* rows;        // profile: sampled rows
-  const int32_t* order_t;     // profile: indices into rows[], grouped by in-frame position (temporal variant); null: few rows, which the workgroups sort themselves
-  int t;                      // profile: number of sampled rows
-  ProfilePlan plan;           // profile: parts of the unmasked pass and of the masked passes
-  int rows_per_group;         // profile: sampled rows per workgroup (the groups are balanced)
-  float2* stats;              // profile: (reference maximum, row sum) per (output slot, head, row)
-  int N, nk, BH;
-  int nqt;                    // workgroups per head: query tiles (dense, sparse) or ceil(t / rows per workgroup) (profile)
-  SparseOrder so;             // sparse: which workgroup takes which (head, query tile)
-  int total;                  // logical workgroups
-  int qo_token_order;         // sparse: q is read and o written in token order also for temporal heads
-  float scale_log2;           // softmax scale * log2(e)
-  int off, video_end, F, P, w_s, w_t, sink;
-};
-
 // Quotient and remainder of v < 2^22 by d without a division; inv = floor((2^32 - 1) / d) (the quotient of the product is the true
 // one or one less).
 __device__ __forceinline__ unsigned divide(unsigned v, unsigned d, unsigned inv, unsigned& rest) {
@@ -327,15 +325,38 @@ inline POuter p_outer(const Geo& g) {
   return o;
 }
 
-// The form for calls with few rows (svg_split.hip).
-struct SplitArgs {
-  AttnArgs a;
+struct AttnArgs {
+  const __bf16* q;
+  const __bf16* k;
+  const __bf16* v;
+  const __bf16* k_t;          // sparse: P-outer copies of k and v read by temporal heads instead of k, v; may be null
+  const __bf16* v_t;
+  void* o;                    // bf16 [B,H,N,D] (dense, sparse) or fp32 [3][BH][t][D] (profile)
+  const uint8_t* labels;      // sparse: per-head pattern, may be null
+  const int32_t* row_table;   // gathering sparse form: token row of every P-outer row, nk * BN entries
+  const int32_t* row_ptr[2];
+  const int32_t* col_idx[2];
+  const int32_t* rows;        // profile: sampled rows
+  const int32_t* order_t;     // profile: indices into rows[], grouped by in-frame position (temporal variant); null: few rows, which the workgroups sort themselves
+  int t;                      // profile: number of sampled rows
+  ProfilePlan plan;           // profile: parts of the unmasked pass and of the masked passes
+  int rows_per_group;         // profile: sampled rows per workgroup (the groups are balanced)
+  float2* stats;              // profile: (reference maximum, row sum) per (output slot, head, row)
+  int N, nk, BH;
+  int nqt;                    // workgroups per head: query tiles (dense, sparse) or ceil(t / rows per workgroup) (profile)
+  SparseOrder so;             // sparse: which workgroup takes which (head, query tile)
+  int total;                  // logical workgroups
+  int qo_token_order;         // sparse: q is read and o written in token order also for temporal heads
+  float scale_log2;           // softmax scale * log2(e)
+  int off, video_end, F, P, w_s, w_t, sink;
+  // the split form
   int blocks_log2;            // workgroups per query tile: bm = 32 << blocks_log2
-  int halves_log2;            // units of 32 keys per key tile: bn = 32 << halves_log2
-  int bn;
+  int halves_log2, bn;        // units of 32 keys per key tile: bn = 32 << halves_log2
   unsigned inv_P;             // floor((2^32 - 1) / P)
   POuter order;
 };
+
+// The form for calls with few rows (svg_split.hip).
 bool split_form(const Geo& g, int mode, int t);      // does the split form take this call? (t: sampled rows of a profiling call)
 bool split_sorts_rows(int t);                        // profiling: needs no row order from profile_order_kernel
 int launch_split(const Geo& g, AttnArgs a, int mode, hipStream_t stream);

@@ -232,8 +232,8 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
 
   // heavy query tiles first, then an eighth of each label's sequence of tiles (the same
   // dispatch order as the bf16 kernel)
-  int bh = 0, grp = 0, pat = 0, cl = -1, head_cl0 = 0;
-  if (!sparse_slot<LW>(a.so, a.BH, a.labels, a.row_ptr[0], a.row_ptr[1], blockIdx.x & 7, blockIdx.x >> 3, bh, grp, pat, cl, head_cl0)) return;
+  int bh = 0, grp = 0, pat = 0, cl = -1, head_cl0 = 0, part;
+  if (!sparse_slot<LW>(a.so, a.BH, a.labels, a.row_ptr[0], a.row_ptr[1], blockIdx.x & 7, blockIdx.x >> 3, bh, grp, pat, cl, head_cl0, part)) return;
   bh = __builtin_amdgcn_readfirstlane(bh);
   grp = __builtin_amdgcn_readfirstlane(grp);
   pat = __builtin_amdgcn_readfirstlane(pat);

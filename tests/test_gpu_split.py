@@ -101,3 +101,39 @@ def test_fp8_with_few_rows(F, P, T, sink):
     for h in (0, 1):
         for o, what in ((few, "few rows"), (general, "general kernel")):
             assert_fp8_attn_close(o[h], ref[0, h], float(np.abs(deq[2][0, h]).max()), f"{what}, head {h}")
+
+
+@pytest.mark.parametrize("text_first, T, heads", [(0, 90, 2), (1, 90, 2), (1, 257, 2), (0, 90, 40)])
+@pytest.mark.parametrize("form", ["sparse", "exact", "gather"])
+@pytest.mark.parametrize("D", [64, 128])
+def test_text_rows_split_in_the_general_kernel(form, D, text_first, T, heads):
+    """Query tiles with text rows, whose lists are many times longer than the others': taken in four parts of 32 rows where
+    they would be the whole time of the pass (two heads), whole where they would not (forty)."""
+    F, P = 5, 2100
+    cfg, sh, g = setup(heads, D, F, P, T, text_first=text_first, block_m=128, block_n=64)
+    cfg.update(w_s=0, w_t=40)
+    sh, g = S.shape_from_config(cfg), O.Geometry.from_config(cfg)
+    nq, nk = S.svg_tile_counts(sh)
+    csr = [S.svg_tile_list_build(sh, p) for p in (0, 1)]
+    heavy = [a for a in range(nq) if min(g.N, (a + 1) * 128) > g.off + F * P or a * 128 < g.off]
+    light = sum(heads // 2 * (int(rp[-1]) - len(heavy) * nk) for rp, _ in csr)
+    slots = 768 if D == 64 else 512
+    assert heads * -(-g.N // 32) > 640 and (5 * nk * slots > 11 * (light + 4 * heads * len(heavy) * nk)) == (heads == 2)
+    q, k, v = make_plain_qkv(1, 2, g.N, D, seed=T)
+    k = (k.float() * torch.linspace(0.2, 3.0, g.N)[None, None, :, None]).bfloat16()
+    rep = lambda x: x.repeat(1, heads // 2, 1, 1).cuda()
+    o = run(form, sh, rep(q), rep(k), rep(v), torch.tensor([0, 1] * (heads // 2), dtype=torch.uint8).cuda())
+    in_order = np.empty(g.N, np.int64)
+    in_order[O.layout_perm(g)] = np.arange(g.N)
+    for h in (0, 1):
+        token = in_order if h else np.arange(g.N)
+        rp, ci = csr[h]
+        for a in heavy + [heavy[-1] - 1 if heavy[-1] == nq - 1 else heavy[-1] + 1, nq // 2]:
+            rows = slice(a * 128, min(g.N, (a + 1) * 128))
+            cols = np.concatenate([np.arange(b * 64, min(g.N, (b + 1) * 64)) for b in ci[rp[a]:rp[a + 1]]])
+            qr, kr, vr = f64(q)[0, h][token[rows]], f64(k)[0, h][token[cols]], f64(v)[0, h][token[cols]]
+            keep = np.ones((len(qr), len(cols)), bool)
+            if form == "exact":
+                keep = (O.temporal_mask if h else O.spatial_mask)(g, token[rows])[:, token[cols]]
+            ref = O.masked_attention(qr, kr, vr, keep, g.scale)
+            assert_attn_close(o[0, heads - 2 + h][torch.from_numpy(token[rows]).cuda()], ref, f"{form} head {h}, tile {a}")
