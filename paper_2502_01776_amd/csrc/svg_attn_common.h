@@ -141,9 +141,10 @@ struct SparseOrder {
   int slots;   // workgroups resident on one XCD (sets the stride, see above)
   int parts_log2;      // workgroups reserved per tile with a text row: 1 << parts_log2
   int nk;              // key tiles, what a tile with a text row keeps
+  int places;          // workgroups resident on the chip
 };
 
-inline SparseOrder sparse_order(int BH, int nqt, int BM, int off, int video_end, int N, int slots, int parts_log2 = 0, int nk = 0) {
+inline SparseOrder sparse_order(int BH, int nqt, int BM, int off, int video_end, int N, int slots, int places = 0, int parts_log2 = 0, int nk = 0) {
   SparseOrder so;
   const int lo = off > 0 ? (off + BM - 1) / BM : 0;
   int hi = video_end < N ? video_end / BM : nqt;
@@ -155,6 +156,7 @@ inline SparseOrder sparse_order(int BH, int nqt, int BM, int off, int video_end,
   so.slots = slots;
   so.parts_log2 = parts_log2;
   so.nk = nk;
+  so.places = places;
   return so;
 }
 
@@ -197,7 +199,7 @@ __device__ __forceinline__ bool sparse_slot(const SparseOrder so, const int BH, 
   part = -1;
   const int nS = BH - nT;
   const long long light = (long long)nS * nnz_s + (long long)nT * nnz_t;
-  const bool split = so.parts_log2 > 0 && 5 * (so.nk * 8ll * so.slots) > 11 * (light + 4ll * BH * so.nh * so.nk);
+  const bool split = so.parts_log2 > 0 && 5ll * so.nk * so.places > 11 * (light + 4ll * BH * so.nh * so.nk);
   // (whole heavy tiles leave the workgroups of the other parts at the end of the grid, where they do not come between)
   const int front = split ? so.hmax << so.parts_log2 : so.hmax;
   if (loc < front) {

@@ -225,6 +225,214 @@ struct Fp8Args {
   POuter order;                // attn_fp8_split_kernel
 };
 
+// --------------------------------------------------------------------------------------------
+// Attention of calls with few rows: as split_kernel (svg_split.hip), 32 query rows per workgroup, every fourth key tile per
+// wavefront, merged through LDS.  The tiles of k8 and v8t hold whole operands in 16-byte pieces, so both go from
+// memory straight to registers and nothing is staged.  6 heads of 960 rows 18.2 -> 9.9 us, 2 of 3290 rows 52.6 -> 21.8.  The
+// line lies at 600 groups of 32 rows (two workgroups fit a CU): time of attn_fp8_kernel over time here, 1 to 48 heads of
+// 272 to 9746 rows, 1.1-2.7 up to 600 groups, 0.93 at 624 with lists of 8 tiles.
+// --------------------------------------------------------------------------------------------
+constexpr int kSplitWaves = 4, kSplitRows = 32, kSplitGroups = 600;
+
+// lds: 64 KB.  Rows row0 .. row0 + 31 of head bh, entries [list_begin, list_end) of pattern pat's list.
+__device__ __forceinline__ void fp8_split_body(const Fp8Args& a, unsigned char* const lds, const int bh, const int row0, const int pat,
+                                               const int list_begin, const int list_end) {
+  constexpr int PART = kSplitRows * kD * 4;      // bytes of a wavefront's O^T
+  float* const tile_max = reinterpret_cast<float*>(lds);      // [2][wavefront][row]; the parts come after the last use
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 5, r = lane & 31;
+  const int32_t* cols = (pat ? a.col_idx[1] : a.col_idx[0]) + list_begin;
+  const int entries = list_end - list_begin;
+  int base = 0, now = lane < entries ? cols[lane] : 0, u = wave;
+  auto next_tile = [&]() -> int {
+    const int n = u;
+    if (n >= entries) return kNoTile;
+    u += kSplitWaves;
+    if (n >= base + 64) {
+      base += 64;
+      now = base + lane < entries ? cols[base + lane] : 0;
+    }
+    return __builtin_amdgcn_readlane(now, n - base);
+  };
+
+  const int qslot = row0 + r, qrow = min(qslot, a.N - 1);
+  int io_row = qrow;
+  if (pat && qrow >= a.off && qrow < a.video_end)
+    io_row = a.off + a.order.token(qrow - a.off);
+  auto read32 = [](const unsigned char* lo, const unsigned char* hi) -> i32x8 {
+    const i32x4 x = *reinterpret_cast<const i32x4*>(lo);
+    const i32x4 y = *reinterpret_cast<const i32x4*>(hi);
+    return i32x8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
+  };
+  i32x8 qreg[2];
+  {
+    const unsigned char* qp = a.q8 + ((size_t)bh * a.N + io_row) * kD + g * 32;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) qreg[s] = read32(qp + s * 64, qp + s * 64 + 16);
+  }
+  const float c_product = a.scale_log2 * a.scales[bh] * a.scales[a.BH + bh];
+  const float c_log2 = c_product == 0.f ? 0x1p-126f : c_product;      // (see attn_fp8_kernel)
+  const float v_scale = a.scales[2 * a.BH + bh];
+  const unsigned char* kh = a.k8 + (size_t)bh * a.nk * kTileBytes + r * kD + g * 32;
+  const int sw = (r >> 3) & 1;
+  const unsigned char* vh = a.v8t + (size_t)bh * a.nk * kTileBytes + g * (kD * 32) + r * 32;
+  i32x8 kreg[4], vreg[4];
+  auto request_k = [&](int tile) {
+    const unsigned char* p = kh + (size_t)tile * kTileBytes;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) kreg[i] = read32(p + (i >> 1) * 32 * kD + (i & 1) * 64, p + (i >> 1) * 32 * kD + (i & 1) * 64 + 16);
+  };
+  auto request_v = [&](int tile) {
+    const unsigned char* p = vh + (size_t)tile * kTileBytes;
+#pragma unroll
+    for (int db = 0; db < 4; ++db) vreg[db] = read32(p + db * 1024 + 16 * sw, p + db * 1024 + 16 * (1 - sw));
+  };
+
+  f32x16 oacc[4], lacc, sacc[2];
+#pragma unroll
+  for (int e = 0; e < 16; ++e) {
+    lacc[e] = 0.f;
+#pragma unroll
+    for (int db = 0; db < 4; ++db) oacc[db][e] = 0.f;
+  }
+  i32x8 ones;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) ones[j] = 0x38383838;
+  asm volatile("" : "+v"(ones));
+  float m_run = kNegBig;
+  auto product = [](const i32x8& x, const i32x8& y, const f32x16& z) -> f32x16 {
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, z, 0, 0, 0, 0, 0, 0);
+  };
+  int tile = next_tile();
+  if (tile != kNoTile) {
+    request_k(tile);
+    request_v(tile);
+  }
+  // A round takes one tile per wavefront.  A weight is rounded against the row maximum up to and including its own tile in
+  // list order, as in attn_fp8_kernel (see the top of the file): the wavefronts tell each other their tiles' maxima.
+  float m_round = kNegBig;      // row maximum over the tiles of all earlier rounds
+  for (int round = 0; round * kSplitWaves < entries; ++round) {
+    const int next = next_tile();
+    const bool own_tile = tile != kNoTile;
+    float tmax = kNegBig;
+    if (own_tile) {
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sacc[kb][e] = 0.f;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) sacc[kb] = product(kreg[2 * kb + s], qreg[s], sacc[kb]);
+      }
+      if (next != kNoTile) request_k(next);
+      if (tile * kBN + kBN > a.N) {
+        int lim = a.N - tile * kBN - 4 * g;
+        asm volatile("" : "+v"(lim));
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            if (32 * kb + 8 * (e >> 2) + (e & 3) >= lim) sacc[kb][e] = -INFINITY;
+      }
+      tmax = sacc[0][0];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) tmax = fmaxf(tmax, sacc[kb][e]);
+      tmax = both_halves_max(tmax);
+    }
+    if (g == 0) tile_max[(round & 1) * kSplitWaves * kSplitRows + wave * kSplitRows + r] = tmax;
+    __syncthreads();
+    float m_new = m_round;
+#pragma unroll
+    for (int w = 0; w < kSplitWaves; ++w) {
+      const float x = tile_max[(round & 1) * kSplitWaves * kSplitRows + w * kSplitRows + r];
+      m_round = fmaxf(m_round, x);
+      if (w <= wave) m_new = m_round;
+    }
+    if (own_tile) {
+      if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
+        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c_log2);
+        m_run = m_new;
+        lacc[0] *= alpha;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
+      }
+      const float mc = m_run * c_log2 - kWeightShift;
+      i32x8 pb;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        float p[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) p[c] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[j >> 2][4 * (j & 3) + c], c_log2, -mc));
+        const int w = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], (int)__float_as_uint(p[0]), false);
+        pb[j] = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], w, true);
+      }
+      lacc = product(ones, pb, lacc);
+#pragma unroll
+      for (int db = 0; db < 4; ++db) oacc[db] = product(vreg[db], pb, oacc[db]);
+      if (next != kNoTile) request_v(next);
+    }
+    tile = next;
+  }
+
+  // ---- merge (see split_kernel); v's scale and the row sum go into a wavefront's share
+  unsigned char* const own = lds + wave * PART;
+  if (entries > 0) __syncthreads();      // the last tile maxima are read
+  if (g == 0) *reinterpret_cast<float2*>(own + r * 8) = make_float2(m_run, lacc[0]);
+  __syncthreads();
+  float2 st[kSplitWaves];
+  float m_all = kNegBig, l_all = 0.f;
+#pragma unroll
+  for (int w = 0; w < kSplitWaves; ++w) st[w] = *reinterpret_cast<const float2*>(lds + w * PART + r * 8);
+  __syncthreads();      // (read by all before the parts are written over them)
+#pragma unroll
+  for (int w = 0; w < kSplitWaves; ++w) m_all = fmaxf(m_all, st[w].y > 0.f ? st[w].x : kNegBig);
+#pragma unroll
+  for (int w = 0; w < kSplitWaves; ++w) {
+    const float x = st[w].y * __builtin_amdgcn_exp2f((st[w].x - m_all) * c_log2);
+    l_all += st[w].y > 0.f ? x : 0.f;
+  }
+  const float share = __builtin_amdgcn_exp2f((m_run - m_all) * c_log2) * v_scale / l_all;
+  const float mine = lacc[0] > 0.f ? share : 0.f;
+#pragma unroll
+  for (int db = 0; db < 4; ++db)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      f32x4 x;
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) x[jj] = oacc[db][4 * i + jj] * mine;
+      *reinterpret_cast<f32x4*>(own + (4 * db + i) * 1024 + lane * 16) = x;
+    }
+  __syncthreads();
+  if (qslot >= a.N) return;
+  __bf16* op = a.o + ((size_t)bh * a.N + io_row) * kD + 32 * wave + 4 * g;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const unsigned char* src = lds + (4 * wave + i) * 1024 + lane * 16;
+    f32x4 sum = *reinterpret_cast<const f32x4*>(src);
+#pragma unroll
+    for (int w = 1; w < kSplitWaves; ++w) sum += *reinterpret_cast<const f32x4*>(src + w * PART);
+    *reinterpret_cast<bf16x4*>(op + 8 * i) = __builtin_convertvector(sum, bf16x4);
+  }
+}
+
+__global__ __launch_bounds__(64 * kSplitWaves, 2) void attn_fp8_split_kernel(Fp8Args a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[kSplitWaves * kSplitRows * kD * 4];
+  const int total = a.BH * a.nqt, per_xcd = (total + 7) >> 3, loc = blockIdx.x >> 3, lid = (blockIdx.x & 7) * per_xcd + loc;
+  if (loc >= per_xcd || lid >= total) return;
+  const int bh = lid / a.nqt, row0 = (lid - bh * a.nqt) * kSplitRows, grp = row0 / kBM;
+  int list_begin = a.row_ptr[0][grp], list_end = a.row_ptr[0][grp + 1], pat = 0;
+  if (a.labels != nullptr) {
+    const int t0 = a.row_ptr[1][grp], t1 = a.row_ptr[1][grp + 1];
+    pat = __builtin_amdgcn_readfirstlane(a.labels[bh] != 0);
+    list_begin = pat ? t0 : list_begin;
+    list_end = pat ? t1 : list_end;
+  }
+  fp8_split_body(a, lds, bh, row0, pat, list_begin, list_end);
+}
+
 template <int LW>
 __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * kStages * kTileBytes];      // K images, then V images
@@ -239,6 +447,14 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
   pat = __builtin_amdgcn_readfirstlane(pat);
   cl = __builtin_amdgcn_readfirstlane(cl);
   head_cl0 = __builtin_amdgcn_readfirstlane(head_cl0);
+  part = __builtin_amdgcn_readfirstlane(part);
+  if (part >= 0) {      // a query tile with text rows that is taken in parts
+    const int row0 = grp * kBM + part * kSplitRows;
+    if (row0 >= a.N) return;
+    const int32_t* rp = a.row_ptr[pat];
+    fp8_split_body(a, lds, bh, row0, pat, __builtin_amdgcn_readfirstlane(rp[grp]), __builtin_amdgcn_readfirstlane(rp[grp + 1]));
+    return;
+  }
 
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
@@ -510,207 +726,6 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
   }
 }
 
-// --------------------------------------------------------------------------------------------
-// Attention of calls with few rows: as split_kernel (svg_split.hip), 32 query rows per workgroup, every fourth key tile per
-// wavefront, merged through LDS.  The tiles of k8 and v8t hold whole operands in 16-byte pieces, so both go from
-// memory straight to registers and nothing is staged.  6 heads of 960 rows 18.2 -> 9.9 us, 2 of 3290 rows 52.6 -> 21.8.  The
-// line lies at 600 groups of 32 rows (two workgroups fit a CU): time of attn_fp8_kernel over time here, 1 to 48 heads of
-// 272 to 9746 rows, 1.1-2.7 up to 600 groups, 0.93 at 624 with lists of 8 tiles.
-// --------------------------------------------------------------------------------------------
-constexpr int kSplitWaves = 4, kSplitRows = 32, kSplitGroups = 600;
-
-__global__ __launch_bounds__(64 * kSplitWaves, 2) void attn_fp8_split_kernel(Fp8Args a) {
-  constexpr int PART = kSplitRows * kD * 4;      // bytes of a wavefront's O^T
-  __shared__ __attribute__((aligned(1024))) unsigned char lds[kSplitWaves * PART];
-  __shared__ float2 part_stats[kSplitWaves][kSplitRows];
-  __shared__ float tile_max[2][kSplitWaves][kSplitRows];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 5, r = lane & 31;
-  const int total = a.BH * a.nqt, per_xcd = (total + 7) >> 3, loc = blockIdx.x >> 3, lid = (blockIdx.x & 7) * per_xcd + loc;
-  if (loc >= per_xcd || lid >= total) return;
-  const int bh = lid / a.nqt, row0 = (lid - bh * a.nqt) * kSplitRows, grp = row0 / kBM;
-  int list_begin = a.row_ptr[0][grp], list_end = a.row_ptr[0][grp + 1], pat = 0;
-  if (a.labels != nullptr) {
-    const int t0 = a.row_ptr[1][grp], t1 = a.row_ptr[1][grp + 1];
-    pat = __builtin_amdgcn_readfirstlane(a.labels[bh] != 0);
-    list_begin = pat ? t0 : list_begin;
-    list_end = pat ? t1 : list_end;
-  }
-  const int32_t* cols = (pat ? a.col_idx[1] : a.col_idx[0]) + list_begin;
-  const int entries = list_end - list_begin;
-  int base = 0, now = lane < entries ? cols[lane] : 0, u = wave;
-  auto next_tile = [&]() -> int {
-    const int n = u;
-    if (n >= entries) return kNoTile;
-    u += kSplitWaves;
-    if (n >= base + 64) {
-      base += 64;
-      now = base + lane < entries ? cols[base + lane] : 0;
-    }
-    return __builtin_amdgcn_readlane(now, n - base);
-  };
-
-  const int qslot = row0 + r, qrow = min(qslot, a.N - 1);
-  int io_row = qrow;
-  if (pat && qrow >= a.off && qrow < a.video_end)
-    io_row = a.off + a.order.token(qrow - a.off);
-  auto read32 = [](const unsigned char* lo, const unsigned char* hi) -> i32x8 {
-    const i32x4 x = *reinterpret_cast<const i32x4*>(lo);
-    const i32x4 y = *reinterpret_cast<const i32x4*>(hi);
-    return i32x8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
-  };
-  i32x8 qreg[2];
-  {
-    const unsigned char* qp = a.q8 + ((size_t)bh * a.N + io_row) * kD + g * 32;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) qreg[s] = read32(qp + s * 64, qp + s * 64 + 16);
-  }
-  const float c_product = a.scale_log2 * a.scales[bh] * a.scales[a.BH + bh];
-  const float c_log2 = c_product == 0.f ? 0x1p-126f : c_product;      // (see attn_fp8_kernel)
-  const float v_scale = a.scales[2 * a.BH + bh];
-  const unsigned char* kh = a.k8 + (size_t)bh * a.nk * kTileBytes + r * kD + g * 32;
-  const int sw = (r >> 3) & 1;
-  const unsigned char* vh = a.v8t + (size_t)bh * a.nk * kTileBytes + g * (kD * 32) + r * 32;
-  i32x8 kreg[4], vreg[4];
-  auto request_k = [&](int tile) {
-    const unsigned char* p = kh + (size_t)tile * kTileBytes;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) kreg[i] = read32(p + (i >> 1) * 32 * kD + (i & 1) * 64, p + (i >> 1) * 32 * kD + (i & 1) * 64 + 16);
-  };
-  auto request_v = [&](int tile) {
-    const unsigned char* p = vh + (size_t)tile * kTileBytes;
-#pragma unroll
-    for (int db = 0; db < 4; ++db) vreg[db] = read32(p + db * 1024 + 16 * sw, p + db * 1024 + 16 * (1 - sw));
-  };
-
-  f32x16 oacc[4], lacc, sacc[2];
-#pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    lacc[e] = 0.f;
-#pragma unroll
-    for (int db = 0; db < 4; ++db) oacc[db][e] = 0.f;
-  }
-  i32x8 ones;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) ones[j] = 0x38383838;
-  asm volatile("" : "+v"(ones));
-  float m_run = kNegBig;
-  auto product = [](const i32x8& x, const i32x8& y, const f32x16& z) -> f32x16 {
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, z, 0, 0, 0, 0, 0, 0);
-  };
-  int tile = next_tile();
-  if (tile != kNoTile) {
-    request_k(tile);
-    request_v(tile);
-  }
-  // A round takes one tile per wavefront.  A weight is rounded against the row maximum up to and including its own tile in
-  // list order, as in attn_fp8_kernel (see the top of the file): the wavefronts tell each other their tiles' maxima.
-  float m_round = kNegBig;      // row maximum over the tiles of all earlier rounds
-  for (int round = 0; round * kSplitWaves < entries; ++round) {
-    const int next = next_tile();
-    const bool own_tile = tile != kNoTile;
-    float tmax = kNegBig;
-    if (own_tile) {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) sacc[kb][e] = 0.f;
-#pragma unroll
-        for (int s = 0; s < 2; ++s) sacc[kb] = product(kreg[2 * kb + s], qreg[s], sacc[kb]);
-      }
-      if (next != kNoTile) request_k(next);
-      if (tile * kBN + kBN > a.N) {
-        int lim = a.N - tile * kBN - 4 * g;
-        asm volatile("" : "+v"(lim));
-#pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-          for (int e = 0; e < 16; ++e)
-            if (32 * kb + 8 * (e >> 2) + (e & 3) >= lim) sacc[kb][e] = -INFINITY;
-      }
-      tmax = sacc[0][0];
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) tmax = fmaxf(tmax, sacc[kb][e]);
-      tmax = both_halves_max(tmax);
-    }
-    if (g == 0) tile_max[round & 1][wave][r] = tmax;
-    __syncthreads();
-    float m_new = m_round;
-#pragma unroll
-    for (int w = 0; w < kSplitWaves; ++w) {
-      const float x = tile_max[round & 1][w][r];
-      m_round = fmaxf(m_round, x);
-      if (w <= wave) m_new = m_round;
-    }
-    if (own_tile) {
-      if (__builtin_amdgcn_ballot_w64(m_new > m_run) != 0) {
-        const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c_log2);
-        m_run = m_new;
-        lacc[0] *= alpha;
-#pragma unroll
-        for (int db = 0; db < 4; ++db)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
-      }
-      const float mc = m_run * c_log2 - kWeightShift;
-      i32x8 pb;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        float p[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) p[c] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[j >> 2][4 * (j & 3) + c], c_log2, -mc));
-        const int w = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], (int)__float_as_uint(p[0]), false);
-        pb[j] = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], w, true);
-      }
-      lacc = product(ones, pb, lacc);
-#pragma unroll
-      for (int db = 0; db < 4; ++db) oacc[db] = product(vreg[db], pb, oacc[db]);
-      if (next != kNoTile) request_v(next);
-    }
-    tile = next;
-  }
-
-  // ---- merge (see split_kernel); v's scale and the row sum go into a wavefront's share
-  if (g == 0) part_stats[wave][r] = make_float2(m_run, lacc[0]);
-  __syncthreads();
-  float2 st[kSplitWaves];
-  float m_all = kNegBig, l_all = 0.f;
-#pragma unroll
-  for (int w = 0; w < kSplitWaves; ++w) st[w] = part_stats[w][r];
-#pragma unroll
-  for (int w = 0; w < kSplitWaves; ++w) m_all = fmaxf(m_all, st[w].y > 0.f ? st[w].x : kNegBig);
-#pragma unroll
-  for (int w = 0; w < kSplitWaves; ++w) {
-    const float x = st[w].y * __builtin_amdgcn_exp2f((st[w].x - m_all) * c_log2);
-    l_all += st[w].y > 0.f ? x : 0.f;
-  }
-  const float share = __builtin_amdgcn_exp2f((m_run - m_all) * c_log2) * v_scale / l_all;
-  const float mine = lacc[0] > 0.f ? share : 0.f;
-  unsigned char* const own = lds + wave * PART + lane * 16;
-#pragma unroll
-  for (int db = 0; db < 4; ++db)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      f32x4 x;
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) x[jj] = oacc[db][4 * i + jj] * mine;
-      *reinterpret_cast<f32x4*>(own + (4 * db + i) * 1024) = x;
-    }
-  __syncthreads();
-  if (qslot >= a.N) return;
-  __bf16* op = a.o + ((size_t)bh * a.N + io_row) * kD + 32 * wave + 4 * g;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const unsigned char* src = lds + (4 * wave + i) * 1024 + lane * 16;
-    f32x4 sum = *reinterpret_cast<const f32x4*>(src);
-#pragma unroll
-    for (int w = 1; w < kSplitWaves; ++w) sum += *reinterpret_cast<const f32x4*>(src + w * PART);
-    *reinterpret_cast<bf16x4*>(op + 8 * i) = __builtin_convertvector(sum, bf16x4);
-  }
-}
-
 }  // namespace
 
 int launch_fp8_quantize(const Geo& g, const void* q, const void* k, const void* v, const uint8_t* labels,
@@ -763,7 +778,7 @@ int launch_fp8_attention(const Geo& g, const void* q8, const void* k8, const voi
   a.nqt = g.nq;
   // (no stride in the dispatch order: this kernel starts the query tiles of a cohort at a common key tile
   // instead, which measured 0.6-1.8 % faster here than the stride with or without that start)
-  a.so = sparse_order(a.BH, a.nqt, kBM, g.off, g.video_end, g.N, 1 << 24);
+  a.so = sparse_order(a.BH, a.nqt, kBM, g.off, g.video_end, g.N, 1 << 24, 512, 2, g.nk);
   a.scale_log2 = g.scale * 1.4426950408889634f;
   a.off = g.off; a.video_end = g.video_end; a.F = g.F; a.P = g.P; a.sink = g.sink;
   a.w_s = g.w_s; a.w_t = g.w_t;
