@@ -113,9 +113,10 @@ struct TileList {
 //  * Where a heavy tile is much longer than an even share of the work it is the whole time of the pass (with few heads or
 //    short lists: 18 heads of 1909 tokens 47 of 51 us).  Then four workgroups take it, 32 rows each, its keys
 //    split over their wavefronts (svg_split.h), dealt to all XCDs.  That costs about 2.5 times the tile's work and takes 0.3 of
-//    its time.  The line, nk > 2.2 (light tiles + 4 heavy tiles) / places, from 2 to 48 heads of 1520 to 18977 tokens
+//    its time.  The line, nk > 2.08 (light tiles + 4 heavy tiles) / places, from 2 to 48 heads of 1520 to 18977 tokens
 //    and both head dimensions, time whole over time split: 1.03-2.3 above it (2 heads of 9746 at head dimension 128: 173 ->
-//    90 us; 8 of 3290: 65 -> 37), 0.79-1.25 just below it (1.7 to 2.1), 0.63-1.0 far below.
+//    90 us; 8 of 3290: 65 -> 37; 8 of 18977, at 2.09: 392 -> 265, FP8 257 -> 183), 0.80-1.15 between 1.3 and it,
+//    0.63-1.0 below.
 //  * The other tiles of all heads with the same label form one sequence (head after head,
 //    ascending query tiles); every XCD takes one contiguous eighth of the spatial sequence
 //    and one of the temporal sequence, the one with the longer lists first.  Each XCD so gets
@@ -199,7 +200,7 @@ __device__ __forceinline__ bool sparse_slot(const SparseOrder so, const int BH, 
   part = -1;
   const int nS = BH - nT;
   const long long light = (long long)nS * nnz_s + (long long)nT * nnz_t;
-  const bool split = so.parts_log2 > 0 && 5ll * so.nk * so.places > 11 * (light + 4ll * BH * so.nh * so.nk);
+  const bool split = so.parts_log2 > 0 && 12ll * so.nk * so.places > 25 * (light + 4ll * BH * so.nh * so.nk);
   // (whole heavy tiles leave the workgroups of the other parts at the end of the grid, where they do not come between)
   const int front = split ? so.hmax << so.parts_log2 : so.hmax;
   if (loc < front) {

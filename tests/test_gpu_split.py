@@ -26,6 +26,11 @@ def run(form, sh, q, k, v, lab):
         S.svg_dense_attn_fwd(sh, q, k, v, o)
         torch.cuda.synchronize()
         return o
+    if form == "fp8":
+        bufs, o = gpu_fp8_quantize(sh, q, k, v, lab), torch.full_like(q, float("nan"))
+        S.svg_sparse_attn_fp8_fwd(sh, *bufs, o, lab, *device_tile_lists(sh))
+        torch.cuda.synchronize()
+        return o
     if form == "gather":
         return gpu_layer_in_place(sh, q, k, v, lab)[0]
     return gpu_layer_kv2(sh, q, k, v, lab, flags=S.SVG_ATTN_ELEMENT_MASK if form == "exact" else 0)[0]
@@ -104,8 +109,7 @@ def test_fp8_with_few_rows(F, P, T, sink):
 
 
 @pytest.mark.parametrize("text_first, T, heads", [(0, 90, 2), (1, 90, 2), (1, 257, 2), (0, 90, 40)])
-@pytest.mark.parametrize("form", ["sparse", "exact", "gather"])
-@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("form, D", [("sparse", 64), ("exact", 64), ("gather", 64), ("sparse", 128), ("exact", 128), ("gather", 128), ("fp8", 128)])
 def test_text_rows_split_in_the_general_kernel(form, D, text_first, T, heads):
     """Query tiles with text rows, whose lists are many times longer than the others': taken in four parts of 32 rows where
     they would be the whole time of the pass (two heads), whole where they would not (forty)."""
@@ -118,22 +122,28 @@ def test_text_rows_split_in_the_general_kernel(form, D, text_first, T, heads):
     heavy = [a for a in range(nq) if min(g.N, (a + 1) * 128) > g.off + F * P or a * 128 < g.off]
     light = sum(heads // 2 * (int(rp[-1]) - len(heavy) * nk) for rp, _ in csr)
     slots = 768 if D == 64 else 512
-    assert heads * -(-g.N // 32) > 640 and (5 * nk * slots > 11 * (light + 4 * heads * len(heavy) * nk)) == (heads == 2)
+    assert heads * -(-g.N // 32) > 640 and (12 * nk * slots > 25 * (light + 4 * heads * len(heavy) * nk)) == (heads == 2)
     q, k, v = make_plain_qkv(1, 2, g.N, D, seed=T)
     k = (k.float() * torch.linspace(0.2, 3.0, g.N)[None, None, :, None]).bfloat16()
     rep = lambda x: x.repeat(1, heads // 2, 1, 1).cuda()
     o = run(form, sh, rep(q), rep(k), rep(v), torch.tensor([0, 1] * (heads // 2), dtype=torch.uint8).cuda())
     in_order = np.empty(g.N, np.int64)
     in_order[O.layout_perm(g)] = np.arange(g.N)
+    fp8 = lambda x: O.fp8_dequantize(*O.fp8_quantize_head(x)) if form == "fp8" else x      # the products' own inputs
     for h in (0, 1):
+        qh, kh, vh = (fp8(f64(x)[0, h]) for x in (q, k, v))
         token = in_order if h else np.arange(g.N)
         rp, ci = csr[h]
         for a in heavy + [heavy[-1] - 1 if heavy[-1] == nq - 1 else heavy[-1] + 1, nq // 2]:
             rows = slice(a * 128, min(g.N, (a + 1) * 128))
             cols = np.concatenate([np.arange(b * 64, min(g.N, (b + 1) * 64)) for b in ci[rp[a]:rp[a + 1]]])
-            qr, kr, vr = f64(q)[0, h][token[rows]], f64(k)[0, h][token[cols]], f64(v)[0, h][token[cols]]
+            qr, kr, vr = qh[token[rows]], kh[token[cols]], vh[token[cols]]
             keep = np.ones((len(qr), len(cols)), bool)
             if form == "exact":
                 keep = (O.temporal_mask if h else O.spatial_mask)(g, token[rows])[:, token[cols]]
             ref = O.masked_attention(qr, kr, vr, keep, g.scale)
-            assert_attn_close(o[0, heads - 2 + h][torch.from_numpy(token[rows]).cuda()], ref, f"{form} head {h}, tile {a}")
+            got, what = o[0, heads - 2 + h][torch.from_numpy(token[rows]).cuda()], f"{form} head {h}, tile {a}"
+            if form == "fp8":
+                assert_fp8_attn_close(got, ref, float(np.abs(vh).max()), what)
+            else:
+                assert_attn_close(got, ref, what)
