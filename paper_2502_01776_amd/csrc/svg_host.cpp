@@ -120,7 +120,8 @@ int make_geo(const svg_shape_t* s, Geo* g) {
   g->text_first = s->text_first;
   g->off = s->text_first ? s->T : 0;
   g->video_end = g->off + s->F * s->P;
-  g->w_s = s->w_s; g->w_t = s->w_t; g->sink = s->sink_first_frame;
+  // (wider windows keep nothing more, and the kernels add a coordinate to the half-window in 32 bits)
+  g->w_s = std::min(s->w_s, s->F); g->w_t = std::min(s->w_t, s->P); g->sink = s->sink_first_frame;
   g->bm = s->block_m; g->bn = s->block_n;
   g->nq = (int)nq;
   g->nk = (int)((n + s->block_n - 1) / s->block_n);

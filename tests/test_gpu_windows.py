@@ -62,3 +62,24 @@ def test_rows_behind_the_last_key_are_never_read(D, tail):
     for h in range(2):
         assert_attn_close(od[0, h], O.dense_attention_head(f64(q)[0, h], f64(k)[0, h], f64(v)[0, h], g))
         assert_attn_close(og[0, h], ref[0, h])
+
+
+@pytest.mark.parametrize("w_s, w_t", [(2 ** 31 - 1, 3), (2 ** 31 - 4, 3), (1, 2 ** 31 - 1), (1, 2 ** 31 - 20)])
+@pytest.mark.parametrize("P, heads", [(40, 2), (41, 2), (40, 80)])
+@pytest.mark.parametrize("blocks, D", [((128, 64), 64), ((128, 64), 128), ((32, 32), 64)])
+def test_windows_as_wide_as_the_type(w_s, w_t, P, heads, blocks, D):
+    """Half-windows at the end of their type keep every key: no error under that mask.  Few heads and many: both forms
+    of the profiling passes."""
+    cfg, sh, g = setup(F=9, P=P, T=5, D=D, text_first=1, w_s=w_s, w_t=w_t, block_m=blocks[0], block_n=blocks[1], sink_first_frame=0)
+    q, k, v = make_plain_qkv(1, 2, g.N, D, seed=P)
+    rows = np.arange(0, g.N, 4, dtype=np.int32)
+    omse, olab = O.profile_heads(f64(q), f64(k), f64(v), rows, g)
+    wide = 0 if w_s > w_t else 1
+    assert (omse[..., wide] == 0).all() and (omse[..., 1 - wide] > 1e-4).all() and (olab == wide).all()
+    many = S.shape_from_config(dict(cfg, H=heads))
+    labels, mse = gpu_profile(many, *[x.repeat(1, heads // 2, 1, 1).cuda() for x in (q, k, v)], rows)
+    mse = mse.cpu().numpy().reshape(heads // 2, 2, 2)
+    # the bounds of the other profiling tests: bf16 rounding of the weights under every measured error
+    for pair in (0, -1):
+        assert np.allclose(mse[pair], omse[0], rtol=0.05, atol=2e-5)
+    assert (labels.cpu().numpy() == wide).all()
