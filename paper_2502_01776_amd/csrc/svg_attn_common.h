@@ -140,12 +140,12 @@ struct SparseOrder {
   int nh;      // tiles with a text row per head (the others, ascending)
   int hmax;    // workgroups per XCD reserved for them
   int slots;   // workgroups resident on one XCD (sets the stride, see above)
-  int parts_log2;      // workgroups reserved per tile with a text row: 1 << parts_log2
+  int parts_log2;      // workgroups reserved per tile with a text row: 1 << parts_log2; 0: none is taken in parts
   int nk;              // key tiles, what a tile with a text row keeps
   int places;          // workgroups resident on the chip
 };
 
-inline SparseOrder sparse_order(int BH, int nqt, int BM, int off, int video_end, int N, int slots, int places = 0, int parts_log2 = 0, int nk = 0) {
+inline SparseOrder sparse_order(int BH, int nqt, int BM, int off, int video_end, int N, int slots, int places, int parts_log2, int nk) {
   SparseOrder so;
   const int lo = off > 0 ? (off + BM - 1) / BM : 0;
   int hi = video_end < N ? video_end / BM : nqt;
@@ -155,7 +155,10 @@ inline SparseOrder sparse_order(int BH, int nqt, int BM, int off, int video_end,
   so.nh = nqt - so.nl;
   so.hmax = so.nh * ((BH + 7) / 8);
   so.slots = slots;
-  so.parts_log2 = parts_log2;
+  // With so many heavy tiles that their parts alone are above the line (see above) whatever the labels say, no workgroups
+  // are reserved for parts: idle, they took up to 6 % of the pass (4000 heads of 220 rows 131 -> 140 us, FP8 201 -> 213),
+  // and from 2^22 heavy tiles on the grid was too large to launch.
+  so.parts_log2 = 12ll * places > 100ll * BH * so.nh ? parts_log2 : 0;
   so.nk = nk;
   so.places = places;
   return so;

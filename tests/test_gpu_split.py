@@ -147,3 +147,18 @@ def test_text_rows_split_in_the_general_kernel(form, D, text_first, T, heads):
                 assert_fp8_attn_close(got, ref, float(np.abs(vh).max()), what)
             else:
                 assert_attn_close(got, ref, what)
+
+
+def test_more_text_tiles_than_a_launch_has_parts_for():
+    """2^22 heads of one video and one text token: one workgroup per query tile fits a launch, four do not."""
+    heads = 2 ** 22
+    cfg, sh, g = setup(heads, 64, 1, 1, 1, block_m=128, block_n=64)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    q, k, v = (torch.randn(1, heads, 2, 64, generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    lab = torch.zeros(heads, dtype=torch.uint8, device="cuda")
+    o = torch.full_like(q, float("nan"))
+    S.svg_sparse_attn_fwd(sh, q, k, v, o, lab, *device_tile_lists(sh))
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(o).all())
+    for h in (0, 1, heads // 2 - 1, heads // 2, heads - 1):
+        assert_attn_close(o[0, h], O.dense_attention_head(*[f64(x[0, h]) for x in (q, k, v)], g), f"head {h}")
