@@ -1137,7 +1137,6 @@ int launch_error_parts(const AttnArgs& a, const float2* stats, float2* partial, 
     case 3: launch_error<D, 3>(a, stats, partial, labels, mse, stream); break;
     case 4: launch_error<D, 4>(a, stats, partial, labels, mse, stream); break;
     case 6: launch_error<D, 6>(a, stats, partial, labels, mse, stream); break;
-    case 8: launch_error<D, 8>(a, stats, partial, labels, mse, stream); break;
     default: return SVG_ERR_UNSUPPORTED;
   }
   int rc = hip_status(hipGetLastError());

@@ -76,25 +76,19 @@ ProfilePlan profile_plan(const Geo& g, int t) {
 //    64: 53.0 -> 50.9, 21.8 -> 21.0); with 16 groups of 3290 rows four masked parts stay better (20.7 against 22).  Head
 //    dimension 64 from 96 groups on: two masked parts, 1.09-1.12 times as fast as the plan's cut at 96 to 138 groups.
 //    Where the unmasked pass is not cut, three parts of each pass: 4 heads of 272 rows 9.5 -> 9.0, 24 of 820 12.9 -> 12.1.
-//  * Few heads whose sampled rows make many groups: the windows of a group are narrow, the masked passes short, and the parts of
-//    the unmasked pass the longest chain of the call.  Eight of them and three: 1.15-1.22 times as fast at 24 to 36 pairs
-//    of 6 to 10 groups (3 heads of 119056 rows 496 -> 424 us); with up to 3 groups 0.80-0.95.
+// The general form keeps the plan's cut.  (Eight parts of the unmasked pass and three of the masked ones for few heads with many
+// groups of rows, whose windows are narrow only where the caller sorts the rows: 60 calls of 1-14 heads, 6200-120000 keys and 641-2400 rows
+// ran at 0.76-1.08 of the plan's speed with rows in random order, median 0.80, and at 0.80-1.21 with sorted ones.)
 ProfilePlan profile_cut(const Geo& g, int t, const ProfilePlan& plan, bool split) {
-  const int groups = (t + g.bm - 1) / g.bm;
   const long long heads = (long long)g.B * g.H;
   ProfilePlan cut = plan;
-  if (plan.n_masked != 4) return cut;
-  if (split) {
-    if (plan.n_full == 1) {
-      cut.n_masked = 3;
-      fill_bounds(&cut, 0, 3, g.nk);
-    } else if (heads * ((t + 31) / 32) >= 24) {
-      cut.n_masked = g.D == 64 && heads * ((t + 31) / 32) >= 96 ? 2 : 3;
-      fill_bounds(&cut, 0, 4, g.nk);
-    }
-  } else if (plan.n_full == 6 && groups >= 6) {
+  if (!split || plan.n_masked != 4) return cut;
+  if (plan.n_full == 1) {
     cut.n_masked = 3;
-    fill_bounds(&cut, 6, 2, g.nk);
+    fill_bounds(&cut, 0, 3, g.nk);
+  } else if (heads * ((t + 31) / 32) >= 24) {
+    cut.n_masked = g.D == 64 && heads * ((t + 31) / 32) >= 96 ? 2 : 3;
+    fill_bounds(&cut, 0, 4, g.nk);
   }
   return cut;
 }

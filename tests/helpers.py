@@ -1,4 +1,6 @@
 """Shared plumbing for the GPU parity tests: upload, run the library, download."""
+import ctypes as C
+
 import numpy as np
 import torch
 
@@ -169,3 +171,46 @@ def assert_fp8_attn_close(got: torch.Tensor, ref: np.ndarray, v_absmax: float, w
     assert err.max() <= 2.0 ** -4 * v_absmax + 1e-2, f"{what}: max-abs {err.max():.4g}"
     rel = np.linalg.norm(g - ref) / max(np.linalg.norm(ref), 1e-30)
     assert rel <= FP8_REL_RMS, f"{what}: relative rms error {rel:.4g}"
+
+
+# ----------------------------------------------------------------------------- the library's own rules
+# Which form of a kernel takes a call, and how a profiling call is cut, are rules inside the library (svg_internal.h,
+# svg_attn_common.h); asked here by their C++ names, so that a test can say which of them it runs.
+DENSE, SPARSE, PROFILE, EXACT, GATHER = range(5)
+
+
+class Geo(C.Structure):
+    _fields_ = [(n, C.c_int) for n in ("B", "H", "F", "P", "T", "D", "N", "off", "video_end", "w_s", "w_t", "sink", "bm", "bn",
+                                       "nq", "nk", "text_first")] + [("scale", C.c_float)]
+
+
+class Plan(C.Structure):
+    _fields_ = [("n_full", C.c_int), ("n_masked", C.c_int), ("full_bound", C.c_int * 17)]
+
+    def slots(self):
+        return self.n_full + 2 * self.n_masked
+
+
+def _rule(name, restype, *args):
+    f = getattr(S.lib(), name)
+    f.restype = restype
+    return f(*args)
+
+
+def _geo(shape):
+    g = Geo()
+    assert _rule("_ZN3svg8make_geoEPK9svg_shapePNS_3GeoE", C.c_int, C.byref(shape), C.byref(g)) == 0
+    return g
+
+
+def takes_split_form(shape, mode, t=0):
+    """Do the passes of this call run in the form that splits the keys over the wavefronts?"""
+    return _rule("_ZN3svg4attn10split_formERKNS_3GeoEii", C.c_bool, C.byref(_geo(shape)), C.c_int(mode), C.c_int(t))
+
+
+def profile_cuts(shape, t):
+    """(the plan the workspace is sized for, the cut a launch takes)"""
+    g = _geo(shape)
+    plan = _rule("_ZN3svg12profile_planERKNS_3GeoEi", Plan, C.byref(g), C.c_int(t))
+    split = C.c_bool(takes_split_form(shape, PROFILE, t))
+    return plan, _rule("_ZN3svg11profile_cutERKNS_3GeoEiRKNS_11ProfilePlanEb", Plan, C.byref(g), C.c_int(t), C.byref(plan), split)

@@ -48,7 +48,5 @@ def test_parts_of_the_unmasked_pass(H, F, P, t, n_full, D):
 
 @pytest.mark.parametrize("H, F, P, t, D", [(6, 5, 1300, 90, 128), (8, 9, 400, 60, 64), (2, 9, 160, 700, 128), (8, 9, 160, 700, 64), (12, 5, 330, 256, 64)])
 def test_cuts_of_the_launch(H, F, P, t, D):
-    """The cuts a launch takes in place of the plan's: four equal parts and three of the split form with 24 groups of rows
-    and more, two masked ones at head dimension 64 with 96 and more, eight parts of the unmasked pass for few heads with many
-    groups."""
+    """Numbers of groups of rows around which the split form cuts its passes otherwise than the plan says."""
     check(dict(get_config("mid64"), D=D, B=1, H=H, F=F, P=P, spatial_heads=[0]), t)
