@@ -228,11 +228,12 @@ struct Fp8Args {
 // --------------------------------------------------------------------------------------------
 // Attention of calls with few rows: as split_kernel (svg_split.hip), 32 query rows per workgroup, every fourth key tile per
 // wavefront, merged through LDS.  The tiles of k8 and v8t hold whole operands in 16-byte pieces, so both go from
-// memory straight to registers and nothing is staged.  6 heads of 960 rows 18.2 -> 9.9 us, 2 of 3290 rows 52.6 -> 21.8.  The
-// line lies at 600 groups of 32 rows (two workgroups fit a CU): time of attn_fp8_kernel over time here, 1 to 48 heads of
-// 272 to 9746 rows, 1.1-2.7 up to 600 groups, 0.93 at 624 with lists of 8 tiles.
+// memory straight to registers and nothing is staged.  6 heads of 960 rows 18.2 -> 9.9 us, 2 of 3290 rows 52.6 -> 21.8.  Two
+// workgroups fit a CU: time of attn_fp8_kernel without parts of text-row tiles over time here, 1 to 48 heads of 200 to 19000 rows, 1.07-2.7 up
+// to 512 groups of 32 rows.  Up to 600, where some CUs take a third, it depends on the lists: 0.98-1.5 from 4096 rows a head on, 0.77-1.03 below
+// (0.73-1.33 with text rows, whose tiles attn_fp8_kernel now takes in parts).
 // --------------------------------------------------------------------------------------------
-constexpr int kSplitWaves = 4, kSplitRows = 32, kSplitGroups = 600;
+constexpr int kSplitWaves = 4, kSplitRows = 32;
 
 // lds: 64 KB.  Rows row0 .. row0 + 31 of head bh, entries [list_begin, list_end) of pattern pat's list.
 __device__ __forceinline__ void fp8_split_body(const Fp8Args& a, unsigned char* const lds, const int bh, const int row0, const int pat,
@@ -762,6 +763,11 @@ int launch_fp8_quantize(const Geo& g, const void* q, const void* k, const void* 
   return hip_status(hipGetLastError());
 }
 
+bool fp8_split_form(const Geo& g) {
+  const long long groups = (long long)g.B * g.H * ((g.N + kSplitRows - 1) / kSplitRows);
+  return groups <= (g.N >= 4096 ? 600 : 512);
+}
+
 int launch_fp8_attention(const Geo& g, const void* q8, const void* k8, const void* v8t, const float* scales,
                          void* o, const uint8_t* labels, const int32_t* row_ptr_s, const int32_t* col_idx_s,
                          const int32_t* row_ptr_t, const int32_t* col_idx_t, hipStream_t stream) {
@@ -784,8 +790,8 @@ int launch_fp8_attention(const Geo& g, const void* q8, const void* k8, const voi
   a.w_s = g.w_s; a.w_t = g.w_t;
   a.order = p_outer(g);
   (void)hipGetLastError();
-  const long long groups = (long long)a.BH * ((a.N + kSplitRows - 1) / kSplitRows);
-  if (groups <= kSplitGroups) {
+  if (fp8_split_form(g)) {
+    const long long groups = (long long)a.BH * ((a.N + kSplitRows - 1) / kSplitRows);
     a.nqt = (a.N + kSplitRows - 1) / kSplitRows;
     hipLaunchKernelGGL(attn_fp8_split_kernel, dim3(8u * (unsigned)((groups + 7) / 8)), dim3(64 * kSplitWaves), 0, stream, a);
     return hip_status(hipGetLastError());

@@ -121,6 +121,7 @@ int launch_norm_rope(const Geo& g, const void* x, void* y, int norm, const float
                      float eps, const float* cos, const float* sin, int pairing, hipStream_t stream);
 int launch_fp8_quantize(const Geo& g, const void* q, const void* k, const void* v, const uint8_t* labels,
                         void* q8, void* k8, void* v8t, float* scales, hipStream_t stream);
+bool fp8_split_form(const Geo& g);      // does the form for calls with few rows take this FP8 call?
 int launch_fp8_attention(const Geo& g, const void* q8, const void* k8, const void* v8t, const float* scales,
                          void* o, const uint8_t* labels, const int32_t* row_ptr_s, const int32_t* col_idx_s,
                          const int32_t* row_ptr_t, const int32_t* col_idx_t, hipStream_t stream);

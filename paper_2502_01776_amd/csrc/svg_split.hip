@@ -76,16 +76,35 @@ int launch_split_one(const AttnArgs& a, unsigned grid, hipStream_t stream) {
 
 namespace attn {
 
-// Where the lines lie, by the number of workgroups (heads x groups of 32 rows), from 300 calls of 2 to 48 heads and 272
-// to 9746 rows with either tile shape, time of attn_kernel over time here:
-//   head dimension 64:  1.03-3.0 up to 624 workgroups, dense 0.9 at 824 (three workgroups fit a CU)
-//   head dimension 128: 1.04-2.6 up to 414, 0.94 at 432 with 32-row query tiles and 9 key tiles, dense 0.87 at 610 (two fit)
+// Where the lines lie, by the number of workgroups (heads x groups of 32 rows), from 1100 calls of 1 to 48 heads and 192
+// to 24000 rows, time of attn_kernel with whole text-row tiles over time here.  A CU holds three workgroups at head dimension 64 and two at 128;
+// beyond one (256) or two (512) to a CU the last of them can cost as much as they save:
+//   dense, exact masks: 1.03-3.0 up to 640 and 416 (0.98 once, at 589); dense 0.9 at 824 and 0.87 at 610
+//   gathering:          64: 1.29-1.60 up to 512; to 640 1.06-1.55 with four heads or more, 0.92-1.32 with fewer (a head's rows lie on few XCDs, so
+//                       unequal lists of the two labels weigh).  128: 0.99-1.8 up to 416
+//   plain sparse:       64: 1.07-1.6 up to 512, 0.87-1.21 from there to 640.  128: 1.27-1.8 up to 256; to 416 0.96-1.40, 0.93-1.01 with fewer
+//                       than 16 key tiles and 336 workgroups or more
+//   32-row query tiles: a lone wavefront walks the list in attn_kernel, so its length decides.  Exact masks 1.0-2.1 up to 640 and 416.  With text rows or 48 key tiles and more 0.96-2.2 up to 600 and
+//                       416.  Shorter ones: sparse at 128 1.08-1.8 up to 256, 0.87-1.01 beyond; at 64 1.0-1.5 up to 256, 0.97-1.02 beyond with
+//                       fewer than 16 key tiles, 0.89-0.97 over 512; dense at 128 with fewer than 16 0.92-0.99 over 256, 1.02-1.13 with more
 //   profiling:          1.1-2.7 up to 144 and 1.07-2.3 up to 72 workgroups per pass and part; 0.91 at 168 and 96.  The K and V that
 //                       they read between them count as well: 64 x 50000 keys 1.32, 38 x 118800 1.66, but 92 x 72500 0.81 and
 //                       128 x 50000 0.79 at head dimension 64; 48 x 50000 1.24 and 38 x 118800 1.36 at 128
 bool split_form(const Geo& g, int mode, int t) {
   const long long heads = (long long)g.B * g.H;
-  if (mode != kProfile) return heads * ((g.N + kRows - 1) / kRows) <= (g.D == 64 ? 640 : 416);
+  const bool d64 = g.D == 64;
+  if (mode != kProfile) {
+    int most = d64 ? 640 : 416;
+    if (g.bm == 128) {
+      if (mode == kSparse) most = d64 ? 512 : g.nk < 16 ? 256 : 416;
+      if (mode == kSparseGather && d64 && heads < 4) most = 512;
+    } else if (mode != kSparseExact) {
+      const bool long_lists = g.T > 0 || g.nk >= 48, few_tiles = g.nk < 16;
+      if (d64) most = long_lists ? 600 : mode == kSparse && few_tiles ? 256 : 512;
+      else if (!long_lists && (mode == kSparse || few_tiles)) most = 256;
+    }
+    return heads * ((g.N + kRows - 1) / kRows) <= most;
+  }
   const long long groups = heads * ((t + kRows - 1) / kRows);
   if (g.F > kMaxFrames || groups > (g.D == 64 ? 144 : 72)) return false;
   return groups <= (g.D == 64 ? 64 : 48) || groups * g.N <= (g.D == 64 ? 3200000 : 1600000);

@@ -208,6 +208,10 @@ def takes_split_form(shape, mode, t=0):
     return _rule("_ZN3svg4attn10split_formERKNS_3GeoEii", C.c_bool, C.byref(_geo(shape)), C.c_int(mode), C.c_int(t))
 
 
+def takes_fp8_split_form(shape):
+    return _rule("_ZN3svg14fp8_split_formERKNS_3GeoE", C.c_bool, C.byref(_geo(shape)))
+
+
 def profile_cuts(shape, t):
     """(the plan the workspace is sized for, the cut a launch takes)"""
     g = _geo(shape)
