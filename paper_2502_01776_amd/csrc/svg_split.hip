@@ -80,12 +80,12 @@ namespace attn {
 // to 24000 rows, time of attn_kernel with whole text-row tiles over time here.  A CU holds three workgroups at head dimension 64 and two at 128;
 // beyond one (256) or two (512) to a CU the last of them can cost as much as they save:
 //   dense, exact masks: 1.03-3.0 up to 640 and 416 (0.98 once, at 589); dense 0.9 at 824 and 0.87 at 610
-//   gathering:          64: 1.29-1.60 up to 512; to 640 1.06-1.55 with four heads or more, 0.92-1.32 with fewer (a head's rows lie on few XCDs, so
-//                       unequal lists of the two labels weigh).  128: 0.99-1.8 up to 416
-//   plain sparse:       64: 1.07-1.6 up to 512, 0.87-1.21 from there to 640.  128: 1.27-1.8 up to 256; to 416 0.96-1.40, 0.93-1.01 with fewer
-//                       than 16 key tiles and 336 workgroups or more
-//   32-row query tiles: a lone wavefront walks the list in attn_kernel, so its length decides.  Exact masks 1.0-2.1 up to 640 and 416.  With text rows or 48 key tiles and more 0.96-2.2 up to 600 and
-//                       416.  Shorter ones: sparse at 128 1.08-1.8 up to 256, 0.87-1.01 beyond; at 64 1.0-1.5 up to 256, 0.97-1.02 beyond with
+//   plain sparse:       64: 1.07-1.6 up to 512, 0.87-1.26 from there to 640.  128: 1.27-1.8 up to 256; to 416 0.96-1.40, 0.93-1.24 with fewer
+//                       than 16 key tiles
+//   gathering:          has the line of plain sparse, so that k and v gathered in place give the bits of the layout passes (beyond it 0.92-1.55 at 64
+//                       and 1.03-1.24 at 128 with fewer than 16 key tiles)
+//   32-row query tiles: a lone wavefront walks the list in attn_kernel, so its length decides.  Exact masks 1.0-2.1 up to 640 and 416.  With text rows or
+//                       48 key tiles and more 0.96-2.2 up to 600 and 416.  Shorter ones: sparse at 128 1.08-1.8 up to 256, 0.87-1.01 beyond; at 64 1.0-1.5 up to 256, 0.97-1.02 beyond with
 //                       fewer than 16 key tiles, 0.89-0.97 over 512; dense at 128 with fewer than 16 0.92-0.99 over 256, 1.02-1.13 with more
 //   profiling:          1.1-2.7 up to 144 and 1.07-2.3 up to 72 workgroups per pass and part; 0.91 at 168 and 96.  The K and V that
 //                       they read between them count as well: 64 x 50000 keys 1.32, 38 x 118800 1.66, but 92 x 72500 0.81 and
@@ -96,8 +96,7 @@ bool split_form(const Geo& g, int mode, int t) {
   if (mode != kProfile) {
     int most = d64 ? 640 : 416;
     if (g.bm == 128) {
-      if (mode == kSparse) most = d64 ? 512 : g.nk < 16 ? 256 : 416;
-      if (mode == kSparseGather && d64 && heads < 4) most = 512;
+      if (mode == kSparse || mode == kSparseGather) most = d64 ? 512 : g.nk < 16 ? 256 : 416;
     } else if (mode != kSparseExact) {
       const bool long_lists = g.T > 0 || g.nk >= 48, few_tiles = g.nk < 16;
       if (d64) most = long_lists ? 600 : mode == kSparse && few_tiles ? 256 : 512;
