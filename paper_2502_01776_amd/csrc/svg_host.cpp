@@ -71,26 +71,30 @@ ProfilePlan profile_plan(const Geo& g, int t) {
 }
 
 // How a launch cuts the passes: as profile_plan says, which also sizes the workspace, or otherwise into no more parts in all.
-//  * The split form (svg_split.hip) has four times the row groups, so with 24 of them or more four parts and three fill the
-//    chip: 48 groups of 9086 rows 72.8 -> 61.4 us, of 3290 rows 33.1 -> 30.2, of 17776 rows 89.4 -> 78.6 (head dimension
-//    64: 53.0 -> 50.9, 21.8 -> 21.0); with 16 groups of 3290 rows four masked parts stay better (20.7 against 22).  Head
-//    dimension 64 from 96 groups on: two masked parts, 1.09-1.12 times as fast as the plan's cut at 96 to 138 groups.
+//  * The split form (svg_split.hip) has four times the row groups, and a part that starts when another has ended lengthens the call by its
+//    own time.  Where the plan's parts do not all find a place at once and four parts and three do, those are taken (from 96 groups on, at head
+//    dimension 64, four and two); fewer than a tenth too many do no harm, the last parts are short ones.  Plan over cut, by groups of rows to an
+//    XCD, 230 calls of 1-100 heads, 1600-55000 keys and 8-1200 rows: head dimension 128 three 1.00-1.31, four 0.80-1.03, five
+//    0.81-1.08, six 0.88-1.26, median 1.06 (48 groups of 9086 rows 72.8 -> 61.4 us); 64 four to seven 0.80-1.07, median 0.93, nine 1.06-1.15,
+//    ten 0.83-1.09, twelve 0.92-1.16.
 //    Where the unmasked pass is not cut, three parts of each pass: 4 heads of 272 rows 9.5 -> 9.0, 24 of 820 12.9 -> 12.1.
 // The general form keeps the plan's cut.  (Eight parts of the unmasked pass and three of the masked ones for few heads with many
 // groups of rows, whose windows are narrow only where the caller sorts the rows: 60 calls of 1-14 heads, 6200-120000 keys and 641-2400 rows
 // ran at 0.76-1.08 of the plan's speed with rows in random order, median 0.80, and at 0.80-1.21 with sorted ones.)
 ProfilePlan profile_cut(const Geo& g, int t, const ProfilePlan& plan, bool split) {
-  const long long heads = (long long)g.B * g.H;
+  if (!split || plan.n_masked != 4) return plan;
   ProfilePlan cut = plan;
-  if (!split || plan.n_masked != 4) return cut;
   if (plan.n_full == 1) {
     cut.n_masked = 3;
     fill_bounds(&cut, 0, 3, g.nk);
-  } else if (heads * ((t + 31) / 32) >= 24) {
-    cut.n_masked = g.D == 64 && heads * ((t + 31) / 32) >= 96 ? 2 : 3;
-    fill_bounds(&cut, 0, 4, g.nk);
+    return cut;
   }
-  return cut;
+  const long long per_xcd = ((long long)g.B * g.H * ((t + 31) / 32) + 7) / 8;
+  cut.n_masked = g.D == 64 && per_xcd >= 12 ? 2 : 3;
+  fill_bounds(&cut, 0, 4, g.nk);
+  auto helps = [&](int places) { return 10 * plan.slots() * per_xcd > 11 * places && cut.slots() * per_xcd <= places; };
+  // all places of an XCD, or at head dimension 128, where two workgroups of a CU get in each other's way, one to a CU
+  return helps(g.D == 64 ? kSlots * 3 / 2 : kSlots) || (g.D == 128 && helps(kSlots / 2)) ? cut : plan;
 }
 
 int make_geo(const svg_shape_t* s, Geo* g) {

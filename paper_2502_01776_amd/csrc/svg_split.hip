@@ -87,9 +87,9 @@ namespace attn {
 //   32-row query tiles: a lone wavefront walks the list in attn_kernel, so its length decides.  Exact masks 1.0-2.1 up to 640 and 416.  With text rows or
 //                       48 key tiles and more 0.96-2.2 up to 600 and 416.  Shorter ones: sparse at 128 1.08-1.8 up to 256, 0.87-1.01 beyond; at 64 1.0-1.5 up to 256, 0.97-1.02 beyond with
 //                       fewer than 16 key tiles, 0.89-0.97 over 512; dense at 128 with fewer than 16 0.92-0.99 over 256, 1.02-1.13 with more
-//   profiling:          1.1-2.7 up to 144 and 1.07-2.3 up to 72 workgroups per pass and part; 0.91 at 168 and 96.  The K and V that
-//                       they read between them count as well: 64 x 50000 keys 1.32, 38 x 118800 1.66, but 92 x 72500 0.81 and
-//                       128 x 50000 0.79 at head dimension 64; 48 x 50000 1.24 and 38 x 118800 1.36 at 128
+//   profiling:          1.0-3.0 up to 128 and 1.05-2.6 up to 72 workgroups per pass and part; 0.97 at 140, 0.91 at 168 and 96.  The K and V that
+//                       they read between them count as well: at head dimension 64 64 x 118800 keys 1.16, but 77 x 34400 0.98, 90 x 29700 0.95,
+//                       92 x 72500 0.81; at 128 48 x 118800 1.09 (28 x 54000 with 10 rows a head 0.97)
 bool split_form(const Geo& g, int mode, int t) {
   const long long heads = (long long)g.B * g.H;
   const bool d64 = g.D == 64;
@@ -105,8 +105,8 @@ bool split_form(const Geo& g, int mode, int t) {
     return heads * ((g.N + kRows - 1) / kRows) <= most;
   }
   const long long groups = heads * ((t + kRows - 1) / kRows);
-  if (g.F > kMaxFrames || groups > (g.D == 64 ? 144 : 72)) return false;
-  return groups <= (g.D == 64 ? 64 : 48) || groups * g.N <= (g.D == 64 ? 3200000 : 1600000);
+  if (g.F > kMaxFrames || groups > (g.D == 64 ? 128 : 72)) return false;
+  return groups <= (g.D == 64 ? 64 : 48) || groups * g.N <= (g.D == 64 ? 2400000 : 1600000);
 }
 
 bool split_sorts_rows(int t) { return t <= kSortRows; }

@@ -58,3 +58,24 @@ def test_numbers_of_workgroups_the_fp8_split_form_takes(N, most):
     per_head = -(-N // 32)
     for H in range(max(1, most // per_head - 2), most // per_head + 3):
         assert takes_fp8_split_form(shape(H, N)) == (H * per_head <= most), H
+
+
+@pytest.mark.parametrize("D, H, N, cut", [
+    (128, 16, 7000, None), (128, 17, 7000, (4, 3)), (128, 24, 7000, (4, 3)), (128, 25, 7000, None), (128, 40, 7000, None), (128, 41, 7000, (4, 3)),
+    (128, 48, 7000, (4, 3)), (128, 49, 7000, None), (64, 24, 7000, None), (64, 56, 7000, None), (64, 57, 7000, (4, 3)), (64, 72, 7000, (4, 3)),
+    (64, 73, 7000, None), (64, 88, 7000, None), (64, 89, 7000, (4, 2)), (64, 96, 7000, (4, 2)), (64, 97, 7000, None), (128, 9, 700, (3, 3))])
+def test_cuts_of_the_split_form(D, H, N, cut):
+    """Fewer parts than the plan where those find a place at once and the plan's do not (one group of rows per head)."""
+    plan, got = profile_cuts(shape(H, N, D), 32)
+    assert takes_split_form(shape(H, N, D), PROFILE, 32) and plan.n_masked == 4
+    assert (got.n_full, got.n_masked) == (cut or (plan.n_full, plan.n_masked))
+    if cut is None:
+        assert bytes(got) == bytes(plan)
+
+
+@pytest.mark.parametrize("D, free, most, keys", [(64, 64, 128, 2400000), (128, 48, 72, 1600000)])
+def test_groups_of_rows_the_split_form_profiles(D, free, most, keys):
+    for N in (1000, 15000, 18751, 22000, 33334, 200000):
+        for H in range(1, most + 3):
+            assert takes_split_form(shape(H, N, D), PROFILE, 20) == (H <= free or (H <= most and H * N <= keys)), (H, N)
+    assert takes_split_form(shape(2, 6100, D, F=61), PROFILE, 20) and not takes_split_form(shape(2, 6200, D, F=62), PROFILE, 20)
