@@ -60,14 +60,15 @@ def test_numbers_of_workgroups_the_fp8_split_form_takes(N, most):
         assert takes_fp8_split_form(shape(H, N)) == (H * per_head <= most), H
 
 
-@pytest.mark.parametrize("D, H, N, cut", [
-    (128, 16, 7000, None), (128, 17, 7000, (4, 3)), (128, 24, 7000, (4, 3)), (128, 25, 7000, None), (128, 40, 7000, None), (128, 41, 7000, (4, 3)),
-    (128, 48, 7000, (4, 3)), (128, 49, 7000, None), (64, 24, 7000, None), (64, 56, 7000, None), (64, 57, 7000, (4, 3)), (64, 72, 7000, (4, 3)),
-    (64, 73, 7000, None), (64, 88, 7000, None), (64, 89, 7000, (4, 2)), (64, 96, 7000, (4, 2)), (64, 97, 7000, None), (128, 9, 700, (3, 3))])
-def test_cuts_of_the_split_form(D, H, N, cut):
-    """Fewer parts than the plan where those find a place at once and the plan's do not (one group of rows per head)."""
-    plan, got = profile_cuts(shape(H, N, D), 32)
-    assert takes_split_form(shape(H, N, D), PROFILE, 32) and plan.n_masked == 4
+@pytest.mark.parametrize("D, H, t, N, cut", [
+    (128, 16, 32, 7000, None), (128, 17, 32, 7000, (4, 3)), (128, 24, 32, 7000, (4, 3)), (128, 25, 32, 7000, None), (128, 40, 32, 7000, None),
+    (128, 41, 32, 7000, (4, 3)), (128, 48, 32, 7000, (4, 3)), (128, 49, 32, 7000, None), (64, 24, 32, 7000, None), (64, 56, 32, 7000, None),
+    (64, 57, 32, 7000, (4, 3)), (64, 72, 32, 7000, (4, 3)), (64, 73, 32, 7000, None), (64, 88, 32, 7000, None), (64, 44, 64, 7000, None),
+    (64, 45, 64, 7000, (4, 2)), (64, 48, 64, 7000, (4, 2)), (64, 49, 64, 7000, None), (128, 9, 32, 700, (3, 3))])
+def test_cuts_of_the_split_form(D, H, t, N, cut):
+    """Fewer parts than the plan where those find a place at once and the plan's do not."""
+    plan, got = profile_cuts(shape(H, N, D), t)
+    assert takes_split_form(shape(H, N, D), PROFILE, t) and plan.n_masked == 4
     assert (got.n_full, got.n_masked) == (cut or (plan.n_full, plan.n_masked))
     if cut is None:
         assert bytes(got) == bytes(plan)
