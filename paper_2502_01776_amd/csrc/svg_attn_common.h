@@ -113,10 +113,13 @@ struct TileList {
 //  * Where a heavy tile is much longer than an even share of the work it is the whole time of the pass (with few heads or
 //    short lists: 18 heads of 1909 tokens 47 of 51 us).  Then four workgroups take it, 32 rows each, its keys
 //    split over their wavefronts (svg_split.h), dealt to all XCDs.  That costs about 2.5 times the tile's work and takes 0.3 of
-//    its time.  The line, nk > 2.08 (light tiles + 4 heavy tiles) / places, from 2 to 48 heads of 1520 to 18977 tokens
-//    and both head dimensions, time whole over time split: 1.03-2.3 above it (2 heads of 9746 at head dimension 128: 173 ->
-//    90 us; 8 of 3290: 65 -> 37; 8 of 18977, at 2.09: 392 -> 265, FP8 257 -> 183), 0.80-1.15 between 1.3 and it,
-//    0.63-1.0 below.
+//    its time, so it needs places that would be empty (ratio: nk places / (light tiles + 4 heavy tiles)) and a heavy list that is long
+//    beside the others, which then take the time of the pass.  Time whole over time in parts, 580 calls of 2 to 92 heads of 190 to 45000
+//    tokens, both head dimensions, FP8 among them (8 heads of 18977 tokens 392 -> 265 us, FP8 257 -> 183):
+//      ratio above 2.08, a heavy list 16 tiles and more longer than the mean other one: 0.96-2.05, median 1.44; in parts
+//      ratio above 3.2, 12 key tiles and more: 0.94-1.65, median 1.23; in parts
+//      ratio 2.08 to 3.2, lists closer than that: 0.76-1.37, median 0.98; whole, as below 12 key tiles (0.92-1.29)
+//      ratio 1.82 to 2.08: 0.77-1.47, median 1.02; 1.3 to 1.82: 0.77-1.27, median 1.01; below: 0.62-1.04; whole
 //  * The other tiles of all heads with the same label form one sequence (head after head,
 //    ascending query tiles); every XCD takes one contiguous eighth of the spatial sequence
 //    and one of the temporal sequence, the one with the longer lists first.  Each XCD so gets
@@ -158,7 +161,7 @@ inline SparseOrder sparse_order(int BH, int nqt, int BM, int off, int video_end,
   // With so many heavy tiles that their parts alone are above the line (see above) whatever the labels say, no workgroups
   // are reserved for parts: idle, they took up to 6 % of the pass (4000 heads of 220 rows 131 -> 140 us, FP8 201 -> 213),
   // and from 2^22 heavy tiles on the grid was too large to launch.
-  so.parts_log2 = 12ll * places > 100ll * BH * so.nh ? parts_log2 : 0;
+  so.parts_log2 = nk >= 12 && 12ll * places > 100ll * BH * so.nh ? parts_log2 : 0;
   so.nk = nk;
   so.places = places;
   return so;
@@ -203,7 +206,8 @@ __device__ __forceinline__ bool sparse_slot(const SparseOrder so, const int BH, 
   part = -1;
   const int nS = BH - nT;
   const long long light = (long long)nS * nnz_s + (long long)nT * nnz_t;
-  const bool split = so.parts_log2 > 0 && 12ll * so.nk * so.places > 25 * (light + 4ll * BH * so.nh * so.nk);
+  const long long longest = (long long)so.nk * so.places, even = light + 4ll * BH * so.nh * so.nk;
+  const bool split = so.parts_log2 > 0 && (5 * longest > 16 * even || (12 * longest > 25 * even && (so.nk - 16ll) * BH * so.nl >= light));
   // (whole heavy tiles leave the workgroups of the other parts at the end of the grid, where they do not come between)
   const int front = split ? so.hmax << so.parts_log2 : so.hmax;
   if (loc < front) {

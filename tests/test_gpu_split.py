@@ -9,7 +9,7 @@ import paper_2502_01776_amd as S
 from oracle import svg_oracle as O
 from workloads import get_config, make_plain_qkv
 from helpers import (f64, gpu_fp8_quantize, gpu_profile, gpu_layer_in_place, gpu_layer_kv2, assert_attn_close, assert_fp8_attn_close,
-                     device_tile_lists, labels_match)
+                     device_tile_lists, labels_match, takes_split_form, DENSE, SPARSE)
 
 pytestmark = pytest.mark.gpu
 
@@ -162,3 +162,22 @@ def test_more_text_tiles_than_a_launch_has_parts_for():
     assert bool(torch.isfinite(o).all())
     for h in (0, 1, heads // 2 - 1, heads // 2, heads - 1):
         assert_attn_close(o[0, h], O.dense_attention_head(*[f64(x[0, h]) for x in (q, k, v)], g), f"head {h}")
+
+
+@pytest.mark.parametrize("D, heads, F, P, T, w_t, parts", [(64, 52, 4, 108, 10, 10, False), (128, 36, 4, 146, 10, 20, False), (64, 26, 4, 336, 104, 30, False),
+                                                           (128, 18, 4, 348, 42, 40, False), (64, 26, 9, 200, 30, 8, True), (128, 2, 5, 2100, 90, 40, True)])
+def test_text_rows_of_short_sequences_are_taken_whole(D, heads, F, P, T, w_t, parts):
+    """Below the line of the parts a text row has the bits of the dense kernel, which walks the same key tiles in the same
+    order; taken in parts it has not."""
+    cfg, sh, g = setup(heads, D, F, P, T, text_first=0, block_m=128, block_n=64)
+    cfg.update(w_s=1, w_t=w_t)
+    sh = S.shape_from_config(cfg)
+    assert not takes_split_form(sh, SPARSE) and not takes_split_form(sh, DENSE)
+    gen = torch.Generator(device="cuda").manual_seed(P)
+    q, k, v = (torch.randn(1, heads, g.N, D, generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    lab = torch.tensor([0, 1] * (heads // 2), dtype=torch.uint8, device="cuda")
+    o, d = run("sparse", sh, q, k, v, lab), run("dense", sh, q, k, v, lab)
+    text = slice(F * P, g.N)
+    assert torch.equal(o[0, ::2, text].view(torch.int16), d[0, ::2, text].view(torch.int16)) == (not parts)
+    assert float((o[0, ::2, text].float() - d[0, ::2, text].float()).abs().max()) <= 2e-2
+
