@@ -1229,7 +1229,7 @@ int launch_attention(const Geo& g, const void* q, const void* k, const void* v, 
   a.labels = labels;
   a.qo_token_order = sparse && qo_token_order ? 1 : 0;
   a.row_ptr[0] = row_ptr_s; a.col_idx[0] = col_idx_s;
-  a.row_ptr[1] = row_ptr_t; a.col_idx[1] = col_idx_t;
+  a.row_ptr[1] = labels ? row_ptr_t : row_ptr_s; a.col_idx[1] = labels ? col_idx_t : col_idx_s;      // (read beside the others, without labels not used)
   if (sparse && row_table) {
     // k and v in token order: build the row table, then the gathering form (the split form needs no table)
     if (element_mask || g.bm != 128) return SVG_ERR_UNSUPPORTED;

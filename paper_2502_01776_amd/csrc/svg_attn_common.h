@@ -182,19 +182,21 @@ __device__ __forceinline__ bool sparse_slot(const SparseOrder so, const int BH, 
                                             const int32_t* rp_s, const int32_t* rp_t, const int xcd, const int loc,
                                             int& bh, int& grp, int& pat, int& cl, int& head_cl0, int& part) {
   const int lane = threadIdx.x & 63;
-  // List tiles of a head's light query tiles, per pattern: asked for before the labels, whose answer they need not wait for.
-  const int nnz_s = so.nl > 0 ? rp_s[so.g_lo + so.nl] - rp_s[so.g_lo] : 0;
-  const int nnz_t = so.nl > 0 && labels != nullptr ? rp_t[so.g_lo + so.nl] - rp_t[so.g_lo] : 0;
   // The labels as bit masks, 64 heads per word (bit = temporal).  Words of their own, not an array: the
   // compiler put an array into LDS (8 KB of it) or scratch memory.
   static_assert(LW == 1 || LW == 4, "one variable per word");
   const bool classed = labels != nullptr && BH <= 64 * LW;
-  auto label_word = [&](int w) -> unsigned long long {
+  auto label = [&](int w) -> int {
     const int h = 64 * w + lane;
-    return classed && 64 * w < BH ? __builtin_amdgcn_ballot_w64(h < BH && labels[h < BH ? h : 0] != 0) : 0ull;
+    return classed && h < BH ? labels[h] : 0;
   };
-  const unsigned long long m0 = label_word(0);
-  const unsigned long long m1 = LW > 1 ? label_word(1) : 0ull, m2 = LW > 1 ? label_word(2) : 0ull, m3 = LW > 1 ? label_word(3) : 0ull;
+  const int l0 = label(0), l1 = LW > 1 ? label(1) : 0, l2 = LW > 1 ? label(2) : 0, l3 = LW > 1 ? label(3) : 0;
+  // List tiles of a head's light query tiles, per pattern, on their way together with the labels: one after the
+  // other they cost the short passes 0.3 us (8-25 us, 1.2 % at the mean of 90 calls).
+  const int nnz_s = rp_s[so.g_lo + so.nl] - rp_s[so.g_lo], nnz_t = rp_t[so.g_lo + so.nl] - rp_t[so.g_lo];
+  const unsigned long long m0 = __builtin_amdgcn_ballot_w64(l0 != 0);
+  const unsigned long long m1 = LW > 1 ? __builtin_amdgcn_ballot_w64(l1 != 0) : 0ull, m2 = LW > 1 ? __builtin_amdgcn_ballot_w64(l2 != 0) : 0ull,
+                           m3 = LW > 1 ? __builtin_amdgcn_ballot_w64(l3 != 0) : 0ull;
   const int nT = __builtin_popcountll(m0) + __builtin_popcountll(m1) + __builtin_popcountll(m2) + __builtin_popcountll(m3);
   auto label_bit = [&](int h) -> int {
     const int w = h >> 6;

@@ -779,7 +779,7 @@ int launch_fp8_attention(const Geo& g, const void* q8, const void* k8, const voi
   a.o = static_cast<__bf16*>(o);
   a.labels = labels;
   a.row_ptr[0] = row_ptr_s; a.col_idx[0] = col_idx_s;
-  a.row_ptr[1] = row_ptr_t; a.col_idx[1] = col_idx_t;
+  a.row_ptr[1] = labels ? row_ptr_t : row_ptr_s; a.col_idx[1] = labels ? col_idx_t : col_idx_s;      // (read beside the others, without labels not used)
   a.N = g.N; a.nk = g.nk; a.BH = g.B * g.H;
   a.nqt = g.nq;
   // (no stride in the dispatch order: this kernel starts the query tiles of a cohort at a common key tile
