@@ -1,6 +1,6 @@
 """Kept-tile lists of every length at which the attention kernels change what they do: none, one and two
 tiles, odd and even numbers, and the ends of the 64 entries that are fetched at a time; with and without a
-ragged last key tile in them."""
+ragged last key tile in them; in the form for few rows and, with more heads, in the general kernels."""
 import numpy as np
 import pytest
 import torch
@@ -9,7 +9,7 @@ import paper_2502_01776_amd as S
 from oracle import svg_oracle as O
 from workloads import get_config, make_plain_qkv
 from helpers import (f64, dev_i32, gpu_fp8_quantize, gpu_layer, gpu_layer_in_place, gpu_layer_kv2, assert_attn_close,
-                     assert_fp8_attn_close)
+                     assert_fp8_attn_close, takes_split_form, takes_fp8_split_form, SPARSE, EXACT, GATHER)
 
 pytestmark = pytest.mark.gpu
 
@@ -32,19 +32,21 @@ def random_lists(nq, nk, last_tile, seed):
 
 @pytest.mark.parametrize("last_tile", [False, True])
 @pytest.mark.parametrize("D, fp8", [(64, False), (128, False), (128, True)])
-def test_list_lengths(D, fp8, last_tile):
-    cfg = dict(get_config("mid128"), B=1, H=1, F=3, P=2812, T=0, D=D, spatial_heads=[0])
+@pytest.mark.parametrize("heads", [1, 3])
+def test_list_lengths(D, fp8, last_tile, heads):
+    cfg = dict(get_config("mid128"), B=1, H=heads, F=3, P=2812, T=0, D=D, spatial_heads=[0])
     cfg["N"] = cfg["F"] * cfg["P"]                      # 8436 = 131 * 64 + 52
     sh, g = S.shape_from_config(cfg), O.Geometry.from_config(cfg)
     nq, nk = S.svg_tile_counts(sh)
     assert nk == 132 and nq >= len(LENGTHS)
+    assert (takes_fp8_split_form(sh) if fp8 else takes_split_form(sh, SPARSE)) == (heads == 1)
     rp, ci = random_lists(nq, nk, last_tile, D + last_tile)
     csr = [dev_i32(rp), dev_i32(ci), dev_i32(rp), dev_i32(ci)]
     # logits that grow along the sequence, so that the reference maximum of the softmax has to follow
     q, k, v = make_plain_qkv(1, 1, g.N, D, seed=D)
     k = (k.float() * torch.linspace(0.2, 3.0, g.N)[None, None, :, None]).bfloat16()
-    qc, kc, vc = q.cuda(), k.cuda(), v.cuda()
-    lab = torch.zeros(1, dtype=torch.uint8, device="cuda")
+    qc, kc, vc = (x.repeat(1, heads, 1, 1).cuda() for x in (q, k, v))
+    lab = torch.zeros(heads, dtype=torch.uint8, device="cuda")
     o = torch.full_like(qc, float("nan"))
     if fp8:
         bufs = gpu_fp8_quantize(sh, qc, kc, vc, lab)
@@ -59,32 +61,36 @@ def test_list_lengths(D, fp8, last_tile):
     for a in tiles:
         rows = slice(a * g.block_m, min(g.N, (a + 1) * g.block_m))
         if LENGTHS[a] == 0:
-            assert (o[0, 0, rows] == 0).all()
+            assert (o[0, :, rows] == 0).all()
         elif fp8:
-            assert_fp8_attn_close(o[0, 0, rows], ref[rows], float(np.abs(vh).max()), f"{LENGTHS[a]} tiles")
+            assert_fp8_attn_close(o[0, heads - 1, rows], ref[rows], float(np.abs(vh).max()), f"{LENGTHS[a]} tiles")
         else:
-            assert_attn_close(o[0, 0, rows], ref[rows], f"{LENGTHS[a]} tiles")
+            assert_attn_close(o[0, heads - 1, rows], ref[rows], f"{LENGTHS[a]} tiles")
 
 
 @pytest.mark.parametrize("last_tile", [False, True])
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("form, blocks", [("gather", (128, 64)), ("exact", (128, 64)), ("exact", (32, 32)), ("plain", (32, 32))])
-def test_list_lengths_of_the_other_forms(form, blocks, D, last_tile):
+@pytest.mark.parametrize("copies", [1, 3])
+def test_list_lengths_of_the_other_forms(form, blocks, D, last_tile, copies):
     """The forms with loops of their own: the gathering one (row numbers fetched a tile ahead of their rows), the one
     under element masks (one tile after the other) and the 32-row ones; a spatial and a temporal head."""
     P = 2812 if blocks[1] == 64 else 1404
-    cfg = dict(get_config("mid128"), B=1, H=2, F=3, P=P, T=0, D=D, w_s=1, w_t=P // 3, spatial_heads=[0],
+    cfg = dict(get_config("mid128"), B=1, H=2 * copies, F=3, P=P, T=0, D=D, w_s=1, w_t=P // 3, spatial_heads=[0],
                block_m=blocks[0], block_n=blocks[1])
     cfg["N"] = cfg["F"] * cfg["P"]                      # 131 full key tiles and a part of one
     sh, g = S.shape_from_config(cfg), O.Geometry.from_config(cfg)
     nq, nk = S.svg_tile_counts(sh)
     assert nk == 132 and nq >= len(LENGTHS) and g.N % blocks[1]
+    # one copy of the two heads is few rows, but for two of the forms with 128-row tiles; three are not
+    split = takes_split_form(sh, {"gather": GATHER, "exact": EXACT, "plain": SPARSE}[form])
+    assert split == (copies == 1 and (blocks[0] == 32 or (form, D) == ("exact", 64)))
     csr = [random_lists(nq, nk, last_tile, 2 * D + 10 * h + last_tile) for h in (0, 1)]
     lists = [dev_i32(x) for rp_ci in csr for x in rp_ci]
     q, k, v = make_plain_qkv(1, 2, g.N, D, seed=D)
     k = (k.float() * torch.linspace(0.2, 3.0, g.N)[None, None, :, None]).bfloat16()
-    qc, kc, vc = q.cuda(), k.cuda(), v.cuda()
-    lab = torch.tensor([0, 1], dtype=torch.uint8, device="cuda")
+    qc, kc, vc = (x.repeat(1, copies, 1, 1).cuda() for x in (q, k, v))
+    lab = torch.tensor([0, 1] * copies, dtype=torch.uint8, device="cuda")
     if form == "gather":
         o, guard_ok = gpu_layer_in_place(sh, qc, kc, vc, lab, lists)
         assert guard_ok
@@ -97,7 +103,7 @@ def test_list_lengths_of_the_other_forms(form, blocks, D, last_tile):
     for h in (0, 1):
         token = in_order if h else np.arange(g.N)       # token of each row of the order the lists refer to
         rp, ci = csr[h]
-        got = f64(o)[0, h][token]
+        got = f64(o[0, 2 * copies - 2 + h])[token]
         for a, n in enumerate(LENGTHS):
             rows = slice(a * g.block_m, min(g.N, (a + 1) * g.block_m))
             cols = np.concatenate([np.arange(b * g.block_n, min(g.N, (b + 1) * g.block_n)) for b in ci[rp[a]:rp[a + 1]]] or

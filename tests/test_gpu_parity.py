@@ -9,7 +9,7 @@ from oracle import svg_oracle as O
 from workloads import get_config, make_qkv, make_plain_qkv, sample_rows, planted_labels
 from helpers import (f64, bits, dev_i32, device_tile_lists, gpu_profile, gpu_layer, gpu_layer_token_order,
                      gpu_layer_kv2, gpu_layer_in_place, assert_attn_close,
-                     labels_match)
+                     labels_match, takes_split_form, DENSE, SPARSE)
 
 pytestmark = pytest.mark.gpu
 
@@ -82,6 +82,20 @@ def test_sparse_attention_per_pattern(name):
 def test_sparse_with_full_list_equals_dense_kernel_bitwise():
     cfg, sh, g = setup("mid128")
     q, k, v = (x.cuda() for x in make_qkv(cfg))
+    rp, ci = O.full_tile_list(g)
+    o1, o2 = torch.zeros_like(q), torch.zeros_like(q)
+    S.svg_sparse_attn_fwd(sh, q, k, v, o1, None, dev_i32(rp), dev_i32(ci), None, None)
+    S.svg_dense_attn_fwd(sh, q, k, v, o2)
+    torch.cuda.synchronize()
+    assert torch.equal(o1.view(torch.int16), o2.view(torch.int16))
+
+
+def test_sparse_with_full_list_equals_the_general_dense_kernel_bitwise():
+    """The same in the kernels of larger calls; without text rows, whose tiles the sparse pass may take in parts."""
+    cfg = dict(get_config("mid128"), H=24, F=7, P=130, T=0, N=910)
+    sh, g = S.shape_from_config(cfg), O.Geometry.from_config(cfg)
+    assert not takes_split_form(sh, DENSE) and not takes_split_form(sh, SPARSE)
+    q, k, v = (x.cuda() for x in make_plain_qkv(1, 24, 910, 128, seed=6))
     rp, ci = O.full_tile_list(g)
     o1, o2 = torch.zeros_like(q), torch.zeros_like(q)
     S.svg_sparse_attn_fwd(sh, q, k, v, o1, None, dev_i32(rp), dev_i32(ci), None, None)

@@ -1,6 +1,6 @@
 """Profiling at the numbers of sampled rows where its route changes: one group of rows (which sorts them
 itself) or several, one error block per head (which writes the label itself) or several, and every number
-of parts the unmasked pass is cut into."""
+of parts the unmasked pass is cut into; in the form for few rows and in the general one."""
 import numpy as np
 import pytest
 import torch
@@ -8,23 +8,25 @@ import torch
 import paper_2502_01776_amd as S
 from oracle import svg_oracle as O
 from workloads import get_config, make_qkv
-from helpers import f64, gpu_profile, labels_match
+from helpers import f64, gpu_profile, labels_match, profile_cuts, takes_split_form, PROFILE
 
 pytestmark = pytest.mark.gpu
 
 
-def check(cfg, t):
+def check(cfg, t, copies=1):
+    """copies: the heads over again, to make them many."""
     cfg["N"] = cfg["F"] * cfg["P"] + cfg["T"]
-    sh, g = S.shape_from_config(cfg), O.Geometry.from_config(cfg)
+    sh, g = S.shape_from_config(dict(cfg, H=cfg["H"] * copies)), O.Geometry.from_config(cfg)
     q, k, v = make_qkv(cfg)
     # unsorted, with text rows and repetitions among them
     rows = np.random.default_rng(t).integers(0, g.N, t).astype(np.int32)
-    qc, kc, vc = q.cuda(), k.cuda(), v.cuda()
+    qc, kc, vc = (x.repeat(1, copies, 1, 1).cuda() for x in (q, k, v))
     labels, mse = gpu_profile(sh, qc, kc, vc, rows)
     omse, olab = O.profile_heads(f64(q), f64(k), f64(v), rows, g)
     # the bounds of the other profiling tests: bf16 rounding of the weights under every measured error
-    assert np.allclose(mse.cpu().numpy().reshape(omse.shape), omse, rtol=0.05, atol=2e-5)
-    assert labels_match(labels, omse, olab)
+    last = slice(-cfg["B"] * cfg["H"], None)
+    assert np.allclose(mse[last].cpu().numpy().reshape(omse.shape), omse, rtol=0.05, atol=2e-5)
+    assert labels_match(labels[last], omse, olab)
     again, mse2 = gpu_profile(sh, qc, kc, vc, rows)
     assert torch.equal(labels, again) and torch.equal(mse, mse2)
     return S.svg_profile_plan(sh, t)
@@ -50,3 +52,30 @@ def test_parts_of_the_unmasked_pass(H, F, P, t, n_full, D):
 def test_cuts_of_the_launch(H, F, P, t, D):
     """Numbers of groups of rows around which the split form cuts its passes otherwise than the plan says."""
     check(dict(get_config("mid64"), D=D, B=1, H=H, F=F, P=P, spatial_heads=[0]), t)
+
+
+@pytest.mark.parametrize("t", [1, 31, 32, 33, 63, 64, 65, 127, 128, 129, 255, 256, 257])
+@pytest.mark.parametrize("blocks, D", [((128, 64), 64), ((128, 64), 128), ((32, 32), 64), ((32, 32), 128)])
+def test_numbers_of_sampled_rows_in_the_general_form(t, blocks, D):
+    """Rows that a workgroup sorts itself (up to two groups) and rows sorted before it."""
+    cfg = dict(get_config("mid64"), D=D, B=1, H=3, spatial_heads=[0, 2], block_m=blocks[0], block_n=blocks[1])
+    copies = 130 // (3 * -(-t // 32)) + 1
+    assert not takes_split_form(S.shape_from_config(dict(cfg, H=3 * copies)), PROFILE, t)
+    check(cfg, t, copies)
+
+
+@pytest.mark.parametrize("H, copies, F, P, t, D, split, cut", [
+    # the split form: the plan's cut, four parts and three, four and two, three and three
+    (8, 1, 9, 400, 60, 64, True, (4, 4)), (6, 1, 5, 1300, 90, 128, True, (4, 3)), (2, 1, 9, 160, 700, 128, True, (4, 3)),
+    (12, 1, 5, 330, 256, 64, True, (4, 2)), (3, 1, 5, 100, 40, 128, True, (3, 3)), (2, 1, 9, 700, 70, 64, True, (6, 4)),
+    # the general form: every number of parts of the unmasked pass, with masked passes whole and cut
+    (2, 2, 70, 20, 40, 64, False, (1, 4)), (2, 2, 70, 14, 40, 128, False, (3, 3)), (2, 80, 5, 140, 40, 128, False, (1, 1)), (2, 2, 70, 30, 150, 128, False, (4, 4)),
+    (2, 80, 5, 330, 40, 64, False, (4, 2)), (4, 1, 9, 700, 700, 128, False, (6, 4)), (2, 260, 5, 330, 40, 64, False, (4, 1)),
+    (2, 100, 9, 700, 40, 64, False, (6, 1))])
+def test_forms_and_cuts(H, copies, F, P, t, D, split, cut):
+    cfg = dict(get_config("mid64"), D=D, B=1, H=H, F=F, P=P, spatial_heads=[0])
+    sh = S.shape_from_config(dict(cfg, H=H * copies))
+    assert takes_split_form(sh, PROFILE, t) == split
+    got = profile_cuts(sh, t)[1]
+    assert (got.n_full, got.n_masked) == cut
+    check(cfg, t, copies)

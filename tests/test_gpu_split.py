@@ -8,8 +8,9 @@ import torch
 import paper_2502_01776_amd as S
 from oracle import svg_oracle as O
 from workloads import get_config, make_plain_qkv
-from helpers import (f64, gpu_fp8_quantize, gpu_profile, gpu_layer_in_place, gpu_layer_kv2, assert_attn_close, assert_fp8_attn_close,
-                     device_tile_lists, labels_match, takes_split_form, DENSE, SPARSE)
+from helpers import (f64, gpu_fp8_quantize, gpu_profile, gpu_layer, gpu_layer_in_place, gpu_layer_kv2, assert_attn_close, assert_fp8_attn_close,
+                     device_tile_lists, labels_match,
+                     takes_split_form, DENSE, GATHER, SPARSE)
 
 pytestmark = pytest.mark.gpu
 
@@ -181,3 +182,19 @@ def test_text_rows_of_short_sequences_are_taken_whole(D, heads, F, P, T, w_t, pa
     assert torch.equal(o[0, ::2, text].view(torch.int16), d[0, ::2, text].view(torch.int16)) == (not parts)
     assert float((o[0, ::2, text].float() - d[0, ::2, text].float()).abs().max()) <= 2e-2
 
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("heads, P, T, w_t, split", [(2, 300, 40, 30, True), (2, 2100, 90, 40, False), (40, 300, 40, 30, False)])
+def test_pipelines_agree_bit_for_bit(D, heads, P, T, w_t, split):
+    """Layout passes, copies of the temporal heads' k and v, and gathering in place: in the split form, with text-row tiles taken
+    in parts and with all tiles taken whole."""
+    cfg, sh, g = setup(heads, D, 5, P, T, text_first=1, block_m=128, block_n=64)
+    cfg["w_t"] = w_t
+    sh = S.shape_from_config(cfg)
+    assert takes_split_form(sh, SPARSE) == takes_split_form(sh, GATHER) == split
+    gen = torch.Generator(device="cuda").manual_seed(P)
+    q, k, v = (torch.randn(1, heads, g.N, D, generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(3))
+    lab = torch.tensor([0, 1] * (heads // 2), dtype=torch.uint8, device="cuda")
+    four = gpu_layer(sh, q, k, v, lab).view(torch.int16)
+    assert torch.equal(four, gpu_layer_kv2(sh, q, k, v, lab)[0].view(torch.int16))
+    assert torch.equal(four, gpu_layer_in_place(sh, q, k, v, lab)[0].view(torch.int16))
