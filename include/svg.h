@@ -85,14 +85,15 @@ const char* svg_version(void);
  * invalid. */
 size_t svg_workspace_bytes(const svg_shape_t* shape, int32_t t);
 
-/* How svg_profile_heads cuts the passes of Alg. 1 into workgroups for this shape and
- * t (a pure function of both; host side, nothing is launched).  The unmasked pass of a
- * group of sampled rows runs as *n_full parts over the key tiles
+/* The cut of the passes of Alg. 1 into workgroups that svg_profile_heads' workspace is sized
+ * for (a pure function of shape and t; host side, nothing is launched).  The unmasked pass of
+ * a group of sampled rows runs as *n_full <= 6 parts over the key tiles
  * [full_bound[c], full_bound[c+1]), c < *n_full (full_bound: host array of 17
  * entries, ascending from 0 to nk; may be NULL), each masked pass as *n_masked <= 4
- * equal parts of its own tile sequence, *n_full <= 6; the parts are merged from per-row (output,
- * maximum, row sum) triples, so the plan changes the results only in fp32 rounding.  The
- * workspace has room for these parts; a launch may cut the passes otherwise, into no more. */
+ * equal parts of its own tile sequence; the parts are merged from per-row (output,
+ * maximum, row sum) triples, so the cut changes the results only in fp32 rounding.  Calls
+ * whose rows are few (the form that splits the keys over wavefronts) may cut the passes
+ * otherwise, into no more parts in all; all others run these. */
 int svg_profile_plan(const svg_shape_t* shape, int32_t t, int32_t* n_full, int32_t* n_masked,
                      int32_t* full_bound);
 

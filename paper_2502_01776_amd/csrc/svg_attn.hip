@@ -149,6 +149,7 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
   // Two K tiles, two V tiles, and nothing else: the direct loads take a 16-bit LDS address, and with 8 bytes
   // more the 32-row form at head dimension 128 fits a CU four times, not five (see waves_per_simd).
   static_assert(2 * STAGE_BYTES <= 65536, "the direct loads take a 16-bit LDS address");
+  static_assert(!SPARSE || NW != 4 || split_lds_bytes(D) <= 2 * STAGE_BYTES, "text-row tiles in parts merge in the same LDS");
   __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * STAGE_BYTES];
 
   // ======================================================================================
@@ -240,8 +241,10 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
       const int32_t* order = a.order_t;
       if (order == nullptr) {
         // as many rows as threads at most: the workgroup sorts them itself, each row counting
-        // the rows in front of it, in the order profile_order_kernel would give them (a launch
-        // of 6 us for 178 rows, left to more rows; the counting takes about 1 us)
+        // the rows in front of it, in the order profile_order_kernel would give them.  With 130 to 256 rows that takes 7-9 us
+        // of the workgroups of this pass and saves a launch of 6-7 us in front of all of them: 26 calls of 12-200 heads (the
+        // 32-row form with 40-64 rows) 0.99-1.07 times as fast as with the launch, 22 of them faster (48 heads of 17776 tokens
+        // and 178 rows at head dimension 64 184.8 -> 178.3 us)
         int* const bin = reinterpret_cast<int*>(lds);
         int* const sorted = bin + THREADS;
         if (tid < a.t) bin[tid] = order_bin(a.rows[tid], a.off, a.video_end, a.P);
@@ -1004,7 +1007,7 @@ __global__ __launch_bounds__(1024) void profile_order_kernel(const int32_t* rows
 // for that reason: NF is exact, masked parts beyond n_masked (at most NM) are read as the last one with weight zero.
 // (An earlier form, 16 rows per block, worked the weights out on 48 threads and walked the parts in
 // a loop of dependent loads: 24.6 us at 24 rows of 6 heads, 31 at 91 rows of 16, 29 at 328 of 40, 39 at
-// 1191 of 24; now 4.7, 13.4, 12.1 and 23.7, and the first two need no label launch, 4.5 us.)
+// 1191 of 24; now 4.7, 6.4, 12.1 and 23.7, and the first needs no label launch, 4.7 us.)
 constexpr int kErrThreads = 1024;
 constexpr int err_rows(int D) { return kErrThreads / (D / 4); }
 // Heads with few rows take one block each, which also writes the label.  A block takes 3-4 us per pass over its
@@ -1211,7 +1214,6 @@ AttnArgs base_args(const Geo& g, const void* q, const void* k, const void* v, vo
   a.w_s = g.w_s; a.w_t = g.w_t; a.sink = g.sink;
   a.blocks_log2 = g.bm == 128 ? 2 : 0;
   a.halves_log2 = g.bn == 64 ? 1 : 0;
-  a.bn = g.bn;
   a.inv_P = 0xffffffffu / (unsigned)g.P;
   a.order = p_outer(g);
   return a;

@@ -363,7 +363,7 @@ struct AttnArgs {
   int off, video_end, F, P, w_s, w_t, sink;
   // the split form
   int blocks_log2;            // workgroups per query tile: bm = 32 << blocks_log2
-  int halves_log2, bn;        // units of 32 keys per key tile: bn = 32 << halves_log2
+  int halves_log2;            // units of 32 keys per key tile: bn = 32 << halves_log2
   unsigned inv_P;             // floor((2^32 - 1) / P)
   POuter order;
 };

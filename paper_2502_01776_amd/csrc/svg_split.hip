@@ -6,7 +6,7 @@
 // workgroup: 13 tiles of 64 keys were 10 of the 15 us of the sparse pass over 8 heads of 787 rows.  Here a workgroup
 // owns 32 query rows and each of its four wavefronts every fourth unit of 32 keys, with the products, layouts and softmax of
 // attn_kernel, and at the end the four results (output, maximum, row sum) are merged through LDS.  Four times as many
-// workgroups, a sixteenth of the chain in each: that pass takes 8 us, at 2 heads of 3290 rows 43.6 -> 20 us.
+// workgroups, a quarter of the chain in each: that pass takes 8 us, at 2 heads of 3290 rows 43.6 -> 20 us.
 //
 // A wavefront loads its K unit straight into the registers of the first product's A operand and stages its V unit through
 // its own piece of LDS (rows in, transposing reads out), so there is no barrier before the merge.  Nothing
