@@ -85,7 +85,11 @@ using namespace attn;
 // ranks swapped): a wavefront that starts a tile is not held up by one that finishes one.
 constexpr int kPrioOutput = 1;
 constexpr int prio_scores(bool sequential) { return sequential ? 2 : 1; }
-constexpr int kCohort = 64;   // dense: consecutive query tiles that share an XCD (and its L2) at a time
+// Dense: the most consecutive query tiles that share an XCD (and its L2) at a time.  Fewer where 64 would not deal the XCDs equal
+// numbers of tiles (launch_one): 186 tiles in 64s use three of the eight XCDs.  Blocks of 64 against equal ones: 186 tiles of 6 heads
+// 114.6 -> 78.9 us at head dimension 128 and 64.3 -> 51.0 at 64, 256 116.9 -> 84.8 and 67.0 -> 55.3, 384 169 -> 148 and 96.7 -> 93.1, 576
+// 393 -> 360 and 244 -> 191, 768 650 -> 540 and 390 -> 300, 2112 1029 -> 1007 and 592 -> 552; multiples of 512 have blocks of 64 as before.
+constexpr int kCohort = 64;
 // LDS operands kept in flight ahead of the products: twelve where the registers allow it (the
 // unmasked passes at head dimension 128; 1.2 % less time than eight, 0.9 % than six), eight in the
 // forms with mask state or row numbers in registers, four at head dimension 64 (three to six measured within 1 %)
@@ -178,12 +182,12 @@ __global__ __launch_bounds__(64 * NW, waves_per_simd(D, NW, MODE)) void attn_ker
     bh = pair / a.nqt;
     grp = pair - bh * a.nqt;
   } else if (MODE == kDense) {
-    // Dense: blocks of kCohort consecutive logical ids go to one XCD, consecutive blocks to
+    // Dense: blocks of up to kCohort consecutive logical ids go to one XCD, consecutive blocks to
     // consecutive XCDs.  An XCD's L2 serves neighbouring query tiles of one head, and at
     // any time all XCDs work on the same one or two heads, whose K/V (61 MB per head at
     // the 120k-token shape) then stay in the memory-side cache in front of HBM; with one
     // head per XCD the dense pass runs into the HBM bandwidth (-11 % time).
-    const int lid = ((loc / kCohort) * 8 + xcd) * kCohort + (loc % kCohort);
+    const int lid = ((loc / a.cohort) * 8 + xcd) * a.cohort + (loc % a.cohort);
     if (lid >= a.total) return;
     bh = lid / a.nqt;
     grp = lid - bh * a.nqt;
@@ -1155,7 +1159,9 @@ int launch_one(AttnArgs a, int rows_total, hipStream_t stream) {
   constexpr int BM = 32 * NW;
   a.nqt = (rows_total + BM - 1) / BM;
   a.total = a.BH * a.nqt;
-  const unsigned per_xcd = (unsigned)((a.total + 8 * kCohort - 1) / (8 * kCohort)) * kCohort;   // dense
+  const int blocks = (a.total + 8 * kCohort - 1) / (8 * kCohort);      // dense: blocks of consecutive tiles per XCD
+  a.cohort = (a.total + 8 * blocks - 1) / (8 * blocks);
+  const unsigned per_xcd = (unsigned)blocks * (unsigned)a.cohort;
   if (MODE == kSparse || MODE == kSparseExact || MODE == kSparseGather) {
     const int slots = 32 * (NW == 4 ? waves_per_simd(D, NW, MODE) : 2);
     a.so = sparse_order(a.BH, a.nqt, BM, a.off, a.video_end, a.N, slots, 8 * slots, NW == 4 ? 2 : 0, a.nk);

@@ -358,6 +358,7 @@ struct AttnArgs {
   int nqt;                    // workgroups per head: query tiles (dense, sparse) or ceil(t / rows per workgroup) (profile)
   SparseOrder so;             // sparse: which workgroup takes which (head, query tile)
   int total;                  // logical workgroups
+  int cohort;                 // dense: consecutive logical workgroups that go to one XCD
   int qo_token_order;         // sparse: q is read and o written in token order also for temporal heads
   float scale_log2;           // softmax scale * log2(e)
   int off, video_end, F, P, w_s, w_t, sink;

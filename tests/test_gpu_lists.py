@@ -132,3 +132,19 @@ def test_fp8_scales_of_heads_around_one_block(P):
         scales = gpu_fp8_quantize(sh, q.cuda(), k.cuda(), v.cuda(), torch.zeros(2, dtype=torch.uint8, device="cuda"))[3]
         want = np.array([[np.abs(f64(x)[0, h]).max() for h in range(2)] for x in (q, k, v)], np.float32) / np.float32(448)
         assert np.array_equal(scales[:6].cpu().numpy().reshape(3, 2), want)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("heads", [21, 63, 64, 65, 127, 129])
+def test_every_dense_query_tile_is_computed(D, heads):
+    """Eight query tiles a head, dealt to the XCDs in blocks of equal size: 512 tiles and fewer in one block each, more in
+    two or three, with and without tiles left over.  All heads hold the same rows, so all outputs have the same bits."""
+    cfg = dict(get_config("mid128"), B=1, H=heads, F=1, P=1000, T=0, D=D, spatial_heads=[0])
+    cfg["N"] = 1000
+    sh, g = S.shape_from_config(cfg), O.Geometry.from_config(cfg)
+    q, k, v = make_plain_qkv(1, 1, g.N, D, seed=D)
+    o = torch.full((1, heads, g.N, D), float("nan"), dtype=torch.bfloat16, device="cuda")
+    S.svg_dense_attn_fwd(sh, *(x.repeat(1, heads, 1, 1).cuda() for x in (q, k, v)), o)
+    torch.cuda.synchronize()
+    assert_attn_close(o[0, 0], O.dense_attention_head(*(f64(x)[0, 0] for x in (q, k, v)), g), "head 0")
+    assert torch.equal(o.view(torch.int16), o[:, :1].expand_as(o).contiguous().view(torch.int16))
