@@ -72,17 +72,20 @@ __device__ __forceinline__ void barrier_loads_done() {
 struct TileList {
   const int32_t* row;
   int len, start, taken, now, ahead;
+  int step, first;      // two teams: every second entry, from this one on
 
   __device__ __forceinline__ int load(int base) const {
-    int i = base + (int)(threadIdx.x & 63);
+    int i = (base + (int)(threadIdx.x & 63)) * step + first;
     if (i >= len) return kNoTile;
     i += start;
     return row[i >= len ? i - len : i];
   }
-  __device__ __forceinline__ void open(const int32_t* row_, int len_, int start_) {
+  __device__ __forceinline__ void open(const int32_t* row_, int len_, int start_, int step_ = 1, int first_ = 0) {
     row = row_;
     len = len_;
     start = start_;
+    step = step_;
+    first = first_;
     taken = 0;
     ahead = load(0);
   }
@@ -373,6 +376,10 @@ struct AttnArgs {
 bool split_form(const Geo& g, int mode, int t);      // does the split form take this call? (t: sampled rows of a profiling call)
 bool split_sorts_rows(int t);                        // profiling: needs no row order from profile_order_kernel
 int launch_split(const Geo& g, AttnArgs a, int mode, hipStream_t stream);
+
+// The form for calls of at most one query tile to a compute unit (svg_teams.hip).
+bool two_teams(const Geo& g);
+int launch_teams(const Geo& g, const AttnArgs& a, int mode, hipStream_t stream);
 
 // Coarse position bin of a sampled row for the temporal profiling pass (text rows first).
 constexpr int kOrderBins = 2048;
