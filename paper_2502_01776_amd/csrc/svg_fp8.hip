@@ -17,18 +17,19 @@
 //                            weights are packed four to a register (E4M3 after scaling by 2^8,
 //                            which puts weights down to 2^-17 of the row maximum inside the
 //                            format's range), and the row sums come out of the matrix unit too:
-//                            a ninth product per tile multiplies the weights with a block of
+//                            a ninth, smaller product per tile multiplies the weights with
 //                            ones, so the denominator is the sum of the ROUNDED weights, the
 //                            result is an exact weighted mean of v rows, and 32 additions per
 //                            lane and tile leave the VALU, which is the busiest unit here.
 //
-// The loop is skewed by one tile: with the scores of tile j in registers, a wavefront takes their
-// exponentials (one long run of VALU work) and then issues the products of tile j + 1's scores
-// and of tile j's output back to back (one long run of matrix work).  The operands of the scores are
-// read from LDS before the exponentials, those of the output behind the products of the scores, and the K and
-// V images come from memory straight into LDS two trips ahead.  At 119k tokens and 15 % of the tiles
-// 13.9 ms; one tile after the other, staged through registers, 15.0 ms on the same box.  The matrix unit is busy
-// 49 % of the cycles, the VALU 63 %.
+// The loop holds the scores of tile j and the weights of tile j - 1: the products of tile j + 1's scores and of tile j - 1's row sums and
+// output are issued one by one with the exponentials of tile j in between, four keys behind each, so that a wavefront covers its
+// own VALU work and two to a SIMD seldom want the same unit.  K and V images come from memory straight into LDS, two tiles to a
+// barrier.  At 119k tokens and 15 % of the tiles 12.81 ms where the form before, exponentials and products in phases of their own, took 13.51, and one
+// barrier a tile 12.95; 7 heads of 8187 rows 119.9 -> 100.4 us, 9 of 3335 43.7 -> 36.0.  Bound by power: 2.67e7 cycles at 1.93 GHz, before
+// 2.88e7 at 2.01; matrix unit 51 % of the cycles, VALU 55 %.  A raised wave priority from the first product to the last: 12.93 ms, and text-row
+// tiles taken in parts, which run beside other workgroups, late (2 heads of 51074 rows 311 -> 334 us).  The maximum of the next tile
+// taken behind its products instead of in front of the exponentials: no difference.
 //
 // The weights of a tile are rounded against the row maximum up to and including that tile, so that the
 // largest weight of a tile that brings a new maximum is a power of two, i.e. exact.  Two tiles to a trip on
@@ -225,6 +226,25 @@ struct Fp8Args {
   POuter order;                // attn_fp8_split_kernel
 };
 
+__device__ __forceinline__ f32x16 product(const i32x8& x, const i32x8& y, const f32x16& z) {
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, z, 0, 0, 0, 0, 0, 0);
+}
+// Row sums of the rounded weights by a 16x16x128 product: half the time and a quarter of the accumulators of a 32x32x64 product
+// with ones.  Its B operand has query lane % 16 in the quarter wavefronts 0 and 2 and query 16 + lane % 16 in 1 and 3; the A
+// operand has ones where the quarter of the column's keys and the quarter that receives the row agree in that, and every
+// lane gets the sum over both halves of its own query's keys, in all four elements.
+__device__ __forceinline__ i32x8 row_sum_operand(int lane) {
+  const int x = ((lane >> 4) & 1) == ((lane >> 2) & 1) ? 0x38383838 : 0;      // E4M3 1.0
+  i32x8 select;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) select[j] = x;
+  asm volatile("" : "+v"(select));
+  return select;
+}
+__device__ __forceinline__ f32x4 row_sum(const i32x8& select, const i32x8& weights, const f32x4& z) {
+  return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(select, weights, z, 0, 0, 0, 0, 0, 0);
+}
+
 // --------------------------------------------------------------------------------------------
 // Attention of calls with few rows: as split_kernel (svg_split.hip), 32 query rows per workgroup, every fourth key tile per
 // wavefront, merged through LDS.  The tiles of k8 and v8t hold whole operands in 16-byte pieces, so both go from
@@ -289,21 +309,14 @@ __device__ __forceinline__ void fp8_split_body(const Fp8Args& a, unsigned char* 
     for (int db = 0; db < 4; ++db) vreg[db] = read32(p + db * 1024 + 16 * sw, p + db * 1024 + 16 * (1 - sw));
   };
 
-  f32x16 oacc[4], lacc, sacc[2];
+  f32x16 oacc[4], sacc[2];
+  f32x4 lacc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    lacc[e] = 0.f;
+  for (int e = 0; e < 16; ++e)
 #pragma unroll
     for (int db = 0; db < 4; ++db) oacc[db][e] = 0.f;
-  }
-  i32x8 ones;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) ones[j] = 0x38383838;
-  asm volatile("" : "+v"(ones));
+  const i32x8 select = row_sum_operand(lane);
   float m_run = kNegBig;
-  auto product = [](const i32x8& x, const i32x8& y, const f32x16& z) -> f32x16 {
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, z, 0, 0, 0, 0, 0, 0);
-  };
   int tile = next_tile();
   if (tile != kNoTile) {
     request_k(tile);
@@ -370,7 +383,7 @@ __device__ __forceinline__ void fp8_split_body(const Fp8Args& a, unsigned char* 
         const int w = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], (int)__float_as_uint(p[0]), false);
         pb[j] = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], w, true);
       }
-      lacc = product(ones, pb, lacc);
+      lacc = row_sum(select, pb, lacc);
 #pragma unroll
       for (int db = 0; db < 4; ++db) oacc[db] = product(vreg[db], pb, oacc[db]);
       if (next != kNoTile) request_v(next);
@@ -532,12 +545,15 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
   // the memory side
   const unsigned lds_wave = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lds_byte*)lds + wave * 1024);
   const int k_src = (tid >> 3) * kD + (((tid & 7) ^ k_swizzle(tid >> 3)) << 4), v_src = tid * 16;
-  auto load_image = [&](const unsigned char* images, int tile, int voffset, unsigned dst) {
-    const u32x4 rsrc = buffer_words(images + (size_t)__builtin_amdgcn_readfirstlane(tile) * kTileBytes, kTileBytes);
+  // (no tile: every address is out of range, nothing is fetched and the unused image reads as zero; a branch around the loads
+  // would cut the trip into blocks, between which the compiler moves the products and exponentials as it likes)
+  auto load_image = [&](const unsigned char* images, int tile_any, int voffset, unsigned dst) {
+    const int tile = __builtin_amdgcn_readfirstlane(tile_any);
+    const u32x4 rsrc = buffer_words(images + (size_t)(tile == kNoTile ? 0 : tile) * kTileBytes, tile == kNoTile ? 0 : kTileBytes);
     load_to_lds(rsrc, voffset, voffset, 0, 4096, dst, 4096);
   };
-  auto load_k = [&](int tile, int j) { load_image(kh, tile, k_src, lds_wave + (j % kStages) * kTileBytes); };
-  auto load_v = [&](int tile, int j) { load_image(vh, tile, v_src, lds_wave + (kStages + j % kStages) * kTileBytes); };
+  auto load_k = [&](int tile, int j) { load_image(kh, tile, k_src, lds_wave + (j & (kStages - 1)) * kTileBytes); };
+  auto load_v = [&](int tile, int j) { load_image(vh, tile, v_src, lds_wave + (kStages + (j & (kStages - 1))) * kTileBytes); };
 
   // ---- operand reads.  K: lane (g, r) reads pieces 4 s + 2 g and 4 s + 2 g + 1 of row r of a
   // 32-key block; V^T: 32 bytes of channel r of a 32-channel block.
@@ -552,163 +568,154 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
     return i32x8{x[0], x[1], x[2], x[3], y[0], y[1], y[2], y[3]};
   };
   auto k_operand = [&](int j, int i) -> i32x8 {              // i = 2 kb + s
-    const unsigned char* p = lds + (j % kStages) * kTileBytes + (i >> 1) * 32 * kD;
+    const unsigned char* p = lds + (j & (kStages - 1)) * kTileBytes + (i >> 1) * 32 * kD;
     const int at = (i & 1) ? k_lo ^ 64 : k_lo;
     return read32(p + at, p + (at ^ 16));
   };
   auto v_operand = [&](int j, int db) -> i32x8 {
-    const unsigned char* p = lds + (kStages + j % kStages) * kTileBytes + db * 1024;
+    const unsigned char* p = lds + (kStages + (j & (kStages - 1))) * kTileBytes + db * 1024;
     return read32(p + v_rd_lo, p + v_rd_hi);
   };
 
-  f32x16 oacc[4], lacc, sacc[2];
+  f32x16 oacc[4], sacc[2][2];      // two sets of scores: a tile's and the next one's
+  f32x4 lacc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int e = 0; e < 16; ++e) {
-    lacc[e] = 0.f;
+  for (int e = 0; e < 16; ++e)
 #pragma unroll
     for (int db = 0; db < 4; ++db) oacc[db][e] = 0.f;
-  }
-  i32x8 ones;          // 32 x E4M3 1.0
-#pragma unroll
-  for (int j = 0; j < 8; ++j) ones[j] = 0x38383838;
-  asm volatile("" : "+v"(ones));
+  const i32x8 select = row_sum_operand(lane);
   float m_run = kNegBig;     // reference maximum of the row, raw logits
   const bool ragged = (a.N % kBN) != 0;
 
-  auto product = [](const i32x8& x, const i32x8& y, const f32x16& z) -> f32x16 {
-    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(x, y, z, 0, 0, 0, 0, 0, 0);
-  };
   // i-th of the four products of S^T = K Q^T: two 32-key blocks x two 64-channel steps
-  auto first_product = [&](const i32x8& k_op, int i) {
+  auto first_product = [&](f32x16 (&sc)[2], const i32x8& k_op, int i) {
     if ((i & 1) == 0) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e) sacc[i >> 1][e] = 0.f;
+      for (int e = 0; e < 16; ++e) sc[i >> 1][e] = 0.f;
     }
-    sacc[i >> 1] = product(k_op, qreg[i & 1], sacc[i >> 1]);
+    sc[i >> 1] = product(k_op, qreg[i & 1], sc[i >> 1]);
   };
-  auto mask_tail = [&](int tile) {       // keys beyond N in the last tile
-    if (!(ragged && tile == a.nk - 1)) return;
-    int lim = a.N - tile * kBN - 4 * g;
+  auto mask_tail = [&](f32x16 (&sc)[2], int tile) {       // keys beyond N in the last tile, and the tile that rounds a list up to an even number
+    if (tile != kNoTile && !(ragged && tile == a.nk - 1)) return;
+    int lim = (tile == kNoTile ? 0 : a.N - tile * kBN) - 4 * g;
     asm volatile("" : "+v"(lim));        // keeps this rarely taken code out of every tile
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int e = 0; e < 16; ++e)
-        if (32 * kb + 8 * (e >> 2) + (e & 3) >= lim) sacc[kb][e] = -INFINITY;
+        if (32 * kb + 8 * (e >> 2) + (e & 3) >= lim) sc[kb][e] = -INFINITY;
   };
-  auto scores = [&](int j, int tile) {   // all four, operands read here, and the mask
-    i32x8 op[4];
+  i32x8 pb[2];
+  float mc = 0.f;
+  auto weights4 = [&](const f32x16 (&sc)[2], i32x8& out, int j) {      // 2^8 exp(s - reference) of four keys
+    float p[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) op[i] = k_operand(j, i);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) first_product(op[i], i);
-    mask_tail(tile);
+    for (int c = 0; c < 4; ++c)
+      p[c] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[j >> 2][4 * (j & 3) + c], c_log2, -mc));
+    // (the first conversion writes the low half of its destination and keeps the rest: giving it
+    // a value that dies here as the "rest" saves a register clear; the second one fills the high half)
+    const int w = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], (int)__float_as_uint(p[0]), false);
+    int packed = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], w, true);
+    asm volatile("" : "+v"(packed));      // here and not where it is used, a trip later
+    out[j] = packed;
   };
-  i32x8 pb;
-  auto weights = [&]() {                 // 2^8 exp(s - reference), four to a register
-    const float mc = m_run * c_log2 - kWeightShift;
+  auto tile_maximum = [&](const f32x16 (&sc)[2]) -> float {
+    float tmax = sc[0][0];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      float p[4];
+    for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, sc[0][e]);
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        p[c] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[j >> 2][4 * (j & 3) + c], c_log2, -mc));
-      // (the first conversion writes the low half of its destination and keeps the rest: giving it
-      // a value that dies here as the "rest" saves a register clear; the second one fills the high half)
-      int w = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], (int)__float_as_uint(p[0]), false);
-      pb[j] = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], w, true);
-    }
-  };
-
-  // ---- main loop.  Trip j holds the scores of tile j; it takes their exponentials, and then issues the
-  // products of tile j + 1's scores and of tile j's output as one batch (see the top of the file).
-  // LDS then holds K of tiles j .. j + 2 and V of j, j + 1, with K of j + 3 and V of j + 2 in flight.
-  int col = list.next(), col1 = list.next(), col2 = list.next();
-  if (col != kNoTile) {
-    load_k(col, 0);
-    load_v(col, 0);
-  }
-  if (col1 != kNoTile) {
-    load_k(col1, 1);
-    load_v(col1, 1);
-  }
-  if (col2 != kNoTile) load_k(col2, 2);
-  wait_loads_to_lds<0>();
-  __syncthreads();
-  asm volatile("" ::"v"(qreg[0]), "v"(qreg[1]));
-  if (col != kNoTile) scores(0, col);
-
-  auto tile_maximum = [&]() -> float {
-    float tmax = sacc[0][0];
-#pragma unroll
-    for (int e = 1; e < 16; ++e) tmax = fmaxf(tmax, sacc[0][e]);
-#pragma unroll
-    for (int e = 0; e < 16; ++e) tmax = fmaxf(tmax, sacc[1][e]);
+    for (int e = 0; e < 16; ++e) tmax = fmaxf(tmax, sc[1][e]);
     return both_halves_max(tmax);
   };
-  auto raise_reference = [&](float tmax) {
-    const float m_new = fmaxf(m_run, tmax);
-    const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c_log2);
-    m_run = m_new;
-    lacc[0] *= alpha;                  // (only this element is ever read)
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
-  };
 
-  // one tile's weights, row sums and output; MORE: and the scores of the next tile.  The loads of the trip are
-  // requested behind its first product: in front of the exponentials a workgroup that has its compute unit
-  // to itself waited for every one of their scalar instructions, behind a product they run beside it.
-  auto trip = [&](auto more_c, int j, auto request_loads) {
-    constexpr bool MORE = decltype(more_c)::value;
-    i32x8 opnd[4];
+  // ---- main loop.  Trip j holds the scores of tile j and the weights of tile j - 1: it takes the exponentials of the former
+  // between the products of tile j + 1's scores and of tile j - 1's row sums and output, a product and four keys at a time.
+  // Trips come in pairs, so that both sets of scores stay in their registers, with one barrier a pair: at its start LDS holds K of tiles
+  // j + 1 and j + 2 and V of j - 1 and j, and the two tiles behind them are on their way into the places of those before.
+  // What lies beyond the list (and in front of it) is a tile of zeros without weight.
+  int col = list.next(), col1 = list.next(), col2 = list.next();
+  if (col != kNoTile) {
+    load_v(kNoTile, 3);
+    load_k(col, 0);
+    load_v(col, 0);
+    load_k(col1, 1);
+    load_k(col2, 2);
+    wait_loads_to_lds<0>();
+    __syncthreads();
+    asm volatile("" ::"v"(qreg[0]), "v"(qreg[1]));
+    i32x8 op[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) opnd[i] = MORE ? k_operand(j + 1, i) : v_operand(j, i);
-    const float tmax = tile_maximum();
-    if (__builtin_amdgcn_ballot_w64(tmax > m_run) != 0) raise_reference(tmax);     // some row of the wavefront has a new maximum
-    weights();
-    __builtin_amdgcn_s_setprio(1);
-    __builtin_amdgcn_sched_barrier(0);
-    lacc = product(ones, pb, lacc);
-    request_loads();
-    if (MORE) {
+    for (int i = 0; i < 4; ++i) op[i] = k_operand(0, i);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        __builtin_amdgcn_sched_barrier(0);
-        first_product(opnd[i], i);
-        __builtin_amdgcn_sched_barrier(0);
-        opnd[i] = v_operand(j, i);
+    for (int i = 0; i < 4; ++i) first_product(sacc[0], op[i], i);
+    mask_tail(sacc[0], col);
+    pb[1] = i32x8{0, 0, 0, 0, 0, 0, 0, 0};
+    __syncthreads();      // the first pair stages K of tile 4 over tile 0's
+    int j = 0, col3 = kNoTile, col4 = kNoTile;
+    auto trip = [&](auto set) {
+      constexpr int CUR = decltype(set)::value;      // which set of scores is tile j's
+      f32x16(&now)[2] = sacc[CUR];
+      f32x16(&next)[2] = sacc[CUR ^ 1];
+      i32x8 opnd[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) opnd[i] = k_operand(j + 1, i);
+      const float tmax = tile_maximum(now);
+      const bool raise = __builtin_amdgcn_ballot_w64(tmax > m_run) != 0;      // some row of the wavefront has a new maximum
+      const float m_new = fmaxf(m_run, tmax);
+      const float alpha = __builtin_amdgcn_exp2f((m_run - m_new) * c_log2);
+      m_run = m_new;
+      mc = m_run * c_log2 - kWeightShift;
+      __builtin_amdgcn_sched_barrier(0);
+      lacc = row_sum(select, pb[CUR ^ 1], lacc);
+      if (CUR == 0) {      // behind a product: in front of it a workgroup alone on its compute unit waited for all their scalar instructions
+        load_k(col3, j + 3);
+        load_v(col1, j + 1);
+        load_k(col4, j + 4);
+        load_v(col2, j + 2);
       }
-    }
-    __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int db = 0; db < 4; ++db) {
-      __builtin_amdgcn_sched_barrier(0);
-      oacc[db] = product(opnd[db], pb, oacc[db]);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    __builtin_amdgcn_s_setprio(0);
-    if (MORE) mask_tail(col1);
-  };
-
-  int j = 0;
-  for (; col1 != kNoTile; ++j) {
-    int col3;
-    trip(std::true_type{}, j, [&]() {
+      for (int n = 0; n < 4; ++n) {
+        const int i = (n >> 1) + 2 * (n & 1);      // the two 32-key blocks in turn
+        first_product(next, opnd[i], i);
+        __builtin_amdgcn_sched_barrier(0);
+        opnd[i] = v_operand(j - 1, i);
+        weights4(now, pb[CUR], n);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        const int db = (n >> 1) + 2 * (n & 1);
+        oacc[db] = product(opnd[db], pb[CUR ^ 1], oacc[db]);
+        __builtin_amdgcn_sched_barrier(0);
+        weights4(now, pb[CUR], 4 + n);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (raise) {
+        lacc[0] *= alpha;                  // (only this element is ever read)
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) oacc[db][e] *= alpha;
+      }
+      mask_tail(next, CUR == 0 ? col1 : col2);
+      ++j;
+    };
+    do {
       col3 = list.next();
-      if (col3 != kNoTile) load_k(col3, j + 3);
-      if (col2 != kNoTile) load_v(col2, j + 2);
-    });
-    // what trip j + 1 reads was requested in trip j - 1: only this trip's four loads may be outstanding
-    if (col3 != kNoTile) wait_loads_to_lds<4>();
-    else wait_loads_to_lds<0>();
-    barrier_loads_done();
-    col = col1;
-    col1 = col2;
-    col2 = col3;
+      col4 = list.next();
+      trip(std::integral_constant<int, 0>{});
+      trip(std::integral_constant<int, 1>{});
+      wait_loads_to_lds<0>();
+      barrier_loads_done();
+      col = col2;
+      col1 = col3;
+      col2 = col4;
+    } while (col != kNoTile);
+    lacc = row_sum(select, pb[1], lacc);
+#pragma unroll
+    for (int db = 0; db < 4; ++db) oacc[db] = product(v_operand(j - 1, db), pb[1], oacc[db]);
   }
-  if (col != kNoTile) trip(std::false_type{}, j, []() {});
 
   // ---- epilogue: oacc[db][4 i + jj] = O[query r][32 db + 8 i + 4 g + jj]; lacc[0] = row sum
   const float l_tot = lacc[0];
