@@ -93,20 +93,26 @@ __device__ __forceinline__ float wave_sum(float x) {      // fixed order: determ
   return x;
 }
 
-template <int D, int NF, int NM>
+// With the unmasked pass in pieces (a.pieces = n_full of them, at most NF) the spatial output is merged from those of the row's window and
+// of the keys that every row keeps.
+struct PieceArgs {
+  ProfilePlan plan;
+  PieceRule rule;
+  int bn;
+};
+
+template <int D, int NF, int NM, bool PIECES>
 __global__ __launch_bounds__(kErrThreads) void profile_error_kernel(const float* ws, const float2* stats, const int32_t* rows,
-                                                                    int BH, int t, int n_masked, float scale_log2, int off,
+                                                                    int BH, int t, int n_full, int n_masked, float scale_log2, int off,
                                                                     int video_end, int rows_per_block, float2* partial,
-                                                                    uint8_t* labels, float* mse) {
+                                                                    uint8_t* labels, float* mse, PieceArgs pieces) {
   constexpr int LANES = D / 4, ROWS = err_rows(D);
   const int bh = blockIdx.y;
   const int row1 = min(t, (int)(blockIdx.x + 1) * rows_per_block);
   const int c = threadIdx.x % LANES;
-  // reassembles one pass from its parts
-  auto merged = [&](auto parts_c, int slot0, int parts, int row) -> f32x4 {
+  // The parts of a pass: loads of all of them, and the pass reassembled from those that `of` names.
+  auto load = [&](auto parts_c, int slot0, int parts, int row, float2* st, f32x4* x) {
     constexpr int PARTS = decltype(parts_c)::value;
-    float2 st[PARTS];
-    f32x4 x[PARTS];
 #pragma unroll
     for (int r = 0; r < PARTS; ++r) {
       const size_t at = ((size_t)(slot0 + min(r, parts - 1)) * BH + bh) * t + row;
@@ -114,14 +120,17 @@ __global__ __launch_bounds__(kErrThreads) void profile_error_kernel(const float*
       x[r] = *reinterpret_cast<const f32x4*>(ws + at * D + 4 * c);
       if (r >= parts) st[r].y = 0.f;
     }
+  };
+  auto merged = [&](auto parts_c, const float2* st, const f32x4* x, auto of) -> f32x4 {
+    constexpr int PARTS = decltype(parts_c)::value;
     float m_max = -3.0e38f;
 #pragma unroll
     for (int r = 0; r < PARTS; ++r)
-      if (st[r].y > 0.f) m_max = fmaxf(m_max, st[r].x);
+      if (of(r) && st[r].y > 0.f) m_max = fmaxf(m_max, st[r].x);
     float w[PARTS], den = 0.f;
 #pragma unroll
     for (int r = 0; r < PARTS; ++r) {
-      w[r] = st[r].y > 0.f ? st[r].y * __builtin_amdgcn_exp2f((st[r].x - m_max) * scale_log2) : 0.f;
+      w[r] = of(r) && st[r].y > 0.f ? st[r].y * __builtin_amdgcn_exp2f((st[r].x - m_max) * scale_log2) : 0.f;
       den += w[r];
     }
     const float inv = den > 0.f ? 1.0f / den : 0.f;
@@ -132,14 +141,33 @@ __global__ __launch_bounds__(kErrThreads) void profile_error_kernel(const float*
       for (int e = 0; e < 4; ++e) o[e] = __builtin_fmaf(w[r] * inv, x[r][e], o[e]);
     return o;
   };
+  const std::integral_constant<int, NF> full_parts;
+  const std::integral_constant<int, NM> masked_parts;
+  auto all = [](int) { return true; };
   float acc_s = 0.f, acc_t = 0.f;
   for (int row0 = blockIdx.x * rows_per_block; row0 < row1; row0 += ROWS) {
     const int own = row0 + (int)threadIdx.x / LANES, row = min(own, t - 1);
     const int n = rows[row];
-    const f32x4 f = merged(std::integral_constant<int, NF>{}, 0, NF, row);
-    const f32x4 os = merged(std::integral_constant<int, NM>{}, NF, n_masked, row);
-    const f32x4 ot = merged(std::integral_constant<int, NM>{}, NF + n_masked, n_masked, row);
-    if (own < row1 && n >= off && n < video_end) {
+    const bool video = n >= off && n < video_end;
+    float2 st[NF], st_m[NM];
+    f32x4 x[NF], x_m[NM];
+    f32x4 f, os;
+    load(full_parts, 0, n_full, row, st, x);
+    if constexpr (PIECES) {
+      load(masked_parts, n_full, n_masked, row, st_m, x_m);
+      int first = 0, last = 0;
+      pieces.rule.window_slots(pieces.plan, video ? (n - off) / pieces.rule.P : 0, pieces.bn, first, last);
+      const int kept = n_full > pieces.plan.n_full + 2 ? n_full - 1 : -1;
+      f = merged(full_parts, st, x, all);
+      os = merged(full_parts, st, x, [&](int r) { return (r >= first && r <= last) || r == kept; });
+    } else {
+      f = merged(full_parts, st, x, all);
+      load(masked_parts, n_full, n_masked, row, st_m, x_m);
+      os = merged(masked_parts, st_m, x_m, all);
+      load(masked_parts, n_full + n_masked, n_masked, row, st_m, x_m);
+    }
+    const f32x4 ot = merged(masked_parts, st_m, x_m, all);
+    if (own < row1 && video) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float ds = f[e] - os[e], dt = f[e] - ot[e];
@@ -185,23 +213,27 @@ inline int error_blocks(int D, int t) {
   return passes <= kErrSinglePasses ? 1 : passes;
 }
 
-template <int D, int NF>
-void launch_error(const AttnArgs& a, const float2* stats, float2* partial, uint8_t* labels, float* mse, hipStream_t stream) {
+template <int D, int NF, bool PIECES>
+void launch_error(const AttnArgs& a, const PieceArgs& pieces, const float2* stats, float2* partial, uint8_t* labels, float* mse, hipStream_t stream) {
   const int blocks = error_blocks(D, a.t);
   const int rows_per_block = blocks == 1 ? a.t : err_rows(D);
-  auto kernel = a.plan.n_masked == 1 ? profile_error_kernel<D, NF, 1> : profile_error_kernel<D, NF, kMaxMaskedParts>;
+  auto kernel = a.plan.n_masked == 1 ? profile_error_kernel<D, NF, 1, PIECES> : profile_error_kernel<D, NF, kMaxMaskedParts, PIECES>;
   hipLaunchKernelGGL(kernel, dim3(blocks, a.BH), dim3(kErrThreads), 0, stream, static_cast<const float*>(a.o), stats, a.rows,
-                     a.BH, a.t, a.plan.n_masked, a.scale_log2, a.off, a.video_end, rows_per_block, partial, labels, mse);
+                     a.BH, a.t, PIECES ? a.pieces : NF, a.plan.n_masked, a.scale_log2, a.off, a.video_end, rows_per_block, partial, labels, mse, pieces);
 }
 
 template <int D>
-int launch_error_parts(const AttnArgs& a, const float2* stats, float2* partial, uint8_t* labels, float* mse, hipStream_t stream) {
+int launch_error_parts(const Geo& g, const AttnArgs& a, const float2* stats, float2* partial, uint8_t* labels, float* mse, hipStream_t stream) {
   (void)hipGetLastError();
-  switch (a.plan.n_full) {      // the numbers of parts profile_plan and profile_cut give the unmasked pass
-    case 1: launch_error<D, 1>(a, stats, partial, labels, mse, stream); break;
-    case 3: launch_error<D, 3>(a, stats, partial, labels, mse, stream); break;
-    case 4: launch_error<D, 4>(a, stats, partial, labels, mse, stream); break;
-    case 6: launch_error<D, 6>(a, stats, partial, labels, mse, stream); break;
+  const PieceArgs pieces = {a.plan, piece_rule(g), g.bn};
+  if (a.pieces > kMaxPieces) return SVG_ERR_UNSUPPORTED;
+  if (a.pieces > 7) launch_error<D, kMaxPieces, true>(a, pieces, stats, partial, labels, mse, stream);
+  else if (a.pieces) launch_error<D, 7, true>(a, pieces, stats, partial, labels, mse, stream);
+  else switch (a.plan.n_full) {      // the numbers of parts profile_plan and profile_cut give the unmasked pass
+    case 1: launch_error<D, 1, false>(a, pieces, stats, partial, labels, mse, stream); break;
+    case 3: launch_error<D, 3, false>(a, pieces, stats, partial, labels, mse, stream); break;
+    case 4: launch_error<D, 4, false>(a, pieces, stats, partial, labels, mse, stream); break;
+    case 6: launch_error<D, 6, false>(a, pieces, stats, partial, labels, mse, stream); break;
     default: return SVG_ERR_UNSUPPORTED;
   }
   int rc = hip_status(hipGetLastError());
@@ -296,11 +328,16 @@ int launch_profile(const Geo& g, const void* q, const void* k, const void* v, co
   a.rows = rows;
   a.t = t;
   // workspace: fp32 outputs [slots][BH][t][D] (parts of the unmasked, the spatial and the
-  // temporal pass), statistics float2 [slots][BH][t], partial error sums float2
+  // temporal pass, or pieces of the unmasked and parts of the temporal one), statistics float2 [slots][BH][t], partial error sums float2
   // [BH][ceil(t/16)], row order int32 [t]
   const bool split = split_form(g, kProfile, t);
   a.plan = profile_cut(g, t, profile_plan(g, t), split);
-  const int ns = a.plan.slots();
+  int ns = a.plan.slots();
+  ProfilePlan cut;
+  if (!split && (a.pieces = profile_pieces(g, t, a.plan, &cut)) != 0) {
+    a.plan = cut;
+    ns = a.pieces + cut.n_masked;
+  }
   const int groups = (t + g.bm - 1) / g.bm;
   a.rows_per_group = (t + groups - 1) / groups;
   const size_t out_floats = (size_t)ns * a.BH * t * g.D;
@@ -319,8 +356,8 @@ int launch_profile(const Geo& g, const void* q, const void* k, const void* v, co
   }
   const int rc = dispatch<kProfile>(g, a, t, stream);
   if (rc != SVG_OK) return rc;
-  return g.D == 128 ? launch_error_parts<128>(a, stats, partial, labels, mse, stream)
-                    : launch_error_parts<64>(a, stats, partial, labels, mse, stream);
+  return g.D == 128 ? launch_error_parts<128>(g, a, stats, partial, labels, mse, stream)
+                    : launch_error_parts<64>(g, a, stats, partial, labels, mse, stream);
 }
 
 }  // namespace svg

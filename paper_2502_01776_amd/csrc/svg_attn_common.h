@@ -355,6 +355,7 @@ struct AttnArgs {
   const int32_t* order_t;     // profile: indices into rows[], grouped by in-frame position (temporal variant); null: few rows, which the workgroups sort themselves
   int t;                      // profile: number of sampled rows
   ProfilePlan plan;           // profile: parts of the unmasked pass and of the masked passes
+  int pieces;                 // profile: output slots of the unmasked pass where it runs in pieces and stands for the spatial pass too, or 0
   int rows_per_group;         // profile: sampled rows per workgroup (the groups are balanced)
   float2* stats;              // profile: (reference maximum, row sum) per (output slot, head, row)
   int N, nk, BH;
@@ -423,6 +424,16 @@ __device__ __forceinline__ int quad_rows_min(int x) {
   x = min(x, __builtin_amdgcn_mov_dpp(x, 0x122, 0xf, 0xf, true));
   x = min(x, __builtin_amdgcn_mov_dpp(x, 0x121, 0xf, 0xf, true));
   return __builtin_amdgcn_readfirstlane(x);
+}
+
+// Minimum over the wavefront.
+__device__ __forceinline__ int wave_min(int x) {
+  x = min(x, __builtin_amdgcn_mov_dpp(x, 0x128, 0xf, 0xf, true));
+  x = min(x, __builtin_amdgcn_mov_dpp(x, 0x124, 0xf, 0xf, true));
+  x = min(x, __builtin_amdgcn_mov_dpp(x, 0x122, 0xf, 0xf, true));
+  x = min(x, __builtin_amdgcn_mov_dpp(x, 0x121, 0xf, 0xf, true));
+  return min(min(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)),
+             min(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
 }
 
 }  // namespace attn

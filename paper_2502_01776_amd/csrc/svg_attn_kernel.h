@@ -178,12 +178,12 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
     const int pairs_per_xcd = (pairs + 7) >> 3;
     const int unit = loc / pairs_per_xcd;
     const int pair = xcd * pairs_per_xcd + (loc - unit * pairs_per_xcd);
-    const int nm = a.plan.n_masked;
-    if (unit >= a.plan.slots() || pair >= pairs) return;
+    const int nm = a.plan.n_masked, ns = a.pieces ? 0 : nm;      // parts of the temporal and of the spatial pass
+    if (unit >= ns + nm + a.plan.n_full || pair >= pairs) return;
     // the masked passes first: their workgroups are the longest ones (mask work on top of
     // about as many tiles), so they should not be the last to start
-    variant = unit < nm ? 1 : unit < 2 * nm ? 2 : 0;         // 0 unmasked, 1 spatial, 2 temporal
-    chunk = unit < nm ? unit : unit < 2 * nm ? unit - nm : unit - 2 * nm;    // which part of its pass
+    variant = unit < ns ? 1 : unit < ns + nm ? 2 : 0;         // 0 unmasked, 1 spatial, 2 temporal
+    chunk = unit < ns ? unit : unit < ns + nm ? unit - ns : unit - ns - nm;    // which part of its pass
     bh = pair / a.nqt;
     grp = pair - bh * a.nqt;
   } else if (MODE == kDense) {
@@ -309,6 +309,24 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
     win_lo[qb] = 0;
     win_hi[qb] = by_position ? a.P : a.N;
   }
+  // Unmasked pass in pieces (PieceRule): the frames of a lane's rows, and of two of the workgroup's rows per lane, from which every
+  // wavefront finds the next key at which a piece of any of them ends.  Two to a register (P is at least 128, so frame numbers stay below 2^15), as the
+  // register budget is full; -1: a text row, which has no part in the errors.
+  const bool pieces = MODE == kProfile && a.pieces && variant == 0;
+  const PieceRule rule = {a.off, a.video_end, keep_head, a.F, a.P, a.w_s};
+  int own_frames = -1, cut_frames = -1;
+  if (pieces) {
+    auto frame = [&](int n) { return n >= a.off && n < a.video_end ? (n - a.off) / a.P : -1; };
+    auto group_row = [&](int i) { return a.rows[min(grp * a.rows_per_group + min(i, a.rows_per_group - 1), a.t - 1)]; };
+    own_frames = (frame(qrow[0]) & 0xffff) | (frame(qrow[1]) << 16);
+    cut_frames = (frame(group_row(lane)) & 0xffff) | (frame(group_row(min(lane + 64, BM - 1))) << 16);
+  }
+  // keeps what is worked out from the value at the rare place that needs it, out of the registers of the loop
+  auto opaque = [](int x) -> int {
+    asm volatile("" : "+v"(x));
+    return x;
+  };
+  auto frame_of = [](int frames, int i) { return i ? frames >> 16 : (int)(short)frames; };
   int c_lo = 0x7fffffff, c_hi = -1;      // profile: smallest and largest coordinate of the workgroup's rows
   if (MODE == kProfile && masked) {
 #pragma unroll
@@ -432,12 +450,6 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   }
   int pseg = 0, pj = 0, pjb = -1;
   auto profile_segment = [&](int sidx, int& k0, int& k1) -> bool {   // false: no more segments
-    if (variant == 0) {      // unmasked pass: the key tiles of part chunk
-      const int t0 = a.plan.full_bound[chunk], t1 = a.plan.full_bound[chunk + 1];
-      k0 = t0 * BN;
-      k1 = min(a.N, t1 * BN) - 1;
-      return sidx == 0;
-    }
     const int nv = variant == 1 ? 1 : a.F;
     if (sidx == 0) {            // text prefix
       k0 = 0;
@@ -481,6 +493,55 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
     }
     return true;
   };
+  // Unmasked pass: a visit is up to BN keys from any key on.  Packed: first key << 8, bit 7 where a piece may end (kCut), number
+  // of keys.  In one run over the keys of the part, or in pieces: the part's video keys, cut where a piece of any row ends, and
+  // behind the last part's the keys every row keeps.
+  constexpr int kCut = 128;
+  int v_key = 0, v_end = 0, v_last = 0, v_region = 2;      // next key, end of the piece and of the part's (video) keys
+  bool v_cut = pieces;
+  if (MODE == kProfile && variant == 0) {
+    v_key = v_end = pieces ? rule.bound(a.plan, chunk, BN) : min(a.N, a.plan.full_bound[chunk] * BN);
+    v_last = pieces ? rule.bound(a.plan, chunk + 1, BN) : min(a.N, a.plan.full_bound[chunk + 1] * BN);
+    if (pieces && chunk == a.plan.n_full - 1) v_region = 0;
+  }
+  auto next_cut = [&](int key) -> int {
+    int c = v_last;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int f = frame_of(opaque(cut_frames), i);
+      int lo, hi;
+      rule.window(f, lo, hi);
+      if (f >= 0 && lo > key) c = min(c, lo);
+      if (f >= 0 && hi > key) c = min(c, hi);
+    }
+    return wave_min(c);
+  };
+  auto next_visit = [&]() -> int {
+    while (v_key >= v_end) {
+      if (v_end < v_last) {
+        v_end = pieces ? next_cut(v_key) : v_last;
+        v_cut = pieces;
+      } else if (v_region == 0) {
+        v_region = 1;
+        v_cut = true;
+        v_key = 0;
+        v_end = v_last = keep_head;
+      } else if (v_region == 1) {
+        v_region = 2;
+        v_cut = v_cut || keep_head == 0;
+        v_key = a.video_end;
+        v_end = v_last = a.N;
+      } else {
+        return kNoTile;
+      }
+    }
+    const int n = min(BN, v_end - v_key);
+    const int visit = (v_key << 8) | (v_cut ? kCut : 0) | n;
+    v_cut = false;
+    v_key += n;
+    return visit;
+  };
+  auto visit_key = [](int visit) { return visit >> 8; };
   auto next_tile = [&]() -> int {
     if (SPARSE) return list.next();
     if (MODE == kDense) {
@@ -489,10 +550,11 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
       lj = j + TEAMS;
       return j;
     }
-    if (pleft <= 0) return kNoTile;     // profile
+    if (variant == 0) return next_visit();      // profile
+    if (pleft <= 0) return kNoTile;
     if (!profile_interval()) return kNoTile;
     --pleft;
-    return pj++;
+    return (pj++ * BN) << 8;
   };
   if (MODE == kProfile && variant != 0 && a.plan.n_masked > 1) {
     // a masked pass in parts: count the tiles of the whole pass, then take the part's share
@@ -573,7 +635,8 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
                     dst + i * THREADS * 16, THREADS * 16);
     } else {
       // the tile index is the same in every lane; saying so keeps the descriptors scalar
-      const int key0 = __builtin_amdgcn_readfirstlane(col_any) * BN;
+      const int col_one = __builtin_amdgcn_readfirstlane(col_any);
+      const int key0 = MODE == kProfile ? visit_key(col_one) : col_one * BN;
       const u32x4 rsrc = buffer_words(src + (size_t)key0 * D, (unsigned)(a.N - key0) * (D * 2));
 #pragma unroll
       for (int i = 0; i < PER_THREAD; i += 2) {
@@ -714,8 +777,8 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
             }
         }
       }
-    } else if (ragged && tile == a.nk - 1) {
-      int lim = a.N - tile * BN - 4 * g;     // keys with 16 kb + i >= lim are out of range
+    } else if (MODE == kProfile ? (tile & (kCut - 1)) != BN : ragged && tile == a.nk - 1) {
+      int lim = (MODE == kProfile ? tile & (kCut - 1) : a.N - tile * BN) - 4 * g;     // keys with 16 kb + i >= lim are out of range
       // opaque to the optimiser: keeps this rarely taken masking code inside the
       // branch instead of being speculated into every tile
       asm volatile("" : "+v"(lim));
@@ -796,6 +859,51 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
     }
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) l_run[qb] += l_loc[qb];
+  };
+
+  // Profiling: one pass's or piece's output of a row (normalised), reference maximum and row sum, to an output slot.
+  auto put = [&](int qb, int slot, float l_tot) {
+    const size_t at = ((size_t)slot * a.BH + bh) * a.t + opaque(qslot[qb]);
+    float* op = static_cast<float*>(a.o) + at * D;
+    if (g == 0) a.stats[at] = make_float2(m_run[qb], l_tot);
+    const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<f32x4*>(op + cb * 16 + 4 * g) = oacc[cb][qb] * inv;
+  };
+  auto start_again = [&](int qb) {      // a piece owes nothing to the ones before it, the reference maximum neither
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) oacc[cb][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m_run[qb] = kNegBig;
+    l_run[qb] = 0.f;
+  };
+  auto cuts_before = [&](int qb, int key) -> int {
+    const int f = frame_of(opaque(own_frames), qb);
+    int lo, hi;
+    rule.window(f, lo, hi);
+    return f < 0 ? 0 : (lo < key) + (hi < key);
+  };
+  // Ends of pieces in front of a key (see PieceRule).  `close`: of all pieces of the video keys.
+  auto end_pieces = [&](int key, bool close) {
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      int at = cuts_before(qb, key);
+      const int to = close ? 3 : cuts_before(qb, key + 1);
+      float l_tot = quarters_sum(l_run[qb]);
+      if (at < to) {
+        for (; at < to; ++at) {
+          if (qslot[qb] < a.t) put(qb, chunk + at, l_tot);
+          start_again(qb);
+          l_tot = 0.f;
+        }
+      }
+    }
+  };
+  auto cut_before = [&](int visit) {
+    if (MODE == kProfile && (visit & kCut) != 0) {
+      const int key = visit_key(visit);
+      const bool kept = key < keep_head || key >= a.video_end;
+      end_pieces(kept ? a.video_end : key, kept);
+    }
   };
 
   // The products.  Operand reads run PF operands ahead of their use (a rolling window of PF operand
@@ -883,7 +991,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
         load_v(col1, rows_k, buf ^ 1);
       }
       col2 = next_tile();
-      const TileMask t = tile_mask(col);
+      const TileMask t = tile_mask(MODE == kProfile ? visit_key(col) / BN : col);
       if (!t.skip) {
         read_k_ahead(buf);
         scores(buf, yes, buf);
@@ -916,6 +1024,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
         rows_v = rows_k;
         if (col3 != kNoTile) rows_k = load_table(col3);
       }
+      cut_before(col);
       read_k_ahead(buf ^ 1);
       softmax(no_drop);
       scores(buf ^ 1, yes, buf);
@@ -930,6 +1039,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
     }
     if (TEAMS > 1 && team == 1 && (n_tiles & 1) && n_tiles > 1) barrier_loads_done();      // the other team's last trip
     if (col != kNoTile) {
+      cut_before(col);
 #pragma unroll
       for (int i = 0; i < PF; ++i) opnd[i] = v_operand(buf, i);
       softmax(no_drop);
@@ -973,19 +1083,23 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   // ======================================================================================
   // Epilogue: normalise and store.  oacc[cb][qb][i] = O[query 16 qb + r][16 cb + 4 g + i]
   // ======================================================================================
+  if (MODE == kProfile && pieces && chunk == a.plan.n_full - 1 && a.pieces == a.plan.n_full + 2) {
+    end_pieces(a.video_end, true);      // no keys that every row keeps: the video keys were the last
+    return;
+  }
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const float l_tot = quarters_sum(l_run[qb]);
     const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
     if (MODE == kProfile) {
-      if (qslot[qb] < a.t) {
-        // output slots: the parts of the unmasked pass, of the spatial pass, of the temporal pass
-        const int slot = variant == 0 ? chunk : a.plan.n_full + (variant - 1) * a.plan.n_masked + chunk;
-        float* op = static_cast<float*>(a.o) + (((size_t)slot * a.BH + bh) * a.t + qslot[qb]) * D;
-        if (g == 0) a.stats[((size_t)slot * a.BH + bh) * a.t + qslot[qb]] = make_float2(m_run[qb], l_tot);
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb) *reinterpret_cast<f32x4*>(op + cb * 16 + 4 * g) = oacc[cb][qb] * inv;
+      // output slots: the parts or pieces of the unmasked pass, the parts of the spatial pass, of the temporal pass
+      int slot = variant == 0 ? chunk : a.plan.n_full + (variant - 1) * a.plan.n_masked + chunk;
+      if (a.pieces) {
+        if (variant != 0) slot = a.pieces + chunk;
+        else if (chunk == a.plan.n_full - 1) slot = a.pieces - 1;
+        else slot += cuts_before(qb, v_last);
       }
+      if (qslot[qb] < a.t) put(qb, slot, l_tot);
     } else if (qslot[qb] < a.N) {
       __bf16* op = static_cast<__bf16*>(a.o) + (head + io_row[qb]) * D;
 #pragma unroll
@@ -1009,7 +1123,7 @@ int launch_one(AttnArgs a, int rows_total, hipStream_t stream) {
     const int per_cu = NW == 4 ? waves_per_simd(D, NW, MODE) : 2;
     a.so = sparse_order(a.BH, a.nqt, BM, a.off, a.video_end, a.N, TEAMS > 1 ? 32 : 32 * per_cu, 256 * per_cu, NW == 4 ? 2 : 0, a.nk);
   }
-  const unsigned grid = MODE == kProfile ? (unsigned)(8 * a.plan.slots() * ((a.total + 7) / 8))
+  const unsigned grid = MODE == kProfile ? (unsigned)(8 * (a.plan.slots() - (a.pieces ? a.plan.n_masked : 0)) * ((a.total + 7) / 8))
                         : MODE == kDense ? 8u * per_xcd : sparse_grid(a.so, a.BH);
   (void)hipGetLastError();   // drop any stale error left by earlier runtime calls of the process
   constexpr bool SPARSE_MODE = MODE == kSparse || MODE == kSparseExact || MODE == kSparseGather;

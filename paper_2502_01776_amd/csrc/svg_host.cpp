@@ -78,7 +78,7 @@ ProfilePlan profile_plan(const Geo& g, int t) {
 //    0.81-1.08, six 0.88-1.26, median 1.06 (48 groups of 9086 rows 72.8 -> 61.4 us); 64 four to seven 0.80-1.07, median 0.93, nine 1.06-1.15,
 //    ten 0.83-1.09, twelve 0.92-1.16.
 //    Where the unmasked pass is not cut, three parts of each pass: 4 heads of 272 rows 9.5 -> 9.0, 24 of 820 12.9 -> 12.1.
-// The general form keeps the plan's cut.  (Eight parts of the unmasked pass and three of the masked ones for few heads with many
+// The general form keeps the plan's cut, or runs the unmasked pass in pieces (below).  (Three passes, eight parts of the unmasked pass and three of the masked ones for few heads with many
 // groups of rows, whose windows are narrow only where the caller sorts the rows: 60 calls of 1-14 heads, 6200-120000 keys and 641-2400 rows
 // ran at 0.76-1.08 of the plan's speed with rows in random order, median 0.80, and at 0.80-1.21 with sorted ones.)
 ProfilePlan profile_cut(const Geo& g, int t, const ProfilePlan& plan, bool split) {
@@ -95,6 +95,33 @@ ProfilePlan profile_cut(const Geo& g, int t, const ProfilePlan& plan, bool split
   auto helps = [&](int places) { return 10 * plan.slots() * per_xcd > 11 * places && cut.slots() * per_xcd <= places; };
   // all places of an XCD, or at head dimension 128, where two workgroups of a CU get in each other's way, one to a CU
   return helps(g.D == 64 ? kSlots * 3 / 2 : kSlots) || (g.D == 128 && helps(kSlots / 2)) ? cut : plan;
+}
+
+// The unmasked pass in pieces, for the general form.  What it saves is the spatial pass, about (2 w_s + 1 + frames of a group's rows) / F of
+// an unmasked one, all of it where the caller's rows come in no order; what it costs is a visit of a few keys, and a piece's store, at every frame
+// boundary where a window of the group ends.  Frames of at least four key tiles, and sequences from 24 tiles on, keep that small.  Profiling, three
+// passes against pieces, rows in ascending and in random order: 48 heads of 17776 tokens at head dimension 64 186 -> 138 and 208 -> 139 us, 48 of
+// 45104 636 -> 458 and 901 -> 462, at 128 40 of 32760 583 -> 427 and 856 -> 419, 24 of 119056 2865 -> 2558 and 4226 -> 2619, 3 of them
+// 505 -> 450 and 762 -> 452.
+// The temporal pass has the plan's parts, which leave its places to two masked passes, except that
+//  * at head dimension 128 one less of three or four is better (11 groups of rows to an XCD and fewer: 485 -> 450 us with four and three
+//    parts, 293 -> 279 with three and two) and leaves room for eight parts of the unmasked pass where the groups are fewest;
+//  * two are better than one where the groups are just too many for the plan to cut it and it visits more than a third of the keys
+//    (471 -> 427 us at 40 heads of 32760 tokens and 328 rows, 296 -> 264 at 96 of 17776 and 178; with 0.28 of the keys 458 -> 485).
+int profile_pieces(const Geo& g, int t, const ProfilePlan& plan, ProfilePlan* cut) {
+  const int kept = g.T > 0 || g.sink ? 1 : 0;
+  const int room = plan.slots() - 2 - kept;      // parts of both passes the workspace holds beside the two cuts and the kept keys
+  if (g.nk < 24 || g.P < 4 * g.bn || room < 2) return 0;
+  const int groups = (t + g.bm - 1) / g.bm;
+  const long long pairs_x = ((long long)g.B * g.H * groups + 7) / 8;
+  *cut = plan;
+  if (g.D == 128 && plan.n_masked >= 3) --cut->n_masked;
+  const long long reach = 2ll * g.w_t + g.bn + g.P / groups;      // positions of a frame the temporal pass visits
+  if (plan.n_masked == 1 && room >= 5 && 4 * pairs_x <= (g.D == 64 ? kSlots * 3 / 2 : kSlots) && 3 * reach > g.P) cut->n_masked = 2;
+  const int most = g.D == 128 && plan.n_masked == 4 ? 8 : 6;
+  const int n_full = std::min(room - cut->n_masked, most), n_small = n_full >= 3 ? 2 : 0;
+  fill_bounds(cut, n_full - n_small, n_small, g.nk);
+  return n_full + 2 + kept;
 }
 
 int make_geo(const svg_shape_t* s, Geo* g) {

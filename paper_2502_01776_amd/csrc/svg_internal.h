@@ -39,6 +39,43 @@ struct ProfilePlan {
 ProfilePlan profile_plan(const Geo& g, int t);
 ProfilePlan profile_cut(const Geo& g, int t, const ProfilePlan& plan, bool split);      // never more slots than the plan
 
+// The unmasked pass in pieces, which makes the spatial pass unnecessary: in F-outer order the video keys a video query keeps under
+// the spatial mask are one run, so its masked output is the unmasked one over a part of the keys.  A row's video keys from
+// keep_head on (the text prefix and the first-frame sink lie in front) are cut where its window begins and ends, on top of the parts, and each piece has an output
+// of its own: the piece of part c behind b of the two cuts is in slot c + b, so there are n_full + 2, and one more where there are keys that
+// every row keeps.  The parts are walked in the order of the keys; the keys that every row keeps come last, in the last part.
+struct PieceRule {
+  int off, video_end, keep_head, F, P, w_s;
+  // start of part c in keys (of part n_full: the end of the last one)
+  __host__ __device__ int bound(const ProfilePlan& plan, int c, int bn) const {
+    if (c == 0) return keep_head;
+    if (c >= plan.n_full) return video_end;
+    const int b = plan.full_bound[c] * bn;
+    return b < keep_head ? keep_head : b > video_end ? video_end : b;
+  }
+  // the window [lo, hi) of a query of frame f
+  __host__ __device__ void window(int f, int& lo, int& hi) const {
+    lo = off + (f > w_s ? f - w_s : 0) * P;
+    hi = off + (f + w_s + 1 < F ? f + w_s + 1 : F) * P;
+    lo = lo > keep_head ? lo : keep_head;
+    hi = hi > keep_head ? hi : keep_head;
+  }
+  // the first and the last slot of the window's pieces
+  __host__ __device__ void window_slots(const ProfilePlan& plan, int f, int bn, int& first, int& last) const {
+    int lo, hi;
+    window(f, lo, hi);
+    first = last = 1;
+    for (int c = 1; c < plan.n_full; ++c) {
+      first += bound(plan, c, bn) <= lo;
+      last += bound(plan, c, bn) <= hi;
+    }
+  }
+};
+inline PieceRule piece_rule(const Geo& g) { return {g.off, g.video_end, g.off + (g.sink ? g.P : 0), g.F, g.P, g.w_s}; }
+// The cut of a call that runs the unmasked pass in pieces, and its number of output slots; 0: it does not.
+int profile_pieces(const Geo& g, int t, const ProfilePlan& plan, ProfilePlan* cut);
+constexpr int kMaxPieces = 11;
+
 // Bytes of workspace svg_profile_heads uses for t rows: fp32 outputs [slots][BH][t][D], float2
 // (maximum, row sum) [slots][BH][t], partial error sums float2 [BH][ceil(t/16)], row order int32 [t].
 inline size_t profile_workspace_bytes(const Geo& g, int t) {

@@ -223,3 +223,11 @@ def profile_cuts(shape, t):
     plan = _rule("_ZN3svg12profile_planERKNS_3GeoEi", Plan, C.byref(g), C.c_int(t))
     split = C.c_bool(takes_split_form(shape, PROFILE, t))
     return plan, _rule("_ZN3svg11profile_cutERKNS_3GeoEiRKNS_11ProfilePlanEb", Plan, C.byref(g), C.c_int(t), C.byref(plan), split)
+
+
+def profile_pieces(shape, t):
+    """(output slots of the unmasked pass in pieces or 0, the cut such a launch takes)"""
+    g, cut = _geo(shape), Plan()
+    plan = profile_cuts(shape, t)[0]
+    n = _rule("_ZN3svg14profile_piecesERKNS_3GeoEiRKNS_11ProfilePlanEPS3_", C.c_int, C.byref(g), C.c_int(t), C.byref(plan), C.byref(cut))
+    return (0, None) if takes_split_form(shape, PROFILE, t) else (n, cut)

@@ -8,16 +8,16 @@ import torch
 import paper_2502_01776_amd as S
 from oracle import svg_oracle as O
 from workloads import get_config, make_qkv
-from helpers import f64, gpu_profile, labels_match, profile_cuts, takes_split_form, PROFILE
+from helpers import f64, gpu_profile, labels_match, profile_cuts, profile_pieces, takes_split_form, PROFILE
 
 pytestmark = pytest.mark.gpu
 
 
-def check(cfg, t, copies=1):
+def check(cfg, t, copies=1, qkv=None):
     """copies: the heads over again, to make them many."""
     cfg["N"] = cfg["F"] * cfg["P"] + cfg["T"]
     sh, g = S.shape_from_config(dict(cfg, H=cfg["H"] * copies)), O.Geometry.from_config(cfg)
-    q, k, v = make_qkv(cfg)
+    q, k, v = qkv or make_qkv(cfg)
     # unsorted, with text rows and repetitions among them
     rows = np.random.default_rng(t).integers(0, g.N, t).astype(np.int32)
     qc, kc, vc = (x.repeat(1, copies, 1, 1).cuda() for x in (q, k, v))
@@ -79,3 +79,30 @@ def test_forms_and_cuts(H, copies, F, P, t, D, split, cut):
     got = profile_cuts(sh, t)[1]
     assert (got.n_full, got.n_masked) == cut
     check(cfg, t, copies)
+
+
+PIECES = dict(get_config("mid64"), B=1, H=2, spatial_heads=[0])
+
+
+@pytest.mark.parametrize("F, P, T, text_first, sink, w_s", [
+    (6, 256, 0, 0, 0, 1), (6, 257, 37, 1, 0, 0), (6, 320, 64, 0, 0, 1), (5, 333, 50, 0, 1, 1), (5, 320, 64, 1, 1, 9),
+    (1, 1600, 0, 0, 0, 0), (1, 1600, 20, 1, 1, 0), (2, 800, 0, 0, 1, 0), (4, 300, 900, 1, 0, 1), (4, 300, 900, 0, 0, 1)])
+@pytest.mark.parametrize("blocks, D, t, copies", [((128, 64), 64, 70, 50), ((128, 64), 128, 129, 20), ((32, 32), 64, 33, 60), ((32, 32), 128, 40, 300)])
+def test_unmasked_pass_in_pieces(F, P, T, text_first, sink, w_s, blocks, D, t, copies):
+    """Windows that end inside key tiles, at their edges, at the ends of the video and of the parts; parts without a video key."""
+    cfg = dict(PIECES, D=D, F=F, P=P, T=T, text_first=text_first, sink_first_frame=sink, w_s=w_s, block_m=blocks[0], block_n=blocks[1])
+    cfg["N"] = F * P + T
+    assert profile_pieces(S.shape_from_config(dict(cfg, H=2 * copies)), t)[0] > 0
+    check(cfg, t, copies)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_a_window_far_below_the_rest_of_its_row(D):
+    """Every other row's window holds logits 200 below those outside it: its output must not depend on them."""
+    cfg = dict(PIECES, D=D, F=6, P=300, T=0, w_s=0, N=1800)
+    q, k, v = make_qkv(cfg, boost_nats=3.0)
+    sign = torch.where(torch.arange(1800) // 300 % 2 == 0, 1.0, -1.0)[:, None]
+    q[..., :1] = (100 * D ** 0.5) ** 0.5
+    k[..., :1] = ((100 * D ** 0.5) ** 0.5 * sign).to(k.dtype)
+    assert profile_pieces(S.shape_from_config(dict(cfg, H=80)), 60)[0] > 0
+    check(cfg, 60, 40, (q, k, v))

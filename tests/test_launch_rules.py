@@ -3,7 +3,7 @@ import pytest
 
 import paper_2502_01776_amd as S
 from workloads import get_config
-from helpers import DENSE, EXACT, GATHER, PROFILE, SPARSE, profile_cuts, takes_fp8_split_form, takes_split_form
+from helpers import DENSE, EXACT, GATHER, PROFILE, SPARSE, profile_cuts, profile_pieces, takes_fp8_split_form, takes_split_form
 
 
 def shape(H, N, D=128, blocks=(128, 64), F=1, T=0, **kw):
@@ -80,3 +80,25 @@ def test_groups_of_rows_the_split_form_profiles(D, free, most, keys):
         for H in range(1, most + 3):
             assert takes_split_form(shape(H, N, D), PROFILE, 20) == (H <= free or (H <= most and H * N <= keys)), (H, N)
     assert takes_split_form(shape(2, 6100, D, F=61), PROFILE, 20) and not takes_split_form(shape(2, 6200, D, F=62), PROFILE, 20)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("blocks", [(128, 64), (32, 32)])
+def test_pieces_of_the_unmasked_pass_fit_the_workspace(D, blocks):
+    """From 24 key tiles and frames of four on, with as many slots as the plan and the error pass hold."""
+    taken = 0
+    for F, P in ((1, 1600), (3, 1000), (13, 1350), (33, 3600), (40, 255), (40, 256), (80, 127), (80, 128)):
+        for T, sink in ((0, 0), (0, 1), (226, 0)):
+            for H in (1, 3, 12, 24, 40, 48, 96, 400, 3000):
+                for t in (1, 40, 178, 328, 1191, 5000):
+                    sh = shape(H, F * P + T, D, blocks, F=F, T=T, sink_first_frame=sink)
+                    plan = profile_cuts(sh, t)[0]
+                    n, cut = profile_pieces(sh, t)
+                    if not n:
+                        continue
+                    taken += 1
+                    assert P >= 4 * blocks[1] and n == cut.n_full + 2 + (T > 0 or sink) and n <= 11
+                    assert n + cut.n_masked <= plan.slots() and cut.n_full >= 1 and 1 <= cut.n_masked <= 4
+                    b = list(cut.full_bound)[:cut.n_full + 1]
+                    assert b[0] == 0 and b[-1] == S.svg_tile_counts(sh)[1] and b == sorted(b)
+    assert taken > 200
