@@ -356,7 +356,6 @@ struct AttnArgs {
   int t;                      // profile: number of sampled rows
   ProfilePlan plan;           // profile: parts of the unmasked pass and of the masked passes
   int pieces;                 // profile: output slots of the unmasked pass where it runs in pieces and stands for the spatial pass too, or 0
-  int rows_per_group;         // profile: sampled rows per workgroup (the groups are balanced)
   float2* stats;              // profile: (reference maximum, row sum) per (output slot, head, row)
   int N, nk, BH;
   int nqt;                    // workgroups per head: query tiles (dense, sparse) or ceil(t / rows per workgroup) (profile)
@@ -366,6 +365,7 @@ struct AttnArgs {
   int qo_token_order;         // sparse: q is read and o written in token order also for temporal heads
   float scale_log2;           // softmax scale * log2(e)
   int off, video_end, F, P, w_s, w_t, sink;
+  int rows_per_group;         // profile: sampled rows per workgroup (the groups are balanced); 0: dealt in 32s
   // the split form
   int blocks_log2;            // workgroups per query tile: bm = 32 << blocks_log2
   int halves_log2;            // units of 32 keys per key tile: bn = 32 << halves_log2

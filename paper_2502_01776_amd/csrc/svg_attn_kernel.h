@@ -232,16 +232,21 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   // This lane's query rows (one per 16-query block), their mask windows, and Q^T as the B operand.
   // ======================================================================================
   int qslot[QB], qrow[QB];       // row (profile: index into rows[])
+  // Profile: the sampled rows are dealt evenly to the row groups, rows_per_group each or (0) in 32s.  A wavefront without rows stages its
+  // share of the tiles and computes nothing; which of a workgroup's it is changes from one to the next, so that no SIMD has them
+  // all.  A lane without a row of its own shadows the group's first row and writes nothing.
+  const int n32 = (a.t + 31) / 32, per_group = MODE == kProfile ? n32 / a.nqt : 0, one_more = n32 - per_group * a.nqt;
+  const int row0 = a.rows_per_group ? min(grp * a.rows_per_group, a.t - 1) : 32 * (grp * per_group + min(grp, one_more));
+  const int row1 = min(row0 + (a.rows_per_group ? a.rows_per_group : 32 * (per_group + (grp < one_more ? 1 : 0))), a.t);
+  const int own32 = (wave + loc) & (NW - 1);
+  const bool active = MODE != kProfile || __builtin_amdgcn_readfirstlane(row0 + own32 * 32) < row1;
   if (MODE == kProfile) {
-    // The sampled rows are dealt evenly to the row groups (rows_per_group each, so that no
-    // group is left with a handful of rows and idle wavefronts); a lane without a row of
-    // its own shadows the group's first row and writes nothing.
     int slot[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-      const int in_group = wave * 32 + qb * 16 + r;
-      qslot[qb] = in_group < a.rows_per_group ? grp * a.rows_per_group + in_group : a.t;
-      slot[qb] = qslot[qb] < a.t ? qslot[qb] : min(grp * a.rows_per_group, a.t - 1);
+      qslot[qb] = row0 + own32 * 32 + qb * 16 + r;
+      qslot[qb] = qslot[qb] < row1 ? qslot[qb] : a.t;
+      slot[qb] = qslot[qb] < a.t ? qslot[qb] : row0;
     }
     // The temporal variant takes the sampled rows grouped by in-frame position, so that
     // a workgroup's rows share a narrow position range and most key tiles can be
@@ -317,9 +322,9 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   int own_frames = -1, cut_frames = -1;
   if (pieces) {
     auto frame = [&](int n) { return n >= a.off && n < a.video_end ? (n - a.off) / a.P : -1; };
-    auto group_row = [&](int i) { return a.rows[min(grp * a.rows_per_group + min(i, a.rows_per_group - 1), a.t - 1)]; };
+    auto group_row = [&](int i) { return a.rows[min(row0 + i, row1 - 1)]; };
     own_frames = (frame(qrow[0]) & 0xffff) | (frame(qrow[1]) << 16);
-    cut_frames = (frame(group_row(lane)) & 0xffff) | (frame(group_row(min(lane + 64, BM - 1))) << 16);
+    cut_frames = (frame(group_row(lane)) & 0xffff) | (frame(group_row(lane + 64)) << 16);
   }
   // keeps what is worked out from the value at the rare place that needs it, out of the registers of the loop
   auto opaque = [](int x) -> int {
@@ -992,7 +997,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
       }
       col2 = next_tile();
       const TileMask t = tile_mask(MODE == kProfile ? visit_key(col) / BN : col);
-      if (!t.skip) {
+      if (active && !t.skip) {
         read_k_ahead(buf);
         scores(buf, yes, buf);
         __builtin_amdgcn_s_setprio(0);
@@ -1009,7 +1014,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
     if (TEAMS > 1 && team == 1 && (n_tiles & 1)) barrier_loads_done();      // the other team's last tile
   } else if constexpr (MODE != kSparseExact) {
     const bool no_drop[QB] = {false, false};
-    if (col != kNoTile) {
+    if (active && col != kNoTile) {
       read_k_ahead(0);
       scores(0, no, 0);
       __builtin_amdgcn_s_setprio(0);
@@ -1024,12 +1029,14 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
         rows_v = rows_k;
         if (col3 != kNoTile) rows_k = load_table(col3);
       }
-      cut_before(col);
-      read_k_ahead(buf ^ 1);
-      softmax(no_drop);
-      scores(buf ^ 1, yes, buf);
-      output(buf, after_scores);
-      mask_scores(col1, TileMask{});
+      if (active) {
+        cut_before(col);
+        read_k_ahead(buf ^ 1);
+        softmax(no_drop);
+        scores(buf ^ 1, yes, buf);
+        output(buf, after_scores);
+        mask_scores(col1, TileMask{});
+      }
       wait_loads_to_lds<0>();
       barrier_loads_done();
       buf ^= 1;
@@ -1038,7 +1045,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
       col2 = col3;
     }
     if (TEAMS > 1 && team == 1 && (n_tiles & 1) && n_tiles > 1) barrier_loads_done();      // the other team's last trip
-    if (col != kNoTile) {
+    if (active && col != kNoTile) {
       cut_before(col);
 #pragma unroll
       for (int i = 0; i < PF; ++i) opnd[i] = v_operand(buf, i);
