@@ -55,7 +55,7 @@ __global__ __launch_bounds__(1024) void profile_order_kernel(const int32_t* rows
 }
 
 // Squared errors of the two masked outputs against the unmasked one (Alg. 1, last
-// block): block (x, bh) sums rows_per_block sampled rows of head bh.  Each of the three outputs of
+// block): block (x, bh) sums err_rows(D) sampled rows of head bh.  Each of the three outputs of
 // a row is first reassembled from the parts its pass was cut into: part r holds its normalised
 // output O_r, its reference maximum m_r and its row sum l_r, and O = sum_r w_r O_r / sum_r w_r with
 // w_r = l_r * 2^((m_r - max_r m_r) * scale_log2); a part that kept no key of the row has
@@ -66,16 +66,15 @@ __global__ __launch_bounds__(1024) void profile_order_kernel(const int32_t* rows
 // row takes D / 4 lanes and a block 1024 / (D / 4) rows at a time; every thread works the
 // weights of its row out itself (the lanes of a row read the same words) and all its loads, of the
 // statistics and of every part, are independent of each other.  The numbers of parts are template arguments
-// for that reason: NF is exact, masked parts beyond n_masked (at most NM) are read as the last one with weight zero.
+// for that reason: NF is exact but for pieces, parts beyond n_full and n_masked (at most NM) are read as the last one with weight zero.
 // (An earlier form, 16 rows per block, worked the weights out on 48 threads and walked the parts in
 // a loop of dependent loads: 24.6 us at 24 rows of 6 heads, 31 at 91 rows of 16, 29 at 328 of 40, 39 at
-// 1191 of 24; now 4.7, 6.4, 12.1 and 23.7, and the first needs no label launch, 4.7 us.)
+// 1191 of 24; then 4.7, 6.4, 12.1 and 23.7.)
 constexpr int kErrThreads = 1024;
 constexpr int err_rows(int D) { return kErrThreads / (D / 4); }
-// Heads with few rows take one block each, which also writes the label.  A block takes 3-4 us per pass over its
-// rows, a label launch 4.7: with three passes 13.1 us in one block, 6.4 + 4.7 in three (16 heads of 91 rows; 48 of 178 at
-// head dimension 64: 15.0, 7.8 + 4.8).
-constexpr int kErrSinglePasses = 2;
+// A head has as many blocks as its rows take passes.  The block that ends last adds their sums up, in a fixed order, and writes the label: it is
+// the one that takes the last of the head's tickets, which the launch before cleared.  (A launch for that took 4.2 us, so heads of up to
+// two passes had one block: 62 rows of 6 heads 10.4 us, 129 rows 6.8 + 4.2.)
 
 __device__ __forceinline__ void store_label(float sum_s, float sum_t, int bh, int t, int D, uint8_t* labels, float* mse) {
   const float per = (float)t * (float)D;
@@ -104,11 +103,10 @@ struct PieceArgs {
 template <int D, int NF, int NM, bool PIECES>
 __global__ __launch_bounds__(kErrThreads) void profile_error_kernel(const float* ws, const float2* stats, const int32_t* rows,
                                                                     int BH, int t, int n_full, int n_masked, float scale_log2, int off,
-                                                                    int video_end, int rows_per_block, float2* partial,
+                                                                    int video_end, float2* partial, unsigned* tickets,
                                                                     uint8_t* labels, float* mse, PieceArgs pieces) {
   constexpr int LANES = D / 4, ROWS = err_rows(D);
   const int bh = blockIdx.y;
-  const int row1 = min(t, (int)(blockIdx.x + 1) * rows_per_block);
   const int c = threadIdx.x % LANES;
   // The parts of a pass: loads of all of them, and the pass reassembled from those that `of` names.
   auto load = [&](auto parts_c, int slot0, int parts, int row, float2* st, f32x4* x) {
@@ -145,8 +143,8 @@ __global__ __launch_bounds__(kErrThreads) void profile_error_kernel(const float*
   const std::integral_constant<int, NM> masked_parts;
   auto all = [](int) { return true; };
   float acc_s = 0.f, acc_t = 0.f;
-  for (int row0 = blockIdx.x * rows_per_block; row0 < row1; row0 += ROWS) {
-    const int own = row0 + (int)threadIdx.x / LANES, row = min(own, t - 1);
+  {
+    const int own = blockIdx.x * ROWS + (int)threadIdx.x / LANES, row = min(own, t - 1);
     const int n = rows[row];
     const bool video = n >= off && n < video_end;
     float2 st[NF], st_m[NM];
@@ -167,7 +165,7 @@ __global__ __launch_bounds__(kErrThreads) void profile_error_kernel(const float*
       load(masked_parts, n_full + n_masked, n_masked, row, st_m, x_m);
     }
     const f32x4 ot = merged(masked_parts, st_m, x_m, all);
-    if (own < row1 && video) {
+    if (own < t && video) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float ds = f[e] - os[e], dt = f[e] - ot[e];
@@ -181,45 +179,43 @@ __global__ __launch_bounds__(kErrThreads) void profile_error_kernel(const float*
   acc_t = wave_sum(acc_t);
   if ((threadIdx.x & 63) == 0) wave_part[threadIdx.x >> 6] = make_float2(acc_s, acc_t);
   __syncthreads();
-  if (threadIdx.x != 0) return;
+  if (threadIdx.x >= 64) return;
   float sum_s = 0.f, sum_t = 0.f;
   for (int w = 0; w < kErrThreads / 64; ++w) {
     sum_s += wave_part[w].x;
     sum_t += wave_part[w].y;
   }
-  if (gridDim.x == 1) store_label(sum_s, sum_t, bh, t, D, labels, mse);
-  else partial[(size_t)bh * gridDim.x + blockIdx.x] = make_float2(sum_s, sum_t);
-}
-
-// Second stage for heads of more than one block: MSE_s, MSE_t and the label from the partial sums.
-__global__ __launch_bounds__(64) void profile_label_kernel(const float2* partial, int n_partial, int t, int D,
-                                                           uint8_t* labels, float* mse) {
-  const int bh = blockIdx.x;
-  float sum_s = 0.f, sum_t = 0.f;
-  for (int i = threadIdx.x; i < n_partial; i += 64) {
-    const float2 p = partial[(size_t)bh * n_partial + i];
-    sum_s += p.x;
-    sum_t += p.y;
+  if (gridDim.x > 1) {
+    float* const mine = reinterpret_cast<float*>(partial + (size_t)bh * gridDim.x);
+    unsigned ticket = 0;
+    if (threadIdx.x == 0) {
+      __hip_atomic_store(mine + 2 * blockIdx.x, sum_s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(mine + 2 * blockIdx.x + 1, sum_t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      ticket = __hip_atomic_fetch_add(tickets + bh, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (__builtin_amdgcn_readfirstlane(ticket) != gridDim.x - 1) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");      // for the lanes that took no ticket
+    sum_s = sum_t = 0.f;
+    for (unsigned i = threadIdx.x; i < gridDim.x; i += 64) {
+      sum_s += __hip_atomic_load(mine + 2 * i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      sum_t += __hip_atomic_load(mine + 2 * i + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    sum_s = wave_sum(sum_s);
+    sum_t = wave_sum(sum_t);
   }
-  sum_s = wave_sum(sum_s);
-  sum_t = wave_sum(sum_t);
   if (threadIdx.x == 0) store_label(sum_s, sum_t, bh, t, D, labels, mse);
 }
 
-// Number of blocks a head's error takes for t sampled rows; profile_workspace_bytes keeps room for
-// ceil(t / 16) partial sums per head, which is at least as many.
-inline int error_blocks(int D, int t) {
-  const int passes = (t + err_rows(D) - 1) / err_rows(D);
-  return passes <= kErrSinglePasses ? 1 : passes;
-}
+// Number of blocks a head's error takes for t sampled rows.  profile_workspace_bytes keeps room for ceil(t / 16) partial sums per
+// head, which is more wherever there are several: the tickets lie behind them.
+inline int error_blocks(int D, int t) { return (t + err_rows(D) - 1) / err_rows(D); }
 
 template <int D, int NF, bool PIECES>
 void launch_error(const AttnArgs& a, const PieceArgs& pieces, const float2* stats, float2* partial, uint8_t* labels, float* mse, hipStream_t stream) {
   const int blocks = error_blocks(D, a.t);
-  const int rows_per_block = blocks == 1 ? a.t : err_rows(D);
   auto kernel = a.plan.n_masked == 1 ? profile_error_kernel<D, NF, 1, PIECES> : profile_error_kernel<D, NF, kMaxMaskedParts, PIECES>;
   hipLaunchKernelGGL(kernel, dim3(blocks, a.BH), dim3(kErrThreads), 0, stream, static_cast<const float*>(a.o), stats, a.rows,
-                     a.BH, a.t, PIECES ? a.pieces : NF, a.plan.n_masked, a.scale_log2, a.off, a.video_end, rows_per_block, partial, labels, mse, pieces);
+                     a.BH, a.t, PIECES ? a.pieces : NF, a.plan.n_masked, a.scale_log2, a.off, a.video_end, partial, a.tickets, labels, mse, pieces);
 }
 
 template <int D>
@@ -236,10 +232,6 @@ int launch_error_parts(const Geo& g, const AttnArgs& a, const float2* stats, flo
     case 6: launch_error<D, 6, false>(a, pieces, stats, partial, labels, mse, stream); break;
     default: return SVG_ERR_UNSUPPORTED;
   }
-  int rc = hip_status(hipGetLastError());
-  const int blocks = error_blocks(D, a.t);
-  if (rc != SVG_OK || blocks == 1) return rc;
-  hipLaunchKernelGGL(profile_label_kernel, dim3(a.BH), dim3(64), 0, stream, partial, blocks, a.t, D, labels, mse);
   return hip_status(hipGetLastError());
 }
 
@@ -347,6 +339,8 @@ int launch_profile(const Geo& g, const void* q, const void* k, const void* v, co
   float2* stats = reinterpret_cast<float2*>(workspace + out_floats);
   float2* partial = stats + (size_t)ns * a.BH * t;
   a.stats = stats;
+  const int blocks = error_blocks(g.D, t);
+  if (blocks > 1) a.tickets = reinterpret_cast<unsigned*>(partial + (size_t)a.BH * blocks);
   if (split ? !split_sorts_rows(t) : t > 2 * g.bm) {
     // (a workgroup sorts as many rows as it has threads)
     int32_t* order = reinterpret_cast<int32_t*>(partial + (size_t)a.BH * ((t + 15) / 16));

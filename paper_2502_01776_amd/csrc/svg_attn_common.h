@@ -356,6 +356,7 @@ struct AttnArgs {
   int t;                      // profile: number of sampled rows
   ProfilePlan plan;           // profile: parts of the unmasked pass and of the masked passes
   int pieces;                 // profile: output slots of the unmasked pass where it runs in pieces and stands for the spatial pass too, or 0
+  unsigned* tickets;          // profile: a word per head that this launch clears for the error pass; may be null
   float2* stats;              // profile: (reference maximum, row sum) per (output slot, head, row)
   int N, nk, BH;
   int nqt;                    // workgroups per head: query tiles (dense, sparse) or ceil(t / rows per workgroup) (profile)
@@ -381,6 +382,12 @@ int launch_split(const Geo& g, AttnArgs a, int mode, hipStream_t stream);
 // The form for calls of at most one query tile to a compute unit (svg_teams.hip).
 bool two_teams(const Geo& g);
 int launch_teams(const Geo& g, const AttnArgs& a, int mode, hipStream_t stream);
+
+// Profiling: the first workgroup clears the tickets of the error pass, which nothing reads in this launch.
+__device__ __forceinline__ void clear_tickets(const AttnArgs& a) {
+  if (blockIdx.x == 0 && a.tickets != nullptr)
+    for (int i = threadIdx.x; i < a.BH; i += blockDim.x) a.tickets[i] = 0;
+}
 
 // Coarse position bin of a sampled row for the temporal profiling pass (text rows first).
 constexpr int kOrderBins = 2048;
