@@ -85,7 +85,9 @@ constexpr int kAmaxPieces = 16;            // 16-byte pieces per thread
 // Heads of up to 1024 rows take one block of 1024 threads, which writes the maximum itself; longer ones
 // several blocks of 256 that meet in an atomic maximum, for which the words are cleared first (a launch that
 // is nothing beside a pass over a long head; without it a whole layer of 960 rows and 6 heads takes 61.9
-// instead of 62.5 us).
+// instead of 62.5 us).  The lanes of a wavefront exchange their maxima in registers, where ten rounds through LDS with a barrier each took
+// 4-5 us of a short block: the whole quantisation of 24 heads of 960 rows 16.5 -> 12.5 us, 20 of 1442 19.5 -> 14.1, 8 of 3910 20.1 -> 15.2, 12 of 8000
+// 39.6 -> 37.0, 24 of 119056 1005 -> 1000; 40 of 32760, whose tensors leave less of themselves in the memory-side cache, 442 -> 446.
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void fp8_amax_kernel(const u32x4* q, const u32x4* k, const u32x4* v,
                                                            unsigned long long pieces_per_head, unsigned* amax,
@@ -94,25 +96,32 @@ __global__ __launch_bounds__(THREADS) void fp8_amax_kernel(const u32x4* q, const
   const u32x4* src = (tensor == 0 ? q : tensor == 1 ? k : v) + (size_t)bh * pieces_per_head;
   const unsigned long long base = (unsigned long long)blockIdx.x * (THREADS * kAmaxPieces) + threadIdx.x;
   unsigned m = 0;
-#pragma unroll 4
-  for (int i = 0; i < kAmaxPieces; ++i) {
-    const unsigned long long u = base + (unsigned long long)i * THREADS;
-    if (u < pieces_per_head) {
-      const u32x4 x = __builtin_nontemporal_load(&src[u]);
+  // as many loads as the registers hold on their way at once
+  constexpr int BATCH = THREADS == 1024 ? 16 : 8;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) m = max(m, max(x[w] & 0x7fffu, (x[w] >> 16) & 0x7fffu));
+  for (int i0 = 0; i0 < kAmaxPieces; i0 += BATCH) {
+    u32x4 x[BATCH];
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      const unsigned long long u = base + (unsigned long long)(i0 + i) * THREADS;
+      x[i] = u32x4{0u, 0u, 0u, 0u};
+      if (u < pieces_per_head) x[i] = __builtin_nontemporal_load(&src[u]);
     }
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) m = max(m, max(x[i][w] & 0x7fffu, (x[i][w] >> 16) & 0x7fffu));
   }
-  __shared__ unsigned red[THREADS];
-  red[threadIdx.x] = m;
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, d, 64));
+  __shared__ unsigned red[THREADS / 64];
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
-  for (unsigned step = THREADS / 2; step > 0; step >>= 1) {
-    if (threadIdx.x < step) red[threadIdx.x] = max(red[threadIdx.x], red[threadIdx.x + step]);
-    __syncthreads();
-  }
   if (threadIdx.x != 0) return;
-  if (gridDim.x == 1) amax[tensor * BH + bh] = red[0] << 16;      // as fp32 bits
-  else atomicMax(&amax[tensor * BH + bh], red[0] << 16);
+#pragma unroll
+  for (int w = 1; w < THREADS / 64; ++w) m = max(m, red[w]);
+  if (gridDim.x == 1) amax[tensor * BH + bh] = m << 16;      // as fp32 bits
+  else atomicMax(&amax[tensor * BH + bh], m << 16);
 }
 
 struct QuantArgs {
