@@ -72,9 +72,12 @@ __global__ __launch_bounds__(1024) void profile_order_kernel(const int32_t* rows
 // 1191 of 24; then 4.7, 6.4, 12.1 and 23.7.)
 constexpr int kErrThreads = 1024;
 constexpr int err_rows(int D) { return kErrThreads / (D / 4); }
-// A head has as many blocks as its rows take passes.  The block that ends last adds their sums up, in a fixed order, and writes the label: it is
-// the one that takes the last of the head's tickets, which the launch before cleared.  (A launch for that took 4.2 us, so heads of up to
-// two passes had one block: 62 rows of 6 heads 10.4 us, 129 rows 6.8 + 4.2.)
+// A head has as many blocks as its rows take passes, and their sums are added up in a fixed order.  Where all heads together have few blocks the one
+// that ends last does it and writes the label: the one that takes the last of the head's tickets, which the launch before cleared.  A launch for that
+// takes 4.2 us, and heads of up to two passes had one block to save it: 62 rows of 6 heads 28.0 -> 25.5 us for the whole of profiling, 91 of 16
+// 56.0 -> 54.3.  A ticket costs an exchange with the memory behind the L2 caches, which slows all blocks down: with 144 blocks 13.2 us against 10.3 + 4.2 (2 us more for the whole call), 25.7
+// against 15.0 + 4.3 with 440 and 62.5 against 23.7 + 4.2 with 912.
+constexpr int kTicketBlocks = 128;
 
 __device__ __forceinline__ void store_label(float sum_s, float sum_t, int bh, int t, int D, uint8_t* labels, float* mse) {
   const float per = (float)t * (float)D;
@@ -185,6 +188,10 @@ __global__ __launch_bounds__(kErrThreads) void profile_error_kernel(const float*
     sum_s += wave_part[w].x;
     sum_t += wave_part[w].y;
   }
+  if (gridDim.x > 1 && tickets == nullptr) {
+    if (threadIdx.x == 0) partial[(size_t)bh * gridDim.x + blockIdx.x] = make_float2(sum_s, sum_t);
+    return;
+  }
   if (gridDim.x > 1) {
     float* const mine = reinterpret_cast<float*>(partial + (size_t)bh * gridDim.x);
     unsigned ticket = 0;
@@ -203,6 +210,21 @@ __global__ __launch_bounds__(kErrThreads) void profile_error_kernel(const float*
     sum_s = wave_sum(sum_s);
     sum_t = wave_sum(sum_t);
   }
+  if (threadIdx.x == 0) store_label(sum_s, sum_t, bh, t, D, labels, mse);
+}
+
+// MSE_s, MSE_t and the label from the partial sums of many blocks.
+__global__ __launch_bounds__(64) void profile_label_kernel(const float2* partial, int n_partial, int t, int D,
+                                                           uint8_t* labels, float* mse) {
+  const int bh = blockIdx.x;
+  float sum_s = 0.f, sum_t = 0.f;
+  for (int i = threadIdx.x; i < n_partial; i += 64) {
+    const float2 p = partial[(size_t)bh * n_partial + i];
+    sum_s += p.x;
+    sum_t += p.y;
+  }
+  sum_s = wave_sum(sum_s);
+  sum_t = wave_sum(sum_t);
   if (threadIdx.x == 0) store_label(sum_s, sum_t, bh, t, D, labels, mse);
 }
 
@@ -232,6 +254,10 @@ int launch_error_parts(const Geo& g, const AttnArgs& a, const float2* stats, flo
     case 6: launch_error<D, 6, false>(a, pieces, stats, partial, labels, mse, stream); break;
     default: return SVG_ERR_UNSUPPORTED;
   }
+  const int rc = hip_status(hipGetLastError());
+  const int blocks = error_blocks(D, a.t);
+  if (rc != SVG_OK || blocks == 1 || a.tickets != nullptr) return rc;
+  hipLaunchKernelGGL(profile_label_kernel, dim3(a.BH), dim3(64), 0, stream, partial, blocks, a.t, D, labels, mse);
   return hip_status(hipGetLastError());
 }
 
@@ -340,7 +366,7 @@ int launch_profile(const Geo& g, const void* q, const void* k, const void* v, co
   float2* partial = stats + (size_t)ns * a.BH * t;
   a.stats = stats;
   const int blocks = error_blocks(g.D, t);
-  if (blocks > 1) a.tickets = reinterpret_cast<unsigned*>(partial + (size_t)a.BH * blocks);
+  if (blocks > 1 && (long long)a.BH * blocks <= kTicketBlocks) a.tickets = reinterpret_cast<unsigned*>(partial + (size_t)a.BH * blocks);
   if (split ? !split_sorts_rows(t) : t > 2 * g.bm) {
     // (a workgroup sorts as many rows as it has threads)
     int32_t* order = reinterpret_cast<int32_t*>(partial + (size_t)a.BH * ((t + 15) / 16));

@@ -106,3 +106,28 @@ def test_a_window_far_below_the_rest_of_its_row(D):
     k[..., :1] = ((100 * D ** 0.5) ** 0.5 * sign).to(k.dtype)
     assert profile_pieces(S.shape_from_config(dict(cfg, H=80)), 60)[0] > 0
     check(cfg, 60, 40, (q, k, v))
+
+
+@pytest.mark.parametrize("H, t", [(2, 33), (2, 200), (32, 129), (80, 33), (80, 65), (80, 129)])
+def test_error_blocks_of_a_head_meet_in_a_graph(H, t):
+    """Several error blocks per head (32 rows each): the last one finds its ticket in a workspace of any content, replay after replay; with more than
+    128 blocks a launch of its own adds their sums up."""
+    cfg = dict(PIECES, D=128, H=H, F=6, P=300, T=20, N=1820, spatial_heads=list(range(0, H, 2)))
+    sh = S.shape_from_config(cfg)
+    q, k, v = make_qkv(cfg, device="cuda")
+    rows = torch.from_numpy(np.random.default_rng(t).integers(0, cfg["N"], t).astype(np.int32)).cuda()
+    ws = torch.full((S.svg_workspace_bytes(sh, t),), 255, dtype=torch.uint8, device="cuda")
+    labels, mse = torch.zeros(H, dtype=torch.uint8, device="cuda"), torch.zeros(H, 2, device="cuda")
+    want = gpu_profile(sh, q, k, v, rows.cpu().numpy())
+    torch.cuda.synchronize()
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=side):
+        S.svg_profile_heads(sh, q, k, v, rows, t, labels, mse, ws, ws.numel())
+    for fill in (255, 0, 1):
+        ws.fill_(fill)
+        labels.fill_(7)
+        mse.fill_(-1.0)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(labels, want[0]) and torch.equal(mse, want[1])
