@@ -77,7 +77,6 @@ constexpr int err_rows(int D) { return kErrThreads / (D / 4); }
 // takes 4.2 us, and heads of up to two passes had one block to save it: 62 rows of 6 heads 28.0 -> 25.5 us for the whole of profiling, 91 of 16
 // 56.0 -> 54.3.  A ticket costs an exchange with the memory behind the L2 caches, which slows all blocks down: with 144 blocks 13.2 us against 10.3 + 4.2 (2 us more for the whole call), 25.7
 // against 15.0 + 4.3 with 440 and 62.5 against 23.7 + 4.2 with 912.
-constexpr int kTicketBlocks = 128;
 
 __device__ __forceinline__ void store_label(float sum_s, float sum_t, int bh, int t, int D, uint8_t* labels, float* mse) {
   const float per = (float)t * (float)D;
@@ -261,17 +260,17 @@ int launch_error_parts(const Geo& g, const AttnArgs& a, const float2* stats, flo
   return hip_status(hipGetLastError());
 }
 
-template <int MODE>
+template <int MODE, bool PIECED = false>
 int dispatch(const Geo& g, const AttnArgs& a, int rows_total, hipStream_t stream) {
   if (split_form(g, MODE, a.t)) return launch_split(g, a, MODE, stream);
   if (g.bm == 128) {
     if (MODE != kProfile && two_teams(g)) return launch_teams(g, a, MODE, stream);
-    return g.D == 128 ? launch_one<128, 4, 64, MODE>(a, rows_total, stream)
-                      : launch_one<64, 4, 64, MODE>(a, rows_total, stream);
+    return g.D == 128 ? launch_one<128, 4, 64, MODE, 1, PIECED>(a, rows_total, stream)
+                      : launch_one<64, 4, 64, MODE, 1, PIECED>(a, rows_total, stream);
   }
   if constexpr (MODE == kSparseGather) return SVG_ERR_UNSUPPORTED;
-  else return g.D == 128 ? launch_one<128, 1, 32, MODE>(a, rows_total, stream)
-                         : launch_one<64, 1, 32, MODE>(a, rows_total, stream);
+  else return g.D == 128 ? launch_one<128, 1, 32, MODE, 1, PIECED>(a, rows_total, stream)
+                         : launch_one<64, 1, 32, MODE, 1, PIECED>(a, rows_total, stream);
 }
 
 // Source rows for the gathering form: table[v] = v (spatial heads), table[entries + v] = token
@@ -377,7 +376,7 @@ int launch_profile(const Geo& g, const void* q, const void* k, const void* v, co
     const int rc = hip_status(hipGetLastError());
     if (rc != SVG_OK) return rc;
   }
-  const int rc = dispatch<kProfile>(g, a, t, stream);
+  const int rc = a.pieces ? dispatch<kProfile, true>(g, a, t, stream) : dispatch<kProfile>(g, a, t, stream);
   if (rc != SVG_OK) return rc;
   return g.D == 128 ? launch_error_parts<128>(g, a, stats, partial, labels, mse, stream)
                     : launch_error_parts<64>(g, a, stats, partial, labels, mse, stream);

@@ -112,7 +112,10 @@ constexpr int waves_per_simd(int D, int NW, int MODE) {
 }
 
 // TEAMS: one, or two teams of NW wavefronts that share the query tile and take its key tiles in turn (svg_teams.hip)
-template <int D, int NW, int BN, int MODE, int LW, int TEAMS = 1>
+// PIECED: profiling with the unmasked pass in pieces (PieceRule) and no spatial pass.  A kernel of its own: as a flag in the profiling kernel
+// the pieces cost the calls that run three passes 24 more spilled scalars in all loops (20 in the 32-row form, which had none): 60 heads of 4800 rows in 32-row
+// tiles 188 us as one kernel, 184 as two, 70 heads of 17500 rows 281 and 279, and calls in pieces, whose kernel has no spatial pass, 123 and 120 (cogvideox_v1), 426 and 418 (cogvideox_v15).
+template <int D, int NW, int BN, int MODE, int LW, int TEAMS = 1, bool PIECED = false>
 __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd(D, NW, MODE)) void attn_kernel(AttnArgs a) {
   constexpr int BM = 32 * NW;            // query rows per workgroup = rows of a query tile
   constexpr int THREADS = 64 * NW;       // of a team
@@ -170,7 +173,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   int bh = 0, grp = 0, variant = 0, chunk = 0;
   if (MODE == kProfile) {
     // (head, row group) pairs are split into 8 contiguous chunks, one per XCD.  Each pair
-    // has 2 n_masked + n_full units: the parts of the spatial pass, of the temporal pass (both
+    // has 2 n_masked + n_full units, or n_masked + n_full in pieces: the parts of the spatial pass, of the temporal pass (both
     // skip most key tiles) and of the unmasked pass.  Units are the outer index inside an
     // XCD's chunk, so neighbouring workgroups stream the same keys for neighbouring row
     // groups of one head.
@@ -178,12 +181,12 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
     const int pairs_per_xcd = (pairs + 7) >> 3;
     const int unit = loc / pairs_per_xcd;
     const int pair = xcd * pairs_per_xcd + (loc - unit * pairs_per_xcd);
-    const int nm = a.plan.n_masked, ns = a.pieces ? 0 : nm;      // parts of the temporal and of the spatial pass
+    const int nm = a.plan.n_masked, ns = PIECED ? 0 : nm;      // parts of the temporal and of the spatial pass
     clear_tickets(a);
     if (unit >= ns + nm + a.plan.n_full || pair >= pairs) return;
     // the masked passes first: their workgroups are the longest ones (mask work on top of
     // about as many tiles), so they should not be the last to start
-    variant = unit < ns ? 1 : unit < ns + nm ? 2 : 0;         // 0 unmasked, 1 spatial, 2 temporal
+    variant = !PIECED && unit < ns ? 1 : unit < ns + nm ? 2 : 0;         // 0 unmasked, 1 spatial, 2 temporal
     chunk = unit < ns ? unit : unit < ns + nm ? unit - ns : unit - ns - nm;    // which part of its pass
     bh = pair / a.nqt;
     grp = pair - bh * a.nqt;
@@ -234,12 +237,12 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   // ======================================================================================
   int qslot[QB], qrow[QB];       // row (profile: index into rows[])
   // Profile: the sampled rows are dealt evenly to the row groups, rows_per_group each or (0) in 32s.  A wavefront without rows stages its
-  // share of the tiles and computes nothing; which of a workgroup's it is changes from one to the next, so that no SIMD has them
-  // all.  A lane without a row of its own shadows the group's first row and writes nothing.
+  // share of the tiles and computes nothing; in pieces which of a workgroup's it is changes from one to the next, so that no SIMD has them
+  // all (in three passes 0.5-2 % slower).  A lane without a row of its own shadows the group's first row and writes nothing.
   const int n32 = (a.t + 31) / 32, per_group = MODE == kProfile ? n32 / a.nqt : 0, one_more = n32 - per_group * a.nqt;
   const int row0 = a.rows_per_group ? min(grp * a.rows_per_group, a.t - 1) : 32 * (grp * per_group + min(grp, one_more));
   const int row1 = min(row0 + (a.rows_per_group ? a.rows_per_group : 32 * (per_group + (grp < one_more ? 1 : 0))), a.t);
-  const int own32 = (wave + loc) & (NW - 1);
+  const int own32 = PIECED ? (wave + loc) & (NW - 1) : wave;
   const bool active = MODE != kProfile || __builtin_amdgcn_readfirstlane(row0 + own32 * 32) < row1;
   if (MODE == kProfile) {
     int slot[QB];
@@ -318,7 +321,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   // Unmasked pass in pieces (PieceRule): the frames of a lane's rows, and of two of the workgroup's rows per lane, from which every
   // wavefront finds the next key at which a piece of any of them ends.  Two to a register (P is at least 128, so frame numbers stay below 2^15), as the
   // register budget is full; -1: a text row, which has no part in the errors.
-  const bool pieces = MODE == kProfile && a.pieces && variant == 0;
+  const bool pieces = PIECED && variant == 0;
   const PieceRule rule = {a.off, a.video_end, keep_head, a.F, a.P, a.w_s};
   int own_frames = -1, cut_frames = -1;
   if (pieces) {
@@ -456,6 +459,12 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   }
   int pseg = 0, pj = 0, pjb = -1;
   auto profile_segment = [&](int sidx, int& k0, int& k1) -> bool {   // false: no more segments
+    if (!PIECED && variant == 0) {      // unmasked pass: the key tiles of part chunk
+      const int t0 = a.plan.full_bound[chunk], t1 = a.plan.full_bound[chunk + 1];
+      k0 = t0 * BN;
+      k1 = min(a.N, t1 * BN) - 1;
+      return sidx == 0;
+    }
     const int nv = variant == 1 ? 1 : a.F;
     if (sidx == 0) {            // text prefix
       k0 = 0;
@@ -499,16 +508,15 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
     }
     return true;
   };
-  // Unmasked pass: a visit is up to BN keys from any key on.  Packed: first key << 8, bit 7 where a piece may end (kCut), number
-  // of keys.  In one run over the keys of the part, or in pieces: the part's video keys, cut where a piece of any row ends, and
-  // behind the last part's the keys every row keeps.
+  // In pieces a tile is a visit of up to BN keys from any key on.  Packed: first key << 8, bit 7 where a piece may end (kCut), number
+  // of keys.  They are the part's video keys, cut where a piece of any row ends, and behind the last part's the keys every row keeps.
   constexpr int kCut = 128;
   int v_key = 0, v_end = 0, v_last = 0, v_region = 2;      // next key, end of the piece and of the part's (video) keys
   bool v_cut = pieces;
-  if (MODE == kProfile && variant == 0) {
-    v_key = v_end = pieces ? rule.bound(a.plan, chunk, BN) : min(a.N, a.plan.full_bound[chunk] * BN);
-    v_last = pieces ? rule.bound(a.plan, chunk + 1, BN) : min(a.N, a.plan.full_bound[chunk + 1] * BN);
-    if (pieces && chunk == a.plan.n_full - 1) v_region = 0;
+  if (pieces) {
+    v_key = v_end = rule.bound(a.plan, chunk, BN);
+    v_last = rule.bound(a.plan, chunk + 1, BN);
+    if (chunk == a.plan.n_full - 1) v_region = 0;
   }
   auto next_cut = [&](int key) -> int {
     int c = v_last;
@@ -525,8 +533,8 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   auto next_visit = [&]() -> int {
     while (v_key >= v_end) {
       if (v_end < v_last) {
-        v_end = pieces ? next_cut(v_key) : v_last;
-        v_cut = pieces;
+        v_end = next_cut(v_key);
+        v_cut = true;
       } else if (v_region == 0) {
         v_region = 1;
         v_cut = true;
@@ -556,11 +564,11 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
       lj = j + TEAMS;
       return j;
     }
-    if (variant == 0) return next_visit();      // profile
+    if (pieces) return next_visit();      // profile
     if (pleft <= 0) return kNoTile;
     if (!profile_interval()) return kNoTile;
     --pleft;
-    return (pj++ * BN) << 8;
+    return PIECED ? (pj++ * BN) << 8 : pj++;
   };
   if (MODE == kProfile && variant != 0 && a.plan.n_masked > 1) {
     // a masked pass in parts: count the tiles of the whole pass, then take the part's share
@@ -642,7 +650,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
     } else {
       // the tile index is the same in every lane; saying so keeps the descriptors scalar
       const int col_one = __builtin_amdgcn_readfirstlane(col_any);
-      const int key0 = MODE == kProfile ? visit_key(col_one) : col_one * BN;
+      const int key0 = PIECED ? visit_key(col_one) : col_one * BN;
       const u32x4 rsrc = buffer_words(src + (size_t)key0 * D, (unsigned)(a.N - key0) * (D * 2));
 #pragma unroll
       for (int i = 0; i < PER_THREAD; i += 2) {
@@ -783,8 +791,8 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
             }
         }
       }
-    } else if (MODE == kProfile ? (tile & (kCut - 1)) != BN : ragged && tile == a.nk - 1) {
-      int lim = (MODE == kProfile ? tile & (kCut - 1) : a.N - tile * BN) - 4 * g;     // keys with 16 kb + i >= lim are out of range
+    } else if (PIECED ? (tile & (kCut - 1)) != BN : ragged && tile == a.nk - 1) {
+      int lim = (PIECED ? tile & (kCut - 1) : a.N - tile * BN) - 4 * g;     // keys with 16 kb + i >= lim are out of range
       // opaque to the optimiser: keeps this rarely taken masking code inside the
       // branch instead of being speculated into every tile
       asm volatile("" : "+v"(lim));
@@ -905,7 +913,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
     }
   };
   auto cut_before = [&](int visit) {
-    if (MODE == kProfile && (visit & kCut) != 0) {
+    if (PIECED && (visit & kCut) != 0) {
       const int key = visit_key(visit);
       const bool kept = key < keep_head || key >= a.video_end;
       end_pieces(kept ? a.video_end : key, kept);
@@ -997,7 +1005,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
         load_v(col1, rows_k, buf ^ 1);
       }
       col2 = next_tile();
-      const TileMask t = tile_mask(MODE == kProfile ? visit_key(col) / BN : col);
+      const TileMask t = tile_mask(PIECED ? visit_key(col) / BN : col);
       if (active && !t.skip) {
         read_k_ahead(buf);
         scores(buf, yes, buf);
@@ -1091,7 +1099,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   // ======================================================================================
   // Epilogue: normalise and store.  oacc[cb][qb][i] = O[query 16 qb + r][16 cb + 4 g + i]
   // ======================================================================================
-  if (MODE == kProfile && pieces && chunk == a.plan.n_full - 1 && a.pieces == a.plan.n_full + 2) {
+  if (PIECED && pieces && chunk == a.plan.n_full - 1 && a.pieces == a.plan.n_full + 2) {
     end_pieces(a.video_end, true);      // no keys that every row keeps: the video keys were the last
     return;
   }
@@ -1102,7 +1110,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
     if (MODE == kProfile) {
       // output slots: the parts or pieces of the unmasked pass, the parts of the spatial pass, of the temporal pass
       int slot = variant == 0 ? chunk : a.plan.n_full + (variant - 1) * a.plan.n_masked + chunk;
-      if (a.pieces) {
+      if (PIECED) {
         if (variant != 0) slot = a.pieces + chunk;
         else if (chunk == a.plan.n_full - 1) slot = a.pieces - 1;
         else slot += cuts_before(qb, v_last);
@@ -1118,7 +1126,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
 }
 
 // rows_total: N for dense / sparse, t for profiling
-template <int D, int NW, int BN, int MODE, int TEAMS = 1>
+template <int D, int NW, int BN, int MODE, int TEAMS = 1, bool PIECED = false>
 int launch_one(AttnArgs a, int rows_total, hipStream_t stream) {
   constexpr int BM = 32 * NW;
   a.nqt = (rows_total + BM - 1) / BM;
@@ -1131,14 +1139,14 @@ int launch_one(AttnArgs a, int rows_total, hipStream_t stream) {
     const int per_cu = NW == 4 ? waves_per_simd(D, NW, MODE) : 2;
     a.so = sparse_order(a.BH, a.nqt, BM, a.off, a.video_end, a.N, TEAMS > 1 ? 32 : 32 * per_cu, 256 * per_cu, NW == 4 ? 2 : 0, a.nk);
   }
-  const unsigned grid = MODE == kProfile ? (unsigned)(8 * (a.plan.slots() - (a.pieces ? a.plan.n_masked : 0)) * ((a.total + 7) / 8))
+  const unsigned grid = MODE == kProfile ? (unsigned)(8 * (a.plan.slots() - (PIECED ? a.plan.n_masked : 0)) * ((a.total + 7) / 8))
                         : MODE == kDense ? 8u * per_xcd : sparse_grid(a.so, a.BH);
   (void)hipGetLastError();   // drop any stale error left by earlier runtime calls of the process
   constexpr bool SPARSE_MODE = MODE == kSparse || MODE == kSparseExact || MODE == kSparseGather;
   if (SPARSE_MODE && a.BH > 64)      // label classes over more than one 64-head word
     hipLaunchKernelGGL((attn_kernel<D, NW, BN, MODE, SPARSE_MODE ? kWideLabelWords : 1, TEAMS>), dim3(grid), dim3(64 * NW * TEAMS), 0, stream, a);
   else
-    hipLaunchKernelGGL((attn_kernel<D, NW, BN, MODE, 1, TEAMS>), dim3(grid), dim3(64 * NW * TEAMS), 0, stream, a);
+    hipLaunchKernelGGL((attn_kernel<D, NW, BN, MODE, 1, TEAMS, PIECED>), dim3(grid), dim3(64 * NW * TEAMS), 0, stream, a);
   return hip_status(hipGetLastError());
 }
 
