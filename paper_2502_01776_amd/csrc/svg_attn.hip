@@ -55,7 +55,7 @@ __global__ __launch_bounds__(1024) void profile_order_kernel(const int32_t* rows
 }
 
 // Squared errors of the two masked outputs against the unmasked one (Alg. 1, last
-// block): block (x, bh) sums err_rows(D) sampled rows of head bh.  Each of the three outputs of
+// block): block (x, bh) sums PASSES times err_rows(D) sampled rows of head bh.  Each of the three outputs of
 // a row is first reassembled from the parts its pass was cut into: part r holds its normalised
 // output O_r, its reference maximum m_r and its row sum l_r, and O = sum_r w_r O_r / sum_r w_r with
 // w_r = l_r * 2^((m_r - max_r m_r) * scale_log2); a part that kept no key of the row has
@@ -70,13 +70,7 @@ __global__ __launch_bounds__(1024) void profile_order_kernel(const int32_t* rows
 // (An earlier form, 16 rows per block, worked the weights out on 48 threads and walked the parts in
 // a loop of dependent loads: 24.6 us at 24 rows of 6 heads, 31 at 91 rows of 16, 29 at 328 of 40, 39 at
 // 1191 of 24; then 4.7, 6.4, 12.1 and 23.7.)
-constexpr int kErrThreads = 1024;
-constexpr int err_rows(int D) { return kErrThreads / (D / 4); }
-// A head has as many blocks as its rows take passes, and their sums are added up in a fixed order.  Where all heads together have few blocks the one
-// that ends last does it and writes the label: the one that takes the last of the head's tickets, which the launch before cleared.  A launch for that
-// takes 4.2 us, and heads of up to two passes had one block to save it: 62 rows of 6 heads 28.0 -> 25.5 us for the whole of profiling, 91 of 16
-// 56.0 -> 54.3.  A ticket costs an exchange with the memory behind the L2 caches, which slows all blocks down: with 144 blocks 13.2 us against 10.3 + 4.2 (2 us more for the whole call), 25.7
-// against 15.0 + 4.3 with 440 and 62.5 against 23.7 + 4.2 with 912.
+// How many blocks a head has, and how their sums come together (the launch before this one cleared the tickets): error_blocks in svg_host.cpp.
 
 __device__ __forceinline__ void store_label(float sum_s, float sum_t, int bh, int t, int D, uint8_t* labels, float* mse) {
   const float per = (float)t * (float)D;
@@ -102,7 +96,7 @@ struct PieceArgs {
   int bn;
 };
 
-template <int D, int NF, int NM, bool PIECES>
+template <int D, int NF, int NM, bool PIECES, int PASSES>
 __global__ __launch_bounds__(kErrThreads) void profile_error_kernel(const float* ws, const float2* stats, const int32_t* rows,
                                                                     int BH, int t, int n_full, int n_masked, float scale_log2, int off,
                                                                     int video_end, float2* partial, unsigned* tickets,
@@ -145,8 +139,9 @@ __global__ __launch_bounds__(kErrThreads) void profile_error_kernel(const float*
   const std::integral_constant<int, NM> masked_parts;
   auto all = [](int) { return true; };
   float acc_s = 0.f, acc_t = 0.f;
-  {
-    const int own = blockIdx.x * ROWS + (int)threadIdx.x / LANES, row = min(own, t - 1);
+#pragma unroll 1
+  for (int pass = 0; pass < PASSES; ++pass) {
+    const int own = (blockIdx.x * PASSES + pass) * ROWS + (int)threadIdx.x / LANES, row = min(own, t - 1);
     const int n = rows[row];
     const bool video = n >= off && n < video_end;
     float2 st[NF], st_m[NM];
@@ -227,34 +222,30 @@ __global__ __launch_bounds__(64) void profile_label_kernel(const float2* partial
   if (threadIdx.x == 0) store_label(sum_s, sum_t, bh, t, D, labels, mse);
 }
 
-// Number of blocks a head's error takes for t sampled rows.  profile_workspace_bytes keeps room for ceil(t / 16) partial sums per
-// head, which is more wherever there are several: the tickets lie behind them.
-inline int error_blocks(int D, int t) { return (t + err_rows(D) - 1) / err_rows(D); }
-
 template <int D, int NF, bool PIECES>
-void launch_error(const AttnArgs& a, const PieceArgs& pieces, const float2* stats, float2* partial, uint8_t* labels, float* mse, hipStream_t stream) {
-  const int blocks = error_blocks(D, a.t);
-  auto kernel = a.plan.n_masked == 1 ? profile_error_kernel<D, NF, 1, PIECES> : profile_error_kernel<D, NF, kMaxMaskedParts, PIECES>;
+void launch_error(const AttnArgs& a, int blocks, const PieceArgs& pieces, const float2* stats, float2* partial, uint8_t* labels, float* mse, hipStream_t stream) {
+  auto kernel = a.plan.n_masked == 1 ? profile_error_kernel<D, NF, 1, PIECES, 1> : profile_error_kernel<D, NF, kMaxMaskedParts, PIECES, 1>;
+  if constexpr (!PIECES)
+    if (blocks == 1 && a.t > err_rows(D)) kernel = a.plan.n_masked == 1 ? profile_error_kernel<D, NF, 1, false, 2> : profile_error_kernel<D, NF, kMaxMaskedParts, false, 2>;
   hipLaunchKernelGGL(kernel, dim3(blocks, a.BH), dim3(kErrThreads), 0, stream, static_cast<const float*>(a.o), stats, a.rows,
                      a.BH, a.t, PIECES ? a.pieces : NF, a.plan.n_masked, a.scale_log2, a.off, a.video_end, partial, a.tickets, labels, mse, pieces);
 }
 
 template <int D>
-int launch_error_parts(const Geo& g, const AttnArgs& a, const float2* stats, float2* partial, uint8_t* labels, float* mse, hipStream_t stream) {
+int launch_error_parts(const Geo& g, const AttnArgs& a, int blocks, const float2* stats, float2* partial, uint8_t* labels, float* mse, hipStream_t stream) {
   (void)hipGetLastError();
   const PieceArgs pieces = {a.plan, piece_rule(g), g.bn};
   if (a.pieces > kMaxPieces) return SVG_ERR_UNSUPPORTED;
-  if (a.pieces > 7) launch_error<D, kMaxPieces, true>(a, pieces, stats, partial, labels, mse, stream);
-  else if (a.pieces) launch_error<D, 7, true>(a, pieces, stats, partial, labels, mse, stream);
+  if (a.pieces > 7) launch_error<D, kMaxPieces, true>(a, blocks, pieces, stats, partial, labels, mse, stream);
+  else if (a.pieces) launch_error<D, 7, true>(a, blocks, pieces, stats, partial, labels, mse, stream);
   else switch (a.plan.n_full) {      // the numbers of parts profile_plan and profile_cut give the unmasked pass
-    case 1: launch_error<D, 1, false>(a, pieces, stats, partial, labels, mse, stream); break;
-    case 3: launch_error<D, 3, false>(a, pieces, stats, partial, labels, mse, stream); break;
-    case 4: launch_error<D, 4, false>(a, pieces, stats, partial, labels, mse, stream); break;
-    case 6: launch_error<D, 6, false>(a, pieces, stats, partial, labels, mse, stream); break;
+    case 1: launch_error<D, 1, false>(a, blocks, pieces, stats, partial, labels, mse, stream); break;
+    case 3: launch_error<D, 3, false>(a, blocks, pieces, stats, partial, labels, mse, stream); break;
+    case 4: launch_error<D, 4, false>(a, blocks, pieces, stats, partial, labels, mse, stream); break;
+    case 6: launch_error<D, 6, false>(a, blocks, pieces, stats, partial, labels, mse, stream); break;
     default: return SVG_ERR_UNSUPPORTED;
   }
   const int rc = hip_status(hipGetLastError());
-  const int blocks = error_blocks(D, a.t);
   if (rc != SVG_OK || blocks == 1 || a.tickets != nullptr) return rc;
   hipLaunchKernelGGL(profile_label_kernel, dim3(a.BH), dim3(64), 0, stream, partial, blocks, a.t, D, labels, mse);
   return hip_status(hipGetLastError());
@@ -364,8 +355,9 @@ int launch_profile(const Geo& g, const void* q, const void* k, const void* v, co
   float2* stats = reinterpret_cast<float2*>(workspace + out_floats);
   float2* partial = stats + (size_t)ns * a.BH * t;
   a.stats = stats;
-  const int blocks = error_blocks(g.D, t);
-  if (blocks > 1 && (long long)a.BH * blocks <= kTicketBlocks) a.tickets = reinterpret_cast<unsigned*>(partial + (size_t)a.BH * blocks);
+  // profile_workspace_bytes keeps room for ceil(t / 16) partial sums per head, which is more than the blocks wherever there are several: the tickets lie behind them
+  const int blocks = error_blocks(g, t, a.plan, a.pieces);
+  if (error_tickets(g, blocks)) a.tickets = reinterpret_cast<unsigned*>(partial + (size_t)a.BH * blocks);
   if (split ? !split_sorts_rows(t) : t > 2 * g.bm) {
     // (a workgroup sorts as many rows as it has threads)
     int32_t* order = reinterpret_cast<int32_t*>(partial + (size_t)a.BH * ((t + 15) / 16));
@@ -378,8 +370,8 @@ int launch_profile(const Geo& g, const void* q, const void* k, const void* v, co
   }
   const int rc = a.pieces ? dispatch<kProfile, true>(g, a, t, stream) : dispatch<kProfile>(g, a, t, stream);
   if (rc != SVG_OK) return rc;
-  return g.D == 128 ? launch_error_parts<128>(g, a, stats, partial, labels, mse, stream)
-                    : launch_error_parts<64>(g, a, stats, partial, labels, mse, stream);
+  return g.D == 128 ? launch_error_parts<128>(g, a, blocks, stats, partial, labels, mse, stream)
+                    : launch_error_parts<64>(g, a, blocks, stats, partial, labels, mse, stream);
 }
 
 }  // namespace svg

@@ -383,12 +383,10 @@ int launch_split(const Geo& g, AttnArgs a, int mode, hipStream_t stream);
 bool two_teams(const Geo& g);
 int launch_teams(const Geo& g, const AttnArgs& a, int mode, hipStream_t stream);
 
-// Profiling: the first workgroup clears the tickets of the error pass, which nothing reads in this launch.  Heads with tickets have two error blocks
-// at least, so there are at most kTicketBlocks / 2 of them, as many as the smallest workgroup has threads.
-constexpr int kTicketBlocks = 128;
+// Profiling: the first workgroup clears the tickets of the error pass, which nothing reads in this launch.
 __device__ __forceinline__ void clear_tickets(const AttnArgs& a) {
-  static_assert(kTicketBlocks / 2 <= 64, "one ticket to a thread");
-  if (blockIdx.x == 0 && a.tickets != nullptr && (int)threadIdx.x < a.BH) a.tickets[threadIdx.x] = 0;
+  if (blockIdx.x == 0 && a.tickets != nullptr)
+    for (int i = threadIdx.x; i < a.BH; i += blockDim.x) a.tickets[i] = 0;
 }
 
 // Coarse position bin of a sampled row for the temporal profiling pass (text rows first).

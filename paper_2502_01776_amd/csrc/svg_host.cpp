@@ -124,6 +124,21 @@ int profile_pieces(const Geo& g, int t, const ProfilePlan& plan, ProfilePlan* cu
   return n_full + 2 + kept;
 }
 
+// A head's squared errors take one block per pass over its rows, and the sums of its blocks are added up in a fixed order: with up to
+// kTicketBlocks blocks in all by the one that takes the last of the head's tickets, with more by a launch of its own.  A launch behind another costs
+// a call 1-2 us.  A ticket costs an exchange with the memory behind the L2 caches, which slows the other blocks down: launch against tickets, whole calls,
+// 4 blocks 18.6 -> 17.7 us and 17.1 -> 16.2, 24 blocks 21.9 -> 21.2, 40 25.2 -> 24.7, 60 78.7 -> 78.4; 76 349.8 -> 350.0, 82 70.3 -> 70.6 and 85.4 -> 85.8, 100 86.5 -> 87.1, 144
+// 95.1 -> 96.4, 200 94.7 -> 96.8, 440 177.6 -> 184.8.
+// Two passes in one block need neither.  The second costs what the parts to be merged cost, 0.5-2 us, and that is less than a ticket with up to three
+// parts of the unmasked pass (6 heads of 1200 rows 18.4 -> 17.8 us and 16.7 -> 16.0, 12 18.8 -> 18.6, 30 27.3 -> 26.9 and 21.9 -> 21.1; but four and four parts 12 heads 20.8 -> 21.9, 20
+// 24.3 -> 25.7, six and four 29.5 -> 31.2), and less than a launch with all but the many outputs of pieces: 50 heads of 2400 rows 53.3 -> 52.0, 80 61.6 -> 58.9, 160 of 1200
+// 52.7 -> 48.7, 180 of 4800 146.1 -> 142.9; in pieces 64 94.9 -> 95.6, 80 95.2 -> 96.3.
+int error_blocks(const Geo& g, int t, const ProfilePlan& cut, int pieces) {
+  const int passes = (t + err_rows(g.D) - 1) / err_rows(g.D);
+  const bool one_block = passes == 2 && !pieces && (cut.n_full <= 3 || 2ll * g.B * g.H > kTicketBlocks);
+  return one_block ? 1 : passes;
+}
+
 int make_geo(const svg_shape_t* s, Geo* g) {
   if (!s) return SVG_ERR_INVALID_ARG;
   if (s->B <= 0 || s->H <= 0 || s->F <= 0 || s->P <= 0 || s->T < 0) return SVG_ERR_INVALID_ARG;

@@ -76,6 +76,13 @@ inline PieceRule piece_rule(const Geo& g) { return {g.off, g.video_end, g.off + 
 int profile_pieces(const Geo& g, int t, const ProfilePlan& plan, ProfilePlan* cut);
 constexpr int kMaxPieces = 11;
 
+// The error pass: rows of a block's pass, blocks of a head, and whether the blocks of a head meet by tickets or in a launch of their own.
+constexpr int kErrThreads = 1024;
+constexpr int err_rows(int D) { return kErrThreads / (D / 4); }
+constexpr int kTicketBlocks = 64;
+int error_blocks(const Geo& g, int t, const ProfilePlan& cut, int pieces);
+inline bool error_tickets(const Geo& g, int blocks) { return blocks > 1 && (long long)g.B * g.H * blocks <= kTicketBlocks; }
+
 // Bytes of workspace svg_profile_heads uses for t rows: fp32 outputs [slots][BH][t][D], float2
 // (maximum, row sum) [slots][BH][t], partial error sums float2 [BH][ceil(t/16)], row order int32 [t].
 inline size_t profile_workspace_bytes(const Geo& g, int t) {

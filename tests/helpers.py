@@ -225,6 +225,13 @@ def profile_cuts(shape, t):
     return plan, _rule("_ZN3svg11profile_cutERKNS_3GeoEiRKNS_11ProfilePlanEb", Plan, C.byref(g), C.c_int(t), C.byref(plan), split)
 
 
+def error_blocks(shape, t):
+    """Blocks a head of a profiling call has in the error pass."""
+    pieces, cut = profile_pieces(shape, t)
+    return _rule("_ZN3svg12error_blocksERKNS_3GeoEiRKNS_11ProfilePlanEi", C.c_int, C.byref(_geo(shape)), C.c_int(t),
+                 C.byref(cut if pieces else profile_cuts(shape, t)[1]), C.c_int(pieces))
+
+
 def profile_pieces(shape, t):
     """(output slots of the unmasked pass in pieces or 0, the cut such a launch takes)"""
     g, cut = _geo(shape), Plan()

@@ -8,7 +8,7 @@ import torch
 import paper_2502_01776_amd as S
 from oracle import svg_oracle as O
 from workloads import get_config, make_qkv
-from helpers import f64, gpu_profile, labels_match, profile_cuts, profile_pieces, takes_split_form, PROFILE
+from helpers import f64, error_blocks, gpu_profile, labels_match, profile_cuts, profile_pieces, takes_split_form, PROFILE
 
 pytestmark = pytest.mark.gpu
 
@@ -110,9 +110,24 @@ def test_a_window_far_below_the_rest_of_its_row(D):
 
 @pytest.mark.parametrize("H, t", [(2, 33), (2, 200), (32, 129), (80, 33), (80, 65), (80, 129)])
 def test_error_blocks_of_a_head_meet_in_a_graph(H, t):
-    """Several error blocks per head (32 rows each): the last one finds its ticket in a workspace of any content, replay after replay; with more than
-    128 blocks a launch of its own adds their sums up."""
-    cfg = dict(PIECES, D=128, H=H, F=6, P=300, T=20, N=1820, spatial_heads=list(range(0, H, 2)))
+    """Several error blocks per head (32 rows each): the last one finds its ticket in a workspace of any content, replay after replay; with many
+    blocks a launch of its own adds their sums up."""
+    replay(dict(PIECES, D=128, H=H, F=6, P=300, T=20, N=1820, spatial_heads=list(range(0, H, 2))), t)
+
+
+@pytest.mark.parametrize("H, F, P, T, D, t, pieces, blocks", [
+    (20, 62, 30, 0, 128, 60, False, 2), (12, 62, 30, 20, 64, 130, False, 3), (4, 62, 256, 0, 64, 120, True, 2), (2, 62, 256, 20, 128, 97, True, 4)])
+def test_tickets_of_the_general_form_in_a_graph(H, F, P, T, D, t, pieces, blocks):
+    """As above; the general form is the one that clears the tickets, in three passes and with the unmasked one in pieces."""
+    cfg = dict(PIECES, D=D, H=H, F=F, P=P, T=T, N=F * P + T, spatial_heads=list(range(0, H, 2)))
+    sh = S.shape_from_config(cfg)
+    assert not takes_split_form(sh, PROFILE, t) and (profile_pieces(sh, t)[0] > 0) == pieces
+    assert error_blocks(sh, t) == blocks and H * blocks <= 64
+    replay(cfg, t)
+
+
+def replay(cfg, t):
+    H = cfg["H"]
     sh = S.shape_from_config(cfg)
     q, k, v = make_qkv(cfg, device="cuda")
     rows = torch.from_numpy(np.random.default_rng(t).integers(0, cfg["N"], t).astype(np.int32)).cuda()

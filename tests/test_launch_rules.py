@@ -3,7 +3,7 @@ import pytest
 
 import paper_2502_01776_amd as S
 from workloads import get_config
-from helpers import DENSE, EXACT, GATHER, PROFILE, SPARSE, profile_cuts, profile_pieces, takes_fp8_split_form, takes_split_form
+from helpers import DENSE, EXACT, GATHER, PROFILE, SPARSE, profile_cuts, profile_pieces, error_blocks, takes_fp8_split_form, takes_split_form
 
 
 def shape(H, N, D=128, blocks=(128, 64), F=1, T=0, **kw):
@@ -102,3 +102,17 @@ def test_pieces_of_the_unmasked_pass_fit_the_workspace(D, blocks):
                     b = list(cut.full_bound)[:cut.n_full + 1]
                     assert b[0] == 0 and b[-1] == S.svg_tile_counts(sh)[1] and b == sorted(b)
     assert taken > 200
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_error_blocks_of_a_head(D):
+    """One to a pass over its rows; two passes in one block where that is less than what brings two blocks together."""
+    rows = 4096 // D
+    few, four, many = shape(20, 1200, D), shape(20, 1680, D), shape(33, 2400, D, F=10)
+    pieces = shape(200, 4914, D, F=6)
+    assert [error_blocks(s, rows) for s in (few, four, many, pieces)] == [1, 1, 1, 1]
+    for t in (rows + 1, 2 * rows):
+        assert profile_cuts(few, t)[1].n_full <= 3 and profile_cuts(four, t)[1].n_full == 4 and profile_pieces(pieces, t)[0]
+        assert [error_blocks(s, t) for s in (few, four, many, pieces)] == [1, 2, 1, 2]
+        assert [error_blocks(shape(H, 2400, D, F=10), t) for H in (31, 32)] == [2, 2]
+    assert [error_blocks(s, 2 * rows + 1) for s in (few, four, many, pieces)] == [3, 3, 3, 3]
