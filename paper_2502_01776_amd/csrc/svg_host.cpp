@@ -33,7 +33,7 @@ void note_hip_error(hipError_t e) { g_last_hip_error = e; }
 //    masked workgroups per pair cannot fill an XCD; then as many parts (up to four) as keep
 //    them within its resident places.  CogVideoX-v1 at 1 % (12 pairs per XCD): three parts,
 //    -32 % time; 0.1 % of the rows at the 119k-token shape (3 pairs): four parts, 3.9 -> 1.3 ms;
-//    with 15 or more pairs per XCD two parts are slower (566 -> 573 us at 40 heads of 32760 rows, 620 -> 639 at 48 of
+//    with 15 or more pairs per XCD two parts of each of three passes are slower (566 -> 573 us at 40 heads of 32760 rows, 620 -> 639 at 48 of
 //    45104, 2839 -> 2914 at 24 of 119056).
 // ---------------------------------------------------------------------------------------------
 namespace {
@@ -103,25 +103,44 @@ ProfilePlan profile_cut(const Geo& g, int t, const ProfilePlan& plan, bool split
 // passes against pieces, rows in ascending and in random order: 48 heads of 17776 tokens at head dimension 64 186 -> 138 and 208 -> 139 us, 48 of
 // 45104 636 -> 458 and 901 -> 462, at 128 40 of 32760 583 -> 427 and 856 -> 419, 24 of 119056 2865 -> 2558 and 4226 -> 2619, 3 of them
 // 505 -> 450 and 762 -> 452.
-// The temporal pass has the plan's parts, which leave its places to two masked passes, except that
-//  * at head dimension 128 one less of three or four is better (11 groups of rows to an XCD and fewer: 485 -> 450 us with four and three
-//    parts, 293 -> 279 with three and two) and leaves room for eight parts of the unmasked pass where the groups are fewest;
-//  * two are better than one where the groups are just too many for the plan to cut it and it visits more than a third of the keys
-//    (471 -> 427 us at 40 heads of 32760 tokens and 328 rows, 296 -> 264 at 96 of 17776 and 178; with 0.28 of the keys 458 -> 485).
+//
+// The parts of the two passes share the workspace of the plan, and an XCD's places.  Taken are as many temporal ones as make the estimated time the
+// shortest: the longest chain of either pass, or the work of an XCD on all its places and, where the parts are more than the places, the last part behind
+// it.  In units of the unmasked pass, whose last two parts have half the length of the others; a masked key tile counts 1.6, and a part more has to promise a tenth.
+// 340 calls of 1-64 heads, 700-130000 keys and 16-1200 rows with one to four temporal parts: 0.7 % slower than with the best number at the mean, 13 % at the most (a tile of 1.2-1.8
+// 0.8-1.5 %).  The plan's number, less one at head dimension 128 and one more at two numbers of groups, was 8-9 % and 60 % slower, and slower than three passes: up to 9 groups of rows
+// to an XCD the temporal pass is the longest chain (30 heads of 9216 tokens and 92 rows with three, four parts 113 -> 90 us, 60 of 4914 and 49 97 -> 79; three
+// passes 88 and 82).  239 calls in all, rows in order: the former numbers 0.62-1.39 times the time of three passes, 0.91 at the mean, these 0.57-1.07 and 0.83.
+// Three passes where they are estimated 15 % shorter with the rows in order: where the workspace leaves the unmasked pass three parts or less (14 heads of 6000 tokens, 663 rows 1.12,
+// 12 of 8100, 883 1.06; of the other calls five were 1-3 % slower in pieces than in three passes).
 int profile_pieces(const Geo& g, int t, const ProfilePlan& plan, ProfilePlan* cut) {
   const int kept = g.T > 0 || g.sink ? 1 : 0;
   const int room = plan.slots() - 2 - kept;      // parts of both passes the workspace holds beside the two cuts and the kept keys
   if (g.nk < 24 || g.P < 4 * g.bn || room < 2) return 0;
   const int groups = (t + g.bm - 1) / g.bm;
-  const long long pairs_x = ((long long)g.B * g.H * groups + 7) / 8;
+  const double pairs_x = (double)(((long long)g.B * g.H * groups + 7) / 8), frames = g.F, positions = g.P;
+  const double places = g.bm == 128 ? (g.D == 64 ? kSlots * 3 / 2 : kSlots) : (g.D == 64 ? 256 : 160);      // 32-row tiles: by LDS and registers
+  const double kMaskedTile = 1.6;
+  const int sides = std::min(2, groups - 1);      // of a group's rows on which other positions lie
+  const double temporal = kMaskedTile * std::min(1.0, ((double)sides * g.w_t + g.bn + positions / groups) / positions);
+  const double spatial = kMaskedTile * std::min(1.0, ((double)sides * g.w_s + 1 + frames / groups) / frames);
+  auto small_parts = [](int n_full) { return n_full >= 3 ? 2 : 0; };
+  auto longest_part = [&](int n_full) { return 2.0 / (2 * n_full - small_parts(n_full)); };
   *cut = plan;
-  if (g.D == 128 && plan.n_masked >= 3) --cut->n_masked;
-  const long long reach = 2ll * g.w_t + g.bn + g.P / groups;      // positions of a frame the temporal pass visits
-  if (plan.n_masked == 1 && room >= 5 && 4 * pairs_x <= (g.D == 64 ? kSlots * 3 / 2 : kSlots) && 3 * reach > g.P) cut->n_masked = 2;
-  const int most = g.D == 128 && plan.n_masked == 4 ? 8 : 6;
-  const int n_full = std::min(room - cut->n_masked, most), n_small = n_full >= 3 ? 2 : 0;
-  fill_bounds(cut, n_full - n_small, n_small, g.nk);
-  return n_full + 2 + kept;
+  double shortest = 0;
+  for (int nm = 1; nm <= kMaxMaskedParts && nm < room; ++nm) {
+    const int nf = std::min(room - nm, kMaxPieces - 3);
+    const double last = nf >= 3 ? longest_part(nf) / 2 : longest_part(nf);
+    const double all = pairs_x * (1 + temporal) / places + (pairs_x * (nf + nm) > places ? last : 0);
+    const double time = std::max({temporal / nm, longest_part(nf), all});
+    if (nm > 1 && 1.1 * time >= shortest) continue;
+    shortest = time;
+    cut->n_masked = nm;
+    fill_bounds(cut, nf - small_parts(nf), small_parts(nf), g.nk);
+  }
+  const double three = std::max({temporal / plan.n_masked, spatial / plan.n_masked, longest_part(plan.n_full),
+                                 pairs_x * (1 + temporal + spatial) / places});
+  return shortest > 1.15 * three ? 0 : cut->n_full + 2 + kept;
 }
 
 // A head's squared errors take one block per pass over its rows, and the sums of its blocks are added up in a fixed order: with up to

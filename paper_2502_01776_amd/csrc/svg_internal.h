@@ -26,9 +26,9 @@ int make_geo(const svg_shape_t* s, Geo* g);
 // sampled rows) pair has one unmasked pass over all nk key tiles and two masked passes over the
 // tiles their windows can reach; each pass is cut along its tile sequence into parts that run as
 // separate workgroups and are merged afterwards from (output, maximum, row sum) triples.  The
-// unmasked pass has n_full <= 6 parts with tile boundaries full_bound[] (the last parts are
+// unmasked pass has n_full <= 8 parts (6 in the plan) with tile boundaries full_bound[] (the last parts are
 // shorter, so that the workgroups finishing last are short ones), each masked pass n_masked <= 4
-// equal parts.  The choice depends on the shape and t only (profile_plan and profile_cut in svg_host.cpp).
+// equal parts.  The choice depends on the shape and t only (profile_plan, profile_cut and profile_pieces in svg_host.cpp).
 constexpr int kMaxProfileParts = 16;
 constexpr int kMaxMaskedParts = 4;
 struct ProfilePlan {

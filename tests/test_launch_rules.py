@@ -116,3 +116,18 @@ def test_error_blocks_of_a_head(D):
         assert [error_blocks(s, t) for s in (few, four, many, pieces)] == [1, 2, 1, 2]
         assert [error_blocks(shape(H, 2400, D, F=10), t) for H in (31, 32)] == [2, 2]
     assert [error_blocks(s, 2 * rows + 1) for s in (few, four, many, pieces)] == [3, 3, 3, 3]
+
+
+@pytest.mark.parametrize("H, F, P, T, D, t, blocks, w_s, w_t, cut", [
+    # up to 9 groups of rows to an XCD the temporal pass is the longest chain unless it has as many parts as there can be
+    (30, 9, 1024, 0, 128, 92, (128, 64), 1, 68, (8, 4)), (14, 37, 3387, 0, 128, 112, (128, 64), 4, 338, (8, 4)), (25, 8, 982, 226, 128, 78, (128, 64), 1, 77, (7, 4)),
+    (30, 34, 676, 0, 128, 229, (128, 64), 3, 92, (7, 3)), (47, 3, 2066, 0, 128, 121, (32, 32), 1, 90, (4, 2)),
+    # where the windows are narrow it is not
+    (8, 25, 3223, 0, 128, 805, (128, 64), 2, 40, (8, 2)), (40, 25, 834, 0, 128, 987, (128, 64), 2, 47, (5, 1)),
+    # on both sides of one and two parts in the plan
+    (37, 21, 1560, 0, 128, 328, (128, 64), 2, 156, (6, 2)), (40, 21, 1560, 0, 128, 328, (128, 64), 2, 156, (4, 2)), (46, 21, 1560, 0, 128, 328, (128, 64), 2, 156, (4, 2)),
+    # three passes: the workspace leaves the unmasked pass three parts
+    (14, 12, 491, 77, 128, 663, (128, 64), 1, 33, None)])
+def test_temporal_parts_beside_the_pieces(H, F, P, T, D, t, blocks, w_s, w_t, cut):
+    n, got = profile_pieces(shape(H, F * P + T, D, blocks, F=F, T=T, w_s=w_s, w_t=w_t), t)
+    assert (got.n_full, got.n_masked) == cut if cut else n == 0
