@@ -1153,10 +1153,13 @@ int launch_one(AttnArgs a, int rows_total, hipStream_t stream) {
                         : MODE == kDense ? 8u * per_xcd : sparse_grid(a.so, a.BH);
   (void)hipGetLastError();   // drop any stale error left by earlier runtime calls of the process
   constexpr bool SPARSE_MODE = MODE == kSparse || MODE == kSparseExact || MODE == kSparseGather;
-  if (SPARSE_MODE && a.BH > 64)      // label classes over more than one 64-head word
-    hipLaunchKernelGGL((attn_kernel<D, NW, BN, MODE, SPARSE_MODE ? kWideLabelWords : 1, TEAMS>), dim3(grid), dim3(64 * NW * TEAMS), 0, stream, a);
-  else
-    hipLaunchKernelGGL((attn_kernel<D, NW, BN, MODE, 1, TEAMS, PIECED>), dim3(grid), dim3(64 * NW * TEAMS), 0, stream, a);
+  if constexpr (SPARSE_MODE && TEAMS == 1) {      // (two teams: 21 heads at most, see two_teams)
+    if (a.BH > 64) {      // label classes over more than one 64-head word
+      hipLaunchKernelGGL((attn_kernel<D, NW, BN, MODE, kWideLabelWords>), dim3(grid), dim3(64 * NW), 0, stream, a);
+      return hip_status(hipGetLastError());
+    }
+  }
+  hipLaunchKernelGGL((attn_kernel<D, NW, BN, MODE, 1, TEAMS, PIECED>), dim3(grid), dim3(64 * NW * TEAMS), 0, stream, a);
   return hip_status(hipGetLastError());
 }
 
