@@ -7,8 +7,8 @@ import torch
 import paper_2502_01776_amd as S
 from oracle import svg_oracle as O
 from workloads import get_config, make_plain_qkv
-from helpers import (f64, gpu_layer_in_place, gpu_layer_kv2, assert_attn_close, takes_split_form, takes_two_teams, DENSE, SPARSE, EXACT, GATHER)
-from test_gpu_lists import test_list_lengths as list_lengths, test_list_lengths_of_the_other_forms as list_lengths_of_the_other_forms
+from helpers import (f64, dev_i32, gpu_layer_in_place, gpu_layer_kv2, assert_attn_close, takes_split_form, takes_two_teams, DENSE, SPARSE, EXACT, GATHER)
+from test_gpu_lists import LENGTHS, random_lists, test_list_lengths as list_lengths, test_list_lengths_of_the_other_forms as list_lengths_of_the_other_forms
 
 MODES = {"dense": DENSE, "sparse": SPARSE, "exact": EXACT, "gather": GATHER}
 
@@ -62,6 +62,29 @@ def test_list_lengths(form, heads, two, D, last_tile):
         list_lengths(D, False, last_tile, heads)
     else:
         list_lengths_of_the_other_forms(form, (128, 64), D, last_tile, heads // 2)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("last_tile", [False, True])
+@pytest.mark.parametrize("D", [64, 128])
+def test_list_lengths_under_element_masks(D, last_tile):
+    """Three heads: two are few rows at head dimension 64, four more than 256 query tiles."""
+    sh, g = setup(3, D, 3, 2812, 0)
+    assert takes_two_teams(sh) and not takes_split_form(sh, EXACT)
+    rp, ci = random_lists(*S.svg_tile_counts(sh), last_tile, 3 * D + last_tile)
+    q, k, v = make_plain_qkv(1, 1, g.N, D, seed=D)
+    k = (k.float() * torch.linspace(0.2, 3.0, g.N)[None, None, :, None]).bfloat16()
+    o = gpu_layer_kv2(sh, *(x.repeat(1, 3, 1, 1).cuda() for x in (q, k, v)), torch.zeros(3, dtype=torch.uint8, device="cuda"),
+                      [dev_i32(x) for x in (rp, ci, rp, ci)], flags=S.SVG_ATTN_ELEMENT_MASK)[0]
+    got, (qh, kh, vh) = f64(o[0, 2]), (f64(x)[0, 0] for x in (q, k, v))
+    for a, n in enumerate(LENGTHS):
+        rows = np.arange(a * g.block_m, min(g.N, (a + 1) * g.block_m))
+        cols = np.concatenate([np.arange(b * g.block_n, min(g.N, (b + 1) * g.block_n)) for b in ci[rp[a]:rp[a + 1]]] or [np.zeros(0, np.int64)])
+        keep = O.spatial_mask(g, rows)[:, cols]
+        some = keep.any(1) if n else np.zeros(len(rows), bool)
+        assert (got[rows][~some] == 0).all(), f"{n} tiles: rows without keys"
+        if some.any():
+            assert_attn_close(torch.from_numpy(got[rows][some]), O.masked_attention(qh[rows[some]], kh[cols], vh[cols], keep[some], g.scale), f"{n} tiles")
 
 
 @pytest.mark.parametrize("D", [64, 128])
