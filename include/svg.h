@@ -94,8 +94,8 @@ size_t svg_workspace_bytes(const svg_shape_t* shape, int32_t t);
  * maximum, row sum) triples, so the cut changes the results only in fp32 rounding.  Calls
  * whose rows are few (the form that splits the keys over wavefronts) may cut the passes
  * otherwise, into no more parts in all.  Others run these, or, from 24 key tiles and frames of 4 block_n
- * tokens on, get the spatial pass's output out of the unmasked pass, with parts of their own for the two that
- * remain in the same workspace. */
+ * tokens on and unless that is estimated to take longer, get the spatial pass's output out of the unmasked pass, with
+ * parts of their own for the two that remain in the same workspace. */
 int svg_profile_plan(const svg_shape_t* shape, int32_t t, int32_t* n_full, int32_t* n_masked,
                      int32_t* full_bound);
 

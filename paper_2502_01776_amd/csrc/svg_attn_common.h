@@ -42,6 +42,7 @@ __device__ __forceinline__ u32x4 buffer_words(const void* base, unsigned bytes) 
 // not in front of this statement, so the statement holds all of it: one for s_mov, four for s_nop 3.  Two loads
 // share it (a statement with the same wait for every load cost 0.0-0.4 % of the attention passes, this one
 // nothing that could be measured).
+// m0 holds a byte address anywhere in the 160 KB of LDS: the second team of svg_teams.hip stages above 64 KB.
 // The statement overwrites m0 and says so; the compiler warns that it will not save a reserved register, once for
 // every place the function is inlined.  Nothing has to be saved: no other instruction of these kernels uses
 // m0 (a test looks through the compiler's output for one).
@@ -148,7 +149,7 @@ struct SparseOrder {
   int slots;   // workgroups resident on one XCD (sets the stride, see above)
   int parts_log2;      // workgroups reserved per tile with a text row: 1 << parts_log2; 0: none is taken in parts
   int nk;              // key tiles, what a tile with a text row keeps
-  int places;          // workgroups resident on the chip
+  int places;          // workgroups resident on the chip; two teams: as with one, the lines of sparse_slot were measured so, and all parts find a place (two_teams)
 };
 
 inline SparseOrder sparse_order(int BH, int nqt, int BM, int off, int video_end, int N, int slots, int places, int parts_log2, int nk) {
@@ -346,7 +347,7 @@ struct AttnArgs {
   const __bf16* v;
   const __bf16* k_t;          // sparse: P-outer copies of k and v read by temporal heads instead of k, v; may be null
   const __bf16* v_t;
-  void* o;                    // bf16 [B,H,N,D] (dense, sparse) or fp32 [3][BH][t][D] (profile)
+  void* o;                    // bf16 [B,H,N,D] (dense, sparse) or fp32 [slots][BH][t][D] (profile)
   const uint8_t* labels;      // sparse: per-head pattern, may be null
   const int32_t* row_table;   // gathering sparse form: token row of every P-outer row, nk * BN entries
   const int32_t* row_ptr[2];

@@ -26,8 +26,9 @@
 // output are issued one by one with the exponentials of tile j in between, four keys behind each, so that a wavefront covers its
 // own VALU work and two to a SIMD seldom want the same unit.  K and V images come from memory straight into LDS, two tiles to a
 // barrier.  At 119k tokens and 15 % of the tiles 12.81 ms where the form before, exponentials and products in phases of their own, took 13.51, and one
-// barrier a tile 12.95; 7 heads of 8187 rows 119.9 -> 100.4 us, 9 of 3335 43.7 -> 36.0.  Bound by power: 2.67e7 cycles at 1.93 GHz, before
-// 2.88e7 at 2.01; matrix unit 51 % of the cycles, VALU 55 %.  A raised wave priority from the first product to the last: 12.93 ms, and text-row
+// barrier a tile 12.95; 7 heads of 8187 rows 119.9 -> 100.4 us, 9 of 3335 43.7 -> 36.0.  In counters 2.89e7 cycles at 2.04 GHz became
+// 2.64e7 at 1.92: the clock falls as the units fill, matrix unit 49 -> 51 % of the cycles, VALU 64 -> 70 %; waiting for data and barriers a wavefront spends 17 % of its
+// time, waiting for issue 31 %.  A raised wave priority from the first product to the last: 12.93 ms, and text-row
 // tiles taken in parts, which run beside other workgroups, late (2 heads of 51074 rows 311 -> 334 us).  The maximum of the next tile
 // taken behind its products instead of in front of the exponentials: no difference.
 //
@@ -87,7 +88,9 @@ constexpr int kAmaxPieces = 16;            // 16-byte pieces per thread
 // is nothing beside a pass over a long head; without it a whole layer of 960 rows and 6 heads takes 61.9
 // instead of 62.5 us).  The lanes of a wavefront exchange their maxima in registers, where ten rounds through LDS with a barrier each took
 // 4-5 us of a short block: the whole quantisation of 24 heads of 960 rows 16.5 -> 12.5 us, 20 of 1442 19.5 -> 14.1, 8 of 3910 20.1 -> 15.2, 12 of 8000
-// 39.6 -> 37.0, 24 of 119056 1005 -> 1000; 40 of 32760, whose tensors leave less of themselves in the memory-side cache, 442 -> 446.
+// 39.6 -> 37.0, 24 of 119056 1000 -> 998; 40 of 32760 441 -> 445 on one
+// card, 435 -> 437 on another (24 of them 268 -> 269, 263 -> 263).  Four or sixteen loads at a time, four in a loop, and tiles converted in the reverse order, those read last
+// first, are no faster there (443-445 and 438-440); four in a loop cost short heads 6 %.
 template <int THREADS>
 __global__ __launch_bounds__(THREADS) void fp8_amax_kernel(const u32x4* q, const u32x4* k, const u32x4* v,
                                                            unsigned long long pieces_per_head, unsigned* amax,
@@ -459,7 +462,7 @@ __global__ __launch_bounds__(64 * kSplitWaves, 2) void attn_fp8_split_kernel(Fp8
 template <int LW>
 __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * kStages * kTileBytes];      // K images, then V images
-  static_assert(sizeof(lds) <= 65536, "the direct loads take a 16-bit LDS address");
+  static_assert(sizeof(lds) <= 81920, "two workgroups fit a CU");
 
   // heavy query tiles first, then an eighth of each label's sequence of tiles (the same
   // dispatch order as the bf16 kernel)

@@ -6,7 +6,7 @@
 // results (output, maximum, row sum) are merged through LDS at the end.  Bound as attn_kernel is with two workgroups on a CU, less the
 // barrier both teams share: 10-15 % of the rate once there are several workgroups to a CU, so it is taken for the first only.  By passes of 1 to 48
 // heads of 1500 to 24000 rows: dense 1.20 times as fast (2 heads of 12142 rows at head dimension 128 214 -> 164 us, 2 of 14545 at 64 171 -> 129),
-// exact masks 1.10 (5 of 5140 92 -> 70), sparse 1.06 (3 of 14112 105 -> 79), gathering 1.05; where text-row tiles are the time of the pass 0.98-1.01.
+// exact masks 1.10 (5 of 5140 92 -> 70), sparse 1.06 (3 of 9900 85 -> 68), gathering 1.05 (89 -> 74); where text-row tiles are the time of the pass 0.98-1.01.
 #include "svg_attn_kernel.h"
 
 namespace svg {
