@@ -26,7 +26,10 @@
 // output are issued one by one with the exponentials of tile j in between, four keys behind each, so that a wavefront covers its
 // own VALU work and two to a SIMD seldom want the same unit.  K and V images come from memory straight into LDS, two tiles to a
 // barrier.  At 119k tokens and 15 % of the tiles 12.81 ms where the form before, exponentials and products in phases of their own, took 13.51, and one
-// barrier a tile 12.95; 7 heads of 8187 rows 119.9 -> 100.4 us, 9 of 3335 43.7 -> 36.0.  In counters 2.89e7 cycles at 2.04 GHz became
+// barrier a tile 12.95; 7 heads of 8187 rows 119.9 -> 100.4 us, 9 of 3335 43.7 -> 36.0.  Tiles go in pairs.  An odd list was rounded up by a tile of zeros behind it, and the one of zeros
+// in front of every list cost it products too, so short lists lost to the form before (61 calls of 184-18676 rows 1.05 times its time, up to 1.16); now the first tile
+// of an odd list is weighted by itself before the pairs: 0.998 of the form before, 81 heads of 539 rows 16.9 -> 15.1 us, 20 of 4000 54.1 -> 51.8, 119k tokens 13.65 -> 13.57 ms.  Leaving
+// the loop between the two tiles of the last pair instead made the loop worse (119k 13.90 -> 14.41).  Even lists of two to four tiles remain up to 1.13 times the form before.  In counters 2.89e7 cycles at 2.04 GHz became
 // 2.64e7 at 1.92: the clock falls as the units fill, matrix unit 49 -> 51 % of the cycles, VALU 64 -> 70 %; waiting for data and barriers a wavefront spends 17 % of its
 // time, waiting for issue 31 %.  A raised wave priority from the first product to the last: 12.93 ms, and text-row
 // tiles taken in parts, which run beside other workgroups, late (2 heads of 51074 rows 311 -> 334 us).  The maximum of the next tile
@@ -607,9 +610,9 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
     }
     sc[i >> 1] = product(k_op, qreg[i & 1], sc[i >> 1]);
   };
-  auto mask_tail = [&](f32x16 (&sc)[2], int tile) {       // keys beyond N in the last tile, and the tile that rounds a list up to an even number
-    if (tile != kNoTile && !(ragged && tile == a.nk - 1)) return;
-    int lim = (tile == kNoTile ? 0 : a.N - tile * kBN) - 4 * g;
+  auto mask_tail = [&](f32x16 (&sc)[2], int tile) {       // keys beyond N in the last tile
+    if (!(ragged && tile == a.nk - 1)) return;
+    int lim = a.N - tile * kBN - 4 * g;
     asm volatile("" : "+v"(lim));        // keeps this rarely taken code out of every tile
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
@@ -644,26 +647,39 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
   // between the products of tile j + 1's scores and of tile j - 1's row sums and output, a product and four keys at a time.
   // Trips come in pairs, so that both sets of scores stay in their registers, with one barrier a pair: at its start LDS holds K of tiles
   // j + 1 and j + 2 and V of j - 1 and j, and the two tiles behind them are on their way into the places of those before.
-  // What lies beyond the list (and in front of it) is a tile of zeros without weight.
+  // The first tile of an odd list is weighted before them; with an even one a tile of zeros without weight lies in front.
+  const int odd = entries & 1;
+  const int col0 = odd ? list.next() : kNoTile;
   int col = list.next(), col1 = list.next(), col2 = list.next();
-  if (col != kNoTile) {
-    load_v(kNoTile, 3);
-    load_k(col, 0);
-    load_v(col, 0);
-    load_k(col1, 1);
-    load_k(col2, 2);
+  if (entries > 0) {
+    int j = odd, col3 = kNoTile, col4 = kNoTile;
+    load_v(col0, j - 1);
+    load_k(col, j);
+    load_v(col, j);
+    load_k(col1, j + 1);
+    load_k(col2, j + 2);
+    if (odd) load_k(col0, 0);
     wait_loads_to_lds<0>();
     __syncthreads();
     asm volatile("" ::"v"(qreg[0]), "v"(qreg[1]));
-    i32x8 op[4];
+    auto scores = [&](f32x16 (&sc)[2], int at, int tile) {
+      i32x8 op[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) op[i] = k_operand(0, i);
+      for (int i = 0; i < 4; ++i) op[i] = k_operand(at, i);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) first_product(sacc[0], op[i], i);
-    mask_tail(sacc[0], col);
+      for (int i = 0; i < 4; ++i) first_product(sc, op[i], i);
+      mask_tail(sc, tile);
+    };
     pb[1] = i32x8{0, 0, 0, 0, 0, 0, 0, 0};
-    __syncthreads();      // the first pair stages K of tile 4 over tile 0's
-    int j = 0, col3 = kNoTile, col4 = kNoTile;
+    if (odd) {
+      scores(sacc[1], 0, col0);
+      m_run = fmaxf(m_run, tile_maximum(sacc[1]));
+      mc = m_run * c_log2 - kWeightShift;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) weights4(sacc[1], pb[1], i);
+    }
+    scores(sacc[0], j, col);
+    __syncthreads();      // the first pair stages K of its fourth tile over the first one's
     auto trip = [&](auto set) {
       constexpr int CUR = decltype(set)::value;      // which set of scores is tile j's
       f32x16(&now)[2] = sacc[CUR];
@@ -713,7 +729,7 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
       mask_tail(next, CUR == 0 ? col1 : col2);
       ++j;
     };
-    do {
+    while (col != kNoTile) {
       col3 = list.next();
       col4 = list.next();
       trip(std::integral_constant<int, 0>{});
@@ -723,7 +739,7 @@ __global__ __launch_bounds__(256, 2) void attn_fp8_kernel(Fp8Args a) {
       col = col2;
       col1 = col3;
       col2 = col4;
-    } while (col != kNoTile);
+    }
     lacc = row_sum(select, pb[1], lacc);
 #pragma unroll
     for (int db = 0; db < 4; ++db) oacc[db] = product(v_operand(j - 1, db), pb[1], oacc[db]);
