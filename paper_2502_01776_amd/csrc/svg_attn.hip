@@ -95,12 +95,15 @@ struct PieceArgs {
   PieceRule rule;
   int bn;
 };
+struct NoPieces {};
+template <bool PIECES>
+using PieceArgsIf = std::conditional_t<PIECES, PieceArgs, NoPieces>;      // (100 bytes of arguments; and gridDim.x brings 256, see clear_tickets)
 
 template <int D, int NF, int NM, bool PIECES, int PASSES>
 __global__ __launch_bounds__(kErrThreads) void profile_error_kernel(const float* ws, const float2* stats, const int32_t* rows,
                                                                     int BH, int t, int n_full, int n_masked, float scale_log2, int off,
                                                                     int video_end, float2* partial, unsigned* tickets,
-                                                                    uint8_t* labels, float* mse, PieceArgs pieces) {
+                                                                    uint8_t* labels, float* mse, unsigned n_blocks, PieceArgsIf<PIECES> pieces) {
   constexpr int LANES = D / 4, ROWS = err_rows(D);
   const int bh = blockIdx.y;
   const int c = threadIdx.x % LANES;
@@ -182,22 +185,22 @@ __global__ __launch_bounds__(kErrThreads) void profile_error_kernel(const float*
     sum_s += wave_part[w].x;
     sum_t += wave_part[w].y;
   }
-  if (gridDim.x > 1 && tickets == nullptr) {
-    if (threadIdx.x == 0) partial[(size_t)bh * gridDim.x + blockIdx.x] = make_float2(sum_s, sum_t);
+  if (n_blocks > 1 && tickets == nullptr) {
+    if (threadIdx.x == 0) partial[(size_t)bh * n_blocks + blockIdx.x] = make_float2(sum_s, sum_t);
     return;
   }
-  if (gridDim.x > 1) {
-    float* const mine = reinterpret_cast<float*>(partial + (size_t)bh * gridDim.x);
+  if (n_blocks > 1) {
+    float* const mine = reinterpret_cast<float*>(partial + (size_t)bh * n_blocks);
     unsigned ticket = 0;
     if (threadIdx.x == 0) {
       __hip_atomic_store(mine + 2 * blockIdx.x, sum_s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(mine + 2 * blockIdx.x + 1, sum_t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       ticket = __hip_atomic_fetch_add(tickets + bh, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (__builtin_amdgcn_readfirstlane(ticket) != gridDim.x - 1) return;
+    if (__builtin_amdgcn_readfirstlane(ticket) != n_blocks - 1) return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");      // for the lanes that took no ticket
     sum_s = sum_t = 0.f;
-    for (unsigned i = threadIdx.x; i < gridDim.x; i += 64) {
+    for (unsigned i = threadIdx.x; i < n_blocks; i += 64) {
       sum_s += __hip_atomic_load(mine + 2 * i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       sum_t += __hip_atomic_load(mine + 2 * i + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -223,12 +226,12 @@ __global__ __launch_bounds__(64) void profile_label_kernel(const float2* partial
 }
 
 template <int D, int NF, bool PIECES>
-void launch_error(const AttnArgs& a, int blocks, const PieceArgs& pieces, const float2* stats, float2* partial, uint8_t* labels, float* mse, hipStream_t stream) {
+void launch_error(const AttnArgs& a, int blocks, const PieceArgsIf<PIECES>& pieces, const float2* stats, float2* partial, uint8_t* labels, float* mse, hipStream_t stream) {
   auto kernel = a.plan.n_masked == 1 ? profile_error_kernel<D, NF, 1, PIECES, 1> : profile_error_kernel<D, NF, kMaxMaskedParts, PIECES, 1>;
   if constexpr (!PIECES)
     if (blocks == 1 && a.t > err_rows(D)) kernel = a.plan.n_masked == 1 ? profile_error_kernel<D, NF, 1, false, 2> : profile_error_kernel<D, NF, kMaxMaskedParts, false, 2>;
   hipLaunchKernelGGL(kernel, dim3(blocks, a.BH), dim3(kErrThreads), 0, stream, static_cast<const float*>(a.o), stats, a.rows,
-                     a.BH, a.t, PIECES ? a.pieces : NF, a.plan.n_masked, a.scale_log2, a.off, a.video_end, partial, a.tickets, labels, mse, pieces);
+                     a.BH, a.t, PIECES ? a.pieces : NF, a.plan.n_masked, a.scale_log2, a.off, a.video_end, partial, a.tickets, labels, mse, (unsigned)blocks, pieces);
 }
 
 template <int D>
@@ -239,10 +242,10 @@ int launch_error_parts(const Geo& g, const AttnArgs& a, int blocks, const float2
   if (a.pieces > 7) launch_error<D, kMaxPieces, true>(a, blocks, pieces, stats, partial, labels, mse, stream);
   else if (a.pieces) launch_error<D, 7, true>(a, blocks, pieces, stats, partial, labels, mse, stream);
   else switch (a.plan.n_full) {      // the numbers of parts profile_plan and profile_cut give the unmasked pass
-    case 1: launch_error<D, 1, false>(a, blocks, pieces, stats, partial, labels, mse, stream); break;
-    case 3: launch_error<D, 3, false>(a, blocks, pieces, stats, partial, labels, mse, stream); break;
-    case 4: launch_error<D, 4, false>(a, blocks, pieces, stats, partial, labels, mse, stream); break;
-    case 6: launch_error<D, 6, false>(a, blocks, pieces, stats, partial, labels, mse, stream); break;
+    case 1: launch_error<D, 1, false>(a, blocks, {}, stats, partial, labels, mse, stream); break;
+    case 3: launch_error<D, 3, false>(a, blocks, {}, stats, partial, labels, mse, stream); break;
+    case 4: launch_error<D, 4, false>(a, blocks, {}, stats, partial, labels, mse, stream); break;
+    case 6: launch_error<D, 6, false>(a, blocks, {}, stats, partial, labels, mse, stream); break;
     default: return SVG_ERR_UNSUPPORTED;
   }
   const int rc = hip_status(hipGetLastError());

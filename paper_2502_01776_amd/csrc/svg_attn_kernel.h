@@ -182,7 +182,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
     const int unit = loc / pairs_per_xcd;
     const int pair = xcd * pairs_per_xcd + (loc - unit * pairs_per_xcd);
     const int nm = a.plan.n_masked, ns = PIECED ? 0 : nm;      // parts of the temporal and of the spatial pass
-    clear_tickets(a);
+    clear_tickets<THREADS * TEAMS>(a);
     if (unit >= ns + nm + a.plan.n_full || pair >= pairs) return;
     // the masked passes first: their workgroups are the longest ones (mask work on top of
     // about as many tiles), so they should not be the last to start

@@ -37,7 +37,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void split_kernel(AttnArgs a) {
   if (MODE == kProfile) {
     const int pairs = a.BH * a.nqt, pairs_per_xcd = (pairs + 7) >> 3, nm = a.plan.n_masked;
     const int unit = loc / pairs_per_xcd, pair = xcd * pairs_per_xcd + (loc - unit * pairs_per_xcd);
-    clear_tickets(a);
+    clear_tickets<64 * kWaves>(a);
     if (unit >= a.plan.slots() || pair >= pairs) return;
     variant = unit < nm ? 1 : unit < 2 * nm ? 2 : 0;
     chunk = unit < nm ? unit : unit < 2 * nm ? unit - nm : unit - 2 * nm;

@@ -164,6 +164,13 @@ def test_three_passes_of_profiling_carry_nothing_of_the_pieces(compiled):
         assert int(spilled[n]) <= (16 if "ELi4ELi64ELi2E" in n else 0), n
 
 
+def test_kernels_of_profiling_take_no_arguments_of_their_launch(compiled):
+    """blockDim and gridDim come in 256 bytes of arguments behind the own ones, which short launches notice."""
+    sizes = dict((n, int(b)) for b, n in re.findall(r"\.kernarg_segment_size: (\d+)\n(?:(?!\.name:).*\n)*?\s*\.name: +(\w+)\n", compiled[0]))
+    for n in [n for n in sizes if "attn_kernel" in n or "profile_error_kernel" in n]:
+        assert sizes[n] <= 352, (n, sizes[n])
+
+
 def test_the_compiler_has_nothing_to_say(compiled):
     """(a warning per inlined load, 600 of them, once hid whatever else there was)"""
     lines = [l for l in compiled[2].splitlines() if "warning" in l and "--hip-link" not in l]
