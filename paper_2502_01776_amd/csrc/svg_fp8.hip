@@ -95,17 +95,19 @@ constexpr int kAmaxPieces = 16;            // 16-byte pieces per thread
 // card, 435 -> 437 on another (24 of them 268 -> 269, 263 -> 263).  Four or sixteen loads at a time, four in a loop, and tiles converted in the reverse order, those read last
 // first, are no faster there (443-445 and 438-440); four in a loop cost short heads 6 %.
 template <int THREADS>
-__global__ __launch_bounds__(THREADS) void fp8_amax_kernel(const u32x4* q, const u32x4* k, const u32x4* v,
+__global__ __launch_bounds__(THREADS, THREADS == 1024 ? 8 : 4) void fp8_amax_kernel(const u32x4* q, const u32x4* k, const u32x4* v,
                                                            unsigned long long pieces_per_head, unsigned* amax,
                                                            int BH) {
   const int bh = blockIdx.y, tensor = blockIdx.z;
   const u32x4* src = (tensor == 0 ? q : tensor == 1 ? k : v) + (size_t)bh * pieces_per_head;
   const unsigned long long base = (unsigned long long)blockIdx.x * (THREADS * kAmaxPieces) + threadIdx.x;
   unsigned m = 0;
-  // as many loads as the registers hold on their way at once
-  constexpr int BATCH = THREADS == 1024 ? 16 : 8;
-#pragma unroll
+  // loads on their way at once: with 1024 threads what two blocks to a compute unit leave registers for (16 were one block: 97 heads of 101 rows 9.6 -> 11.4 us, now 8.9; 145 of
+  // 194 13.5 -> 15.5, now 12.6; 102 of 740 28.5 -> 30.1, now 29.0; eight 9.5, 13.4 and 29.4), and none of a batch that lies behind the head
+  constexpr int BATCH = THREADS == 1024 ? 4 : 8, UNROLL = THREADS == 1024 ? 1 : kAmaxPieces / BATCH;
+#pragma unroll UNROLL
   for (int i0 = 0; i0 < kAmaxPieces; i0 += BATCH) {
+    if (THREADS == 1024 && base - threadIdx.x + i0 * THREADS >= pieces_per_head) break;
     u32x4 x[BATCH];
 #pragma unroll
     for (int i = 0; i < BATCH; ++i) {

@@ -171,6 +171,13 @@ def test_kernels_of_profiling_take_no_arguments_of_their_launch(compiled):
         assert sizes[n] <= 352, (n, sizes[n])
 
 
+def test_two_blocks_of_the_largest_magnitudes_fit_a_compute_unit(compiled):
+    """1024 threads each, for heads of up to 1024 rows: 64 vector registers."""
+    used = dict(re.findall(r"\.name: +(\w+)\n(?:(?!\.name:).*\n)*?\s*\.vgpr_count: +(\d+)", compiled[0]))
+    for n in [n for n in used if "fp8_amax_kernelILi1024E" in n]:
+        assert int(used[n]) <= 64
+
+
 def test_the_compiler_has_nothing_to_say(compiled):
     """(a warning per inlined load, 600 of them, once hid whatever else there was)"""
     lines = [l for l in compiled[2].splitlines() if "warning" in l and "--hip-link" not in l]
