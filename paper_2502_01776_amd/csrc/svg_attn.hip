@@ -305,6 +305,17 @@ AttnArgs base_args(const Geo& g, const void* q, const void* k, const void* v, vo
 
 }  // namespace
 
+// Equal blocks, one more or less to an XCD, except where whole blocks to all XCDs leave no more tiles than an XCD has compute units: one XCD then
+// has a tile to each of its compute units behind the others, and its neighbours in L2 stay 64.  512 k + r tiles, blocks of 64 against equal ones: r = 1-32
+// 109.6 -> 114.2 us (27 heads of 19 tiles, head dimension 128; 58.5 -> 61.4 at 64), 1511 -> 1610 (60 of 60), 0.94-1.00 in 40 calls; r = 40-128 146.2 -> 136.1 (24 of 23; 92.3 -> 73.6),
+// 187.1 -> 182.2 (56 of 19; 110.8 -> 97.3), 1.01-1.32 in 19.  With 32-row tiles 0.98-1.00 and 0.98-1.25.
+namespace attn {
+int dense_cohort(int tiles, int most) {
+  const int blocks = (tiles + 8 * most - 1) / (8 * most);
+  return blocks > 1 && tiles - (blocks - 1) * 8 * most <= kXcdUnits ? most : (tiles + 8 * blocks - 1) / (8 * blocks);
+}
+}  // namespace attn
+
 int launch_attention(const Geo& g, const void* q, const void* k, const void* v, const void* k_t, const void* v_t,
                      void* o, const uint8_t* labels, const int32_t* row_ptr_s, const int32_t* col_idx_s,
                      const int32_t* row_ptr_t, const int32_t* col_idx_t, bool sparse,

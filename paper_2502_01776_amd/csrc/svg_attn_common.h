@@ -143,6 +143,7 @@ constexpr int kWideLabelWords = 4;     // label classes are formed for up to 64 
 
 struct SparseOrder {
   int g_lo;    // a head's query tiles without a text row are [g_lo, g_lo + nl)
+constexpr int kXcdUnits = 32;          // compute units of an XCD
   int nl;
   int nh;      // tiles with a text row per head (the others, ascending)
   int hmax;    // workgroups per XCD reserved for them
@@ -399,6 +400,9 @@ __device__ __forceinline__ int order_bin(int n, int off, int video_end, int P) {
   const int p = (n - off) % P;
   return 1 + (int)(((long long)p * (kOrderBins - 1)) / P);
 }
+// Query tiles that go to one XCD in a row in a dense pass, `most` at the most.
+int dense_cohort(int tiles, int most);
+
 
 // Lanes l and l^32 own the two halves of one query's keys.  v_permlane32_swap with
 // both operands equal returns {x[l % 32], x[32 + l % 32]} in every lane, so the

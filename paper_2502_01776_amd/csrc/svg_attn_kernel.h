@@ -87,7 +87,7 @@ using namespace attn;
 constexpr int kPrioOutput = 1;
 constexpr int prio_scores(bool sequential) { return sequential ? 2 : 1; }
 // Dense: the most consecutive query tiles that share an XCD (and its L2) at a time.  Fewer where 64 would not deal the XCDs equal
-// numbers of tiles (launch_one): 186 tiles in 64s use three of the eight XCDs.  Blocks of 64 against equal ones: 186 tiles of 6 heads
+// numbers of tiles (dense_cohort): 186 tiles in 64s use three of the eight XCDs.  Blocks of 64 against equal ones: 186 tiles of 6 heads
 // 114.6 -> 78.9 us at head dimension 128 and 64.3 -> 51.0 at 64, 256 116.9 -> 84.8 and 67.0 -> 55.3, 384 169 -> 148 and 96.7 -> 93.1, 576
 // 393 -> 360 and 244 -> 191, 768 650 -> 540 and 390 -> 300, 2112 1029 -> 1007 and 592 -> 552; multiples of 512 have blocks of 64 as before.
 constexpr int kCohort = 64;
@@ -1143,7 +1143,7 @@ int launch_one(AttnArgs a, int rows_total, hipStream_t stream) {
   a.total = a.BH * a.nqt;
   constexpr int COHORT = kCohort / TEAMS;
   const int blocks = (a.total + 8 * COHORT - 1) / (8 * COHORT);      // dense: blocks of consecutive tiles per XCD
-  a.cohort = (a.total + 8 * blocks - 1) / (8 * blocks);
+  a.cohort = dense_cohort(a.total, COHORT);
   const unsigned per_xcd = (unsigned)blocks * (unsigned)a.cohort;
   if (MODE == kSparse || MODE == kSparseExact || MODE == kSparseGather) {
     const int per_cu = NW == 4 ? waves_per_simd(D, NW, MODE) : 2;

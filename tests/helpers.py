@@ -213,6 +213,11 @@ def takes_two_teams(shape):
     return _rule("_ZN3svg4attn9two_teamsERKNS_3GeoE", C.c_bool, C.byref(_geo(shape)))
 
 
+def dense_cohort(tiles, most):
+    """Query tiles that go to one XCD in a row in a dense pass."""
+    return _rule("_ZN3svg4attn12dense_cohortEii", C.c_int, C.c_int(tiles), C.c_int(most))
+
+
 def takes_fp8_split_form(shape):
     return _rule("_ZN3svg14fp8_split_formERKNS_3GeoE", C.c_bool, C.byref(_geo(shape)))
 

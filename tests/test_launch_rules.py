@@ -3,7 +3,7 @@ import pytest
 
 import paper_2502_01776_amd as S
 from workloads import get_config
-from helpers import DENSE, EXACT, GATHER, PROFILE, SPARSE, profile_cuts, profile_pieces, error_blocks, takes_fp8_split_form, takes_split_form
+from helpers import DENSE, EXACT, GATHER, PROFILE, SPARSE, profile_cuts, profile_pieces, error_blocks, takes_fp8_split_form, takes_split_form, dense_cohort
 
 
 def shape(H, N, D=128, blocks=(128, 64), F=1, T=0, **kw):
@@ -131,3 +131,12 @@ def test_error_blocks_of_a_head(D):
 def test_temporal_parts_beside_the_pieces(H, F, P, T, D, t, blocks, w_s, w_t, cut):
     n, got = profile_pieces(shape(H, F * P + T, D, blocks, F=F, T=T, w_s=w_s, w_t=w_t), t)
     assert (got.n_full, got.n_masked) == cut if cut else n == 0
+
+
+@pytest.mark.parametrize("most", [64, 32])
+def test_blocks_of_dense_tiles(most):
+    """Equal ones, but whole ones where they leave one XCD a tile to each of its 32 compute units at the most; every tile in one of them."""
+    for tiles in list(range(1, 40 * most)) + [10 ** 6, 10 ** 6 + 77]:
+        n, got = -(-tiles // (8 * most)), dense_cohort(tiles, most)
+        left = tiles - (n - 1) * 8 * most
+        assert got == (most if n > 1 and left <= 32 else -(-tiles // (8 * n))) and 1 <= got <= most and 8 * n * got >= tiles
