@@ -148,13 +148,15 @@ int profile_pieces(const Geo& g, int t, const ProfilePlan& plan, ProfilePlan* cu
 // a call 1-2 us.  A ticket costs an exchange with the memory behind the L2 caches, which slows the other blocks down: launch against tickets, whole calls,
 // 4 blocks 18.6 -> 17.7 us and 17.1 -> 16.2, 24 blocks 21.9 -> 21.2, 40 25.2 -> 24.7, 60 78.7 -> 78.4; 76 349.8 -> 350.0, 82 70.3 -> 70.6 and 85.4 -> 85.8, 100 86.5 -> 87.1, 144
 // 95.1 -> 96.4, 200 94.7 -> 96.8, 440 177.6 -> 184.8.
-// Two passes in one block need neither.  The second costs what the parts to be merged cost, 0.5-2 us, and that is less than a ticket with up to three
+// Two passes in one block need neither.  The second costs what its rows and the parts to be merged cost, 0.5-2 us, and that is less than a ticket where it is three eighths full at most (24-58
+// us, 46 calls: 0.4 us less, and 0-4 % of 1-32 heads with 2 rows in it; half full even, full 2-11 % more), with up to three
 // parts of the unmasked pass (6 heads of 1200 rows 18.4 -> 17.8 us and 16.7 -> 16.0, 12 18.8 -> 18.6, 30 27.3 -> 26.9 and 21.9 -> 21.1; but four and four parts 12 heads 20.8 -> 21.9, 20
 // 24.3 -> 25.7, six and four 29.5 -> 31.2), and less than a launch with all but the many outputs of pieces: 50 heads of 2400 rows 53.3 -> 52.0, 80 61.6 -> 58.9, 160 of 1200
 // 52.7 -> 48.7, 180 of 4800 146.1 -> 142.9; in pieces 64 94.9 -> 95.6, 80 95.2 -> 96.3.
 int error_blocks(const Geo& g, int t, const ProfilePlan& cut, int pieces) {
   const int passes = (t + err_rows(g.D) - 1) / err_rows(g.D);
-  const bool one_block = passes == 2 && !pieces && (cut.n_full <= 3 || 2ll * g.B * g.H > kTicketBlocks);
+  const bool nearly_one = 8 * (t - err_rows(g.D)) <= 3 * err_rows(g.D);
+  const bool one_block = passes == 2 && !pieces && (cut.n_full <= 3 || nearly_one || 2ll * g.B * g.H > kTicketBlocks);
   return one_block ? 1 : passes;
 }
 

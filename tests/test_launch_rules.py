@@ -106,15 +106,17 @@ def test_pieces_of_the_unmasked_pass_fit_the_workspace(D, blocks):
 
 @pytest.mark.parametrize("D", [64, 128])
 def test_error_blocks_of_a_head(D):
-    """One to a pass over its rows; two passes in one block where that is less than what brings two blocks together."""
+    """One to a pass over its rows; two passes in one block where that is less than what brings two blocks together: few parts, a second pass of
+    at most three eighths, or blocks too many for tickets."""
     rows = 4096 // D
     few, four, many = shape(20, 1200, D), shape(20, 1680, D), shape(33, 2400, D, F=10)
     pieces = shape(200, 4914, D, F=6)
     assert [error_blocks(s, rows) for s in (few, four, many, pieces)] == [1, 1, 1, 1]
-    for t in (rows + 1, 2 * rows):
+    for t in (rows + 1, rows * 11 // 8, rows * 11 // 8 + 1, 2 * rows):
         assert profile_cuts(few, t)[1].n_full <= 3 and profile_cuts(four, t)[1].n_full == 4 and profile_pieces(pieces, t)[0]
-        assert [error_blocks(s, t) for s in (few, four, many, pieces)] == [1, 2, 1, 2]
-        assert [error_blocks(shape(H, 2400, D, F=10), t) for H in (31, 32)] == [2, 2]
+        two = 1 if t <= rows * 11 // 8 else 2
+        assert [error_blocks(s, t) for s in (few, four, many, pieces)] == [1, two, 1, 2]
+        assert [error_blocks(shape(H, 2400, D, F=10), t) for H in (31, 32)] == [two, two]
     assert [error_blocks(s, 2 * rows + 1) for s in (few, four, many, pieces)] == [3, 3, 3, 3]
 
 
