@@ -128,7 +128,11 @@ struct TileList {
 //    ascending query tiles); every XCD takes one contiguous eighth of the spatial sequence
 //    and one of the temporal sequence, the one with the longer lists first.  Each XCD so gets
 //    the same share of both kinds of work whatever the labels are, and consecutive workgroups
-//    of an XCD still are nearby query tiles of one head (overlapping key windows).
+//    of an XCD still are nearby query tiles of one head (overlapping key windows).  Where a compute unit holds one workgroup (two teams)
+//    and the 32 of an XCD would not do for both eighths rounded up by themselves, what the second sequence has beyond a multiple of eight goes to the XCDs that
+//    the first has left out (xcd_share): 138 and 115 tiles gave an XCD 33 (11 heads of 2910 rows 19.6 us with one team, 23.4 with two, so 17.4, exact
+//    24.1, 28.1, 20.7; head dimension 128 29.0, 35.0, 26.1).  Not so elsewhere: the last tile of an eighth has a short list at the end of a sequence (6 heads of 21885 rows with the first-frame sink, 1026 tiles for 512 places, 478
+//    -> 578 us), and text-row tiles decide how full an XCD is where there are any (0.88-1.07).
 //  * Inside the part of a head that an XCD takes, the query tiles are dispatched with a stride:
 //    0, r, 2r, ..., then 1, r+1, ...  A workgroup walks its list one key tile per tile time, the
 //    window of query tile g + 1 lies BM / BN = 2 key tiles above that of g, and in steady state
@@ -139,11 +143,11 @@ struct TileList {
 //    the two patterns differ in length).
 // With more than 256 heads the labels are not looked at: one sequence in head order.
 // --------------------------------------------------------------------------------------------
+constexpr int kXcdUnits = 32;          // compute units of an XCD
 constexpr int kWideLabelWords = 4;     // label classes are formed for up to 64 * kWideLabelWords heads
 
 struct SparseOrder {
   int g_lo;    // a head's query tiles without a text row are [g_lo, g_lo + nl)
-constexpr int kXcdUnits = 32;          // compute units of an XCD
   int nl;
   int nh;      // tiles with a text row per head (the others, ascending)
   int hmax;    // workgroups per XCD reserved for them
@@ -177,12 +181,20 @@ inline unsigned sparse_grid(const SparseOrder& so, int BH) {
   return 8u * (unsigned)(((long long)so.hmax << so.parts_log2) + (long long)BH * so.nl / 8 + 2);
 }
 
+// Where the share of XCD xcd of n things begins if the n % 8 left over go one each to the XCDs from first_extra on, XCD 0 behind XCD 7.
+__host__ __device__ inline int xcd_share(long long n, int xcd, int first_extra) {
+  const int extra = (int)(n & 7), wrapped = first_extra + extra - 8;
+  const int behind = xcd - first_extra;
+  const int given = (wrapped > 0 ? (xcd < wrapped ? xcd : wrapped) : 0) + (behind < 0 ? 0 : behind < extra ? behind : extra);
+  return (int)(xcd * (n >> 3)) + given;
+}
+
 // Which (head, query tile, pattern) does this workgroup take?  false: none.  For a tile without
 // text rows, cl is its index in its label's sequence and head_cl0 the index of its head's first
 // tile there (cl = -1 for a heavy tile).  Every value returned is the same in all lanes.
 // (LW: 64-head words of label bits; the kernels are built for 1 and for kWideLabelWords, and the
 // launcher takes the wide form only when there are more than 64 heads)
-template <int LW>
+template <int LW, int TEAMS = 1>
 __device__ __forceinline__ bool sparse_slot(const SparseOrder so, const int BH, const uint8_t* labels,
                                             const int32_t* rp_s, const int32_t* rp_t, const int xcd, const int loc,
                                             int& bh, int& grp, int& pat, int& cl, int& head_cl0, int& part) {
@@ -239,8 +251,15 @@ __device__ __forceinline__ bool sparse_slot(const SparseOrder so, const int BH, 
   if (nT > 0 && nS > 0) first = nnz_t > nnz_s;
   const int nA = first ? nT : nS;
   const long long NA = (long long)nA * so.nl, NB = (long long)(BH - nA) * so.nl;
-  const int a0 = (int)((xcd * NA) >> 3), a1 = (int)(((xcd + 1) * NA) >> 3);
-  const int b0 = (int)((xcd * NB) >> 3), b1 = (int)(((xcd + 1) * NB) >> 3);
+  int a0, a1, b0, b1;
+  if (TEAMS > 1 && so.nh == 0 && BH * so.nl > 8 * kXcdUnits - 16) {
+    const int left = (int)(NA & 7);
+    a0 = xcd_share(NA, xcd, 0), a1 = xcd_share(NA, xcd + 1, 0);
+    b0 = xcd_share(NB, xcd, left), b1 = xcd_share(NB, xcd + 1, left);
+  } else {
+    a0 = (int)((xcd * NA) >> 3), a1 = (int)(((xcd + 1) * NA) >> 3);
+    b0 = (int)((xcd * NB) >> 3), b1 = (int)(((xcd + 1) * NB) >> 3);
+  }
   int c = first;
   if (l < a1 - a0) {
     cl = a0 + l;
@@ -381,6 +400,9 @@ bool split_form(const Geo& g, int mode, int t);      // does the split form take
 bool split_sorts_rows(int t);                        // profiling: needs no row order from profile_order_kernel
 int launch_split(const Geo& g, AttnArgs a, int mode, hipStream_t stream);
 
+// Query tiles that go to one XCD in a row in a dense pass, `most` at the most.
+int dense_cohort(int tiles, int most);
+
 // The form for calls of at most one query tile to a compute unit (svg_teams.hip).
 bool two_teams(const Geo& g);
 int launch_teams(const Geo& g, const AttnArgs& a, int mode, hipStream_t stream);
@@ -400,9 +422,6 @@ __device__ __forceinline__ int order_bin(int n, int off, int video_end, int P) {
   const int p = (n - off) % P;
   return 1 + (int)(((long long)p * (kOrderBins - 1)) / P);
 }
-// Query tiles that go to one XCD in a row in a dense pass, `most` at the most.
-int dense_cohort(int tiles, int most);
-
 
 // Lanes l and l^32 own the two halves of one query's keys.  v_permlane32_swap with
 // both operands equal returns {x[l % 32], x[32 + l % 32]} in every lane, so the

@@ -205,7 +205,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   int pat = 0, cl = -1, head_cl0 = 0;
   if (SPARSE) {
     int part;
-    if (!sparse_slot<LW>(a.so, a.BH, a.labels, a.row_ptr[0], a.row_ptr[1], xcd, loc, bh, grp, pat, cl, head_cl0, part)) return;
+    if (!sparse_slot<LW, TEAMS>(a.so, a.BH, a.labels, a.row_ptr[0], a.row_ptr[1], xcd, loc, bh, grp, pat, cl, head_cl0, part)) return;
     bh = __builtin_amdgcn_readfirstlane(bh);
     grp = __builtin_amdgcn_readfirstlane(grp);
     pat = __builtin_amdgcn_readfirstlane(pat);

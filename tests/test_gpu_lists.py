@@ -148,3 +148,25 @@ def test_every_dense_query_tile_is_computed(D, heads):
     torch.cuda.synchronize()
     assert_attn_close(o[0, 0], O.dense_attention_head(*(f64(x)[0, 0] for x in (q, k, v)), g), "head 0")
     assert torch.equal(o.view(torch.int16), o[:, :1].expand_as(o).contiguous().view(torch.int16))
+
+
+@pytest.mark.parametrize("tiles", [1, 3, 25])
+@pytest.mark.parametrize("text", [0, 1])
+@pytest.mark.parametrize("heads, temporal", [(5, [1]), (8, [0, 3, 7]), (11, [0, 2, 4, 6, 8]), (9, []), (10, list(range(10))), (70, list(range(0, 70, 3)))])
+def test_every_sparse_query_tile_is_computed(heads, temporal, text, tiles):
+    """Every mixture of labels is dealt to the XCDs in shares that take each tile once.  All heads hold the same rows and keep every key, so all
+    outputs have the bits of the dense pass."""
+    cfg = dict(get_config("mid128"), B=1, H=heads, F=1, P=128 * tiles - 5, T=text, D=64, w_s=1, w_t=128 * tiles, spatial_heads=[0])
+    cfg["N"] = cfg["P"] + text
+    sh = S.shape_from_config(cfg)
+    x = [t.repeat(1, heads, 1, 1).cuda() for t in make_plain_qkv(1, 1, cfg["N"], 64, seed=tiles)]
+    lab = torch.zeros(heads, dtype=torch.uint8, device="cuda")
+    lab[temporal] = 1
+    lists = [dev_i32(a) for p in (S.SVG_HEAD_SPATIAL, S.SVG_HEAD_TEMPORAL) for a in S.svg_tile_list_build(sh, p)]
+    o, want = torch.full_like(x[0], float("nan")), torch.full_like(x[0], float("nan"))
+    S.svg_sparse_attn_fwd_ex(sh, *x, o, lab, *lists, flags=S.SVG_ATTN_QO_TOKEN_ORDER)
+    S.svg_dense_attn_fwd(sh, *x, want)
+    torch.cuda.synchronize()
+    assert torch.allclose(o.float(), want[:, :1].float(), atol=2e-2, rtol=0) and torch.isfinite(o).all()
+    if not text:
+        assert torch.equal(o.view(torch.int16), want.view(torch.int16))
