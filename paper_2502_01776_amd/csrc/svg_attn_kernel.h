@@ -161,6 +161,12 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   static_assert(!SPARSE || NW != 4 || split_lds_bytes(D) <= 2 * STAGE_BYTES, "text-row tiles in parts merge in the same LDS");
   static_assert(TEAMS == 1 || (TEAMS == 2 && NW == 4 && MODE != kProfile), "two teams take the general passes over 128-row query tiles");
   __shared__ __attribute__((aligned(1024))) unsigned char all_lds[TEAMS * 2 * STAGE_BYTES];
+  // A loop of four- and eight-byte instructions runs at a rate of its own from each of the two places it can begin at in a group of eight bytes: which of them are cut by the
+  // lines the instructions come in.  Most forms do not notice, these lose up to 8 % where it begins on a multiple of eight, with few workgroups to a CU above all (gathering at head
+  // dimension 64, one head of 42210 rows 132.9 us and 122.9, 24 of 1960 37.2 and 35.7; exact masks 18 of 6960 98.5 and 96.5; 32-row tiles, 8 heads of 16842 502 and 494), so four
+  // bytes are put in front of theirs.  Where it begins is in a test: more or less code in front turns it round.
+  if constexpr (TEAMS == 1 && LW == 1 && ((D == 64 && NW == 4 && (MODE == kSparseGather || MODE == kSparseExact)) || (D == 128 && NW == 1 && MODE == kSparse)))
+    asm volatile("s_nop 0");
   const int team = TEAMS == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / THREADS);
   unsigned char* const lds = all_lds + team * 2 * STAGE_BYTES;
 

@@ -178,6 +178,29 @@ def test_two_blocks_of_the_largest_magnitudes_fit_a_compute_unit(compiled):
         assert int(used[n]) <= 64
 
 
+def test_loops_that_notice_where_they_begin(compiled, tmp_path):
+    """Four bytes behind a multiple of eight, where these three forms are up to 8 % faster than on one: a line of assembly in front of them sees to it."""
+    tools = os.path.join(os.path.dirname(os.path.dirname(B.hipcc_path())), "llvm", "bin")
+    (tmp_path / "k.s").write_text(compiled[0])
+    subprocess.run([os.path.join(tools, "clang"), "-x", "assembler", "-target", "amdgcn-amd-amdhsa", "-mcpu=gfx950", "-c", "k.s", "-o", "k.o"], cwd=tmp_path, check=True)
+    listing = subprocess.run([os.path.join(tools, "llvm-objdump"), "-d", "--no-show-raw-insn", "k.o"], cwd=tmp_path, check=True, capture_output=True, text=True).stdout
+    heads = {}
+    for block in re.split(r"(?m)^(?=[0-9a-f]+ <\w+>:)", listing):
+        form = re.match(r"[0-9a-f]+ <\w*11attn_kernelILi(\d+)ELi(\d)ELi\d+ELi(\d)ELi1ELi1E", block)
+        if not form:
+            continue
+        ins = [(int(at, 16), op, args) for op, args, at in re.findall(r"(?m)^\s+(\S+) *(.*?) *// ([0-9A-F]+):", block)]
+        for at, op, args in ins:
+            if op.startswith(("s_cbranch", "s_branch")):
+                words = int(args.split()[0])
+                to = at + 4 + 4 * (words - 65536 if words >= 32768 else words)
+                if to < at and 16 <= sum("mfma" in o for a, o, _ in ins if to <= a <= at) <= 64:
+                    heads.setdefault(tuple(int(x) for x in form.groups()), to)
+                    break
+    for form in ((64, 4, 4), (64, 4, 3), (128, 1, 1)):      # gathering, exact masks, 32-row tiles
+        assert not heads or heads[form] % 8 == 4, (form, hex(heads[form]))
+
+
 def test_the_compiler_has_nothing_to_say(compiled):
     """(a warning per inlined load, 600 of them, once hid whatever else there was)"""
     lines = [l for l in compiled[2].splitlines() if "warning" in l and "--hip-link" not in l]
