@@ -448,7 +448,11 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   //             is enough: the element mask is still applied inside every visited tile.
   // ======================================================================================
   TileList list = {};                // sparse
-  int lj = team;                     // dense: counter
+  int lj = team, l_end = 0;          // dense: counter; profile, unmasked pass: counter and end of the tiles of part chunk
+  if (MODE == kProfile && !PIECED && variant == 0) {
+    lj = a.plan.full_bound[chunk];
+    l_end = a.plan.full_bound[chunk + 1];
+  }
   int n_tiles = a.nk;                // two teams: tiles of the workgroup
   if (SPARSE) {
     const int32_t* rp = a.row_ptr[pat];
@@ -465,12 +469,6 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   }
   int pseg = 0, pj = 0, pjb = -1;
   auto profile_segment = [&](int sidx, int& k0, int& k1) -> bool {   // false: no more segments
-    if (!PIECED && variant == 0) {      // unmasked pass: the key tiles of part chunk
-      const int t0 = a.plan.full_bound[chunk], t1 = a.plan.full_bound[chunk + 1];
-      k0 = t0 * BN;
-      k1 = min(a.N, t1 * BN) - 1;
-      return sidx == 0;
-    }
     const int nv = variant == 1 ? 1 : a.F;
     if (sidx == 0) {            // text prefix
       k0 = 0;
@@ -562,7 +560,9 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
     return visit;
   };
   auto visit_key = [](int visit) { return visit >> 8; };
-  // masks: is it asked by the loop of the masked passes?  In pieces each loop then holds the state of its own walk only: 32 spilled scalars become 14,
+  // masks: is it asked by the loop of the masked passes?  Each loop then holds the state of its own walk only.  In three passes no scalar is spilled (14 and 10 were in 128-row tiles) and a tenth of
+  // the code is gone: 187 calls 1.02-1.05 times as fast as with one walk for both loops, whose code was 1-6 % slower in 32-row tiles at head dimension 128 once it had no pieces in it (97 heads of 850 rows
+  // 41.9 us, now 39.4).  In pieces 32 spilled scalars become 14,
   // a tile of the temporal pass at head dimension 64 996 instructions 827, and 124 calls take 0.94-1.01 of the time, 0.983 at the mean (48 heads of 17776 rows 119 -> 115 us).
   auto next_tile = [&](auto masks) -> int {
     if (SPARSE) return list.next();
@@ -572,7 +572,10 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
       lj = j + TEAMS;
       return j;
     }
-    if constexpr (PIECED && !decltype(masks)::value) return next_visit();      // profile
+    if constexpr (!decltype(masks)::value) {      // profile
+      if constexpr (PIECED) return next_visit();
+      return lj < l_end ? lj++ : kNoTile;
+    }
     if (pleft <= 0) return kNoTile;
     if (!profile_interval()) return kNoTile;
     --pleft;
@@ -984,7 +987,7 @@ __global__ __launch_bounds__(64 * NW * TEAMS, TEAMS > 1 ? TEAMS : waves_per_simd
   // ======================================================================================
   const bool sequential = MASKABLE && masked;
   int col, col1, col2 = kNoTile;
-  if (PIECED && sequential) {
+  if (MODE == kProfile && sequential) {
     col = next_tile(yes);
     col1 = next_tile(yes);
   } else {

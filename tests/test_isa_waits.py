@@ -155,13 +155,13 @@ def test_m0_is_used_by_the_direct_loads_only(compiled):
 
 
 def test_three_passes_of_profiling_carry_nothing_of_the_pieces(compiled):
-    """The kernel without pieces keeps its scalars in registers as it did before there was one with them (13 and 8 spilled at
-    128-row tiles, none at 32; as one kernel 36 and 20), and the loops of the one with them know nothing of each other's walk (32 and 10)."""
+    """The loops of either kernel know nothing of each other's walk: without pieces all scalars stay in registers (14 and 10 spilled at 128-row tiles
+    otherwise, as one kernel with the pieces 36 and 20), with them 14 are spilled at 128-row tiles (32)."""
     names = [k.name for k in compiled[1] if re.search(r"11attn_kernelILi\d+ELi\d+ELi\d+ELi2E", k.name)]
     spilled = dict(re.findall(r"\.name: +(\w+)\n(?:(?!\.name:).*\n)*?\s*\.sgpr_spill_count: (\d+)", compiled[0]))
     assert len(names) in (0, 8) and 2 * sum("ELb1E" in n for n in names) == len(names)      # (none in the FP8 file)
     for n in names:
-        assert int(spilled[n]) <= (16 if "ELi4ELi64ELi2E" in n else 0), n
+        assert int(spilled[n]) <= (16 if "ELi4ELi64ELi2E" in n and "ELb1E" in n else 0), n
 
 
 def test_kernels_of_profiling_take_no_arguments_of_their_launch(compiled):
